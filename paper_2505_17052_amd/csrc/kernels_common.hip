@@ -32,147 +32,167 @@ void launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st) {
 // double so that positions in the thousands keep full float accuracy.
 // For the matrix-core attention: the list of (request, row group, KV chunk)
 // work items and the per (request, row group) merge groups.
+//
+// One kernel, bound by latency alone: every block scans the (at most 256) requests' sizes itself and then fills its
+// own share, so no block waits for another and no second launch is needed.  The first n_row_blocks blocks take 16 rows
+// of one request each, the others four work items (one per wave).  The ancestor sets of a tree come from pointer
+// doubling in LDS (six rounds for 64 nodes); a depth is the number of ancestors.  (One thread per request walking
+// its tree, and a second kernel for the tables, took 55 + 6 us for 8 trees of 64 nodes and 5 + 5 us for 16 chains of 8.)
 // ---------------------------------------------------------------------------
 struct PlanDev {
     DevPlan p;
     int32_t *seq_len, *pend_n, *pend_P;
     uint32_t *err;
     int vocab, hd, G;          // G = query heads per KV head
-    double rope_base;
     int chunk_pages;
     const int32_t *tokens, *parents;
     const int32_t *page_table;
     int max_pages;
 };
+static_assert(sizeof(PlanArgs) + sizeof(PlanDev) + 64 <= 4096, "kernel arguments of the plan");
 
-__global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d) {
-    __shared__ int s_row0[SEV_MAX_BATCH + 1];
-    __shared__ int s_item0[SEV_MAX_BATCH + 1];
-    __shared__ int s_grp0[SEV_MAX_BATCH + 1];
-    const int t = threadIdx.x;
-    const int B = a.B;
-    int my_items = 0, my_groups = 0, my_chunks = 0;
-    if (t < B) {
-        const int slot = a.slot[t], P = a.prefix[t], n = a.nd[t];
-        if (d.seq_len[slot] != P) atomicOr(d.err, 1u);
-        d.pend_n[slot] = 0;                      // a new verify drops whatever was pending
-        d.pend_P[slot] = P;
-        my_groups = (d.G * n + 31) / 32;
-        const int pages = (max(P + n, a.pad_tokens) + SEV_PAGE - 1) / SEV_PAGE;
-        my_chunks = (pages + d.chunk_pages - 1) / d.chunk_pages;
-        my_items = my_groups * my_chunks;
-        s_row0[t + 1] = n;
-        s_item0[t + 1] = my_items;
-        s_grp0[t + 1] = my_groups;
-    }
-    __syncthreads();
-    if (t == 0) {
-        s_row0[0] = s_item0[0] = s_grp0[0] = 0;
-        for (int b = 0; b < B; ++b) {
-            s_row0[b + 1] += s_row0[b];
-            s_item0[b + 1] += s_item0[b];
-            s_grp0[b + 1] += s_grp0[b];
-        }
-    }
-    __syncthreads();
-    if (t < B) {
-        const int slot = a.slot[t], P = a.prefix[t], n = a.nd[t], row0 = s_row0[t];
-        d.p.req_slot[t] = slot;
-        d.p.req_P[t] = P;
-        d.p.req_n[t] = n;
-        d.p.req_row0[t] = row0;
-        if (t == B - 1) d.p.req_row0[B] = s_row0[B];
-        // trees: parents precede children, so one forward sweep gives depth and ancestor set
-        // (the rows of chains are filled in parallel by plan_fill_kernel)
-        unsigned long long anc_prev = 0;
-        int depth_prev = -1;
-        for (int i = 0; d.parents && i < n; ++i) {
-            int par = d.parents[t * a.k_max + i];
-            if (par < -1 || par >= i) { atomicOr(d.err, 2u); par = -1; }
-            unsigned long long anc;
-            int depth;
-            if (par < 0) { anc = 0; depth = 0; }
-            else if (par == i - 1) { anc = anc_prev; depth = depth_prev + 1; }
-            else { anc = d.p.row_anc[row0 + par]; depth = d.p.row_pos[row0 + par] - P + 1; }
-            anc |= 1ull << i;
-            int tok = d.tokens[t * a.tok_stride + a.tok_off + i];
-            if (tok < 0 || tok >= d.vocab) { atomicOr(d.err, 4u); tok = 0; }
-            d.p.row_req[row0 + i] = t;
-            d.p.row_node[row0 + i] = i;
-            d.p.row_pos[row0 + i] = P + depth;
-            d.p.row_anc[row0 + i] = anc;
-            d.p.row_tok[row0 + i] = tok;
-            d.p.row_kvloc[row0 + i] = d.page_table[(size_t)slot * d.max_pages + (P + i) / SEV_PAGE] * SEV_PAGE + (P + i) % SEV_PAGE;
-            anc_prev = anc;
-            depth_prev = depth;
-        }
-        // attention work items of this request: its pages are split evenly over my_chunks chunks
-        const int pages = (max(P + n, a.pad_tokens) + SEV_PAGE - 1) / SEV_PAGE;
-        const int cpp = (pages + my_chunks - 1) / my_chunks;
-        // item order: chunk by chunk, the row groups of one chunk side by side (the attention kernel puts them on
-        // one XCD, where the chunk is then fetched from memory once for all of them)
-        const int it0 = s_item0[t], g0 = s_grp0[t];
-        for (int rg = 0; rg < my_groups; ++rg) {
-            d.p.mg_rec[g0 + rg] = make_int4(rg | (my_chunks << 16), it0 + rg, n | (my_groups << 16), row0);
-            for (int c = 0; c < my_chunks; ++c) {
-                const int p0 = c * cpp, it = it0 + c * my_groups + rg;
-                d.p.it_a[it] = make_int4(rg, p0, min(cpp, pages - p0), P);
-                d.p.it_b[it] = make_int4(n, row0, t, slot);
-            }
-        }
-    }
+#define PLAN_ROWS 16           // rows per row block
+#define PLAN_ITEMS 4           // work items per item block
+
+__global__ void theta_kernel(double *theta, int hd, double rope_base) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < hd / 2) theta[i] = pow(rope_base, -2.0 * (double)i / (double)hd);
 }
 
-// Second half of the plan, one thread per entry: the rows of chain blocks (request, node, position,
-// token, cache location), the physical page ids of every attention work item (padded with the
-// chunk's last page, so that the attention kernel can load its page ids without knowing the chunk
-// length) and the rotary table (cos, sin)(pos * theta_i), computed in double.
-__device__ __forceinline__ int find_request(const int32_t *row0, int B, int m) {
-    int lo = 0, hi = B - 1;                                   // largest b with row0[b] <= m
+void launch_theta(const sev_kv *kv, hipStream_t st) {
+    const int hd = kv->model->d.head_dim;
+    hipLaunchKernelGGL(theta_kernel, dim3((hd / 2 + 63) / 64), dim3(64), 0, st, kv->plan.theta, hd, (double)kv->model->d.rope_base);
+}
+
+// largest b in [0, B) with first[b] <= m (first ascends, first[0] = 0; entries of empty requests never win)
+__device__ __forceinline__ int plan_find(const int *first, int B, int m) {
+    int lo = 0, hi = B - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (row0[mid] <= m) lo = mid; else hi = mid - 1;
+        if (first[mid] <= m) lo = mid; else hi = mid - 1;
     }
     return lo;
 }
 
-__global__ __launch_bounds__(256) void plan_fill_kernel(PlanArgs a, PlanDev d, int n_items, int rows) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (!d.parents && idx < rows) {
-        const int b = find_request(d.p.req_row0, a.B, idx), i = idx - d.p.req_row0[b];
-        const int P = d.p.req_P[b], slot = d.p.req_slot[b];
-        int tok = d.tokens[b * a.tok_stride + a.tok_off + i];
-        if (tok < 0 || tok >= d.vocab) { atomicOr(d.err, 4u); tok = 0; }
-        d.p.row_req[idx] = b;
-        d.p.row_node[idx] = i;
-        d.p.row_pos[idx] = P + i;
-        d.p.row_anc[idx] = i < 63 ? (2ull << i) - 1ull : ~0ull;
-        d.p.row_tok[idx] = tok;
-        d.p.row_kvloc[idx] = d.page_table[(size_t)slot * d.max_pages + (P + i) / SEV_PAGE] * SEV_PAGE + (P + i) % SEV_PAGE;
+__global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_row_blocks, int n_items) {
+    __shared__ int s_first[4][SEV_MAX_BATCH];                  // per request: first row, merge group, work item, row block
+    __shared__ int s_tot[4][4];
+    __shared__ unsigned long long s_anc[2][SEV_MAX_DRAFT];
+    __shared__ int s_up[2][SEV_MAX_DRAFT];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int B = a.B;
+    int mine[4] = {0, 0, 0, 0};
+    if (t < B) {
+        const int n = a.nd[t];
+        const int pages = (max(a.prefix[t] + n, a.pad_tokens) + SEV_PAGE - 1) / SEV_PAGE;
+        mine[0] = n;
+        mine[1] = (d.G * n + 31) / 32;
+        mine[2] = mine[1] * ((pages + d.chunk_pages - 1) / d.chunk_pages);
+        mine[3] = (n + PLAN_ROWS - 1) / PLAN_ROWS;
     }
-    if (idx < n_items * SEV_ATT_MAX_CP) {
-        const int it = idx / SEV_ATT_MAX_CP, i = idx - it * SEV_ATT_MAX_CP;
-        const int4 ia = d.p.it_a[it], ib = d.p.it_b[it];
-        d.p.it_pages[idx] = d.page_table[(size_t)ib.w * d.max_pages + ia.y + min(i, ia.z - 1)];
-    }
-    const int half = d.hd / 2;
-    if (idx < rows * half) {
-        const int r = idx / half, i = idx - r * half;
-        int pos;
-        if (d.parents) pos = d.p.row_pos[r];                  // written by plan_kernel
-        else {
-            const int b = find_request(d.p.req_row0, a.B, r);
-            pos = d.p.req_P[b] + r - d.p.req_row0[b];
+    int inc[4] = {mine[0], mine[1], mine[2], mine[3]};
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int y = __shfl_up(inc[q], o);
+            if (lane >= o) inc[q] += y;
         }
-        const double theta = pow(d.rope_base, -2.0 * (double)i / (double)d.hd);
-        double s, c;
-        sincos((double)pos * theta, &s, &c);
-        d.p.row_cs[idx] = make_float2((float)c, (float)s);
+    if (lane == 63)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s_tot[q][wave] = inc[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        int before = 0;
+        for (int w = 0; w < wave; ++w) before += s_tot[q][w];
+        s_first[q][t] = before + inc[q] - mine[q];
     }
+    __syncthreads();
+
+    const int blk = blockIdx.x;
+    if (blk < n_row_blocks) {                                   // 16 rows of one request
+        const int b = plan_find(s_first[3], B, blk);
+        const int i0 = (blk - s_first[3][b]) * PLAN_ROWS;
+        const int slot = a.slot[b], P = a.prefix[b], n = a.nd[b], row0 = s_first[0][b];
+        if (i0 == 0 && t == 0) {
+            if (d.seq_len[slot] != P) atomicOr(d.err, 1u);
+            d.pend_n[slot] = 0;                                 // a new verify drops whatever was pending
+            d.pend_P[slot] = P;
+            d.p.req_slot[b] = slot;
+            d.p.req_P[b] = P;
+            d.p.req_n[b] = n;
+            d.p.req_row0[b] = row0;
+        }
+        int cur = 0;
+        if (d.parents) {                                        // trees: n <= 64 nodes, parents precede children
+            if (t < SEV_MAX_DRAFT) {
+                int par = -1;
+                if (t < n) {
+                    par = d.parents[b * a.k_max + t];
+                    if (par < -1 || par >= t) { atomicOr(d.err, 2u); par = -1; }
+                }
+                s_anc[0][t] = 1ull << t;
+                s_up[0][t] = par;
+            }
+            __syncthreads();
+            for (int r = 0; r < 6; ++r, cur ^= 1) {             // after r rounds: the ancestors up to 2^r - 1 levels up
+                if (t < SEV_MAX_DRAFT) {
+                    const int up = s_up[cur][t];
+                    s_anc[cur ^ 1][t] = s_anc[cur][t] | (up >= 0 ? s_anc[cur][up] : 0ull);
+                    s_up[cur ^ 1][t] = up >= 0 ? s_up[cur][up] : -1;
+                }
+                __syncthreads();
+            }
+        }
+        if (t < PLAN_ROWS && i0 + t < n) {
+            const int i = i0 + t, row = row0 + i;
+            int tok = d.tokens[a.tok0[b] + i];
+            if (tok < 0 || tok >= d.vocab) { atomicOr(d.err, 4u); tok = 0; }
+            const unsigned long long anc = d.parents ? s_anc[cur][i] : (i < 63 ? (2ull << i) - 1ull : ~0ull);
+            d.p.row_req[row] = b;
+            d.p.row_node[row] = i;
+            d.p.row_pos[row] = P + (d.parents ? __popcll(anc) - 1 : i);
+            d.p.row_anc[row] = anc;
+            d.p.row_tok[row] = tok;
+            d.p.row_kvloc[row] = d.page_table[(size_t)slot * d.max_pages + (P + i) / SEV_PAGE] * SEV_PAGE + (P + i) % SEV_PAGE;
+        }
+        const int half = d.hd / 2, rows = min(PLAN_ROWS, n - i0);
+        for (int e = t; e < rows * half; e += 256) {
+            const int r = e / half, i = e - r * half, node = i0 + r;
+            const int pos = P + (d.parents ? __popcll(s_anc[cur][node]) - 1 : node);
+            double s, c;
+            sincos((double)pos * d.p.theta[i], &s, &c);
+            d.p.row_cs[(size_t)(row0 + node) * half + i] = make_float2((float)c, (float)s);
+        }
+        return;
+    }
+    // attention work items.  A request's pages are split evenly over its chunks; item order: chunk by chunk, the row
+    // groups of one chunk side by side (the attention kernel puts them on one XCD, where the chunk is then fetched from
+    // memory once for all of them).  The page list is padded with the chunk's last page, so that the attention kernel
+    // can load its page ids without knowing the chunk length.
+    const int it = (blk - n_row_blocks) * PLAN_ITEMS + wave;
+    if (it >= n_items) return;
+    const int b = plan_find(s_first[2], B, it);
+    const int slot = a.slot[b], P = a.prefix[b], n = a.nd[b];
+    const int pages = (max(P + n, a.pad_tokens) + SEV_PAGE - 1) / SEV_PAGE;
+    const int groups = (d.G * n + 31) / 32, chunks = (pages + d.chunk_pages - 1) / d.chunk_pages;
+    const int cpp = (pages + chunks - 1) / chunks;
+    const int local = it - s_first[2][b], c = local / groups, rg = local - c * groups;
+    const int p0 = c * cpp, np = min(cpp, pages - p0);
+    if (lane == 0) {
+        d.p.it_a[it] = make_int4(rg, p0, np, P);
+        d.p.it_b[it] = make_int4(n, s_first[0][b], b, slot);
+        if (c == 0) d.p.mg_rec[s_first[1][b] + rg] = make_int4(rg | (chunks << 16), it, n | (groups << 16), s_first[0][b]);
+    }
+#pragma unroll
+    for (int i = lane; i < SEV_ATT_MAX_CP; i += 64)
+        d.p.it_pages[(size_t)it * SEV_ATT_MAX_CP + i] = d.page_table[(size_t)slot * d.max_pages + p0 + min(i, np - 1)];
 }
 
 void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_tokens, const int32_t *parents, int rows,
                  int chunk_pages, int n_items, hipStream_t st) {
+    (void)rows;
     PlanDev d;
     d.p = kv->plan;
     d.seq_len = kv->seq_len;
@@ -182,66 +202,67 @@ void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_toke
     d.vocab = kv->model->d.vocab;
     d.hd = kv->model->d.head_dim;
     d.G = kv->model->d.n_q_heads / kv->model->d.n_kv_heads;
-    d.rope_base = (double)kv->model->d.rope_base;
     d.chunk_pages = chunk_pages;
     d.tokens = draft_tokens;
     d.parents = parents;
     d.page_table = kv->page_table;
     d.max_pages = kv->max_pages_per_req;
-    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(256), 0, st, pa, d);
-    const int64_t entries = std::max<int64_t>((int64_t)n_items * SEV_ATT_MAX_CP, (int64_t)rows * std::max(1, d.hd / 2));
-    hipLaunchKernelGGL(plan_fill_kernel, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, st, pa, d, n_items, rows);
+    int row_blocks = 0;
+    for (int b = 0; b < pa.B; ++b) row_blocks += (pa.nd[b] + PLAN_ROWS - 1) / PLAN_ROWS;
+    hipLaunchKernelGGL(plan_kernel, dim3((unsigned)(row_blocks + (n_items + PLAN_ITEMS - 1) / PLAN_ITEMS)), dim3(256), 0, st, pa, d,
+                       row_blocks, n_items);
 }
 
 // ---------------------------------------------------------------------------
 // greedy acceptance (paper section 4.1: accepted candidates plus one additional
-// token from the server's own forward pass).  One thread per request.
+// token from the server's own forward pass).  One wave per request, one lane per candidate: a step of the walk is a
+// ballot over (parent, token), so the kernel is two loads deep whatever the tree (a thread per request, searching the
+// children in memory, took 50 us for 8 trees of 64 nodes and 11 us for chains of 8).
 // ---------------------------------------------------------------------------
-__global__ void accept_kernel(DevPlan p, int B, int k_max, int mode, const int32_t *tokens, const int32_t *parents,
-                              const int32_t *row_argmax, const int32_t *next_tok, int32_t *pend_n, int32_t *pend_a,
-                              int32_t *pend_bonus, int32_t *pend_path, int32_t *accept_len, int32_t *bonus_out,
-                              int32_t *path_out) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
+__global__ __launch_bounds__(64) void accept_kernel(DevPlan p, int k_max, int mode, const int32_t *tokens, const int32_t *parents,
+                                                    const int32_t *row_argmax, const int32_t *next_tok, int32_t *pend_n, int32_t *pend_a,
+                                                    int32_t *pend_bonus, int32_t *pend_path, int32_t *accept_len, int32_t *bonus_out,
+                                                    int32_t *path_out, int32_t *argmax_out) {
+    const int b = blockIdx.x, c = threadIdx.x;
     const int slot = p.req_slot[b], n = p.req_n[b], row0 = p.req_row0[b];
-    int32_t *path = pend_path + (size_t)slot * SEV_MAX_DRAFT;
-    int a = 0, want;
-    if (mode == 1) {                       // append: keep the whole chain
-        for (int i = 0; i < n && i < SEV_MAX_DRAFT; ++i) path[i] = i;     // (longer appended blocks are never re-ordered)
+    const bool live = c < n;
+    const int tok = live ? tokens[(size_t)b * k_max + c] : -1;
+    int par = live ? (parents ? parents[(size_t)b * k_max + c] : c - 1) : -2;
+    if (live && (par < -1 || par >= c)) par = -1;
+    const int am = live ? row_argmax[row0 + c] : 0;
+    int a = 0, want = next_tok[slot], mine = -1;
+    if (mode == 1) {                       // append: keep the whole chain (longer appended blocks are never re-ordered)
         a = n;
+        mine = live ? c : -1;
         want = row_argmax[row0 + n - 1];
     } else {
-        want = next_tok[slot];
         int cur = -1;
         while (true) {
-            int nxt = -1;
-            // children of `cur` come after it; the lowest matching index wins
-            for (int c = cur + 1; c < n; ++c) {
-                const int par = parents ? parents[b * k_max + c] : c - 1;
-                const int par_ok = (par < -1 || par >= c) ? -1 : par;
-                if (par_ok == cur && tokens[b * k_max + c] == want) { nxt = c; break; }
-            }
-            if (nxt < 0) break;
-            path[a++] = nxt;
-            cur = nxt;
-            want = row_argmax[row0 + nxt];
+            const unsigned long long hit = __ballot(par == cur && tok == want);     // children come after their parent; the lowest matching index wins
+            if (!hit) break;
+            cur = __ffsll((long long)hit) - 1;
+            if (c == a) mine = cur;
+            ++a;
+            want = __shfl(am, cur);
         }
     }
-    for (int i = a; i < SEV_MAX_DRAFT; ++i) path[i] = -1;
-    pend_n[slot] = n;
-    pend_a[slot] = a;
-    pend_bonus[slot] = want;
-    accept_len[b] = a;
-    bonus_out[b] = want;
-    if (path_out)
-        for (int i = 0; i < k_max; ++i) path_out[b * k_max + i] = i < a ? path[i] : -1;
+    pend_path[(size_t)slot * SEV_MAX_DRAFT + c] = mine;
+    if (path_out && c < k_max) path_out[(size_t)b * k_max + c] = mine;
+    if (argmax_out && live) argmax_out[row0 + c] = am;
+    if (c == 0) {
+        pend_n[slot] = n;
+        pend_a[slot] = a;
+        pend_bonus[slot] = want;
+        accept_len[b] = a;
+        bonus_out[b] = want;
+    }
 }
 
 void launch_accept(const sev_kv *kv, int B, int k_max, int mode, const int32_t *draft_tokens, const int32_t *parents,
-                   int32_t *accept_len, int32_t *bonus, int32_t *accept_path, hipStream_t st) {
-    hipLaunchKernelGGL(accept_kernel, dim3((B + 63) / 64), dim3(64), 0, st, kv->plan, B, k_max, mode, draft_tokens,
+                   int32_t *accept_len, int32_t *bonus, int32_t *accept_path, int32_t *argmax_out, hipStream_t st) {
+    hipLaunchKernelGGL(accept_kernel, dim3(B), dim3(64), 0, st, kv->plan, k_max, mode, draft_tokens,
                        parents, kv->row_argmax, kv->next_tok, kv->pend_n, kv->pend_a, kv->pend_bonus, kv->pend_path,
-                       accept_len, bonus, accept_path);
+                       accept_len, bonus, accept_path, argmax_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -582,7 +603,10 @@ void launch_commit(const sev_kv *kv, const int32_t *slots, int B, bool rollback,
     SlotList sl;
     for (int b = 0; b < B; ++b) sl.s[b] = slots ? slots[b] : b;
     KvGeom g = sev_kv_geom(kv);
-    if (!rollback) {
+    // accepted candidates of a chain are in place already (candidate j sits at position P + j): only trees may have to move
+    bool trees = false;
+    for (int b = 0; b < B; ++b) trees |= kv->host_tree[sl.s[b]] != 0;
+    if (!rollback && trees) {
         const int n = g.L * g.Hkv * g.hd;
         dim3 grid((n + 255) / 256, B);
         if (kv->model->d.dtype == SEV_BF16)

@@ -240,6 +240,7 @@ extern "C" int sev_kv_create(const sev_model *m, int max_requests, int max_rows,
     memset(kv->prof_ms, 0, sizeof(kv->prof_ms));
     memset(kv->prof_n, 0, sizeof(kv->prof_n));
     kv->host_pages.assign(max_requests, 0);
+    kv->host_tree.assign(max_requests, 0);
 
     const bool bf = d.dtype == SEV_BF16;
     const size_t rows_pad = align_up((size_t)max_rows, 128);
@@ -283,6 +284,7 @@ extern "C" int sev_kv_create(const sev_model *m, int max_requests, int max_rows,
     const size_t o_ssq = take(2 * rows_pad * 8);
     const size_t o_tmp = take(2 * SEV_MAX_BATCH * 4);
     const size_t o_rst = take(rows_pad * 8);
+    const size_t o_th = take((size_t)(d.head_dim / 2) * 8);
     kv->ws_bytes = off;
     hipError_t e = hipMalloc((void **)&kv->ws, kv->ws_bytes);
     if (e != hipSuccess) {
@@ -339,7 +341,9 @@ extern "C" int sev_kv_create(const sev_model *m, int max_requests, int max_rows,
     kv->tmp_bonus = kv->tmp_accept + SEV_MAX_BATCH;
     kv->ssq[0] = (unsigned long long *)(w + o_ssq);
     kv->ssq[1] = kv->ssq[0] + rows_pad;
+    kv->plan.theta = (double *)(w + o_th);
     launch_fill_i32(kv->next_tok, -1, max_requests, 0);
+    launch_theta(kv, 0);
     {   // set-up for sev_verify_sample_static: look the static scratch up for this device now (a failure only
         // matters to that entry point, which reports it)
         void *unused = nullptr;
@@ -584,10 +588,7 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
     PlanArgs pa;
     pa.B = c.B;
     pa.k_max = c.tok_stride;
-    pa.mode = c.mode & 1;
     pa.pad_tokens = 0;
-    pa.tok_stride = c.tok_stride;
-    pa.tok_off = c.tok_off;
     int64_t rows = 0;
     for (int b = 0; b < c.B; ++b) {
         const int slot = c.slots ? c.slots[b] : b;
@@ -600,9 +601,10 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
         if ((int64_t)P + n > (int64_t)kv->host_pages[slot] * SEV_PAGE)
             return sev_fail(SEV_ENOSPACE, "request %d: %d+%d tokens exceed the %d pages of slot %d", b, P, n,
                             kv->host_pages[slot], slot);
-        pa.slot[b] = slot;
+        pa.slot[b] = (uint16_t)slot;
         pa.prefix[b] = P;
         pa.nd[b] = n;
+        pa.tok0[b] = b * c.tok_stride + c.tok_off;
         rows += n;
     }
     if (rows > kv->max_rows) return sev_fail(SEV_ENOSPACE, "%lld tokens exceed max_rows=%d", (long long)rows, kv->max_rows);
@@ -623,6 +625,7 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
         if (cp < 0) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
     }
     kv->plan.causal = c.parents ? 0 : 1;
+    for (int b = 0; b < c.B; ++b) kv->host_tree[pa.slot[b]] = c.parents ? 1 : 0;
     {
         Prof p(kv, st, PROF_OTHER);
         launch_plan(kv, pa, c.tokens, c.parents, (int)rows, cp, n_items, st);
@@ -635,9 +638,7 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
             launch_sample(kv, c.B, c.tok_stride, (int)rows, c.tokens, c.parents, c.logits, c.draft_probs, kv->row_stats, c.temperature,
                           c.u_accept, c.u_emit, c.accept_len, c.bonus_token, c.accept_path, st);
         else
-            launch_accept(kv, c.B, c.tok_stride, c.mode & 1, c.tokens, c.parents, c.accept_len, c.bonus_token, c.accept_path, st);
-        if (c.row_argmax)
-            SEV_HIP(hipMemcpyAsync(c.row_argmax, kv->row_argmax, (size_t)rows * 4, hipMemcpyDeviceToDevice, st));
+            launch_accept(kv, c.B, c.tok_stride, c.mode & 1, c.tokens, c.parents, c.accept_len, c.bonus_token, c.accept_path, c.row_argmax, st);
     }
     SEV_HIP(hipGetLastError());
     return SEV_OK;

@@ -50,14 +50,15 @@ struct sev_model {
     int kv_dim;  // Hkv * hd
 };
 
-// Per-call description handed to the plan kernel by value.
+// Per-call description handed to the plan kernel by value (together with PlanDev it stays below the 4 KiB that a
+// kernel's arguments may take; slots are below 65536, see sev_kv_create).
 struct PlanArgs {
-    int B, k_max, mode;
+    int B, k_max;
     int pad_tokens;           // > 0: attention walks every request's pages up to this many tokens (padded-KV comparison variant)
-    int tok_stride, tok_off;  // token of node i of request b: tokens[b * tok_stride + tok_off + i]
-    int32_t slot[SEV_MAX_BATCH];
+    uint16_t slot[SEV_MAX_BATCH];
     int32_t prefix[SEV_MAX_BATCH];
     int32_t nd[SEV_MAX_BATCH];
+    int32_t tok0[SEV_MAX_BATCH];   // token of node i of request b: tokens[tok0[b] + i]
 };
 
 // Device-side call plan (one per sev_kv; rebuilt by every verify).
@@ -69,6 +70,7 @@ struct DevPlan {
     int32_t *row_kvloc;       // physical page * 16 + token in page of the cache position P + node the row is written to
     unsigned long long *row_anc;
     float2 *row_cs;           // [rows][hd/2] (cos, sin) of pos * theta_i
+    double *theta;            // [hd/2] theta_i = base^(-2i/hd), written once when the handle is created
     // attention work items (bf16 path): a = {row group, first page, pages, prefix length},
     // b = {draft nodes, first row, request, 0}; pages = physical page ids of the chunk, SEV_ATT_MAX_CP per item
     int4 *it_a, *it_b;
@@ -135,6 +137,7 @@ struct sev_kv {
 
     // host mirrors
     std::vector<int> host_pages;   // pages assigned per slot
+    std::vector<char> host_tree;   // per slot: the last verified block was a tree (its commit may have to move K/V)
     // profiling
     int prof_on;
     std::vector<ProfSpan> spans;
@@ -160,8 +163,9 @@ void launch_fill_f32(float *p, float v, int64_t n, hipStream_t st);
 void launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st);
 void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_tokens, const int32_t *parents, int rows,
                  int chunk_pages, int n_items, hipStream_t st);
+void launch_theta(const sev_kv *kv, hipStream_t st);
 void launch_accept(const sev_kv *kv, int B, int k_max, int mode, const int32_t *draft_tokens, const int32_t *parents,
-                   int32_t *accept_len, int32_t *bonus, int32_t *accept_path, hipStream_t st);
+                   int32_t *accept_len, int32_t *bonus, int32_t *accept_path, int32_t *argmax_out, hipStream_t st);
 void launch_sample(const sev_kv *kv, int B, int k_max, int rows, const int32_t *tokens, const int32_t *parents, const float *logits,
                    const float *draft_probs, float2 *stats, float temperature, const float *u_acc, const float *u_emit,
                    int32_t *accept_len, int32_t *emitted, int32_t *accept_path, hipStream_t st);

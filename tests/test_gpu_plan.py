@@ -1,0 +1,78 @@
+"""The call plan (rows, ancestor sets, work items) and the acceptance walk at the edges of their blocks: block lengths around
+the 16 rows of a plan block, the deepest tree (64 levels), the widest, ragged batches up to 256 requests.  Decisions are
+compared with the oracle's acceptance on the GPU's own arg-max (whole numbers: exact); a tree that is a chain must give the
+chain's logits bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import verify_oracle as vo
+from tests.helpers import announce
+
+pytestmark = pytest.mark.gpu
+SHAPE, SEED = synth.MINI_BF16, 606
+
+
+@pytest.fixture(scope="module")
+def setup():
+    import paper_2505_17052_amd as sev
+    from paper_2505_17052_amd import harness
+    return sev, harness, harness.build_model(SHAPE, SEED)
+
+
+def _tree(rng, n, kind):
+    if kind == "deep":
+        return np.arange(-1, n - 1)
+    if kind == "wide":
+        return np.array([-1] + [0] * (n - 1))
+    if kind == "roots":
+        return np.full(n, -1)
+    return np.array([-1] + [int(rng.integers(max(-1, i - 9), i)) for i in range(1, n)])
+
+
+@pytest.mark.parametrize("ns,kinds", [((1,), ("deep",)), ((64,), ("deep",)), ((15, 16, 17, 64), ("random",)), ((64, 2, 33), ("wide", "roots", "random")),
+                                      ((31, 32, 63, 1), ("deep", "random")), ((3,) * 256, ("random", "wide"))])
+def test_tree_decisions(setup, ns, kinds):
+    sev, harness, model = setup
+    rng = np.random.default_rng(len(ns) * 100 + ns[0])
+    B, k = len(ns), max(ns)
+    lens = [int(x) for x in rng.integers(1, 70, B)]
+    announce(f"plan: {B} requests, nodes {sorted(set(ns))}, {kinds}")
+    batch = harness.Batch(model, SHAPE, [p + k for p in lens], max_rows=sum(ns), seed=SEED)
+    batch.prefill([rng.integers(0, SHAPE.vocab, p) for p in lens])
+    nxt = [batch.kv.get_state(b)[1] for b in range(B)]
+    par = np.full((B, k), -1, dtype=np.int32)
+    tok = rng.integers(0, SHAPE.vocab, (B, k)).astype(np.int32)
+    for b, n in enumerate(ns):
+        par[b, :n] = _tree(rng, n, kinds[b % len(kinds)])
+    dev = lambda x: torch.tensor(x, device="cuda")
+    right = rng.random((B, k)) < 0.8
+    for rounds in range(5):                                  # each round makes one more level follow the model's own arg-max
+        out = sev.verify_ex(model, batch.kv, lens, dev(tok), k, draft_lens=ns, parents=dev(par), want_path=True, want_argmax=True)
+        am, row0 = out["row_argmax"].cpu().numpy(), np.concatenate([[0], np.cumsum(ns)])
+        path = out["accept_path"].cpu().numpy()
+        for b, n in enumerate(ns):
+            rows = am[row0[b]:row0[b] + n]
+            want_len, want_tok, want_path = vo.accept_tree(tok[b, :n], par[b, :n], nxt[b], rows)
+            assert int(out["accept_len"][b]) == want_len and int(out["bonus_token"][b]) == want_tok
+            assert path[b].tolist() == list(want_path) + [-1] * (k - want_len)
+            for i in range(n):
+                if right[b, i]:
+                    tok[b, i] = nxt[b] if par[b, i] < 0 else rows[par[b, i]]
+    assert batch.kv.get_state(0)[2] == 0
+    if ns == (64,) or ns == (1,):                            # a chain given as a tree: the same rows, masks and positions
+        a = sev.verify_ex(model, batch.kv, lens, dev(tok), k, parents=dev(par), want_logits=True)
+        c = sev.verify_ex(model, batch.kv, lens, dev(tok), k, want_logits=True)
+        assert torch.equal(a["logits"], c["logits"])
+
+
+def test_malformed_parents_are_flagged(setup):
+    sev, harness, model = setup
+    batch = harness.Batch(model, SHAPE, [80], max_rows=64, seed=SEED)
+    batch.prefill([np.arange(5)])
+    par = np.array([[-1, 0, 2, 1]], dtype=np.int32)          # node 2 names itself
+    announce("plan: malformed parents")
+    out = sev.verify_ex(model, batch.kv, [5], torch.zeros((1, 4), dtype=torch.int32, device="cuda"), 4, parents=torch.tensor(par, device="cuda"))
+    torch.cuda.synchronize()
+    assert batch.kv.get_state(0)[2] & 2 and 0 <= int(out["accept_len"][0]) <= 4
