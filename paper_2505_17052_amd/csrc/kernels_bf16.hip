@@ -1286,12 +1286,26 @@ static void launch_gemm(GemmArgs ga, const GemmCfg &c, int m_tiles, hipStream_t 
     }
 }
 
-void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, int n_items, int n_groups, int sib, bool att_direct,
-                  float *logits_out, hipStream_t st) {
+// Rows of a chunk picked into compact buffers: q planes and residual stream of the tokens that a prefill still needs in its
+// last layer.  One block per row.
+struct TailSrc {
+    int32_t row[SEV_MAX_BATCH];
+};
+__global__ __launch_bounds__(256) void tail_gather_kernel(TailSrc src, const uint4 *q, const uint4 *h, uint4 *q2, uint4 *h2, int M, int F, int q8, int h4) {
+    const int i = blockIdx.x, r = src.row[i];
+    for (int c = threadIdx.x; c < 2 * q8; c += 256) {
+        const int pl = c >= q8, e = c - pl * q8;
+        q2[((size_t)pl * F + i) * q8 + e] = q[((size_t)pl * M + r) * q8 + e];
+    }
+    for (int c = threadIdx.x; c < h4; c += 256) h2[(size_t)i * h4 + c] = h[(size_t)r * h4 + c];
+}
+
+void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList &att_all, float *logits_out, const TailRows *tail, hipStream_t st) {
+    AttList att = att_all;
     const sev_model_desc &d = m->d;
     KvGeom g = sev_kv_geom(kv);
-    const int m_tiles_real = (rows + 31) / 32;
-    const int m_tiles = (m_tiles_real + 3) / 4 * 4;
+    int m_tiles_real = (rows + 31) / 32;
+    int m_tiles = (m_tiles_real + 3) / 4 * 4;
     auto Wp = [&](size_t off) { return (const uint4 *)(m->arena + off); };
     auto Gp = [&](size_t off) { return (const float *)(m->arena + off); };
     uint16_t *xa = (uint16_t *)kv->xa, *qp = (uint16_t *)kv->q_buf, *op = (uint16_t *)kv->o_buf, *act = (uint16_t *)kv->act;
@@ -1303,10 +1317,13 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, int n_items, 
                            kv->plan.row_tok, Gp(m->layers[0].g_attn), kv->h, xa, kv->ssq[1], kv->ssq[0], d.d_model, m_tiles);
     }
     const GemmCfg pq = choose_cfg(G_QKV, m_tiles_real, m->n_qkv / 32, d.d_model / 16, kv->part_elems, kv->tune);
-    const GemmCfg po = choose_cfg(G_O, m_tiles_real, d.d_model / 32, m->q_dim / 16, kv->part_elems, kv->tune);
-    const GemmCfg pg = choose_cfg(G_GU, m_tiles_real, d.d_ffn / 16, d.d_model / 16, kv->part_elems, kv->tune);
-    const GemmCfg pd = choose_cfg(G_DOWN, m_tiles_real, d.d_model / 32, d.d_ffn / 16, kv->part_elems, kv->tune);
-    const GemmCfg pl = choose_cfg(G_LM, m_tiles_real, d.vocab / 32, d.d_model / 16, kv->part_elems, kv->tune);
+    GemmCfg po, pg, pd;
+    auto choose = [&]() {
+        po = choose_cfg(G_O, m_tiles_real, d.d_model / 32, m->q_dim / 16, kv->part_elems, kv->tune);
+        pg = choose_cfg(G_GU, m_tiles_real, d.d_ffn / 16, d.d_model / 16, kv->part_elems, kv->tune);
+        pd = choose_cfg(G_DOWN, m_tiles_real, d.d_model / 32, d.d_ffn / 16, kv->part_elems, kv->tune);
+    };
+    choose();
     GemmArgs base;
     memset(&base, 0, sizeof(base));
     base.m_tiles_total = m_tiles;
@@ -1326,20 +1343,41 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, int n_items, 
             ga.k_layer = g.pool + (size_t)l * g.layer_stride; ga.v_offset = g.v_offset; ga.q_planes = qp;
             launch_gemm<EPI_QKV>(ga, pq, m_tiles_real, st);
         }
+        if (tail && l == d.n_layers - 1) {
+            // The rest of the last layer and the head only feed the next token of the prompts that end here: their last
+            // rows go on alone, as blocks of one node (of 8 chunks of 512 rows at the 8B shape: LM head 8 x 0.81 ms, and
+            // attention, O, gate/up and down of the last layer 8 x 0.45 ms for rows nobody reads).
+            if (!tail->F) return;
+            TailSrc src;
+            memcpy(src.row, tail->src, sizeof(src.row));
+            hipLaunchKernelGGL(tail_gather_kernel, dim3(tail->F), dim3(256), 0, st, src, (const uint4 *)qp, (const uint4 *)kv->h, (uint4 *)kv->tail_q,
+                               (uint4 *)kv->tail_h, rows, tail->F, m->q_dim / 8, d.d_model / 4);
+            launch_plan(kv, tail->pa, tail->tokens, nullptr, tail->F, tail->att.chunk_pages, tail->att.n_items, st);
+            rows = tail->F;
+            B = tail->F;
+            att = tail->att;
+            m_tiles_real = (rows + 31) / 32;
+            m_tiles = (m_tiles_real + 3) / 4 * 4;
+            qp = kv->tail_q;
+            base.h = kv->tail_h;
+            base.M = rows;
+            base.m_tiles_total = m_tiles;
+            choose();
+        }
         {
             Prof p(kv, st, PROF_ATTN);
-            const bool once = n_groups == B;             // one row group per request: every K/V byte is read by one block
+            const bool once = att.n_groups == B;         // one row group per request: every K/V byte is read by one block
 #define SEV_ATTN(WAVES_, DIRECT_, ONCE_, THREADS_, LDS_)                                                                                   \
-    hipLaunchKernelGGL((attn_bf16_kernel<WAVES_, DIRECT_, ONCE_>), dim3((unsigned)((n_items / sib + 7) / 8 * 8 * sib * d.n_kv_heads)), dim3(THREADS_), LDS_, st, \
+    hipLaunchKernelGGL((attn_bf16_kernel<WAVES_, DIRECT_, ONCE_>), dim3((unsigned)((att.n_items / att.sib + 7) / 8 * 8 * att.sib * d.n_kv_heads)), dim3(THREADS_), LDS_, st, \
                        kv->plan.it_a, kv->plan.it_b, kv->plan.it_pages, qp, g.pool, (size_t)l * g.layer_stride, g.v_offset, rows,           \
-                       d.n_q_heads | (d.n_kv_heads << 16), kv->plan, g, n_items | (sib << 24), kv->att_o, kv->att_ml, scale_log2e, op, m_tiles)
-            if (att_direct) {                            // one block of 8 waves per (request, row group, KV head): no chunks, no merge
+                       d.n_q_heads | (d.n_kv_heads << 16), kv->plan, g, att.n_items | (att.sib << 24), kv->att_o, kv->att_ml, scale_log2e, op, m_tiles)
+            if (att.direct) {                            // one block of 8 waves per (request, row group, KV head): no chunks, no merge
                 const size_t lds = (size_t)(8 * 64 * 64 + 2 * 8 * 64) * 4;      // 8 merge slots
                 if (once) SEV_ATTN(8, true, true, 512, lds); else SEV_ATTN(8, true, false, 512, lds);
             } else {
                 const size_t lds = (size_t)(4 * 64 * 64 + 2 * 4 * 64) * 4;   // 4 merge slots
                 if (once) SEV_ATTN(4, false, true, 256, lds); else SEV_ATTN(4, false, false, 256, lds);
-                hipLaunchKernelGGL(attn_merge_kernel, dim3(n_groups, d.n_kv_heads), dim3(256), 0, st, (const int4 *)kv->plan.mg_rec,
+                hipLaunchKernelGGL(attn_merge_kernel, dim3(att.n_groups, d.n_kv_heads), dim3(256), 0, st, (const int4 *)kv->plan.mg_rec,
                                    (const float *)kv->att_o, (const float2 *)kv->att_ml, op, d.n_q_heads, d.n_kv_heads, m_tiles);
             }
 #undef SEV_ATTN
@@ -1369,6 +1407,7 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, int n_items, 
     }
     {   // LM head with fused arg-max
         Prof p(kv, st, PROF_GEMM_LM);
+        const GemmCfg pl = choose_cfg(G_LM, m_tiles_real, d.vocab / 32, d.d_model / 16, kv->part_elems, kv->tune);
         GemmArgs ga = base;
         ga.W = Wp(m->off_lm); ga.X = (const uint4 *)xa; ga.n_tiles = d.vocab / 32; ga.k_steps = d.d_model / 16; ga.N = d.vocab;
         ga.ssq_in = kv->ssq[1];

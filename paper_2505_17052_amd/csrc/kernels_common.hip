@@ -116,9 +116,11 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_
         const int i0 = (blk - s_first[3][b]) * PLAN_ROWS;
         const int slot = a.slot[b], P = a.prefix[b], n = a.nd[b], row0 = s_first[0][b];
         if (i0 == 0 && t == 0) {
-            if (d.seq_len[slot] != P) atomicOr(d.err, 1u);
-            d.pend_n[slot] = 0;                                 // a new verify drops whatever was pending
-            d.pend_P[slot] = P;
+            if (!a.tail) {
+                if (d.seq_len[slot] != P) atomicOr(d.err, 1u);
+                d.pend_n[slot] = 0;                             // a new verify drops whatever was pending
+                d.pend_P[slot] = P;
+            }
             d.p.req_slot[b] = slot;
             d.p.req_P[b] = P;
             d.p.req_n[b] = n;
@@ -231,10 +233,10 @@ __global__ __launch_bounds__(64) void accept_kernel(DevPlan p, int k_max, int mo
     if (live && (par < -1 || par >= c)) par = -1;
     const int am = live ? row_argmax[row0 + c] : 0;
     int a = 0, want = next_tok[slot], mine = -1;
-    if (mode == 1) {                       // append: keep the whole chain (longer appended blocks are never re-ordered)
+    if (mode == 1) {                       // append: keep the whole chain
         a = n;
         mine = live ? c : -1;
-        want = row_argmax[row0 + n - 1];
+        want = __shfl(am, n - 1);
     } else {
         int cur = -1;
         while (true) {
@@ -282,7 +284,6 @@ __global__ void commit_copy_kernel(SlotList sl, KvGeom g, const int32_t *page_ta
     const int slot = sl.s[blockIdx.y];
     if (pend_n[slot] == 0) return;
     const int a = pend_a[slot], P = pend_P[slot];
-    if (a > SEV_MAX_DRAFT) return;                       // an appended block longer than any draft: already in place
     const int32_t *path = pend_path + (size_t)slot * SEV_MAX_DRAFT;
     bool moved = false;
     for (int j = 0; j < a; ++j) moved |= (path[j] != j);
@@ -315,6 +316,31 @@ __global__ void commit_state_kernel(SlotList sl, int B, int rollback, int32_t *s
         next_tok[slot] = pend_bonus[slot];
     }
     pend_n[slot] = 0;
+}
+
+// After a chunk of a prefill: every listed slot grows by its tokens; a prompt that ended takes the arg-max after its last
+// token as its next token (row[b] = its entry of row_argmax), the others have none yet (row[b] = -1).
+struct PrefillState {
+    uint16_t slot[SEV_MAX_BATCH];
+    int32_t n[SEV_MAX_BATCH], row[SEV_MAX_BATCH];
+};
+
+__global__ void prefill_state_kernel(PrefillState s, int B, const int32_t *row_argmax, int32_t *seq_len, int32_t *next_tok) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= B) return;
+    const int slot = s.slot[b];
+    seq_len[slot] += s.n[b];
+    next_tok[slot] = s.row[b] >= 0 ? row_argmax[s.row[b]] : -1;
+}
+
+void launch_prefill_state(const sev_kv *kv, const PlanArgs &pa, const int32_t *row, hipStream_t st) {
+    PrefillState s;
+    for (int b = 0; b < pa.B; ++b) {
+        s.slot[b] = pa.slot[b];
+        s.n[b] = pa.nd[b];
+        s.row[b] = row[b];
+    }
+    hipLaunchKernelGGL(prefill_state_kernel, dim3((pa.B + 63) / 64), dim3(64), 0, st, s, pa.B, kv->row_argmax, kv->seq_len, kv->next_tok);
 }
 
 // ---------------------------------------------------------------------------

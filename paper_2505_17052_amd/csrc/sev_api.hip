@@ -282,7 +282,8 @@ extern "C" int sev_kv_create(const sev_model *m, int max_requests, int max_rows,
     const size_t o_am = take(rows_pad * 4);
     const size_t o_lg = take(bf ? 4 : rows_pad * (size_t)d.vocab * 4);
     const size_t o_ssq = take(2 * rows_pad * 8);
-    const size_t o_tmp = take(2 * SEV_MAX_BATCH * 4);
+    const size_t tail_rows = std::min(max_requests, SEV_MAX_BATCH);
+    const size_t o_tq = take(bf ? tail_rows * 2 * m->q_dim * 2 : 4), o_thid = take(bf ? tail_rows * d.d_model * 4 : 4);
     const size_t o_rst = take(rows_pad * 8);
     const size_t o_th = take((size_t)(d.head_dim / 2) * 8);
     kv->ws_bytes = off;
@@ -337,8 +338,8 @@ extern "C" int sev_kv_create(const sev_model *m, int max_requests, int max_rows,
     kv->row_argmax = (int32_t *)(w + o_am);
     kv->logits_f32 = (float *)(w + o_lg);
     kv->row_stats = (float2 *)(w + o_rst);
-    kv->tmp_accept = (int32_t *)(w + o_tmp);
-    kv->tmp_bonus = kv->tmp_accept + SEV_MAX_BATCH;
+    kv->tail_q = (uint16_t *)(w + o_tq);
+    kv->tail_h = (float *)(w + o_thid);
     kv->ssq[0] = (unsigned long long *)(w + o_ssq);
     kv->ssq[1] = kv->ssq[0] + rows_pad;
     kv->plan.theta = (double *)(w + o_th);
@@ -510,7 +511,7 @@ extern "C" const char *sev_profile_name(int which) {
 // all run at once, one per compute unit, with chunks as small as that allows (measured on the
 // 8B-shape workloads).  Work lists that do not fit even with the largest chunks fall back to 64-page
 // chunks.  The pages of a request are then split evenly over its chunks.
-static int pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, int *n_items, int *n_groups, int *sib, bool *direct) {
+static bool pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, AttList *out) {
     const sev_model_desc &d = kv->model->d;
     const int G = d.n_q_heads / d.n_kv_heads;
     static int n_cu = 0;
@@ -524,10 +525,11 @@ static int pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, int *n_items, 
     for (int b = 0; b < pa.B; ++b) total_groups += (G * pa.nd[b] + 31) / 32;
     // row groups per request when all requests have the same number (the attention kernel then keeps the groups that
     // share a KV chunk on one XCD), else 1
-    *sib = (G * pa.nd[0] + 31) / 32;
+    out->sib = (G * pa.nd[0] + 31) / 32;
     for (int b = 1; b < pa.B; ++b)
-        if ((G * pa.nd[b] + 31) / 32 != *sib) *sib = 1;
-    if (*sib > 127) *sib = 1;
+        if ((G * pa.nd[b] + 31) / 32 != out->sib) out->sib = 1;
+    if (out->sib > 127) out->sib = 1;
+    out->n_groups = (int)total_groups;
     auto items_for = [&](int64_t cp) {
         int64_t items = 0;
         for (int b = 0; b < pa.B; ++b) {
@@ -541,16 +543,16 @@ static int pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, int *n_items, 
     // sequence and writes the attention output itself: no partial results, no merge kernel.  Longer
     // sequences are faster split over several compute units (measured on the 8B-shape workloads: one
     // compute unit needs about 0.75 us per page pair and SIMD).
-    *direct = false;
+    out->direct = false;
     int64_t max_pages = 0;
     for (int b = 0; b < pa.B; ++b)
         max_pages = std::max<int64_t>(max_pages, (std::max(pa.prefix[b] + pa.nd[b], pa.pad_tokens) + SEV_PAGE - 1) / SEV_PAGE);
     if (!kv->tune.cp && max_pages <= 64 && total_groups * d.n_kv_heads * 2 >= n_cu &&
         total_groups <= kv->max_items) {
-        *direct = true;
-        *n_items = (int)total_groups;
-        *n_groups = (int)total_groups;
-        return SEV_ATT_MAX_CP;
+        out->direct = true;
+        out->n_items = (int)total_groups;
+        out->chunk_pages = SEV_ATT_MAX_CP;
+        return true;
     }
     int64_t cp = 0;
     for (int64_t c = 8; c <= SEV_ATT_MAX_CHUNK; c += 8)
@@ -560,22 +562,22 @@ static int pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, int *n_items, 
     for (;; cp = std::min<int64_t>(cp * 2, SEV_ATT_MAX_CHUNK)) {
         const int64_t items = items_for(cp);
         if (items <= kv->max_items) {
-            *n_items = (int)items;
-            *n_groups = (int)total_groups;
-            return (int)cp;
+            out->n_items = (int)items;
+            out->chunk_pages = (int)cp;
+            return true;
         }
-        if (cp >= SEV_ATT_MAX_CHUNK) return -1;
+        if (cp >= SEV_ATT_MAX_CHUNK) return false;
     }
 }
 
-// One block forward: the shared body of sev_verify_ex and sev_prefill.  The caller has checked the
+// One block forward: the shared body of sev_verify_ex and sev_verify_sample.  The caller has checked the
 // public limits; here: slots, capacity, row budget.
 struct BlockCall {
     const int32_t *slots, *prefix_lens, *lens;   // host; lens == nullptr: every request has n_all nodes
     int n_all;
-    const int32_t *tokens;                       // device: node i of request b at tokens[b * tok_stride + tok_off + i]
-    int tok_stride, tok_off;
-    const int32_t *parents;                      // device [B][tok_stride] or nullptr (chains)
+    const int32_t *tokens;                       // device [B][k_max]
+    int k_max;
+    const int32_t *parents;                      // device [B][k_max] or nullptr (chains)
     int B, mode;
     int32_t *accept_len, *bonus_token, *accept_path, *row_argmax;
     float *logits;
@@ -587,7 +589,8 @@ struct BlockCall {
 static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStream_t st) {
     PlanArgs pa;
     pa.B = c.B;
-    pa.k_max = c.tok_stride;
+    pa.k_max = c.k_max;
+    pa.tail = 0;
     pa.pad_tokens = 0;
     int64_t rows = 0;
     for (int b = 0; b < c.B; ++b) {
@@ -604,7 +607,7 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
         pa.slot[b] = (uint16_t)slot;
         pa.prefix[b] = P;
         pa.nd[b] = n;
-        pa.tok0[b] = b * c.tok_stride + c.tok_off;
+        pa.tok0[b] = b * c.k_max;
         rows += n;
     }
     if (rows > kv->max_rows) return sev_fail(SEV_ENOSPACE, "%lld tokens exceed max_rows=%d", (long long)rows, kv->max_rows);
@@ -618,27 +621,23 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
                 return sev_fail(SEV_ENOSPACE, "request %d: padding to %d tokens exceeds the %d pages of slot %d", b, pa.pad_tokens,
                                 kv->host_pages[pa.slot[b]], pa.slot[b]);
     }
-    int n_items = 0, n_groups = 0, sib = 1, cp = 64;
-    bool att_direct = false;
-    if (m->d.dtype == SEV_BF16) {
-        cp = pick_chunk_pages(kv, pa, &n_items, &n_groups, &sib, &att_direct);
-        if (cp < 0) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
-    }
+    AttList att = {0, 0, 1, 64, false};
+    if (m->d.dtype == SEV_BF16 && !pick_chunk_pages(kv, pa, &att)) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
     kv->plan.causal = c.parents ? 0 : 1;
     for (int b = 0; b < c.B; ++b) kv->host_tree[pa.slot[b]] = c.parents ? 1 : 0;
     {
         Prof p(kv, st, PROF_OTHER);
-        launch_plan(kv, pa, c.tokens, c.parents, (int)rows, cp, n_items, st);
+        launch_plan(kv, pa, c.tokens, c.parents, (int)rows, att.chunk_pages, att.n_items, st);
     }
     if (m->d.dtype == SEV_F32) f32_forward(m, kv, (int)rows, c.B, c.logits, st);
-    else bf16_forward(m, kv, (int)rows, c.B, n_items, n_groups, sib, att_direct, c.logits, st);
+    else bf16_forward(m, kv, (int)rows, c.B, att, c.logits, nullptr, st);
     {
         Prof p(kv, st, PROF_OTHER);
         if (c.draft_probs)
-            launch_sample(kv, c.B, c.tok_stride, (int)rows, c.tokens, c.parents, c.logits, c.draft_probs, kv->row_stats, c.temperature,
+            launch_sample(kv, c.B, c.k_max, (int)rows, c.tokens, c.parents, c.logits, c.draft_probs, kv->row_stats, c.temperature,
                           c.u_accept, c.u_emit, c.accept_len, c.bonus_token, c.accept_path, st);
         else
-            launch_accept(kv, c.B, c.tok_stride, c.mode & 1, c.tokens, c.parents, c.accept_len, c.bonus_token, c.accept_path, c.row_argmax, st);
+            launch_accept(kv, c.B, c.k_max, c.mode & 1, c.tokens, c.parents, c.accept_len, c.bonus_token, c.accept_path, c.row_argmax, st);
     }
     SEV_HIP(hipGetLastError());
     return SEV_OK;
@@ -660,7 +659,7 @@ extern "C" int sev_verify_ex(const sev_model *m, sev_kv *kv, const sev_verify_ar
     BlockCall c;
     memset(&c, 0, sizeof(c));
     c.slots = a->slots; c.prefix_lens = a->prefix_lens; c.lens = a->draft_lens; c.n_all = a->k_max;
-    c.tokens = a->draft_tokens; c.tok_stride = a->k_max; c.tok_off = 0; c.parents = a->parents;
+    c.tokens = a->draft_tokens; c.k_max = a->k_max; c.parents = a->parents;
     c.B = a->B; c.mode = a->mode;
     c.accept_len = a->accept_len; c.bonus_token = a->bonus_token; c.accept_path = a->accept_path;
     c.row_argmax = a->row_argmax; c.logits = a->logits;
@@ -683,7 +682,7 @@ extern "C" int sev_verify_sample(const sev_model *m, sev_kv *kv, const sev_sampl
     BlockCall c;
     memset(&c, 0, sizeof(c));
     c.slots = a->slots; c.prefix_lens = a->prefix_lens; c.lens = a->draft_lens; c.n_all = a->k_max;
-    c.tokens = a->draft_tokens; c.tok_stride = a->k_max; c.tok_off = 0; c.parents = a->parents;
+    c.tokens = a->draft_tokens; c.k_max = a->k_max; c.parents = a->parents;
     c.B = a->B; c.mode = 0;
     c.accept_len = a->accept_len; c.bonus_token = a->emitted_token; c.accept_path = a->accept_path; c.logits = a->logits_ws;
     c.draft_probs = a->draft_probs; c.u_accept = a->u_accept; c.u_emit = a->u_emit; c.temperature = a->temperature;
@@ -739,15 +738,20 @@ extern "C" int sev_verify_sample_static(const sev_model *m, sev_kv *kv, const se
     return sev_verify_sample(m, kv, &b, stream);
 }
 
-// Prefill: long chains are fed through the same forward pass in chunks that fit the row budget, each
-// chunk appended (all tokens kept) and committed before the next one starts.
+// Prefill: the prompts' tokens go through the same forward pass in chunks of as many rows as the workspace holds, filled
+// request after request (a chunk may end one prompt, hold a whole one and begin a third), each chunk appended before the
+// next one starts.  2048 rows is where the GEMMs stop gaining from more; fewer are taken only if the attention's work list
+// would not hold them (very long prefixes).
+#define SEV_PREFILL_ROWS 2048
+
 extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots, const int32_t *start_lens,
                            const int32_t *n_tokens, const int32_t *tokens, int B, int t_max, void *stream) {
     if (!m || !kv) return sev_fail(SEV_EINVAL, "null argument");
     if (kv->model != m) return sev_fail(SEV_EINVAL, "cache was created for another model");
     if (B < 1 || B > SEV_MAX_BATCH) return sev_fail(SEV_EINVAL, "B=%d outside 1..%d", B, SEV_MAX_BATCH);
     if (!start_lens || !n_tokens || !tokens || t_max < 1) return sev_fail(SEV_EINVAL, "start_lens, n_tokens and tokens are required");
-    int64_t longest = 0;
+    if ((int64_t)B * t_max > INT32_MAX) return sev_fail(SEV_EINVAL, "%d x %d tokens", B, t_max);
+    uint16_t sl[SEV_MAX_BATCH];
     for (int b = 0; b < B; ++b) {
         if (n_tokens[b] < 1 || n_tokens[b] > t_max) return sev_fail(SEV_EINVAL, "request %d: %d tokens outside 1..%d", b, n_tokens[b], t_max);
         const int slot = slots ? slots[b] : b;
@@ -755,48 +759,64 @@ extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots,
         if (start_lens[b] < 0 || (int64_t)start_lens[b] + n_tokens[b] > (int64_t)kv->host_pages[slot] * SEV_PAGE)
             return sev_fail(SEV_ENOSPACE, "request %d: %d+%d tokens exceed the %d pages of slot %d", b, start_lens[b], n_tokens[b],
                             kv->host_pages[slot], slot);
-        longest = std::max<int64_t>(longest, n_tokens[b]);
+        sl[b] = (uint16_t)slot;
+        for (int e = 0; e < b; ++e)
+            if (sl[e] == slot) return sev_fail(SEV_EINVAL, "slot %d listed twice", slot);
     }
     hipStream_t st = (hipStream_t)stream;
-    // chunk length: all still-active requests advance together; rows of a chunk fit max_rows, and a request's
-    // rows per chunk stay moderate so that the attention work list fits
-    int32_t sl[SEV_MAX_BATCH], pre[SEV_MAX_BATCH], len[SEV_MAX_BATCH], idx[SEV_MAX_BATCH];
-    for (int64_t done = 0; done < longest;) {
-        int act = 0;
-        for (int b = 0; b < B; ++b)
-            if (n_tokens[b] > done) idx[act++] = b;
-        const int64_t ch = std::max<int64_t>(1, std::min<int64_t>(512, kv->max_rows / act));
-        for (int r = 0; r < act; ++r) {
-            const int b = idx[r];
-            sl[r] = slots ? slots[b] : b;
-            pre[r] = start_lens[b] + (int32_t)done;
-            len[r] = (int32_t)std::min<int64_t>(ch, n_tokens[b] - done);
-        }
-        // the chunk's rows must be contiguous per request in the token array: request r reads row idx[r] of tokens.
-        // Requests that have finished leave holes in the batch, so each active request is issued with its own row.
-        // (B is small on this path; one block call per chunk covers all requests when none has finished.)
-        bool dense = (act == B);
-        if (dense) {
-            BlockCall c;
-            memset(&c, 0, sizeof(c));
-            c.slots = sl; c.prefix_lens = pre; c.lens = len; c.tokens = tokens; c.tok_stride = t_max; c.tok_off = (int)done;
-            c.B = act; c.mode = 1; c.accept_len = kv->tmp_accept; c.bonus_token = kv->tmp_bonus;
-            const int rc = run_block(m, kv, c, st);
-            if (rc != SEV_OK) return rc;
-            launch_commit(kv, sl, act, false, st);
-        } else {
-            for (int r = 0; r < act; ++r) {
-                BlockCall c;
-                memset(&c, 0, sizeof(c));
-                c.slots = sl + r; c.prefix_lens = pre + r; c.lens = len + r;
-                c.tokens = tokens + (size_t)idx[r] * t_max; c.tok_stride = t_max; c.tok_off = (int)done;
-                c.B = 1; c.mode = 1; c.accept_len = kv->tmp_accept; c.bonus_token = kv->tmp_bonus;
-                const int rc = run_block(m, kv, c, st);
-                if (rc != SEV_OK) return rc;
-                launch_commit(kv, sl + r, 1, false, st);
+    const bool bf = m->d.dtype == SEV_BF16;
+    kv->plan.causal = 1;
+    for (int b = 0; b < B; ++b) kv->host_tree[sl[b]] = 0;
+    int32_t done[SEV_MAX_BATCH] = {0};
+    for (int first = 0; first < B;) {                     // `first`: the first prompt with tokens left
+        PlanArgs pa;
+        AttList att = {0, 0, 1, 64, false};
+        TailRows tail;
+        int32_t row[SEV_MAX_BATCH];                       // entry of row_argmax that holds a finished prompt's next token
+        int rows = 0;
+        for (int budget = std::min(kv->max_rows, SEV_PREFILL_ROWS);; budget = (budget + 1) / 2) {
+            memset(&pa, 0, sizeof(pa));
+            memset(&tail, 0, sizeof(tail));
+            pa.k_max = t_max;
+            rows = 0;
+            for (int b = first; b < B && rows < budget; ++b) {
+                const int n = std::min(n_tokens[b] - done[b], budget - rows), r = pa.B++;
+                pa.slot[r] = sl[b];
+                pa.prefix[r] = start_lens[b] + done[b];
+                pa.nd[r] = n;
+                pa.tok0[r] = b * t_max + done[b];
+                row[r] = -1;
+                rows += n;
+                if (done[b] + n == n_tokens[b]) {         // its last token goes on to the head
+                    const int f = tail.F++;
+                    tail.pa.slot[f] = sl[b];
+                    tail.pa.prefix[f] = start_lens[b] + n_tokens[b] - 1;
+                    tail.pa.nd[f] = 1;
+                    tail.pa.tok0[f] = b * t_max + n_tokens[b] - 1;
+                    tail.src[f] = rows - 1;
+                    row[r] = bf ? f : rows - 1;
+                }
             }
+            if (!bf || pick_chunk_pages(kv, pa, &att)) break;
+            if (budget == 1) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
         }
-        done += ch;
+        tail.pa.B = tail.F;
+        tail.pa.k_max = t_max;
+        tail.pa.tail = 1;
+        tail.tokens = tokens;
+        if (bf && tail.F && !pick_chunk_pages(kv, tail.pa, &tail.att)) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
+        {
+            Prof p(kv, st, PROF_OTHER);
+            launch_plan(kv, pa, tokens, nullptr, rows, att.chunk_pages, att.n_items, st);
+        }
+        if (bf) bf16_forward(m, kv, rows, pa.B, att, nullptr, &tail, st);
+        else f32_forward(m, kv, rows, pa.B, nullptr, st);
+        {
+            Prof p(kv, st, PROF_OTHER);
+            launch_prefill_state(kv, pa, row, st);
+        }
+        for (int r = 0; r < pa.B; ++r) done[first + r] += pa.nd[r];
+        while (first < B && done[first] == n_tokens[first]) ++first;
     }
     SEV_HIP(hipGetLastError());
     return SEV_OK;

@@ -54,6 +54,7 @@ struct sev_model {
 // kernel's arguments may take; slots are below 65536, see sev_kv_create).
 struct PlanArgs {
     int B, k_max;
+    int tail;                 // 1: rows of blocks that are already in the cache (end of a prefill): the slots' state is left alone
     int pad_tokens;           // > 0: attention walks every request's pages up to this many tokens (padded-KV comparison variant)
     uint16_t slot[SEV_MAX_BATCH];
     int32_t prefix[SEV_MAX_BATCH];
@@ -131,7 +132,8 @@ struct sev_kv {
     float *lm_val;            // [tiles][rows] partial arg-max values
     int32_t *lm_idx;
     int32_t *row_argmax;      // [rows]
-    int32_t *tmp_accept, *tmp_bonus;         // [SEV_MAX_BATCH] outputs of internal block runs (prefill)
+    uint16_t *tail_q;         // bf16, end of a prefill: q planes [2][requests][Hq*hd] and residual rows [requests][d] of the last
+    float *tail_h;            //   token of every prompt that ends in the chunk
     float2 *row_stats;        // [rows] (largest logit, sum of exp((logit - max) / T)) of the stochastic rule
     float *logits_f32;        // f32 path only: [rows][vocab]
 
@@ -169,6 +171,7 @@ void launch_accept(const sev_kv *kv, int B, int k_max, int mode, const int32_t *
 void launch_sample(const sev_kv *kv, int B, int k_max, int rows, const int32_t *tokens, const int32_t *parents, const float *logits,
                    const float *draft_probs, float2 *stats, float temperature, const float *u_acc, const float *u_emit,
                    int32_t *accept_len, int32_t *emitted, int32_t *accept_path, hipStream_t st);
+void launch_prefill_state(const sev_kv *kv, const PlanArgs &pa, const int32_t *row, hipStream_t st);
 void launch_commit(const sev_kv *kv, const int32_t *slots_dev_by_value, int B, bool rollback, hipStream_t st);
 void launch_kv_copy(const sev_kv *kv, int slot, int layer, int start, int n, void *k, void *v, int to_cache, hipStream_t st);
 void launch_argmax_rows_f32(const float *logits, int rows, int vocab, int32_t *out, hipStream_t st);
@@ -179,5 +182,18 @@ void f32_forward(const sev_model *m, sev_kv *kv, int rows, int B, float *logits_
 
 // bf16 path
 void launch_pack_bf16(uint16_t *dst, const uint16_t *src, int n_rows, int K, int mode, int tile_add, hipStream_t st);
-void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, int n_items, int n_groups, int sib, bool att_direct,
-                  float *logits_out, hipStream_t st);
+
+// Work list of the attention over one batch of blocks (see pick_chunk_pages).
+struct AttList {
+    int n_items, n_groups, sib, chunk_pages;
+    bool direct;
+};
+// End of a prefill chunk: only the last token of each of F prompts is wanted from the last layer on (F = 0: none).
+struct TailRows {
+    int F;
+    PlanArgs pa;                     // the F tokens as blocks of one node behind their own prefix
+    AttList att;
+    int32_t src[SEV_MAX_BATCH];      // their rows in the chunk
+    const int32_t *tokens;
+};
+void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList &att, float *logits_out, const TailRows *tail, hipStream_t st);

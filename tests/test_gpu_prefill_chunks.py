@@ -1,0 +1,52 @@
+"""sev_prefill over batches of unequal prompts: row budgets that cut prompts anywhere, chunks that end no prompt, one, or
+several, a one-token prompt, prefixes that are already there.  K/V against the oracle's prefill (relative rms: 2e-4 in layer
+0, where only float32 sums differ, 8e-3 in the deeper layers, whose one-step flips of the rounded cache feed each other) and
+the next token, which comes from the last row alone, where the oracle's arg-max is firm."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import verify_oracle as vo
+from tests.helpers import oracle_model, announce
+
+pytestmark = pytest.mark.gpu
+SHAPE, SEED, LENS = synth.MINI_BF16, 606, [5, 130, 1, 64, 33]
+
+
+@pytest.fixture(scope="module")
+def setup():
+    from paper_2505_17052_amd import harness
+    om = oracle_model(SHAPE, SEED, dtype=np.float32)
+    rng = np.random.default_rng(9)
+    prompts = [rng.integers(0, SHAPE.vocab, n) for n in LENS]
+    caches, firm = [], []
+    for p in prompts:
+        caches.append(vo.prefill(om, p, len(p)))
+        t = np.sort(vo.forward_blocks(om, [vo.Cache(om, len(p))], [p], [vo.chain_parents(len(p))])[0][0][-1])[-2:]
+        firm.append(t[1] - t[0] >= 0.05)
+    return harness, harness.build_model(SHAPE, SEED), prompts, caches, firm
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+@pytest.mark.parametrize("budget,split", [(3, 0), (32, 0), (64, 0), (65, 0), (232, 0), (512, 0), (48, 1), (512, 1)])
+def test_ragged_prompts(setup, budget, split):
+    harness, model, prompts, caches, firm = setup
+    announce(f"prefill chunks: prompts {LENS}, {budget} rows, {'in two calls' if split else 'in one call'}")
+    batch = harness.Batch(model, SHAPE, [n + 4 for n in LENS], max_rows=budget, seed=SEED)
+    if split:                                                # the second call continues the first one's prefixes
+        batch.prefill([p[:len(p) // 2] for p in prompts if len(p) > 1], [b for b, p in enumerate(prompts) if len(p) > 1])
+        batch.prefill([p[len(p) // 2:] for p in prompts])
+    else:
+        batch.prefill(prompts)
+    for b, n in enumerate(LENS):
+        length, nxt, flags = batch.kv.get_state(b)
+        assert (length, flags) == (n, 0)
+        if firm[b]:
+            assert nxt == caches[b].next_tok
+        for l in range(SHAPE.n_layers):
+            k, v = batch.export_kv(b, l, 0, n)
+            assert _rel(k, caches[b].K[l][:n]) < (2e-4 if l == 0 else 8e-3) and _rel(v, caches[b].V[l][:n]) < (2e-4 if l == 0 else 8e-3)
