@@ -21,179 +21,310 @@ __global__ void embed_f32_kernel(const float *E, const int32_t *row_tok, float *
     for (int i = threadIdx.x; i < d; i += blockDim.x) dst[i] = src[i];
 }
 
-// y = x * rsqrt(mean(x^2) + eps) * g, one block per row
-__global__ __launch_bounds__(256) void rmsnorm_f32_kernel(const float *h, const float *g, float *y, int d, float eps) {
-    __shared__ float red[256];
-    const float *x = h + (size_t)blockIdx.x * d;
-    float ss = 0.f;
-    for (int i = threadIdx.x; i < d; i += 256) ss += x[i] * x[i];
-    red[threadIdx.x] = ss;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
-    }
-    const float r = 1.0f / sqrtf(red[0] / (float)d + eps);
-    for (int i = threadIdx.x; i < d; i += 256) y[(size_t)blockIdx.x * d + i] = x[i] * r * g[i];
-}
+// ---------------------------------------------------------------------------
+// Y[m][c] = sum_k X[m][k] * W[c][k], with the norm in front and the stage behind it fused in.
+//
+// A wave owns P column PAIRS x R rows and splits K over its lanes (16 bytes per lane and matrix row), so nothing goes
+// through LDS and no barrier is needed; the 64 partial sums are then folded by exchanging halves (an accumulator array of
+// V values takes V - 1 exchanges instead of 6 V) and every group of 64 / V lanes ends up with one finished pair.  A pair
+// is what the following stage has to see together: the two halves of a rotary pair, gate and up of one feed-forward
+// column, or just two neighbouring columns.
+//
+// What binds it at the sizes this path is for (a few rows, K of a few hundred) is latency and the number of launches: K
+// is one to three loads deep per lane, all in flight at once, and the norm (its sum of squares is a by-product of reading
+// X), rotary embedding, cache append, SwiGLU and residual addition cost no launch of their own.  The kernel before it
+// took K in steps of 32 through LDS, two barriers each, with N / 64 blocks: O and down (N = 256) ran on 4 blocks and took
+// 38 us on average with K = 256 and 688 and four rows; 3.5 us now.  One request, 4 candidates: 548 -> 76 us a step.
+// ---------------------------------------------------------------------------
+enum { F32_PLAIN = 0, F32_RESID, F32_SWIGLU, F32_QKV };
 
-// Y[m][n] (+)= sum_k X[m][k] * W[n][k].  Block: 64 columns x 16 rows, K tiled by 32 through LDS.
-template <bool ACC>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *X, const float *W, float *Y, int M, int N, int K) {
-    __shared__ float Ws[64][33];
-    __shared__ float Xs[16][33];
-    const int tn = threadIdx.x & 63, tm = threadIdx.x >> 6;
-    const int n0 = blockIdx.x * 64, m0 = blockIdx.y * 16;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += 32) {
-        for (int i = threadIdx.x; i < 64 * 32; i += 256) {
-            const int r = i >> 5, c = i & 31;
-            Ws[r][c] = (n0 + r < N && k0 + c < K) ? W[(size_t)(n0 + r) * K + k0 + c] : 0.f;
-        }
-        for (int i = threadIdx.x; i < 16 * 32; i += 256) {
-            const int r = i >> 5, c = i & 31;
-            Xs[r][c] = (m0 + r < M && k0 + c < K) ? X[(size_t)(m0 + r) * K + k0 + c] : 0.f;
-        }
-        __syncthreads();
+struct GemmF32 {
+    const float *X, *W, *gain;       // gain: RMS norm of X in front (its gains), or null
+    float *Y;
+    int M, K, N, n_pairs;            // N: row stride of Y
+    float inv_k, eps;
+    // F32_QKV
+    const float2 *row_cs;
+    const int32_t *row_kvloc;
+    float *k_layer, *v_layer;
+    int hd, Hq, Hkv;
+};
+
+// Sum over the wave of V values per lane: lane ends up with value lane / (64 / V).
+template <int V>
+__device__ __forceinline__ float wave_sum_split(float (&a)[V], int lane) {
+    int off = 32;
 #pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            const float w = Ws[tn][k];
+    for (int cnt = V; cnt > 1; cnt >>= 1, off >>= 1) {
+        const bool up = lane & off;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[j] += Xs[tm + 4 * j][k] * w;
-        }
-        __syncthreads();
-    }
-    if (n0 + tn < N) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = m0 + tm + 4 * j;
-            if (m < M) {
-                float *y = Y + (size_t)m * N + n0 + tn;
-                *y = ACC ? *y + acc[j] : acc[j];
+        for (int i = 0; i < V / 2; ++i)
+            if (i < cnt / 2) {
+                const float keep = up ? a[i + cnt / 2] : a[i], send = up ? a[i] : a[i + cnt / 2];
+                a[i] = keep + __shfl_xor(send, off);
             }
+    }
+    for (; off > 0; off >>= 1) a[0] += __shfl_xor(a[0], off);
+    return a[0];
+}
+
+template <int R, int P, int EPI, bool VEC>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g) {
+    constexpr int V = R * P, E = VEC ? 4 : 1;
+    const int lane = threadIdx.x & 63;
+    const int pair0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * P, m0 = blockIdx.y * R;
+    if (pair0 >= g.n_pairs) return;                           // (no barrier in this kernel)
+    auto cols = [&](int j, int &c0, int &c1) {
+        if constexpr (EPI == F32_SWIGLU) { c0 = j; c1 = g.n_pairs + j; }
+        else if constexpr (EPI == F32_QKV) { const int half = g.hd >> 1, head = j / half; c0 = head * g.hd + j - head * half; c1 = c0 + half; }
+        else { c0 = 2 * j; c1 = min(2 * j + 1, g.N - 1); }
+    };
+    const float *w0[P], *w1[P], *x[R];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        int c0, c1;
+        cols(min(pair0 + p, g.n_pairs - 1), c0, c1);
+        w0[p] = g.W + (size_t)c0 * g.K;
+        w1[p] = g.W + (size_t)c1 * g.K;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = g.X + (size_t)min(m0 + r, g.M - 1) * g.K;
+    float a0[V], a1[V], ss[R];
+#pragma unroll
+    for (int i = 0; i < V; ++i) a0[i] = a1[i] = 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) ss[r] = 0.f;
+    auto load = [&](const float *p, float (&v)[E]) {
+        if constexpr (VEC) {
+            const float4 q = *(const float4 *)p;
+            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+        } else v[0] = *p;
+    };
+    const bool norm = g.gain != nullptr;
+#pragma unroll (R * P <= 8 ? 2 : 1)
+    for (int k = lane * E; k < g.K; k += 64 * E) {            // (VEC: K is a multiple of 4)
+        float wa[P][E], wb[P][E], gn[E];
+#pragma unroll
+        for (int p = 0; p < P; ++p) { load(w0[p] + k, wa[p]); load(w1[p] + k, wb[p]); }
+        if (norm) load(g.gain + k, gn);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float xv[E];
+            load(x[r] + k, xv);
+            if (norm) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) { ss[r] += xv[e] * xv[e]; xv[e] *= gn[e]; }
+            }
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    a0[p * R + r] += xv[e] * wa[p][e];
+                    a1[p * R + r] += xv[e] * wb[p][e];
+                }
         }
     }
-}
-
-static void gemm_f32(const float *X, const float *W, float *Y, int M, int N, int K, bool acc, hipStream_t st) {
-    dim3 grid((N + 63) / 64, (M + 15) / 16);
-    if (acc) hipLaunchKernelGGL(gemm_f32_kernel<true>, grid, dim3(256), 0, st, X, W, Y, M, N, K);
-    else hipLaunchKernelGGL(gemm_f32_kernel<false>, grid, dim3(256), 0, st, X, W, Y, M, N, K);
-}
-
-// Rotary embedding of q (in place) and k, and append of k, v to the paged cache at position P + node.
-// grid (rows, Hq + Hkv): blocks y < Hq rotate a query head, the others handle a KV head.
-__global__ void rope_kv_f32_kernel(float *qkv, DevPlan p, KvGeom g, const int32_t *page_table, int max_pages, int layer,
-                                   int Hq, int n_qkv) {
-    const int m = blockIdx.x, hy = blockIdx.y, hd = g.hd, half = hd / 2;
-    const float2 *cs = p.row_cs + (size_t)m * half;
-    float *row = qkv + (size_t)m * n_qkv;
-    if (hy < Hq) {
-        float *q = row + hy * hd;
-        for (int i = threadIdx.x; i < half; i += blockDim.x) {
-            const float a = q[i], b = q[i + half], c = cs[i].x, s = cs[i].y;
-            q[i] = a * c - b * s;
-            q[i + half] = b * c + a * s;
+    float va = wave_sum_split<V>(a0, lane), vb = wave_sum_split<V>(a1, lane);
+    constexpr int LPV = 64 / V;
+    const int idx = lane / LPV, p = idx / R, r = idx - p * R, m = m0 + r, j = pair0 + p;
+    if (norm) {
+        float sq[V];                                          // the same fold, so that every lane ends with its own row's sum
+#pragma unroll
+        for (int i = 0; i < V; ++i) sq[i] = ss[i % R];
+        const float rs = 1.0f / sqrtf(wave_sum_split<V>(sq, lane) * g.inv_k + g.eps);
+        va *= rs;
+        vb *= rs;
+    }
+    if (lane % LPV || m >= g.M || j >= g.n_pairs) return;
+    int c0, c1;
+    cols(j, c0, c1);
+    float *y = g.Y + (size_t)m * g.N;
+    if constexpr (EPI == F32_SWIGLU) {
+        y[j] = va / (1.0f + expf(-va)) * vb;
+    } else if constexpr (EPI == F32_QKV) {
+        // rotary embedding of q and k; k and v go to the paged cache at position P + node
+        const int half = g.hd >> 1, head = j / half, i = j - head * half;
+        if (head < g.Hq + g.Hkv) {
+            const float2 cs = g.row_cs[(size_t)m * half + i];
+            const float t = va * cs.x - vb * cs.y;
+            vb = vb * cs.x + va * cs.y;
+            va = t;
         }
-        return;
-    }
-    const int h = hy - Hq, b = p.row_req[m];
-    const int tok = p.req_P[b] + p.row_node[m];
-    const int slot = p.req_slot[b];
-    const size_t blk = (size_t)SEV_PAGE * hd;
-    const size_t pb = ((size_t)page_table[(size_t)slot * max_pages + tok / SEV_PAGE] * g.Hkv + h) * blk;
-    float *kc = (float *)(g.pool + (size_t)layer * g.layer_stride) + pb + (size_t)(tok % SEV_PAGE) * hd;
-    float *vc = (float *)(g.pool + (size_t)layer * g.layer_stride + g.v_offset) + pb + (size_t)(tok % SEV_PAGE) * hd;
-    const float *k = row + Hq * hd + h * hd;
-    const float *v = row + (Hq + g.Hkv) * hd + h * hd;
-    for (int i = threadIdx.x; i < half; i += blockDim.x) {
-        const float a = k[i], bb = k[i + half], c = cs[i].x, s = cs[i].y;
-        kc[i] = a * c - bb * s;
-        kc[i + half] = bb * c + a * s;
-        vc[i] = v[i];
-        vc[i + half] = v[i + half];
+        if (head < g.Hq) {
+            y[c0] = va;
+            y[c1] = vb;
+        } else {
+            const bool is_k = head < g.Hq + g.Hkv;
+            const int loc = g.row_kvloc[m], h = head - g.Hq - (is_k ? 0 : g.Hkv);
+            float *c = (is_k ? g.k_layer : g.v_layer) + (((size_t)(loc >> 4) * g.Hkv + h) * SEV_PAGE + (loc & 15)) * g.hd + i;
+            c[0] = va;
+            c[half] = vb;
+        }
+    } else if constexpr (EPI == F32_RESID) {
+        y[c0] += va;
+        if (c1 != c0) y[c1] += vb;
+    } else {
+        y[c0] = va;
+        if (c1 != c0) y[c1] = vb;
     }
 }
 
-// Masked attention of one (row, query head) per wave over the request's paged cache:
-// all prefix positions, plus the block's nodes that are ancestors-or-self of the row's node (chains:
-// the nodes up to the row's own, whatever the block length).
-__global__ __launch_bounds__(64) void attn_f32_kernel(const float *qkv, float *out, DevPlan p, KvGeom g,
-                                                      const int32_t *page_table, int max_pages, int layer, int Hq,
-                                                      int n_qkv, float scale) {
-    const int m = blockIdx.x, j = blockIdx.y, lane = threadIdx.x, hd = g.hd;
+template <int EPI>
+static void gemm_f32(GemmF32 g, hipStream_t st) {
+    const bool vec = g.K % 4 == 0;       // matrices start on 256 bytes (or a multiple of K values behind that), so every row is 16-byte aligned then
+    // rows of a wave: as many as there are, up to 16; two pairs per wave (half the reads of X) only where there are
+    // waves enough without them (4 per compute unit)
+    const int R = g.M <= 4 ? 4 : (g.M <= 8 ? 8 : 16);
+    const int rb = (g.M + R - 1) / R;
+    const int P = R == 16 && (int64_t)g.n_pairs * rb >= 2048 ? 2 : 1;
+    const dim3 grid((unsigned)((g.n_pairs + 4 * P - 1) / (4 * P)), (unsigned)rb);
+#define SEV_F32_LAUNCH(R_, P_)                                                                                                \
+    do {                                                                                                                      \
+        if (vec) hipLaunchKernelGGL((gemm_f32_kernel<R_, P_, EPI, true>), grid, dim3(256), 0, st, g);                         \
+        else hipLaunchKernelGGL((gemm_f32_kernel<R_, P_, EPI, false>), grid, dim3(256), 0, st, g);                            \
+    } while (0)
+    if (R == 4) SEV_F32_LAUNCH(4, 1);
+    else if (R == 8) SEV_F32_LAUNCH(8, 1);
+    else if (P == 1) SEV_F32_LAUNCH(16, 1);
+    else SEV_F32_LAUNCH(16, 2);
+#undef SEV_F32_LAUNCH
+}
+
+// ---------------------------------------------------------------------------
+// Masked attention of one (row, query head) per block over the request's paged cache: all prefix positions, plus the
+// block's nodes that are ancestors-or-self of the row's node (chains: the nodes up to the row's own, whatever the length).
+//
+// LPK lanes share a key (four of its dims each), so a block walks 256 / LPK keys at a time with an online softmax per lane
+// group; the groups meet once, at the end, in LDS.  Four keys of a group are in flight together.  Latency binds it (a
+// prefix of 64 is one round of loads).  One wave per (row, head) that took the keys one after the other needed 0.7 us per
+// key: 46.6 us at 68 positions, 6.4 us now (8 chains of 16 on prefixes of 100 to 1000: a step of 2135 us, now 386).
+// ---------------------------------------------------------------------------
+template <int LPK, bool VEC>
+__global__ __launch_bounds__(256) void attn_f32_kernel(const float *qkv, float *out, DevPlan p, const float *Kl, const float *Vl, int Hkv, int hd,
+                                                       const int32_t *page_table, int max_pages, int Hq, int n_qkv, float scale) {
+    constexpr int NG = 256 / LPK, U = 4;
+    __shared__ float s_m[NG], s_l[NG], s_o[NG * LPK * 4];
+    const int m = blockIdx.x, j = blockIdx.y, e = threadIdx.x % LPK, gid = threadIdx.x / LPK;
     const int b = p.row_req[m], P = p.req_P[b], n = p.req_n[b], slot = p.req_slot[b];
     const unsigned long long anc = p.row_anc[m];
     const int node = p.row_node[m];
-    const int h = (j * g.Hkv) / Hq;
-    const float *q = qkv + (size_t)m * n_qkv + j * hd;
+    const int h = (j * Hkv) / Hq;
     const int32_t *pt = page_table + (size_t)slot * max_pages;
-    const size_t blk = (size_t)SEV_PAGE * hd;
-    const float *Kl = (const float *)(g.pool + (size_t)layer * g.layer_stride);
-    const float *Vl = (const float *)(g.pool + (size_t)layer * g.layer_stride + g.v_offset);
-    float qv[4], acc[4] = {0.f, 0.f, 0.f, 0.f};
+    const int d0 = 4 * e;
+    auto load = [&](const float *v, float (&o)[4]) {
+        if constexpr (VEC) {
+            const float4 q = d0 < hd ? *(const float4 *)(v + d0) : make_float4(0.f, 0.f, 0.f, 0.f);
+            o[0] = q.x; o[1] = q.y; o[2] = q.z; o[3] = q.w;
+        } else {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) qv[r] = (lane + 64 * r < hd) ? q[lane + 64 * r] : 0.f;
+            for (int i = 0; i < 4; ++i) o[i] = d0 + i < hd ? v[d0 + i] : 0.f;
+        }
+    };
+    float q[4], acc[4] = {0.f, 0.f, 0.f, 0.f};
+    load(qkv + (size_t)m * n_qkv + j * hd, q);
     float mx = -INFINITY, den = 0.f;
-    for (int t = 0; t < P + n; ++t) {
-        if (t >= P && (p.causal ? (t - P > node) : !((anc >> (t - P)) & 1ull))) continue;
-        const size_t pb = ((size_t)pt[t / SEV_PAGE] * g.Hkv + h) * blk + (size_t)(t % SEV_PAGE) * hd;
-        float s = 0.f;
+    const int T = p.causal ? P + node + 1 : P + n;
+    for (int t0 = gid; t0 < T; t0 += NG * U) {
+        float kf[U][4], vf[U][4], s[U];
+        bool vis[U];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (lane + 64 * r < hd) s += qv[r] * Kl[pb + lane + 64 * r];
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-        s *= scale;
-        const float mn = fmaxf(mx, s);
-        const float corr = expf(mx - mn), pe = expf(s - mn);
-        den = den * corr + pe;
+        for (int u = 0; u < U; ++u) {
+            const int t = t0 + u * NG, tc = min(t, T - 1);
+            vis[u] = t < T && (p.causal || t < P || ((anc >> (t - P)) & 1ull));
+            const size_t at = (((size_t)pt[tc / SEV_PAGE] * Hkv + h) * SEV_PAGE + tc % SEV_PAGE) * hd;
+            load(Kl + at, kf[u]);
+            load(Vl + at, vf[u]);
+        }
+        float mn = mx;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (lane + 64 * r < hd) acc[r] = acc[r] * corr + pe * Vl[pb + lane + 64 * r];
+        for (int u = 0; u < U; ++u) {
+            float d = (q[0] * kf[u][0] + q[1] * kf[u][1]) + (q[2] * kf[u][2] + q[3] * kf[u][3]);
+#pragma unroll
+            for (int o = LPK / 2; o > 0; o >>= 1) d += __shfl_xor(d, o);
+            s[u] = d * scale;
+            if (vis[u]) mn = fmaxf(mn, s[u]);
+        }
+        const float base = mn == -INFINITY ? 0.f : mn, corr = expf(mx - base);
+        den *= corr;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] *= corr;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float pe = vis[u] ? expf(s[u] - base) : 0.f;
+            den += pe;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] += vis[u] ? pe * vf[u][i] : 0.f;
+        }
         mx = mn;
     }
+    if (e == 0) { s_m[gid] = mx; s_l[gid] = den; }
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-        if (lane + 64 * r < hd) out[(size_t)m * (Hq * hd) + j * hd + lane + 64 * r] = acc[r] / den;
+    for (int i = 0; i < 4; ++i) s_o[(gid * LPK + e) * 4 + i] = acc[i];
+    __syncthreads();
+    float top = -INFINITY;                                    // every row sees itself: some group has a finite maximum
+#pragma unroll
+    for (int g = 0; g < NG; ++g) top = fmaxf(top, s_m[g]);
+    if ((int)threadIdx.x < hd) {
+        float l = 0.f, o = 0.f;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const float w = expf(s_m[g] - top);
+            l += w * s_l[g];
+            o += w * s_o[g * LPK * 4 + threadIdx.x];
+        }
+        out[(size_t)m * (Hq * hd) + j * hd + threadIdx.x] = o / l;
+    }
 }
 
-__global__ void swiglu_f32_kernel(const float *gu, float *act, int F, int64_t total) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int64_t m = i / F;
-    const int f = (int)(i - m * F);
-    const float gt = gu[m * 2 * F + f], up = gu[m * 2 * F + F + f];
-    act[i] = gt / (1.0f + expf(-gt)) * up;
+static void attn_f32(const sev_model *m, sev_kv *kv, int rows, int layer, hipStream_t st) {
+    const sev_model_desc &d = m->d;
+    const KvGeom g = sev_kv_geom(kv);
+    const float *K = (const float *)(g.pool + (size_t)layer * g.layer_stride), *V = (const float *)((const char *)K + g.v_offset);
+    const float scale = 1.0f / sqrtf((float)d.head_dim);
+    const bool vec = d.head_dim % 4 == 0;
+#define SEV_ATTN_F32(LPK_)                                                                                                    \
+    do {                                                                                                                      \
+        if (vec) hipLaunchKernelGGL((attn_f32_kernel<LPK_, true>), dim3(rows, d.n_q_heads), dim3(256), 0, st, (const float *)kv->q_buf, (float *)kv->o_buf,  \
+                                    kv->plan, K, V, d.n_kv_heads, d.head_dim, kv->page_table, kv->max_pages_per_req, d.n_q_heads, m->n_qkv, scale);       \
+        else hipLaunchKernelGGL((attn_f32_kernel<LPK_, false>), dim3(rows, d.n_q_heads), dim3(256), 0, st, (const float *)kv->q_buf, (float *)kv->o_buf,      \
+                                kv->plan, K, V, d.n_kv_heads, d.head_dim, kv->page_table, kv->max_pages_per_req, d.n_q_heads, m->n_qkv, scale);           \
+    } while (0)
+    if (d.head_dim <= 32) SEV_ATTN_F32(8);
+    else if (d.head_dim <= 64) SEV_ATTN_F32(16);
+    else if (d.head_dim <= 128) SEV_ATTN_F32(32);
+    else SEV_ATTN_F32(64);
+#undef SEV_ATTN_F32
 }
 
 void f32_forward(const sev_model *m, sev_kv *kv, int rows, int B, float *logits_out, hipStream_t st) {
     (void)B;
     const sev_model_desc &d = m->d;
-    KvGeom g = sev_kv_geom(kv);
-    const float *arena = nullptr;
+    const KvGeom geo = sev_kv_geom(kv);
     auto W = [&](size_t off) { return (const float *)(m->arena + off); };
-    (void)arena;
-    float *h = kv->h, *xa = (float *)kv->xa, *qkv = (float *)kv->q_buf, *ob = (float *)kv->o_buf,
-          *act = (float *)kv->act, *gu = kv->part;
+    float *h = kv->h, *qkv = (float *)kv->q_buf, *ob = (float *)kv->o_buf, *act = (float *)kv->act;
     hipLaunchKernelGGL(embed_f32_kernel, dim3(rows), dim3(256), 0, st, W(m->off_embed), kv->plan.row_tok, h, d.d_model);
-    const float scale = 1.0f / sqrtf((float)d.head_dim);
+    // X [rows][K] (normed in front where there are gains) times W, n_pairs column pairs, into rows of N
+    auto gemm = [&](const float *X, const float *gain, const float *Wm, float *Y, int N, int n_pairs, int K) {
+        GemmF32 g = {};
+        g.X = X; g.W = Wm; g.gain = gain; g.Y = Y;
+        g.M = rows; g.K = K; g.N = N; g.n_pairs = n_pairs;
+        g.inv_k = 1.0f / (float)K; g.eps = d.rms_eps;
+        return g;
+    };
     for (int l = 0; l < d.n_layers; ++l) {
         const LayerOffsets &lo = m->layers[l];
-        hipLaunchKernelGGL(rmsnorm_f32_kernel, dim3(rows), dim3(256), 0, st, h, W(lo.g_attn), xa, d.d_model, d.rms_eps);
-        gemm_f32(xa, W(lo.wqkv), qkv, rows, m->n_qkv, d.d_model, false, st);
-        hipLaunchKernelGGL(rope_kv_f32_kernel, dim3(rows, d.n_q_heads + d.n_kv_heads), dim3(64), 0, st, qkv, kv->plan, g,
-                           kv->page_table, kv->max_pages_per_req, l, d.n_q_heads, m->n_qkv);
-        hipLaunchKernelGGL(attn_f32_kernel, dim3(rows, d.n_q_heads), dim3(64), 0, st, qkv, ob, kv->plan, g,
-                           kv->page_table, kv->max_pages_per_req, l, d.n_q_heads, m->n_qkv, scale);
-        gemm_f32(ob, W(lo.wo), h, rows, d.d_model, m->q_dim, true, st);
-        hipLaunchKernelGGL(rmsnorm_f32_kernel, dim3(rows), dim3(256), 0, st, h, W(lo.g_ffn), xa, d.d_model, d.rms_eps);
-        gemm_f32(xa, W(lo.wgu), gu, rows, 2 * d.d_ffn, d.d_model, false, st);
-        const int64_t tot = (int64_t)rows * d.d_ffn;
-        hipLaunchKernelGGL(swiglu_f32_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, gu, act, d.d_ffn, tot);
-        gemm_f32(act, W(lo.wd), h, rows, d.d_model, d.d_ffn, true, st);
+        GemmF32 q = gemm(h, W(lo.g_attn), W(lo.wqkv), qkv, m->n_qkv, m->n_qkv / 2, d.d_model);
+        q.row_cs = kv->plan.row_cs; q.row_kvloc = kv->plan.row_kvloc;
+        q.k_layer = (float *)(geo.pool + (size_t)l * geo.layer_stride);
+        q.v_layer = (float *)(geo.pool + (size_t)l * geo.layer_stride + geo.v_offset);
+        q.hd = d.head_dim; q.Hq = d.n_q_heads; q.Hkv = d.n_kv_heads;
+        gemm_f32<F32_QKV>(q, st);
+        attn_f32(m, kv, rows, l, st);
+        gemm_f32<F32_RESID>(gemm(ob, nullptr, W(lo.wo), h, d.d_model, (d.d_model + 1) / 2, m->q_dim), st);
+        gemm_f32<F32_SWIGLU>(gemm(h, W(lo.g_ffn), W(lo.wgu), act, d.d_ffn, d.d_ffn, d.d_model), st);
+        gemm_f32<F32_RESID>(gemm(act, nullptr, W(lo.wd), h, d.d_model, (d.d_model + 1) / 2, d.d_ffn), st);
     }
-    hipLaunchKernelGGL(rmsnorm_f32_kernel, dim3(rows), dim3(256), 0, st, h, W(m->off_gfinal), xa, d.d_model, d.rms_eps);
     float *lg = logits_out ? logits_out : kv->logits_f32;
-    gemm_f32(xa, W(m->off_lm), lg, rows, d.vocab, d.d_model, false, st);
+    gemm_f32<F32_PLAIN>(gemm(h, W(m->off_gfinal), W(m->off_lm), lg, d.vocab, (d.vocab + 1) / 2, d.d_model), st);
     launch_argmax_rows_f32(lg, rows, d.vocab, kv->row_argmax, st);
 }
