@@ -199,6 +199,8 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(const uint16_t *E, cons
 //   EPI_SWIGLU act = split(silu(gate) * up), gate and up rows interleaved in the weight tiles
 //   EPI_ARGMAX per-wave arg-max of every row (+ optional float32 logits); never split
 // ---------------------------------------------------------------------------
+__host__ __device__ constexpr int gemm_ks(int MT, int NT) { return MT * NT >= 12 ? 1 : 2; }      // k-steps per pipeline stage
+
 enum { EPI_QKV = 0, EPI_SWIGLU = 1, EPI_ARGMAX = 2, EPI_RESID = 3 };
 
 struct GemmArgs {
@@ -395,14 +397,19 @@ __device__ __forceinline__ void ssq_commit(const GemmArgs &g, float (*red)[STRID
 // scalars as well: the library is built with kernel-argument preloading, which hands the first 16
 // dwords of the argument block to the wave in registers at launch, so the first loads can be issued
 // without waiting for a scalar load of the argument block.
-template <int MT, int NT, int EPI, int PF>
+//
+// HALF: the wave's last column tile is shared with the wave beside it, each of the two doing half of the row tiles, so that
+// a block covers 4 (NT - 1) + 2 column tiles (6, 10 or 14) and every wave has the same MT (NT - 1/2) tiles of work.  The
+// odd wave of a pair carries its row tiles in the order "upper half first": its shared tile then uses the same registers
+// as the even wave's, and no fragment is indexed by a run-time value.
+template <int MT, int NT, int EPI, int PF, bool HALF = false>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const uint4 *X_, int n_tiles_, int k_steps_, int m_tiles_total_,
                                                         int col_groups_, int m_blocks_, int splits_, GemmArgs g) {
     g.W = W_; g.X = X_; g.n_tiles = n_tiles_; g.k_steps = k_steps_; g.m_tiles_total = m_tiles_total_;
     g.col_groups = col_groups_; g.m_blocks = m_blocks_; g.splits = splits_ & 0xffff;
     const int tpb = splits_ >> 16;                      // column tiles per block: 4 * NT, or fewer (the last wave then has fewer tiles)
-    // a pipeline stage is KS k-steps of 16: two for the narrow tiles, one for NT = 4 (same 32 MFMAs per wave with MT = 4)
-    constexpr int KS = NT == 4 ? 1 : 2;
+    // a pipeline stage is KS k-steps of 16: two for the narrow tiles, one from 12 tiles per wave on (24 ... 32 MFMAs)
+    constexpr int KS = gemm_ks(MT, NT);
     constexpr int XI = KS * MT / 2;                     // 16-byte activation loads per thread and stage
     static_assert(KS * MT % 2 == 0, "a stage of activations must be a whole number of 4 KiB");
     extern __shared__ u32x4 xs[];                       // [2 buffers][KS k-steps][MT][2 planes][64 lanes]
@@ -418,9 +425,17 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     const int split = q % g.splits;
     const int cg = (q / g.splits) * 8 + (blockIdx.x & 7);
     if (cg >= g.col_groups) return;                      // whole block leaves before any barrier
-    const int tile0 = cg * tpb + wave * NT;
-    const int my_tiles = min(NT, min(tpb - wave * NT, g.n_tiles - tile0));        // may be <= 0: the wave then only helps with the activations
+    const int block_tiles = min(tpb, g.n_tiles - cg * tpb);
+    // column tile a of the wave, within the block: those past block_tiles do not exist (the wave then only helps with the activations)
+    auto lct = [&](int a) { return !HALF ? wave * NT + a : (a < NT - 1 ? wave * (NT - 1) + a : 4 * (NT - 1) + (wave >> 1)); };
+    auto have = [&](int a) { return lct(a) < block_tiles; };
+    auto coltile = [&](int a) { return cg * tpb + lct(a); };
     const int mt0 = mb * MT;
+    constexpr int MH = MT / 2;
+    static_assert(!HALF || MT % 2 == 0, "a shared tile is split into two halves of the row tiles");
+    const int par = HALF ? wave & 1 : 0;
+    auto rt = [&](int b) { return !HALF ? b : (b < MH ? b + par * MH : b - par * MH); };      // row tile behind register slot b
+    auto rows_of = [&](int a) { return HALF && a == NT - 1 ? MH : MT; };                       // slots of column tile a
     const int n_stages = g.k_steps / KS;
     const int s_begin = (int)((unsigned)n_stages * (unsigned)split / (unsigned)g.splits);          // small numbers: 32-bit division
     const int s_end = (int)((unsigned)n_stages * (unsigned)(split + 1) / (unsigned)g.splits);
@@ -439,7 +454,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     const u32x4 *wp[NT];
 #pragma unroll
     for (int a = 0; a < NT; ++a) {
-        const int t = min(tile0 + a, g.n_tiles - 1);
+        const int t = min(coltile(a), g.n_tiles - 1);
         wp[a] = (const u32x4 *)g.W + ((size_t)t * g.k_steps) * 64 + lane;
     }
     // The gate/up GEMM reads its weights through a buffer descriptor that covers exactly the block's column tiles: a
@@ -447,17 +462,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     // end, where a load returns zeros and reads nothing, so the loop stays free of branches and the missing tile
     // costs no memory traffic.
     constexpr bool WBUF = EPI == EPI_SWIGLU && MT <= 2;      // the 128-row blocks never run narrower than 4 * NT tiles
-    const int block_tiles = min(tpb, g.n_tiles - cg * tpb);
     const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
         (void *)((const u32x4 *)g.W + (size_t)cg * tpb * g.k_steps * 64), 0, block_tiles * g.k_steps * 1024, 0x00020000);
     int woff[NT];
 #pragma unroll
-    for (int a = 0; a < NT; ++a) woff[a] = (((wave * NT + a) * g.k_steps) * 64 + lane) * 16;
+    for (int a = 0; a < NT; ++a) woff[a] = ((lct(a) * g.k_steps) * 64 + lane) * 16;
     auto load_w = [&](int a, int step) -> u32x4 {      // 16 bytes per lane of k-step `step` of the wave's column tile a
         // The streaming hint keeps the weights from displacing the activations in the L2s (gate/up: 7 % faster with it).
         // The QKV projection streams the fewest weights per activation byte and is 4 % faster with plain loads.
         if constexpr (WBUF) return __builtin_amdgcn_raw_buffer_load_b128(wrs, woff[a] + step * 1024, 0, 2);      // 2: streaming hint
-        else if constexpr (EPI == EPI_QKV) return wp[a][(size_t)step * 64];
+        // Blocks of 3 and 4 row tiles come with several row blocks, which share the weights through their XCD's L2: plain
+        // loads there (256 rows of the 70B shape: a step of 8.41 -> 8.29 ms).
+        else if constexpr (EPI == EPI_QKV || (EPI != EPI_ARGMAX && (MT == 3 || MT == 4))) return wp[a][(size_t)step * 64];
         else return __builtin_nontemporal_load(&wp[a][(size_t)step * 64]);
     };
     // Software pipeline.  Loads return in issue order, so a wait on one load drains every older one:
@@ -491,7 +507,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     // same moment, i.e. hammer a few L2 channels while the others idle.  The row blocks of a column
     // group share the rotation, so they still read their common weight tiles together.  Short split-K
     // slices keep the common start: they are mostly pipeline fill, where sharing the first misses wins.
-    const int rot = n >= 64 ? (int)((unsigned)cg * (unsigned)n / (unsigned)g.col_groups) : 0;
+    // So do four and more row blocks: their activations no longer fit an L2, and the column groups of an XCD then share
+    // what one of them fetched (512 rows: a step of 17.0 -> 16.7 ms, 2048 rows -2 %).
+    const int rot = n >= 64 && g.m_blocks < 4 ? (int)((unsigned)cg * (unsigned)n / (unsigned)g.col_groups) : 0;
     auto phys = [&](int t) {                                        // logical stage -> stage index in K
         int i = min(t, n - 1) + rot;
         if (i >= n) i -= n;
@@ -527,7 +545,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     unsigned long long sq_rows[MT];
 #pragma unroll
     for (int b = 0; b < MT; ++b) {
-        const int m = (mt0 + b) * 32 + mrow;
+        const int m = (mt0 + rt(b)) * 32 + mrow;
         sq_rows[b] = (g.splits == 1 && g.ssq_in && m < g.M) ? g.ssq_in[m] : 0ull;
     }
     // the rest of the argument block (epilogue pointers): fetched now, behind the first loads
@@ -540,12 +558,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
 #pragma unroll
         for (int b = 0; b < MT; ++b)
 #pragma unroll
-            for (int pl = 0; pl < 2; ++pl) xf[ks][b][pl] = xs[((ks * MT + b) * 2 + pl) * 64 + lane];
+            for (int pl = 0; pl < 2; ++pl) xf[ks][b][pl] = xs[((ks * MT + rt(b)) * 2 + pl) * 64 + lane];
     __syncthreads();                                    // stage 0 overwrites buffer 0 early: every wave must have read its X(0) fragments
 
     // One group of PF stages.  The last group of a slice issues no global loads: what it would
     // prefetch lies beyond the slice, and the epilogue would have to wait for those loads to return
     // before it may reuse their registers.
+    auto last_use = [&](int b) { return HALF && b >= MH ? NT - 2 : NT - 1; };                  // column tile after which fragment b is refilled
     auto group = [&](int base, auto load_tag) {
         constexpr bool LOAD = decltype(load_tag)::value;
 #pragma unroll
@@ -555,6 +574,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
                 if (st >= n) break;                     // padding of the slice (uniform): nothing left to multiply
             }
             const u32x4 *xnext = xs + ((u + 1) & 1) * STAGE_U4 + lane;      // X(st+1)
+            const u32x4 *xnext_lo = xnext + (HALF ? par * MH * 128 : 0), *xnext_hi = xnext - (HALF ? par * MH * 128 : 0);
             // X(st+2): registers -> the LDS buffer whose fragments (stage st) were read during stage st-1
             const bool live = st + 2 < n;
             u32x4 *xd = xs + (u & 1) * STAGE_U4 + threadIdx.x;
@@ -574,8 +594,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
                     for (int pl = 0; pl < 2; ++pl)
 #pragma unroll
                         for (int b = 0; b < MT; ++b) {
+                            if (b >= rows_of(a)) continue;
                             acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, as_bf16x8(xf[ks][b][pl]), acc[a][b], 0, 0, 0);
-                            if (a == NT - 1) xf[ks][b][pl] = xnext[((ks * MT + b) * 2 + pl) * 64];
+                            if (a == last_use(b)) xf[ks][b][pl] = (b < MH ? xnext_lo : xnext_hi)[((ks * MT + b) * 2 + pl) * 64];
                         }
                     if constexpr (LOAD) wreg[u][a][ks] = load_w(a, KS * sw + ks);
                     if (ks == 0 && a == 0) {
@@ -593,13 +614,15 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
             for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
                 for (int a = 0; a < NT; ++a) {
-                    if (a < NT - 1) {
+                    if (a < NT - (HALF ? 2 : 1)) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 2 * MT, 0);
                     } else {
 #pragma unroll
                         for (int i = 0; i < 2 * MT; ++i) {
+                            const int b = i % MT;
+                            if (b >= rows_of(a)) continue;
                             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                            if (a == last_use(b)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                         }
                     }
                     if constexpr (LOAD) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
@@ -621,10 +644,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
         // exchange layout [slice][column tile][row tile][4][64 lanes] float4: register order, 1 KiB per store instruction
 #pragma unroll
         for (int a = 0; a < NT; ++a)
-            if (a < my_tiles) {
+            if (have(a)) {
 #pragma unroll
-                for (int b = 0; b < MT; ++b) {
-                    float4 *mine = (float4 *)g.part + (((size_t)split * g.n_tiles + tile0 + a) * g.m_tiles_total + mt0 + b) * 256 + lane;
+                for (int b = 0; b < rows_of(a); ++b) {
+                    float4 *mine = (float4 *)g.part + (((size_t)split * g.n_tiles + coltile(a)) * g.m_tiles_total + mt0 + rt(b)) * 256 + lane;
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         mine[j * 64] = make_float4(acc[a][b][4 * j], acc[a][b][4 * j + 1], acc[a][b][4 * j + 2], acc[a][b][4 * j + 3]);
@@ -639,20 +662,20 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
 #pragma unroll
         for (int b = 0; b < MT; ++b) {
             ss[b] = 0.f;
-            const int m = (mt0 + b) * 32 + mrow;
+            const int m = (mt0 + rt(b)) * 32 + mrow;
             const float rs_b = g.ssq_in ? rms_scale(sq_rows[b], g.inv_d, g.eps) : 1.0f;
 #pragma unroll
             for (int a = 0; a < NT; ++a)
-                if (a < my_tiles) {
-                    const TilePre pre = tile_pre<EPI, true>(g, tile0 + a, m, nsub, rs_b);
-                    ss[b] += tile_epilogue<EPI>(g, acc[a][b], tile0 + a, m, nsub, pre);
+                if (b < rows_of(a) && have(a)) {
+                    const TilePre pre = tile_pre<EPI, true>(g, coltile(a), m, nsub, rs_b);
+                    ss[b] += tile_epilogue<EPI>(g, acc[a][b], coltile(a), m, nsub, pre);
                 }
         }
         if constexpr (EPI == EPI_RESID) {
 #pragma unroll
             for (int b = 0; b < MT; ++b) {
                 ss[b] += __shfl_xor(ss[b], 32);
-                if (lane < 32) red[wave][b * 32 + mrow] = ss[b];
+                if (lane < 32) red[wave][rt(b) * 32 + mrow] = ss[b];
             }
             ssq_commit(g, red, MT * 32, mt0 * 32, cg == 0);
         }
@@ -661,16 +684,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
         // positive, so it only matters for the logits that are written out
 #pragma unroll
         for (int b = 0; b < MT; ++b) {
-            const int m = (mt0 + b) * 32 + mrow;
+            const int m = (mt0 + rt(b)) * 32 + mrow;
             const float rsb = (g.logits && g.ssq_in && m < g.M) ? rms_scale(sq_rows[b], g.inv_d, g.eps) : 1.0f;
             float bv = -INFINITY;
             int bi = 0x7fffffff;
 #pragma unroll
             for (int a = 0; a < NT; ++a) {
-                if (a >= my_tiles) continue;
+                if (b >= rows_of(a) || !have(a)) continue;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const int nn = (tile0 + a) * 32 + 8 * j + nsub;
+                    const int nn = coltile(a) * 32 + 8 * j + nsub;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const float v = acc[a][b][4 * j + r];
@@ -1125,7 +1148,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int4 *mg_rec, con
 // ---------------------------------------------------------------------------
 struct GemmCfg {
     int MT, NT, S, PF;
-    int T;                  // column tiles per block (4 * NT unless a narrower block fills the chip better)
+    bool half;              // the last of the NT column tiles is shared by two waves: 4 (NT - 1) + 2 tiles per block
+    int T;                  // column tiles per block (cols() unless a narrower block fills the chip better)
+    int cols() const { return half ? 4 * (NT - 1) + 2 : 4 * NT; }
 };
 
 enum { G_QKV = 0, G_O, G_GU, G_DOWN, G_LM };
@@ -1144,10 +1169,9 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
     }
     c.PF = 4;
     c.S = 1;
+    c.half = false;
     const bool splittable = which != G_LM;
-    auto blocks_of = [&](const GemmCfg &x) {
-        return ((n_tiles + 4 * x.NT - 1) / (4 * x.NT)) * ((m_tiles + x.MT - 1) / x.MT);
-    };
+    auto blocks_of = [&](const GemmCfg &x) { return (n_tiles + x.cols() - 1) / x.cols() * ((m_tiles + x.MT - 1) / x.MT); };
     auto pick_s = [&]() {
         c.S = 1;
         if (!splittable) return;
@@ -1172,11 +1196,17 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
         if (which == G_GU) {
             // never split: compare with the 128 x 512 blocks by rounds of blocks x tiles per block (the wide block's
             // tiles are 14 % cheaper: one weight fragment feeds four row tiles and the stage has one barrier)
+            // The 128 x 448 block (half tiles) does 7/8 of the 128 x 512 block's work per round and is taken where it
+            // needs no more rounds: 896 column tiles (8B shape) are 224 or 256 blocks per 4 row blocks.  The chip runs
+            // at its power limit here, so a fuller last round buys less than its 12 %: 512 rows 194 -> 188 us, 2048 rows
+            // 766 -> 731 us, 256 rows of the 70B shape 422 -> 412 us.
             GemmCfg wide = c;
             wide.MT = 4; wide.NT = 4;
+            GemmCfg wide_half = wide;
+            wide_half.half = true;
+            const int r_wide = (blocks_of(wide) + 255) / 256, r_half = (blocks_of(wide_half) + 255) / 256;
             const double cost_few = (double)((blocks_of(c) + 255) / 256) * c.MT * c.NT;
-            const double cost_wide = (double)((blocks_of(wide) + 255) / 256) * 16 * 0.86;
-            if (cost_wide < cost_few) c = wide;
+            if (r_wide * 16 * 0.86 < cost_few) c = r_half <= r_wide ? wide_half : wide;
         } else {
             // split GEMMs: the slices must stay long (64 k-steps).  O and down (light epilogues) may also take the
             // 128 x 512 block with more slices; the two are compared by rounds x tiles x (k-steps + pipeline fill) plus
@@ -1207,6 +1237,19 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
             const int wide_blocks = blocks_of(c) * c.S, narrow_blocks = blocks_of(narrow);
             if (narrow.S == 1 && c.S > 1 && narrow_blocks <= 256 &&
                 (narrow_blocks > wide_blocks || (narrow_blocks == wide_blocks && k_steps < 512))) c = narrow;
+            // QKV unsplit: the block shape by rounds x time of one round (us at K = 4096, measured at 512 and 2048 rows of
+            // the 8B shape, whose 192 column tiles are 24, 32, 16 or 12 column groups): 512 rows 64 x 256 66 -> 64 x 192
+            // 60 us, 2048 rows 128 x 256 233 -> 128 x 384 176 us
+            if (which == G_QKV && c.S == 1) {
+                static const struct { int MT, NT; bool half; int us; } shapes[] = {{2, 2, true, 60}, {2, 2, false, 66}, {4, 2, false, 116}, {4, 3, false, 176}, {4, 4, false, 195}};
+                int best = 0;
+                for (const auto &x : shapes) {
+                    GemmCfg y = c;
+                    y.MT = x.MT; y.NT = x.NT; y.half = x.half;
+                    const int t = (blocks_of(y) + 255) / 256 * x.us;
+                    if (!best || t < best) { best = t; c = y; }
+                }
+            }
         }
     }
     // short slices are mostly pipeline fill: halve the block width instead of splitting that deep
@@ -1216,11 +1259,14 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
     }
     if (tune.has_gemm[which]) {                          // "MT,NT,S,PF"; S = 0 keeps the automatic split
         const int mt = tune.gemm[which][0], nt = tune.gemm[which][1], sp = tune.gemm[which][2], pf = tune.gemm[which][3];
-        if (mt >= 1 && mt <= 5 && (nt == 1 || nt == 2 || (nt == 4 && mt == 4 && pf == 4)) &&
+        const bool half = nt > 10;                           // 15 (QKV), 35 (gate/up): a shared half tile
+        if (mt >= 1 && mt <= 5 && (half ? (pf == 4 && ((which == G_QKV && mt == 2 && nt == 15) || (which == G_GU && mt == 4 && nt == 35))) :
+                                   (nt == 1 || nt == 2 || ((nt == 4 || (nt == 3 && which == G_QKV)) && mt == 4 && pf == 4))) &&
             sp >= 0 && sp <= 32 && (pf == 4 || (pf == 6 && mt <= 2)) &&
             (m_tiles + mt - 1) / mt * mt <= (m_tiles + 3) / 4 * 4) {     // the row blocks must stay inside the padded row tiles
             c.MT = mt;
-            c.NT = (nt == 4 && c.MT != 4) ? 2 : nt;
+            c.NT = half ? nt / 10 + 1 : nt;
+            c.half = half;
             c.PF = pf;
             pick_s();
             if (splittable && sp > 0) c.S = sp;
@@ -1231,8 +1277,8 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
     // wave of a block then has fewer tiles than the others) if that brings the block count closer to the number of
     // compute units.  With few rows the kernel is bound by the requests a compute unit can keep in flight, so every
     // unit counts: the 8B shape has 896 column tiles, 112 x 2 = 224 blocks of 8 or 128 x 2 = 256 blocks of 7.
-    c.T = 4 * c.NT;
-    if (c.S == 1 && which == G_GU && c.MT <= 2) {
+    c.T = c.cols();
+    if (c.S == 1 && which == G_GU && c.MT <= 2 && !c.half) {
         const int m_blocks = (m_tiles + c.MT - 1) / c.MT;
         auto blocks_t = [&](int t) { return ((n_tiles + t - 1) / t) * m_blocks; };
         for (int t = 4 * c.NT - 1; t >= 3 * c.NT + 1; --t)
@@ -1240,7 +1286,7 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
     }
     if (tune.tpb) {                                      // tuning experiments: tiles per block of the gate/up GEMM
         const int t = tune.tpb;
-        if (which == G_GU && c.S == 1 && t >= 3 * c.NT + 1 && t <= 4 * c.NT) c.T = t;
+        if (which == G_GU && c.S == 1 && !c.half && t >= 3 * c.NT + 1 && t <= 4 * c.NT) c.T = t;
     }
     // the exchange buffer holds S slices of (padded columns) x (padded rows)
     const size_t slice = (size_t)n_tiles * ((m_tiles + 3) / 4 * 4) * 1024;
@@ -1265,15 +1311,21 @@ static void launch_gemm(GemmArgs ga, const GemmCfg &c, int m_tiles, hipStream_t 
     ga.nt = c.NT;
     const int g8 = (ga.col_groups + 7) / 8 * 8;
     dim3 grid((unsigned)(g8 * ga.m_blocks * ga.splits));
-    const size_t lds = (size_t)2 * (c.NT == 4 ? 1 : 2) * c.MT * 2 * 64 * 16;
-#define SEV_LAUNCH(MT_, NT_, PF_)                                                                                     \
-    hipLaunchKernelGGL((gemm_bf16_kernel<MT_, NT_, EPI, PF_>), grid, dim3(256), lds, st, ga.W, ga.X, ga.n_tiles, ga.k_steps,         \
+    const size_t lds = (size_t)2 * gemm_ks(c.MT, c.NT) * c.MT * 2 * 64 * 16;
+#define SEV_LAUNCH(MT_, NT_, PF_, ...)                                                                                \
+    hipLaunchKernelGGL((gemm_bf16_kernel<MT_, NT_, EPI, PF_ __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), lds, st, ga.W, ga.X, ga.n_tiles, ga.k_steps,         \
                        ga.m_tiles_total, ga.col_groups, ga.m_blocks, ga.splits | (c.T << 16), ga)
 #define SEV_BY_NT(MT_, PF_)                                                                                           \
     do {                                                                                                              \
         if (c.NT == 2) SEV_LAUNCH(MT_, 2, PF_); else SEV_LAUNCH(MT_, 1, PF_);                                         \
     } while (0)
-    if (c.MT == 4 && c.NT == 4) SEV_LAUNCH(4, 4, 4);
+    if (c.half) {
+        if constexpr (EPI == EPI_SWIGLU) SEV_LAUNCH(4, 4, 4, true);
+        if constexpr (EPI == EPI_QKV) SEV_LAUNCH(2, 2, 4, true);
+    } else if (c.MT == 4 && c.NT == 4) SEV_LAUNCH(4, 4, 4);
+    else if (c.MT == 4 && c.NT == 3) {
+        if constexpr (EPI == EPI_QKV) SEV_LAUNCH(4, 3, 4);
+    }
     else if (c.MT == 5) SEV_BY_NT(5, 4);
     else if (c.MT == 4) SEV_BY_NT(4, 4);
     else if (c.MT == 3) SEV_BY_NT(3, 4);

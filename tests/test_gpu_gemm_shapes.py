@@ -1,0 +1,49 @@
+"""GEMM blocks whose waves share a column tile (64 x 192 for QKV, 128 x 448 for gate/up) and the 128 x 384 QKV block, forced on
+a small model through the tuning variables, against the oracle: 225 rows (the last row tile holds one row), a gate/up matrix of
+88 column tiles (the last block has 4 of 14) and 32 QKV tiles (2 of 6 in the last block of six, 8 of 12), whole and split K.
+Tolerances: the two-plane activations keep 16 bits, so logits of order one are off by 1e-4 and less; keys and values are
+rounded to bf16 (one step is 2^-7 of the value) and may lie one step apart."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import verify_oracle as vo
+from tests.helpers import announce, oracle_model
+
+pytestmark = pytest.mark.gpu
+SHAPE = synth.workload.ModelShape("gemm-shapes", 2, 512, 6, 1, 128, 1408, 4224, 500000.0, "bf16")
+SEED = 77
+
+
+@pytest.fixture(scope="module")
+def setup():
+    import paper_2505_17052_amd as sev
+    from paper_2505_17052_amd import harness
+    om = oracle_model(SHAPE, SEED, dtype=np.float32, gains=True)
+    rng = np.random.default_rng(5)
+    lens = [int(x) for x in rng.integers(3, 40, 15)]
+    prompts = [rng.integers(0, SHAPE.vocab, p) for p in lens]
+    tok = rng.integers(0, SHAPE.vocab, (15, 15)).astype(np.int32)
+    caches = [vo.prefill(om, p, len(p) + 15) for p in prompts]
+    want = np.concatenate(vo.forward_blocks(om, caches, list(tok), [vo.chain_parents(15)] * 15)[0])
+    return sev, harness, harness.build_model(SHAPE, SEED, gains=True), lens, prompts, tok, caches, want
+
+
+@pytest.mark.parametrize("qkv,gate_up", [("", ""), ("2,15,1,4", "4,35,1,4"), ("2,15,3,4", "4,35,2,4"), ("4,3,1,4", "4,4,1,4"), ("4,3,2,4", "4,2,1,4")])
+def test_forced_shapes(setup, monkeypatch, qkv, gate_up):
+    sev, harness, model, lens, prompts, tok, caches, want = setup
+    if qkv:
+        monkeypatch.setenv("SEV_TUNE_QKV", qkv)
+        monkeypatch.setenv("SEV_TUNE_GU", gate_up)
+    announce(f"GEMM shapes: QKV {qkv or 'automatic'}, gate/up {gate_up or 'automatic'}")
+    batch = harness.Batch(model, SHAPE, [p + 15 for p in lens], max_rows=225, seed=SEED)
+    batch.prefill(prompts)
+    for b, p in enumerate(lens):
+        for got, ref in zip(batch.export_kv(b, 1, 0, p), (caches[b].K[1][:p], caches[b].V[1][:p])):
+            assert np.all(np.abs(got - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-3)
+    out = sev.verify_ex(model, batch.kv, lens, torch.tensor(tok, device="cuda"), 15, want_argmax=True, want_logits=True)
+    torch.cuda.synchronize()
+    diff = np.abs(out["logits"].cpu().numpy() - want)
+    announce(f"  logits max {diff.max():.2e} mean {diff.mean():.2e}")
+    assert diff.max() < 3e-2 and diff.mean() < 3e-3
