@@ -822,6 +822,73 @@ __global__ __launch_bounds__(256) void lm_reduce_kernel(const float *val, const 
 // sequence (DIRECT) normalises and writes the O projection's operand itself.  Masking: keys < P are visible to every row; key P + j is visible
 // to a row iff bit j of the row's ancestor mask is set.
 // ---------------------------------------------------------------------------
+// Online softmax over one pair of pages, first half.  sh: scores of the lane's query (row `node` of the block; row_live: it
+// exists) against keys 8j + 4 half + r of the pair (register 4j + r); jbase = draft-node index of the lane's first key
+// (negative: prefix); pages = how many pages of the pair belong to the chunk.  Masks the scores, moves the running maximum, rescales the running sum and the accumulators, and returns the
+// exponents' offset.
+// MASKED = false: a pair whose 32 keys all lie in the committed prefix (every row sees every key); most pairs are.
+template <bool MASKED>
+__device__ __forceinline__ float attn_max(const f32x16 &sh, float (&sc)[16], int jbase, int pages, unsigned long long anc, int node, bool row_live, int causal,
+                                         float scale_log2e, float &mrun, float &lrun, f32x16 (&oacc)[4]) {
+    // (no memory access sits under control flow inside a pair step: the compiler's wait counts then stay exact)
+    float mx = -INFINITY;
+    // sc holds the raw scores (masked ones: -inf); the softmax scale goes into the one multiply-add in front of
+    // each exponential
+    if constexpr (!MASKED) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            sc[r] = sh[r];
+            mx = fmaxf(mx, sc[r]);
+        }
+    }
+#pragma unroll
+    for (int j4 = 0; MASKED && j4 < 4; ++j4) {
+        // 4-bit visibility of keys j..j+3: prefix keys (index < 0) always, draft key i iff ancestor bit i
+        // (the mask has no bits at or above n); plain shifts and selects
+        const int j = jbase + 8 * j4;
+        const unsigned up = j < 64 ? (unsigned)(anc >> max(j, 0)) : 0u;             // j >= 0 (the tail of the last page can reach past 63)
+        const unsigned dn = (unsigned)((anc << (-max(j, -3))) | ((1ull << (-max(j, -3))) - 1ull));   // -3 <= j < 0
+        unsigned vis4 = j >= 0 ? up : (j <= -4 ? 0xFu : dn);
+        // chains (any length): key j is visible iff j <= the row's own node index
+        const int dcs = node - j;
+        const unsigned visc = dcs >= 3 ? 0xFu : (dcs < 0 ? 0u : (2u << dcs) - 1u);
+        vis4 = causal ? (row_live ? visc : 0xFu) : vis4;
+        vis4 = (j4 >> 1) < pages ? vis4 : 0u;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float v = ((vis4 >> r) & 1u) ? sh[4 * j4 + r] : -INFINITY;
+            sc[4 * j4 + r] = v;
+            mx = fmaxf(mx, v);
+        }
+    }
+    const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);      // (lanes & 31, that + 32)
+    mx = fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1])) * scale_log2e;      // (the scale is positive)
+    const float mnew = fmaxf(mrun, mx);
+    const float muse = (mnew == -INFINITY) ? 0.f : mnew;
+    const float alpha = __builtin_amdgcn_exp2f(mrun - muse);
+    mrun = mnew;
+    lrun *= alpha;
+    // the running maximum rarely moves after the first pairs: the 64 accumulator registers are rescaled only when
+    // some row's maximum did (alpha is exactly 1 otherwise, so skipping changes nothing)
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0ull) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[t][r] *= alpha;
+    }
+    return muse;
+}
+
+// Second half: the probabilities, two scores at a time, as hi/lo planes, and their sum.
+__device__ __forceinline__ void attn_exp2(float (&sc)[16], int r, float scale_log2e, float muse) {
+    sc[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, -muse));
+    sc[r + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r + 1], scale_log2e, -muse));
+}
+__device__ __forceinline__ void attn_split(const float (&sc)[16], int r, float &ps, uint32_t (&ph)[8], uint32_t (&pl_)[8]) {
+    ps += sc[r] + sc[r + 1];
+    split_pack2(sc[r], sc[r + 1], ph[r / 2], pl_[r / 2]);
+}
+
 // ONCE: every K/V byte is read by exactly one block (each request has a single row group); its loads then carry the
 // streaming hint.
 template <int WAVES, bool DIRECT, bool ONCE>
@@ -934,12 +1001,10 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void attn_bf16_kern
         for (int r = 0; r < 16; ++r) oacc[t][r] = 0.f;
     float mrun = -INFINITY, lrun = 0.f;
 
-    // MASKED = false: a pair whose 32 keys all lie in the committed prefix (every row sees every key); most pairs are.
     auto pair_step = [&](int i, auto prefetch_tag, auto masked_tag) {
         constexpr bool PREFETCH = decltype(prefetch_tag)::value;
         constexpr bool MASKED = decltype(masked_tag)::value;
         const int lp0 = 2 * (wave + WAVES * i);             // chunk-local pages of the pair
-        const bool has1 = (lp0 + 1) < npages;
         // scores of this lane's query against keys 8j + 4*half + r of the pair (j = 0..3 -> register 4j + r)
         f32x16 sh;
 #pragma unroll
@@ -950,62 +1015,16 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void attn_bf16_kern
             sh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), as_bf16x8(qf[1][ks]), sh, 0, 0, 0);
         }
         if (PREFETCH) load_k(i + 1);
-        const int jbase = (page0 + lp0) * 16 + 4 * half - P;    // draft-node index of key register 0 (negative: prefix)
-        // (no memory access sits under control flow inside a pair step: the compiler's wait counts then stay exact)
-        float sc[16];
-        float mx = -INFINITY;
-        // sc holds the raw scores (masked ones: -inf); the softmax scale goes into the one multiply-add in front of
-        // each exponential
-        if constexpr (!MASKED) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                sc[r] = sh[r];
-                mx = fmaxf(mx, sc[r]);
-            }
-        }
-#pragma unroll
-        for (int j4 = 0; MASKED && j4 < 4; ++j4) {
-            // 4-bit visibility of keys j..j+3: prefix keys (index < 0) always, draft key i iff ancestor bit i
-            // (the mask has no bits at or above n); plain shifts and selects
-            const int j = jbase + 8 * j4;
-            const unsigned up = j < 64 ? (unsigned)(anc >> max(j, 0)) : 0u;             // j >= 0 (the tail of the last page can reach past 63)
-            const unsigned dn = (unsigned)((anc << (-max(j, -3))) | ((1ull << (-max(j, -3))) - 1ull));   // -3 <= j < 0
-            unsigned vis4 = j >= 0 ? up : (j <= -4 ? 0xFu : dn);
-            // chains (any length): key j is visible iff j <= the row's own node index
-            const int dcs = node - j;
-            const unsigned visc = dcs >= 3 ? 0xFu : (dcs < 0 ? 0u : (2u << dcs) - 1u);
-            vis4 = p.causal ? (row_live ? visc : 0xFu) : vis4;
-            if (j4 >= 2) vis4 = has1 ? vis4 : 0u;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float v = ((vis4 >> r) & 1u) ? sh[4 * j4 + r] : -INFINITY;
-                sc[4 * j4 + r] = v;
-                mx = fmaxf(mx, v);
-            }
-        }
-        mx = fmaxf(mx, __shfl_xor(mx, 32)) * scale_log2e;      // (the scale is positive)
-        const float mnew = fmaxf(mrun, mx);
-        const float muse = (mnew == -INFINITY) ? 0.f : mnew;
-        const float alpha = __builtin_amdgcn_exp2f(mrun - muse);
-        mrun = mnew;
-        float ps = 0.f;
         uint32_t ph[8], pl_[8];
+        float sc[16];
+        const float muse = attn_max<MASKED>(sh, sc, (page0 + lp0) * 16 + 4 * half - P, npages - lp0, anc, node, row_live, p.causal, scale_log2e, mrun, lrun, oacc);
+        float ps = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
-            const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r], scale_log2e, -muse));
-            const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[r + 1], scale_log2e, -muse));
-            ps += p0 + p1;
-            split_pack2(p0, p1, ph[r / 2], pl_[r / 2]);
+            attn_exp2(sc, r, scale_log2e, muse);
+            attn_split(sc, r, ps, ph, pl_);
         }
-        lrun = lrun * alpha + ps;
-        // the running maximum rarely moves after the first pairs: the 64 accumulator registers are rescaled only when
-        // some row's maximum did (alpha is exactly 1 otherwise, so skipping changes nothing)
-        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0ull) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[t][r] *= alpha;
-        }
+        lrun += ps;
         // page kk of the pair is contraction step kk: its 8 slots of this lane are score registers 8kk .. 8kk+7
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
@@ -1088,8 +1107,208 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void attn_bf16_kern
     }
 }
 
+// The same attention for requests with many query rows (prefill chunks, large trees): a block of 4 waves takes four row
+// groups (128 query rows) of a request, a wave each, and walks the pages with all of them, so that a page pair comes
+// through the L2 once per 128 rows: it is staged in LDS (two buffers of 16 KiB, one barrier per pair; a wave fetches one
+// of the pair's four 4 KiB page blocks, one pair ahead in registers).  The waves need no merge, and on chains the walk
+// ends at the last key that the block's rows see.
+//
+// With K/V read per row group (attn_bf16_kernel) this work was bound by the bytes that the compute units can pull (16 KiB
+// per pair and wave, 35 bytes per ns and unit): 1.85 us per pair step and SIMD.  Now 0.85 us; its 32 MFMAs are 0.5 us of
+// that, staging 0.2 us (0.65 us without it).  The rest is the vector work, which is therefore spread between the MFMAs.
+// grid: Hkv x n_items; KV head = block id % Hkv, which with 8 KV heads puts all blocks of a head on one XCD.
+template <bool DIRECT>
+__global__ __launch_bounds__(256, 2) void attn_bf16_shared_kernel(const int4 *it_a, const int4 *it_b, const int32_t *it_pages, const uint16_t *q_planes,
+                                                                  const char *pool, size_t layer_off, size_t v_off, int M, int heads,
+                                                                  const unsigned long long *row_anc, int causal, int n_items, float scale_log2e,
+                                                                  float *att_o, float2 *att_ml, uint16_t *o_pack, int m_tiles) {
+    __shared__ u32x4 kv[2][1024];                       // per buffer: K page 0, K page 1, V page 0, V page 1 of one head
+    const int Hq = heads & 0xffff, Hkv = heads >> 16, G = Hq / Hkv;
+    const int kvh = (int)blockIdx.x % Hkv, idx = (int)blockIdx.x / Hkv;
+    // Items of a request ascend in work on chains (later rows see more keys).  They are taken from the top and from the
+    // bottom in turn, the other way round in the second half of the grid: neighbours then add up to the same work, and so do
+    // blocks half the grid apart, whichever of them share a compute unit.
+    const int pr = idx >> 1;
+    const int item = ((idx & 1) != 0) == (4 * pr >= n_items) ? n_items - 1 - pr : pr;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int4 ia = it_a[item], ib = it_b[item];
+    const int page0 = ia.y, npages = ia.z, P = ia.w, n = ib.x, row0 = ib.y;
+    const int rows = G * n, R0 = ia.x * 128;
+    // keys that query rows first .. last of the request (row R = query head R / n of the group, node R % n) see
+    auto keys = [&](int first, int last) {
+        if (first >= rows) return 0;
+        last = min(last, rows - 1);
+        const int hf = first / n, hl = last / n;
+        return P + (!causal || hf != hl ? n : last - hl * n + 1);
+    };
+    auto pairs = [&](int k) { return (max(0, min(npages, (k + SEV_PAGE - 1) / SEV_PAGE - page0)) + 1) >> 1; };
+    const int n_pairs = pairs(keys(R0, R0 + 127)), my_pairs = pairs(keys(R0 + 32 * wave, R0 + 32 * wave + 31));
+    // this wave fetches page (wave & 1) of every pair, K or V; its page ids of up to 128 pairs sit in two registers
+    const int32_t *pl = it_pages + (size_t)item * SEV_ATT_MAX_CP + (wave & 1);
+    const int pt0 = pl[2 * lane], pt1 = pl[128 + 2 * lane];
+    const size_t page_stride = (size_t)Hkv * 4096;
+    const char *src = pool + layer_off + (wave >> 1 ? v_off : 0) + (size_t)kvh * 4096 + lane * 16;
+    u32x4 sa[4], sb[4];
+    auto load = [&](int i, u32x4 (&to)[4]) {
+        const int pg = i < 64 ? __builtin_amdgcn_readlane(pt0, i) : __builtin_amdgcn_readlane(pt1, i - 64);
+        const char *a = src + (size_t)pg * page_stride;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) to[j] = *(const u32x4 *)(a + j * 1024);
+    };
+    auto put = [&](int buf, const u32x4 (&from)[4]) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) kv[buf][wave * 256 + j * 64 + lane] = from[j];
+    };
+    const int last = max(n_pairs - 1, 0), ahead = wave >> 1 ? 1 : 2;      // the keys run one pair ahead of the values
+    load(0, sa);                                         // (the page list is padded: always a valid page)
+    load(min(1, last), sb);
+
+    const int qrow = lane & 31, half = lane >> 5;
+    const int R = R0 + 32 * wave + qrow;
+    const bool row_live = R < rows;
+    const int hg = row_live ? R / n : 0, node = row_live ? R - hg * n : 0;
+    u32x4 qf[2][8];
+    {
+        const uint16_t *qp = q_planes + (size_t)(row0 + node) * Hq * 128 + (size_t)(kvh * G + hg) * 128 + 8 * half;
+#pragma unroll
+        for (int pn = 0; pn < 2; ++pn)
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) qf[pn][ks] = *(const u32x4 *)(qp + (size_t)pn * M * Hq * 128 + 16 * ks);     // dead rows read row (row0, head 0)
+    }
+    const unsigned long long anc = row_live ? row_anc[row0 + node] : 0ull;
+    f32x16 oacc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[t][r] = 0.f;
+    float mrun = -INFINITY, lrun = 0.f;
+
+    const u32x4 *kb = kv[0] + ((lane >> 4) & 1) * 256 + half * 16 + (lane & 15), *vb = kv[0] + 512 + lane;
+    f32x16 sh;
+    // Pair i: softmax of its scores, and its values.  The scores of pair i + 1 are computed in between, MFMA by MFMA among
+    // the vector instructions of this pair's probabilities: a wave by itself then keeps the matrix pipe and the vector unit
+    // busy at the same time.
+    auto step = [&](int i, auto masked_tag) {
+        constexpr bool MASKED = decltype(masked_tag)::value;
+        float sc[16];
+        const float muse = attn_max<MASKED>(sh, sc, (page0 + 2 * i) * 16 + 4 * half - P, npages - 2 * i, anc, node, row_live, causal, scale_log2e, mrun, lrun, oacc);
+        const u32x4 *ki = kb + ((i + 1) & 1) * 1024, *vi = vb + (i & 1) * 1024;
+        u32x4 f[4];                                      // the next four fragments: keys, then values, four products ahead
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) f[ks] = ki[ks * 32];
+        auto next = [&](int j) { return j < 8 ? ki[j * 32] : vi[((j - 8) >> 2) * 256 + ((j - 8) & 3) * 64]; };
+        uint32_t ph[8], pl_[8];
+        float ps = 0.f;
+        __builtin_amdgcn_sched_barrier(0);               // (the scheduler left alone puts the vector instructions in front of the MFMAs)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sh[r] = 0.f;        // (past the last pair the scores are those of a buffer's old contents: never used)
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            sh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(f[ks & 3]), as_bf16x8(qf[0][ks]), sh, 0, 0, 0);
+            attn_exp2(sc, 2 * ks, scale_log2e, muse);
+            __builtin_amdgcn_sched_barrier(0);
+            sh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(f[ks & 3]), as_bf16x8(qf[1][ks]), sh, 0, 0, 0);
+            attn_split(sc, 2 * ks, ps, ph, pl_);
+            f[ks & 3] = next(ks + 4);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        lrun += ps;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const bf16x8 pH = as_bf16x8((u32x4){ph[4 * kk], ph[4 * kk + 1], ph[4 * kk + 2], ph[4 * kk + 3]});
+            const bf16x8 pL = as_bf16x8((u32x4){pl_[4 * kk], pl_[4 * kk + 1], pl_[4 * kk + 2], pl_[4 * kk + 3]});
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) {
+                const bf16x8 v = as_bf16x8(f[dt]);
+                oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pH, oacc[dt], 0, 0, 0);
+                oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pL, oacc[dt], 0, 0, 0);
+                if (kk == 0) {
+                    f[dt] = next(12 + dt);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    };
+    // Buffer i & 1 holds pair i.  In step i the keys of pair i + 1 and the values of pair i are read; the keys of pair i + 2
+    // and the values of pair i + 1 go where those of i and i - 1 were last read before the previous barrier, and what comes
+    // two steps later is requested (past the end: the last pair once more).
+    put(0, sa);
+    if (ahead == 2) put(1, sb);
+    load(min(ahead, last), sa);
+    load(min(ahead + 1, last), sb);
+    __syncthreads();
+    {
+        u32x4 f[8];
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) f[ks] = kb[ks * 32];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sh[r] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            sh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(f[ks]), as_bf16x8(qf[0][ks]), sh, 0, 0, 0);
+            sh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(f[ks]), as_bf16x8(qf[1][ks]), sh, 0, 0, 0);
+        }
+    }
+    __syncthreads();                                    // step 0 overwrites the keys of pair 0
+    // pairs of two pages that all rows of the wave see: in the prefix, on chains up to the first row's own node
+    const int Rw = R0 + 32 * wave;
+    const int seen = causal && Rw < rows && Rw / n == min(Rw + 31, rows - 1) / n ? P + Rw % n + 1 : P;
+    const int n_plain = max(0, min(my_pairs, min(seen / SEV_PAGE - page0, npages) >> 1));
+    auto stage = [&](int i, u32x4 (&st)[4]) {
+        put((i + ahead) & 1, st);
+        load(min(i + ahead + 2, last), st);
+    };
+    // Two steps a turn, one per staging register set (a plain pair left over takes the masked path; so does, wholly masked,
+    // the step that fills up an odd count).  Three loops: one with branches around the steps copies the accumulators.
+    int i = 0;
+    for (; i + 1 < n_plain; i += 2) {
+        stage(i, sa);
+        step(i, std::false_type{});
+        __syncthreads();
+        stage(i + 1, sb);
+        step(i + 1, std::false_type{});
+        __syncthreads();
+    }
+    for (; i < my_pairs; i += 2) {
+        stage(i, sa);
+        step(i, std::true_type{});
+        __syncthreads();
+        stage(i + 1, sb);
+        step(i + 1, std::true_type{});
+        __syncthreads();
+    }
+    for (; i < n_pairs; i += 2) {                       // rows of this wave see no more, those of another wave do
+        stage(i, sa);
+        __syncthreads();
+        stage(i + 1, sb);
+        __syncthreads();
+    }
+
+    const float l = lrun + __shfl_xor(lrun, 32);        // the other half of the row's keys
+    const size_t base = ((size_t)item * Hkv + kvh) * 128 + 32 * wave + qrow;
+    if (!DIRECT && half == 0) att_ml[base] = make_float2(mrun, l);
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {                      // register quad: dims 32 (q / 4) + 8 (q % 4) + 4 half .. +3
+        const int dim = 32 * (q >> 2) + 8 * (q & 3) + 4 * half;
+        const float o[4] = {oacc[q >> 2][4 * (q & 3)], oacc[q >> 2][4 * (q & 3) + 1], oacc[q >> 2][4 * (q & 3) + 2], oacc[q >> 2][4 * (q & 3) + 3]};
+        if constexpr (DIRECT) {
+            if (row_live) {
+                uint32_t hi[2], lo[2];
+                split_pack2(o[0] * inv, o[1] * inv, hi[0], lo[0]);
+                split_pack2(o[2] * inv, o[3] * inv, hi[1], lo[1]);
+                const int m = row0 + node, kk = (kvh * G + hg) * 128 + dim;
+                *(uint2 *)(o_pack + xpack_index(m, kk, 0, m_tiles)) = make_uint2(hi[0], hi[1]);
+                *(uint2 *)(o_pack + xpack_index(m, kk, 1, m_tiles)) = make_uint2(lo[0], lo[1]);
+            }
+        } else {
+            *(float4 *)(att_o + base * 128 + dim) = make_float4(o[0], o[1], o[2], o[3]);
+        }
+    }
+}
+
 // cross-chunk merge + normalisation; writes the attention output as hi/lo fragments for the O projection.
-// grid (merge groups, Hkv), 256 threads: thread owns (row q = t/8, 16 dims).
+// grid (merge groups, Hkv, row groups per work item), 256 threads: thread owns (row q = t/8, 16 dims).
 __global__ __launch_bounds__(256) void attn_merge_kernel(const int4 *mg_rec, const float *att_o, const float2 *att_ml, uint16_t *o_pack,
                                                          int Hq, int Hkv, int m_tiles) {
     // (all arguments are scalars: preloaded at wave launch; one 16-byte record describes the group)
@@ -1097,7 +1316,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int4 *mg_rec, con
     const int4 rec = mg_rec[grpi];
     const int rg = rec.x & 0xffff, cnt = rec.x >> 16, item0 = rec.y, n = rec.z & 0xffff, stride = rec.z >> 16, row0 = rec.w, G = Hq / Hkv;
     const int q = threadIdx.x >> 3, d0 = (threadIdx.x & 7) * 16;
-    const int R = rg * 32 + q;
+    const int per = 32 * gridDim.z, sub = 32 * blockIdx.z + q;            // rows of a work item, row in it
+    const int R = rg * per + sub;
     if (R >= G * n) return;
     const int hg = R / n, node = R - hg * n;
     // chunks are combined four at a time with a running maximum: all loads of a batch are issued together
@@ -1110,7 +1330,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int4 *mg_rec, con
         float4 o[4][4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const size_t base = ((size_t)(item0 + min(c0 + u, cnt - 1) * stride) * Hkv + kvh) * 32 + q;
+            const size_t base = ((size_t)(item0 + min(c0 + u, cnt - 1) * stride) * Hkv + kvh) * per + sub;
             ml[u] = att_ml[base];
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[u][e] = *(const float4 *)(att_o + base * 128 + d0 + 4 * e);
@@ -1404,7 +1624,7 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
             memcpy(src.row, tail->src, sizeof(src.row));
             hipLaunchKernelGGL(tail_gather_kernel, dim3(tail->F), dim3(256), 0, st, src, (const uint4 *)qp, (const uint4 *)kv->h, (uint4 *)kv->tail_q,
                                (uint4 *)kv->tail_h, rows, tail->F, m->q_dim / 8, d.d_model / 4);
-            launch_plan(kv, tail->pa, tail->tokens, nullptr, tail->F, tail->att.chunk_pages, tail->att.n_items, st);
+            launch_plan(kv, tail->pa, tail->tokens, nullptr, tail->F, tail->att, st);
             rows = tail->F;
             B = tail->F;
             att = tail->att;
@@ -1423,15 +1643,25 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
     hipLaunchKernelGGL((attn_bf16_kernel<WAVES_, DIRECT_, ONCE_>), dim3((unsigned)((att.n_items / att.sib + 7) / 8 * 8 * att.sib * d.n_kv_heads)), dim3(THREADS_), LDS_, st, \
                        kv->plan.it_a, kv->plan.it_b, kv->plan.it_pages, qp, g.pool, (size_t)l * g.layer_stride, g.v_offset, rows,           \
                        d.n_q_heads | (d.n_kv_heads << 16), kv->plan, g, att.n_items | (att.sib << 24), kv->att_o, kv->att_ml, scale_log2e, op, m_tiles)
-            if (att.direct) {                            // one block of 8 waves per (request, row group, KV head): no chunks, no merge
+            if (att.quad > 1) {                          // blocks of 128 query rows, K/V through LDS
+                const dim3 grid((unsigned)(att.n_items * d.n_kv_heads));
+#define SEV_ATTN_SHARED(DIRECT_)                                                                                                            \
+    hipLaunchKernelGGL((attn_bf16_shared_kernel<DIRECT_>), grid, dim3(256), 0, st, (const int4 *)kv->plan.it_a, (const int4 *)kv->plan.it_b,      \
+                       (const int32_t *)kv->plan.it_pages, (const uint16_t *)qp, (const char *)g.pool, (size_t)l * g.layer_stride, g.v_offset, rows,  \
+                       d.n_q_heads | (d.n_kv_heads << 16), (const unsigned long long *)kv->plan.row_anc, kv->plan.causal, att.n_items, scale_log2e,  \
+                       kv->att_o, kv->att_ml, op, m_tiles)
+                if (att.direct) SEV_ATTN_SHARED(true); else SEV_ATTN_SHARED(false);
+#undef SEV_ATTN_SHARED
+            } else if (att.direct) {                     // one block of 8 waves per (request, row group, KV head): no chunks, no merge
                 const size_t lds = (size_t)(8 * 64 * 64 + 2 * 8 * 64) * 4;      // 8 merge slots
                 if (once) SEV_ATTN(8, true, true, 512, lds); else SEV_ATTN(8, true, false, 512, lds);
             } else {
                 const size_t lds = (size_t)(4 * 64 * 64 + 2 * 4 * 64) * 4;   // 4 merge slots
                 if (once) SEV_ATTN(4, false, true, 256, lds); else SEV_ATTN(4, false, false, 256, lds);
-                hipLaunchKernelGGL(attn_merge_kernel, dim3(att.n_groups, d.n_kv_heads), dim3(256), 0, st, (const int4 *)kv->plan.mg_rec,
-                                   (const float *)kv->att_o, (const float2 *)kv->att_ml, op, d.n_q_heads, d.n_kv_heads, m_tiles);
             }
+            if (!att.direct)
+                hipLaunchKernelGGL(attn_merge_kernel, dim3(att.n_groups, d.n_kv_heads, att.quad), dim3(256), 0, st, (const int4 *)kv->plan.mg_rec,
+                                   (const float *)kv->att_o, (const float2 *)kv->att_ml, op, d.n_q_heads, d.n_kv_heads, m_tiles);
 #undef SEV_ATTN
         }
         {   // output projection; residual add, FFN-norm operand and scale in its epilogue

@@ -45,6 +45,7 @@ struct PlanDev {
     uint32_t *err;
     int vocab, hd, G;          // G = query heads per KV head
     int chunk_pages;
+    int group_rows;            // query rows per work item (32, or 128 where four waves share the K/V)
     const int32_t *tokens, *parents;
     const int32_t *page_table;
     int max_pages;
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_
         const int n = a.nd[t];
         const int pages = (max(a.prefix[t] + n, a.pad_tokens) + SEV_PAGE - 1) / SEV_PAGE;
         mine[0] = n;
-        mine[1] = (d.G * n + 31) / 32;
+        mine[1] = (d.G * n + d.group_rows - 1) / d.group_rows;
         mine[2] = mine[1] * ((pages + d.chunk_pages - 1) / d.chunk_pages);
         mine[3] = (n + PLAN_ROWS - 1) / PLAN_ROWS;
     }
@@ -178,7 +179,7 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_
     const int b = plan_find(s_first[2], B, it);
     const int slot = a.slot[b], P = a.prefix[b], n = a.nd[b];
     const int pages = (max(P + n, a.pad_tokens) + SEV_PAGE - 1) / SEV_PAGE;
-    const int groups = (d.G * n + 31) / 32, chunks = (pages + d.chunk_pages - 1) / d.chunk_pages;
+    const int groups = (d.G * n + d.group_rows - 1) / d.group_rows, chunks = (pages + d.chunk_pages - 1) / d.chunk_pages;
     const int cpp = (pages + chunks - 1) / chunks;
     const int local = it - s_first[2][b], c = local / groups, rg = local - c * groups;
     const int p0 = c * cpp, np = min(cpp, pages - p0);
@@ -193,8 +194,9 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_
 }
 
 void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_tokens, const int32_t *parents, int rows,
-                 int chunk_pages, int n_items, hipStream_t st) {
+                 const AttList &att, hipStream_t st) {
     (void)rows;
+    const int n_items = att.n_items;
     PlanDev d;
     d.p = kv->plan;
     d.seq_len = kv->seq_len;
@@ -204,7 +206,8 @@ void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_toke
     d.vocab = kv->model->d.vocab;
     d.hd = kv->model->d.head_dim;
     d.G = kv->model->d.n_q_heads / kv->model->d.n_kv_heads;
-    d.chunk_pages = chunk_pages;
+    d.chunk_pages = att.chunk_pages;
+    d.group_rows = 32 * att.quad;
     d.tokens = draft_tokens;
     d.parents = parents;
     d.page_table = kv->page_table;

@@ -544,9 +544,42 @@ static bool pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, AttList *out)
     // sequences are faster split over several compute units (measured on the 8B-shape workloads: one
     // compute unit needs about 0.75 us per page pair and SIMD).
     out->direct = false;
+    out->quad = 1;
     int64_t max_pages = 0;
     for (int b = 0; b < pa.B; ++b)
         max_pages = std::max<int64_t>(max_pages, (std::max(pa.prefix[b] + pa.nd[b], pa.pad_tokens) + SEV_PAGE - 1) / SEV_PAGE);
+    // Many query rows per request: blocks of four row groups that share K/V in LDS, where three quarters of their waves
+    // have rows.  Two of them run on a compute unit; chunks as small as one round of those allows, whole sequences (no
+    // merge) where the blocks fill the chip without a split.  Attention of a layer, with its merge: 2048 rows of one prompt
+    // on an empty prefix 213 -> 85 us, on 2048 cached tokens 379 -> 198 us, 8 trees of 64 nodes (256 rows each) 76 -> 65 us.
+    // (Blocks of eight row groups, one per unit, took 105, 211 and 65 us: half the staging, but one block's imbalance.)
+    {
+        int64_t quads = 0;
+        for (int b = 0; b < pa.B; ++b) quads += (G * pa.nd[b] + 127) / 128;
+        auto quad_items = [&](int64_t cp) {
+            int64_t items = 0;
+            for (int b = 0; b < pa.B; ++b) items += (G * pa.nd[b] + 127) / 128 * (((pa.prefix[b] + pa.nd[b] + SEV_PAGE - 1) / SEV_PAGE + cp - 1) / cp);
+            return items;
+        };
+        int64_t c = 8;
+        while (c < SEV_ATT_MAX_CP && quad_items(c) * d.n_kv_heads > 2 * (int64_t)n_cu) c += 8;
+        // a merge costs what six more page pairs do: sequences that are hardly longer than a chunk stay whole
+        const bool whole = max_pages <= std::min<int64_t>(c + 12, SEV_ATT_MAX_CP);
+        if (whole) c = SEV_ATT_MAX_CP;
+        const int64_t items = quad_items(c);
+        // chunks of 8 pages: there is little to share, and the many chunks cost in the merge, unless a request has ten row
+        // groups and more (one tree of 32 nodes on 1000 tokens: 18 us so, 14 us one row group per block)
+        const bool worth = c >= 16 || total_groups >= 10 * (int64_t)pa.B;
+        if (!pa.pad_tokens && !kv->tune.cp && worth && total_groups >= 3 * quads && (whole ? items : 4 * items) <= kv->max_items) {
+            out->quad = 4;
+            out->sib = 1;
+            out->n_groups = (int)quads;
+            out->direct = whole;
+            out->n_items = (int)items;
+            out->chunk_pages = (int)c;
+            return true;
+        }
+    }
     if (!kv->tune.cp && max_pages <= 64 && total_groups * d.n_kv_heads * 2 >= n_cu &&
         total_groups <= kv->max_items) {
         out->direct = true;
@@ -621,13 +654,13 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
                 return sev_fail(SEV_ENOSPACE, "request %d: padding to %d tokens exceeds the %d pages of slot %d", b, pa.pad_tokens,
                                 kv->host_pages[pa.slot[b]], pa.slot[b]);
     }
-    AttList att = {0, 0, 1, 64, false};
+    AttList att = {0, 0, 1, 64, false, 1};
     if (m->d.dtype == SEV_BF16 && !pick_chunk_pages(kv, pa, &att)) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
     kv->plan.causal = c.parents ? 0 : 1;
     for (int b = 0; b < c.B; ++b) kv->host_tree[pa.slot[b]] = c.parents ? 1 : 0;
     {
         Prof p(kv, st, PROF_OTHER);
-        launch_plan(kv, pa, c.tokens, c.parents, (int)rows, att.chunk_pages, att.n_items, st);
+        launch_plan(kv, pa, c.tokens, c.parents, (int)rows, att, st);
     }
     if (m->d.dtype == SEV_F32) f32_forward(m, kv, (int)rows, c.B, c.logits, st);
     else bf16_forward(m, kv, (int)rows, c.B, att, c.logits, nullptr, st);
@@ -770,7 +803,7 @@ extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots,
     int32_t done[SEV_MAX_BATCH] = {0};
     for (int first = 0; first < B;) {                     // `first`: the first prompt with tokens left
         PlanArgs pa;
-        AttList att = {0, 0, 1, 64, false};
+        AttList att = {0, 0, 1, 64, false, 1};
         TailRows tail;
         int32_t row[SEV_MAX_BATCH];                       // entry of row_argmax that holds a finished prompt's next token
         int rows = 0;
@@ -807,7 +840,7 @@ extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots,
         if (bf && tail.F && !pick_chunk_pages(kv, tail.pa, &tail.att)) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
         {
             Prof p(kv, st, PROF_OTHER);
-            launch_plan(kv, pa, tokens, nullptr, rows, att.chunk_pages, att.n_items, st);
+            launch_plan(kv, pa, tokens, nullptr, rows, att, st);
         }
         if (bf) bf16_forward(m, kv, rows, pa.B, att, nullptr, &tail, st);
         else f32_forward(m, kv, rows, pa.B, nullptr, st);

@@ -76,7 +76,7 @@ struct DevPlan {
     // b = {draft nodes, first row, request, 0}; pages = physical page ids of the chunk, SEV_ATT_MAX_CP per item
     int4 *it_a, *it_b;
     int32_t *it_pages;
-    int4 *mg_rec;             // [merge groups] {row group | chunks << 16, first work item, draft nodes | item stride << 16, first row}
+    int4 *mg_rec;             // [merge groups] {row group (of 32 or 128 rows) | chunks << 16, first work item, draft nodes | item stride << 16, first row}
     int causal;               // 1: blocks are chains (node i sees nodes <= i; any length), 0: trees (ancestor masks, <= 64 nodes)
 };
 
@@ -160,11 +160,18 @@ struct Prof {
 // ---------------------------------------------------------------------------
 // launchers (defined in the kernel translation units)
 // ---------------------------------------------------------------------------
+// Work list of the attention over one batch of blocks (see pick_chunk_pages).
+struct AttList {
+    int n_items, n_groups, sib, chunk_pages;
+    bool direct;
+    int quad;                // row groups of 32 query rows per work item: 1, or 4 (a block of four waves that share K/V in LDS)
+};
+
 // common
 void launch_fill_f32(float *p, float v, int64_t n, hipStream_t st);
 void launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st);
 void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_tokens, const int32_t *parents, int rows,
-                 int chunk_pages, int n_items, hipStream_t st);
+                 const AttList &att, hipStream_t st);
 void launch_theta(const sev_kv *kv, hipStream_t st);
 void launch_accept(const sev_kv *kv, int B, int k_max, int mode, const int32_t *draft_tokens, const int32_t *parents,
                    int32_t *accept_len, int32_t *bonus, int32_t *accept_path, int32_t *argmax_out, hipStream_t st);
@@ -183,11 +190,6 @@ void f32_forward(const sev_model *m, sev_kv *kv, int rows, int B, float *logits_
 // bf16 path
 void launch_pack_bf16(uint16_t *dst, const uint16_t *src, int n_rows, int K, int mode, int tile_add, hipStream_t st);
 
-// Work list of the attention over one batch of blocks (see pick_chunk_pages).
-struct AttList {
-    int n_items, n_groups, sib, chunk_pages;
-    bool direct;
-};
 // End of a prefill chunk: only the last token of each of F prompts is wanted from the last layer on (F = 0: none).
 struct TailRows {
     int F;
