@@ -538,8 +538,8 @@ static bool pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, AttList *out)
         }
         return items;
     };
-    // Whole sequences: when every request is short (64 pages: at most 4 page pairs per wave) and there are
-    // enough (request, row group, KV head) blocks for half the chip, a block of 8 waves takes the whole
+    // Whole sequences: when every request is short (32 pages: at most 2 page pairs per wave, which cost less than a merge;
+    // or 64 pages, if there are enough (request, row group, KV head) blocks for half the chip), a block of 8 waves takes the whole
     // sequence and writes the attention output itself: no partial results, no merge kernel.  Longer
     // sequences are faster split over several compute units (measured on the 8B-shape workloads: one
     // compute unit needs about 0.75 us per page pair and SIMD).
@@ -580,8 +580,8 @@ static bool pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, AttList *out)
             return true;
         }
     }
-    if (!kv->tune.cp && max_pages <= 64 && total_groups * d.n_kv_heads * 2 >= n_cu &&
-        total_groups <= kv->max_items) {
+    if (!kv->tune.cp && total_groups <= kv->max_items &&
+        (max_pages <= 32 || (max_pages <= 64 && total_groups * d.n_kv_heads * 2 >= n_cu))) {
         out->direct = true;
         out->n_items = (int)total_groups;
         out->chunk_pages = SEV_ATT_MAX_CP;
