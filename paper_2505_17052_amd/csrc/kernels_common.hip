@@ -633,7 +633,8 @@ void launch_commit(const sev_kv *kv, const int32_t *slots, int B, bool rollback,
     for (int b = 0; b < B; ++b) sl.s[b] = slots ? slots[b] : b;
     KvGeom g = sev_kv_geom(kv);
     // accepted candidates of a chain are in place already (candidate j sits at position P + j): only trees may have to move
-    bool trees = false;
+    // (a captured commit may be replayed after any block)
+    bool trees = !rollback && sev_capturing(st);
     for (int b = 0; b < B; ++b) trees |= kv->host_tree[sl.s[b]] != 0;
     if (!rollback && trees) {
         const int n = g.L * g.Hkv * g.hd;

@@ -603,6 +603,19 @@ static bool pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, AttList *out)
     }
 }
 
+bool sev_capturing(hipStream_t st) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
+}
+
+// Which slots' pending blocks are trees, for the commit.  A tree that is captured into a graph may be replayed between any
+// later calls: its slots count as trees for good (2).
+static void sev_note_block(sev_kv *kv, const PlanArgs &pa, bool tree, hipStream_t st) {
+    const char mark = tree ? (sev_capturing(st) ? 2 : 1) : 0;
+    for (int b = 0; b < pa.B; ++b)
+        if (kv->host_tree[pa.slot[b]] != 2) kv->host_tree[pa.slot[b]] = mark;
+}
+
 // One block forward: the shared body of sev_verify_ex and sev_verify_sample.  The caller has checked the
 // public limits; here: slots, capacity, row budget.
 struct BlockCall {
@@ -657,7 +670,7 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
     AttList att = {0, 0, 1, 64, false, 1};
     if (m->d.dtype == SEV_BF16 && !pick_chunk_pages(kv, pa, &att)) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
     kv->plan.causal = c.parents ? 0 : 1;
-    for (int b = 0; b < c.B; ++b) kv->host_tree[pa.slot[b]] = c.parents ? 1 : 0;
+    sev_note_block(kv, pa, c.parents != nullptr, st);
     {
         Prof p(kv, st, PROF_OTHER);
         launch_plan(kv, pa, c.tokens, c.parents, (int)rows, att, st);
@@ -796,10 +809,10 @@ extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots,
         for (int e = 0; e < b; ++e)
             if (sl[e] == slot) return sev_fail(SEV_EINVAL, "slot %d listed twice", slot);
     }
+    if (B > kv->max_rows) return sev_fail(SEV_ENOSPACE, "%d prompts exceed max_rows=%d", B, kv->max_rows);
     hipStream_t st = (hipStream_t)stream;
     const bool bf = m->d.dtype == SEV_BF16;
     kv->plan.causal = 1;
-    for (int b = 0; b < B; ++b) kv->host_tree[sl[b]] = 0;
     int32_t done[SEV_MAX_BATCH] = {0};
     for (int first = 0; first < B;) {                     // `first`: the first prompt with tokens left
         PlanArgs pa;
@@ -830,14 +843,14 @@ extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots,
                     row[r] = bf ? f : rows - 1;
                 }
             }
-            if (!bf || pick_chunk_pages(kv, pa, &att)) break;
+            tail.pa.B = tail.F;
+            tail.pa.k_max = t_max;
+            tail.pa.tail = 1;
+            tail.tokens = tokens;
+            if (!bf || (pick_chunk_pages(kv, pa, &att) && (!tail.F || pick_chunk_pages(kv, tail.pa, &tail.att)))) break;
             if (budget == 1) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
         }
-        tail.pa.B = tail.F;
-        tail.pa.k_max = t_max;
-        tail.pa.tail = 1;
-        tail.tokens = tokens;
-        if (bf && tail.F && !pick_chunk_pages(kv, tail.pa, &tail.att)) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
+        sev_note_block(kv, pa, false, st);
         {
             Prof p(kv, st, PROF_OTHER);
             launch_plan(kv, pa, tokens, nullptr, rows, att, st);

@@ -139,7 +139,7 @@ struct sev_kv {
 
     // host mirrors
     std::vector<int> host_pages;   // pages assigned per slot
-    std::vector<char> host_tree;   // per slot: the last verified block was a tree (its commit may have to move K/V)
+    std::vector<char> host_tree;   // per slot: the last verified block was a tree (its commit may have to move K/V); 2: captured
     // profiling
     int prof_on;
     std::vector<ProfSpan> spans;
@@ -166,6 +166,8 @@ struct AttList {
     bool direct;
     int quad;                // row groups of 32 query rows per work item: 1, or 4 (a block of four waves that share K/V in LDS)
 };
+
+bool sev_capturing(hipStream_t st);
 
 // common
 void launch_fill_f32(float *p, float v, int64_t n, hipStream_t st);

@@ -76,3 +76,51 @@ def test_malformed_parents_are_flagged(setup):
     out = sev.verify_ex(model, batch.kv, [5], torch.zeros((1, 4), dtype=torch.int32, device="cuda"), 4, parents=torch.tensor(par, device="cuda"))
     torch.cuda.synchronize()
     assert batch.kv.get_state(0)[2] & 2 and 0 <= int(out["accept_len"][0]) <= 4
+
+
+def test_commit_of_captured_blocks(setup):
+    """A tree's accepted K/V move at the commit also where the block or the commit itself was captured before, and other blocks
+    came between (bit for bit what the eager calls leave)."""
+    sev, harness, model = setup
+    announce("commit: captured tree block, captured commit")
+    P, k = 21, 3
+    batch = harness.Batch(model, SHAPE, [P + k], max_rows=32, seed=SEED)
+    batch.prefill([np.arange(P) % SHAPE.vocab])
+    nxt = batch.kv.get_state(0)[1]
+    dev = lambda x: torch.tensor([x], dtype=torch.int32, device="cuda")
+    par, other = dev([-1, -1, 1]), dev([1, 2, 3])
+    tok = dev([(nxt + 1) % SHAPE.vocab, nxt, 0])
+    tok[0, 2] = sev.verify_ex(model, batch.kv, [P], tok, k, parents=par, want_argmax=True)["row_argmax"][1]
+    tree = lambda: sev.verify_ex(model, batch.kv, [P], tok, k, parents=par)
+
+    def moved():
+        out = [x for l in range(SHAPE.n_layers) for x in batch.export_kv(0, l, P, 2)]
+        assert batch.kv.get_state(0)[0] == P + 2
+        batch.kv.set_state(None, [P], [nxt])
+        sev.verify_ex(model, batch.kv, [P], other, k)           # a chain writes over the block
+        return out
+
+    assert int(tree()["accept_len"][0]) == 2
+    sev.kv_commit(batch.kv, None, 1)
+    want = moved()
+    block, commit = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(commit):
+        sev.kv_commit(batch.kv, None, 1)
+    for _ in range(3):
+        tree()
+        commit.replay()
+        assert all(np.array_equal(a, b) for a, b in zip(moved(), want))
+    with torch.cuda.graph(block):
+        tree()
+    for _ in range(3):
+        sev.verify_ex(model, batch.kv, [P], other, k)
+        block.replay()
+        sev.kv_commit(batch.kv, None, 1)
+        assert all(np.array_equal(a, b) for a, b in zip(moved(), want))
+
+
+def test_prefill_of_more_prompts_than_rows_is_refused(setup):
+    sev, harness, model = setup
+    batch = harness.Batch(model, SHAPE, [16] * 3, max_rows=2, seed=SEED)
+    with pytest.raises(Exception, match="max_rows"):
+        sev.prefill(model, batch.kv, [0] * 3, [1] * 3, torch.zeros((3, 1), dtype=torch.int32, device="cuda"))

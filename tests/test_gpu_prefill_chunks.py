@@ -32,7 +32,7 @@ def _rel(a, b):
     return float(np.linalg.norm(a - b) / np.linalg.norm(b))
 
 
-@pytest.mark.parametrize("budget,split", [(3, 0), (32, 0), (64, 0), (65, 0), (232, 0), (512, 0), (48, 1), (512, 1)])
+@pytest.mark.parametrize("budget,split", [(5, 0), (32, 0), (64, 0), (65, 0), (232, 0), (512, 0), (48, 1), (512, 1)])
 def test_ragged_prompts(setup, budget, split):
     harness, model, prompts, caches, firm = setup
     announce(f"prefill chunks: prompts {LENS}, {budget} rows, {'in two calls' if split else 'in one call'}")
