@@ -608,12 +608,15 @@ bool sev_capturing(hipStream_t st) {
     return hipStreamIsCapturing(st, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
 }
 
-// Which slots' pending blocks are trees, for the commit.  A tree that is captured into a graph may be replayed between any
-// later calls: its slots count as trees for good (2).
-static void sev_note_block(sev_kv *kv, const PlanArgs &pa, bool tree, hipStream_t st) {
-    const char mark = tree ? (sev_capturing(st) ? 2 : 1) : 0;
-    for (int b = 0; b < pa.B; ++b)
-        if (kv->host_tree[pa.slot[b]] != 2) kv->host_tree[pa.slot[b]] = mark;
+// Which slots' pending blocks are trees, for the commit: a tree is noted before its launch, and the note goes once a chain has
+// been enqueued in its place.  A capture runs nothing, so whatever is pending stays: a captured chain leaves the notes alone,
+// and a captured tree may be replayed between any later calls, so its slots count as trees for good (2).
+static void sev_note_block(sev_kv *kv, const uint16_t *slot, int B, bool tree, hipStream_t st) {
+    const bool capturing = sev_capturing(st);
+    if (capturing && !tree) return;
+    const char mark = tree ? (capturing ? 2 : 1) : 0;
+    for (int b = 0; b < B; ++b)
+        if (kv->host_tree[slot[b]] != 2) kv->host_tree[slot[b]] = mark;
 }
 
 // One block forward: the shared body of sev_verify_ex and sev_verify_sample.  The caller has checked the
@@ -670,7 +673,7 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
     AttList att = {0, 0, 1, 64, false, 1};
     if (m->d.dtype == SEV_BF16 && !pick_chunk_pages(kv, pa, &att)) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
     kv->plan.causal = c.parents ? 0 : 1;
-    sev_note_block(kv, pa, c.parents != nullptr, st);
+    if (c.parents) sev_note_block(kv, pa.slot, pa.B, true, st);
     {
         Prof p(kv, st, PROF_OTHER);
         launch_plan(kv, pa, c.tokens, c.parents, (int)rows, att, st);
@@ -686,6 +689,7 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
             launch_accept(kv, c.B, c.k_max, c.mode & 1, c.tokens, c.parents, c.accept_len, c.bonus_token, c.accept_path, c.row_argmax, st);
     }
     SEV_HIP(hipGetLastError());
+    if (!c.parents) sev_note_block(kv, pa.slot, pa.B, false, st);
     return SEV_OK;
 }
 
@@ -850,7 +854,6 @@ extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots,
             if (!bf || (pick_chunk_pages(kv, pa, &att) && (!tail.F || pick_chunk_pages(kv, tail.pa, &tail.att)))) break;
             if (budget == 1) return sev_fail(SEV_ENOSPACE, "attention work list does not fit");
         }
-        sev_note_block(kv, pa, false, st);
         {
             Prof p(kv, st, PROF_OTHER);
             launch_plan(kv, pa, tokens, nullptr, rows, att, st);
@@ -865,6 +868,7 @@ extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots,
         while (first < B && done[first] == n_tokens[first]) ++first;
     }
     SEV_HIP(hipGetLastError());
+    sev_note_block(kv, sl, B, false, st);
     return SEV_OK;
 }
 

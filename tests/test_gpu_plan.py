@@ -119,6 +119,40 @@ def test_commit_of_captured_blocks(setup):
         assert all(np.array_equal(a, b) for a, b in zip(moved(), want))
 
 
+@pytest.mark.parametrize("captured", ["chain", "sampled", "prefill"])
+def test_commit_after_a_capture_that_never_ran(setup, captured):
+    """Capturing a chain block runs nothing: a tree that is pending on the slot stays pending, and its commit still moves the
+    accepted K/V (bit for bit what the uninterrupted sequence leaves)."""
+    sev, harness, model = setup
+    announce(f"commit: eager tree, captured {captured}, eager commit")
+    P, k = 21, 3
+    batch = harness.Batch(model, SHAPE, [P + k], max_rows=32, seed=SEED)
+    batch.prefill([np.arange(P) % SHAPE.vocab])
+    nxt = batch.kv.get_state(0)[1]
+    dev = lambda x: torch.tensor([x], dtype=torch.int32, device="cuda")
+    par, chain = dev([-1, -1, 1]), dev([1, 2, 3])
+    tok = dev([(nxt + 1) % SHAPE.vocab, nxt, 0])
+    tok[0, 2] = sev.verify_ex(model, batch.kv, [P], tok, k, parents=par, want_argmax=True)["row_argmax"][1]
+    q, u = torch.full((k, SHAPE.vocab), 1.0 / SHAPE.vocab, device="cuda"), torch.full((1, k), 0.5, device="cuda")
+    call = {"chain": lambda: sev.verify_ex(model, batch.kv, [P], chain, k),
+            "sampled": lambda: sev.verify_sample(model, batch.kv, [P], chain, k, q, u, u[:, 0].contiguous(), 1.0),
+            "prefill": lambda: sev.prefill(model, batch.kv, [P], [k], chain)}[captured]
+
+    def committed(interrupt):
+        batch.kv.set_state(None, [P], [nxt])
+        sev.verify_ex(model, batch.kv, [P], chain, k)           # a chain: the block's old K/V are gone
+        assert int(sev.verify_ex(model, batch.kv, [P], tok, k, parents=par)["accept_len"][0]) == 2
+        if interrupt:
+            with torch.cuda.graph(torch.cuda.CUDAGraph()):
+                call()
+        sev.kv_commit(batch.kv, None, 1)
+        assert batch.kv.get_state(0)[0] == P + 2
+        return [x for l in range(SHAPE.n_layers) for x in batch.export_kv(0, l, P, 2)]
+
+    want = committed(False)
+    assert all(np.array_equal(a, b) for a, b in zip(committed(True), want))
+
+
 def test_prefill_of_more_prompts_than_rows_is_refused(setup):
     sev, harness, model = setup
     batch = harness.Batch(model, SHAPE, [16] * 3, max_rows=2, seed=SEED)
