@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_
         }
         if (t < PLAN_ROWS && i0 + t < n) {
             const int i = i0 + t, row = row0 + i;
-            int tok = d.tokens[a.tok0[b] + i];
+            int tok = d.tokens[(size_t)(a.first + b) * a.k_max + a.tok0[b] + i];
             if (tok < 0 || tok >= d.vocab) { atomicOr(d.err, 4u); tok = 0; }
             const unsigned long long anc = d.parents ? s_anc[cur][i] : (i < 63 ? (2ull << i) - 1ull : ~0ull);
             d.p.row_req[row] = b;

@@ -639,6 +639,7 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
     PlanArgs pa;
     pa.B = c.B;
     pa.k_max = c.k_max;
+    pa.first = 0;
     pa.tail = 0;
     pa.pad_tokens = 0;
     int64_t rows = 0;
@@ -656,7 +657,7 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
         pa.slot[b] = (uint16_t)slot;
         pa.prefix[b] = P;
         pa.nd[b] = n;
-        pa.tok0[b] = b * c.k_max;
+        pa.tok0[b] = 0;
         rows += n;
     }
     if (rows > kv->max_rows) return sev_fail(SEV_ENOSPACE, "%lld tokens exceed max_rows=%d", (long long)rows, kv->max_rows);
@@ -800,7 +801,6 @@ extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots,
     if (kv->model != m) return sev_fail(SEV_EINVAL, "cache was created for another model");
     if (B < 1 || B > SEV_MAX_BATCH) return sev_fail(SEV_EINVAL, "B=%d outside 1..%d", B, SEV_MAX_BATCH);
     if (!start_lens || !n_tokens || !tokens || t_max < 1) return sev_fail(SEV_EINVAL, "start_lens, n_tokens and tokens are required");
-    if ((int64_t)B * t_max > INT32_MAX) return sev_fail(SEV_EINVAL, "%d x %d tokens", B, t_max);
     uint16_t sl[SEV_MAX_BATCH];
     for (int b = 0; b < B; ++b) {
         if (n_tokens[b] < 1 || n_tokens[b] > t_max) return sev_fail(SEV_EINVAL, "request %d: %d tokens outside 1..%d", b, n_tokens[b], t_max);
@@ -827,14 +827,15 @@ extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots,
         for (int budget = std::min(kv->max_rows, SEV_PREFILL_ROWS);; budget = (budget + 1) / 2) {
             memset(&pa, 0, sizeof(pa));
             memset(&tail, 0, sizeof(tail));
-            pa.k_max = t_max;
+            pa.k_max = tail.pa.k_max = t_max;
+            pa.first = tail.pa.first = first;             // the chunk's prompts are consecutive, and so are those that end in it
             rows = 0;
             for (int b = first; b < B && rows < budget; ++b) {
                 const int n = std::min(n_tokens[b] - done[b], budget - rows), r = pa.B++;
                 pa.slot[r] = sl[b];
                 pa.prefix[r] = start_lens[b] + done[b];
                 pa.nd[r] = n;
-                pa.tok0[r] = b * t_max + done[b];
+                pa.tok0[r] = done[b];
                 row[r] = -1;
                 rows += n;
                 if (done[b] + n == n_tokens[b]) {         // its last token goes on to the head
@@ -842,13 +843,12 @@ extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots,
                     tail.pa.slot[f] = sl[b];
                     tail.pa.prefix[f] = start_lens[b] + n_tokens[b] - 1;
                     tail.pa.nd[f] = 1;
-                    tail.pa.tok0[f] = b * t_max + n_tokens[b] - 1;
+                    tail.pa.tok0[f] = n_tokens[b] - 1;
                     tail.src[f] = rows - 1;
                     row[r] = bf ? f : rows - 1;
                 }
             }
             tail.pa.B = tail.F;
-            tail.pa.k_max = t_max;
             tail.pa.tail = 1;
             tail.tokens = tokens;
             if (!bf || (pick_chunk_pages(kv, pa, &att) && (!tail.F || pick_chunk_pages(kv, tail.pa, &tail.att)))) break;

@@ -54,12 +54,13 @@ struct sev_model {
 // kernel's arguments may take; slots are below 65536, see sev_kv_create).
 struct PlanArgs {
     int B, k_max;
+    int first;                // row of the token array that belongs to request 0
     int tail;                 // 1: rows of blocks that are already in the cache (end of a prefill): the slots' state is left alone
     int pad_tokens;           // > 0: attention walks every request's pages up to this many tokens (padded-KV comparison variant)
     uint16_t slot[SEV_MAX_BATCH];
     int32_t prefix[SEV_MAX_BATCH];
     int32_t nd[SEV_MAX_BATCH];
-    int32_t tok0[SEV_MAX_BATCH];   // token of node i of request b: tokens[tok0[b] + i]
+    int32_t tok0[SEV_MAX_BATCH];   // token of node i of request b: tokens[(first + b) * k_max + tok0[b] + i], counted in 64 bits
 };
 
 // Device-side call plan (one per sev_kv; rebuilt by every verify).

@@ -50,3 +50,23 @@ def test_ragged_prompts(setup, budget, split):
         for l in range(SHAPE.n_layers):
             k, v = batch.export_kv(b, l, 0, n)
             assert _rel(k, caches[b].K[l][:n]) < (2e-4 if l == 0 else 8e-3) and _rel(v, caches[b].V[l][:n]) < (2e-4 if l == 0 else 8e-3)
+
+
+def test_token_array_beyond_32_bits(setup):
+    """Prompts in a token array of more than 2^31 entries (rows of 2^30 + 16 and more), the last of them behind entry 2^31:
+    the caches and next tokens of the same prompts in an array that just holds them, bit for bit."""
+    harness, model, prompts, caches, firm = setup
+    import paper_2505_17052_amd as sev
+    for B, t_max in ((2, 2 ** 30 + 16), (3, 2 ** 30 + 16)):
+        announce(f"prefill: {B} prompts in rows of {t_max} tokens")
+        lens = LENS[:B]
+        got = []
+        wide = torch.empty((B, t_max), dtype=torch.int32, device="cuda")
+        narrow = torch.zeros((B, max(lens)), dtype=torch.int32, device="cuda")
+        for tokens in (wide, narrow):
+            for b, p in enumerate(prompts[:B]):
+                tokens[b, :len(p)] = torch.tensor(p.astype(np.int32), device="cuda")
+            batch = harness.Batch(model, SHAPE, [n + 4 for n in lens], max_rows=48, seed=SEED)
+            sev.prefill(model, batch.kv, [0] * B, lens, tokens)
+            got.append([x for b, n in enumerate(lens) for x in (*batch.export_kv(b, SHAPE.n_layers - 1, 0, n), *batch.kv.get_state(b))])
+        assert all(np.array_equal(a, b) for a, b in zip(*got))
