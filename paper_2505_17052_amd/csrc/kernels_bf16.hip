@@ -469,11 +469,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     for (int a = 0; a < NT; ++a) woff[a] = ((lct(a) * g.k_steps) * 64 + lane) * 16;
     auto load_w = [&](int a, int step) -> u32x4 {      // 16 bytes per lane of k-step `step` of the wave's column tile a
         // The streaming hint keeps the weights from displacing the activations in the L2s (gate/up: 7 % faster with it).
-        // The QKV projection streams the fewest weights per activation byte and is 4 % faster with plain loads.
+        // The QKV projection streams the fewest weights per activation byte and is 4 % faster with plain loads.  Blocks of 3
+        // and 4 row tiles keep the hint although their row blocks share the weights through an L2; plain loads there, timed in
+        // turn: 192 rows of the 8B shape gate/up 88.6 -> 89.8 us and QKV behind it 33.5 -> 34.4, 416 rows down 105.2 -> 106.7,
+        // 480 rows of the 70B shape O 131.3 -> 132.9.  The one that gains from plain loads is down of the 70B shape at 176 rows
+        // (178.5 -> 176.4, where gate/up loses twice that).
         if constexpr (WBUF) return __builtin_amdgcn_raw_buffer_load_b128(wrs, woff[a] + step * 1024, 0, 2);      // 2: streaming hint
-        // Blocks of 3 and 4 row tiles come with several row blocks, which share the weights through their XCD's L2: plain
-        // loads there (256 rows of the 70B shape: a step of 8.41 -> 8.29 ms).
-        else if constexpr (EPI == EPI_QKV || (EPI != EPI_ARGMAX && (MT == 3 || MT == 4))) return wp[a][(size_t)step * 64];
+        else if constexpr (EPI == EPI_QKV) return wp[a][(size_t)step * 64];
         else return __builtin_nontemporal_load(&wp[a][(size_t)step * 64]);
     };
     // Software pipeline.  Loads return in issue order, so a wait on one load drains every older one:
