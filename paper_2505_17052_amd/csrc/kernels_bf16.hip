@@ -1313,15 +1313,16 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_shared_kernel(const int4 *it
 // grid (merge groups, Hkv, row groups per work item), 256 threads: thread owns (row q = t/8, 16 dims).
 __global__ __launch_bounds__(256) void attn_merge_kernel(const int4 *mg_rec, const float *att_o, const float2 *att_ml, uint16_t *o_pack,
                                                          int Hq, int Hkv, int m_tiles) {
-    // (all arguments are scalars: preloaded at wave launch; one 16-byte record describes the group)
+    // (all arguments are scalars: preloaded at wave launch; one 16-byte record describes the group of PER query rows)
     const int grpi = blockIdx.x, kvh = blockIdx.y;
     const int4 rec = mg_rec[grpi];
     const int rg = rec.x & 0xffff, cnt = rec.x >> 16, item0 = rec.y, n = rec.z & 0xffff, stride = rec.z >> 16, row0 = rec.w, G = Hq / Hkv;
     const int q = threadIdx.x >> 3, d0 = (threadIdx.x & 7) * 16;
-    const int per = 32 * gridDim.z, sub = 32 * blockIdx.z + q;            // rows of a work item, row in it
-    const int R = rg * per + sub;
+    const int sub = PER == 32 ? q : 32 * blockIdx.z + q;                  // row of the work item
+    const int R = rg * PER + sub;
     if (R >= G * n) return;
     const int hg = R / n, node = R - hg * n;
+template <int PER>
     // chunks are combined four at a time with a running maximum: all loads of a batch are issued together
     // (a group rarely has more than four chunks, so the kernel is one round of loads deep)
     float mg = -INFINITY, l = 0.f, acc[16];
@@ -1332,7 +1333,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int4 *mg_rec, con
         float4 o[4][4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const size_t base = ((size_t)(item0 + min(c0 + u, cnt - 1) * stride) * Hkv + kvh) * per + sub;
+            const size_t base = ((size_t)(item0 + min(c0 + u, cnt - 1) * stride) * Hkv + kvh) * PER + sub;
             ml[u] = att_ml[base];
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[u][e] = *(const float4 *)(att_o + base * 128 + d0 + 4 * e);
@@ -1672,9 +1673,13 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
                 const size_t lds = (size_t)(4 * 64 * 64 + 2 * 4 * 64) * 4;   // 4 merge slots
                 if (once) SEV_ATTN(4, false, true, 256, lds); else SEV_ATTN(4, false, false, 256, lds);
             }
-            if (!att.direct)
-                hipLaunchKernelGGL(attn_merge_kernel, dim3(att.n_groups, d.n_kv_heads, att.quad), dim3(256), 0, st, (const int4 *)kv->plan.mg_rec,
-                                   (const float *)kv->att_o, (const float2 *)kv->att_ml, op, d.n_q_heads, d.n_kv_heads, m_tiles);
+#define SEV_MERGE(PER_)                                                                                                                     \
+    hipLaunchKernelGGL((attn_merge_kernel<PER_>), dim3(att.n_groups, d.n_kv_heads, PER_ / 32), dim3(256), 0, st, (const int4 *)kv->plan.mg_rec,  \
+                       (const float *)kv->att_o, (const float2 *)kv->att_ml, op, d.n_q_heads, d.n_kv_heads, m_tiles)
+            if (!att.direct) {
+                if (att.quad > 1) SEV_MERGE(128); else SEV_MERGE(32);
+            }
+#undef SEV_MERGE
 #undef SEV_ATTN
         }
         {   // output projection; residual add, FFN-norm operand and scale in its epilogue
