@@ -1311,6 +1311,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_shared_kernel(const int4 *it
 
 // cross-chunk merge + normalisation; writes the attention output as hi/lo fragments for the O projection.
 // grid (merge groups, Hkv, row groups per work item), 256 threads: thread owns (row q = t/8, 16 dims).
+template <int PER>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const int4 *mg_rec, const float *att_o, const float2 *att_ml, uint16_t *o_pack,
                                                          int Hq, int Hkv, int m_tiles) {
     // (all arguments are scalars: preloaded at wave launch; one 16-byte record describes the group of PER query rows)
@@ -1322,7 +1323,6 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int4 *mg_rec, con
     const int R = rg * PER + sub;
     if (R >= G * n) return;
     const int hg = R / n, node = R - hg * n;
-template <int PER>
     // chunks are combined four at a time with a running maximum: all loads of a batch are issued together
     // (a group rarely has more than four chunks, so the kernel is one round of loads deep)
     float mg = -INFINITY, l = 0.f, acc[16];
