@@ -1395,6 +1395,8 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
     c.half = false;
     const bool splittable = which != G_LM;
     auto blocks_of = [&](const GemmCfg &x) { return (n_tiles + x.cols() - 1) / x.cols() * ((m_tiles + x.MT - 1) / x.MT); };
+    // rounds of unsplit blocks on the fullest XCD (32 units): column group c runs on XCD c % 8 with all its row blocks
+    auto rounds_of = [&](const GemmCfg &x) { return (((n_tiles + x.cols() - 1) / x.cols() + 7) / 8 * ((m_tiles + x.MT - 1) / x.MT) + 31) / 32; };
     auto pick_s = [&]() {
         c.S = 1;
         if (!splittable) return;
@@ -1420,16 +1422,15 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
             // never split: compare with the 128 x 512 blocks by rounds of blocks x tiles per block (the wide block's
             // tiles are 14 % cheaper: one weight fragment feeds four row tiles and the stage has one barrier)
             // The 128 x 448 block (half tiles) does 7/8 of the 128 x 512 block's work per round and is taken where it
-            // needs no more rounds: 896 column tiles (8B shape) are 224 or 256 blocks per 4 row blocks.  The chip runs
+            // needs no more rounds on any XCD: 896 column tiles (8B shape) are 224 or 256 blocks per 4 row blocks.  The chip runs
             // at its power limit here, so a fuller last round buys less than its 12 %: 512 rows 194 -> 188 us, 2048 rows
             // 766 -> 731 us, 256 rows of the 70B shape 422 -> 412 us.
             GemmCfg wide = c;
             wide.MT = 4; wide.NT = 4;
             GemmCfg wide_half = wide;
             wide_half.half = true;
-            const int r_wide = (blocks_of(wide) + 255) / 256, r_half = (blocks_of(wide_half) + 255) / 256;
             const double cost_few = (double)((blocks_of(c) + 255) / 256) * c.MT * c.NT;
-            if (r_wide * 16 * 0.86 < cost_few) c = r_half <= r_wide ? wide_half : wide;
+            if ((blocks_of(wide) + 255) / 256 * 16 * 0.86 < cost_few) c = rounds_of(wide_half) <= rounds_of(wide) ? wide_half : wide;
         } else {
             // split GEMMs: the slices must stay long (64 k-steps).  O and down (light epilogues) may also take the
             // 128 x 512 block with more slices; the two are compared by rounds x tiles x (k-steps + pipeline fill) plus
@@ -1460,16 +1461,20 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
             const int wide_blocks = blocks_of(c) * c.S, narrow_blocks = blocks_of(narrow);
             if (narrow.S == 1 && c.S > 1 && narrow_blocks <= 256 &&
                 (narrow_blocks > wide_blocks || (narrow_blocks == wide_blocks && k_steps < 512))) c = narrow;
-            // QKV unsplit: the block shape by rounds x time of one round (us at K = 4096, measured at 512 and 2048 rows of
-            // the 8B shape, whose 192 column tiles are 24, 32, 16 or 12 column groups): 512 rows 64 x 256 66 -> 64 x 192
-            // 60 us, 2048 rows 128 x 256 233 -> 128 x 384 176 us
+            // QKV unsplit: the block shape by rounds x time of one full round (us at K = 4096, 8B shape).  Rounds are those of
+            // the fullest XCD: 20 column groups of 11 row blocks are 220 blocks, but 3 x 11 = 33 on an XCD, two rounds (70B
+            // shape, 1408 rows: 128 x 512 713 us, 128 x 256 448).  Over 17 row counts from 512 to 2048 in both shapes the choice is
+            // within 3 % of the best shape in all but one, and 4.5 % there (512 rows of the 8B shape 64 x 256 66 -> 64 x 192
+            // 59 us, 768 rows 102 -> 96 x 256 88, 2048 rows 128 x 256 235 -> 128 x 384 173).
             if (which == G_QKV && c.S == 1) {
-                static const struct { int MT, NT; bool half; int us; } shapes[] = {{2, 2, true, 60}, {2, 2, false, 66}, {4, 2, false, 116}, {4, 3, false, 176}, {4, 4, false, 195}};
+                static const struct { int MT, NT; bool half; int us; } shapes[] = {{2, 2, true, 55}, {2, 2, false, 62}, {3, 2, false, 88},
+                    {4, 2, false, 112}, {5, 2, false, 130}, {4, 3, false, 164}, {4, 4, false, 205}};
                 int best = 0;
                 for (const auto &x : shapes) {
                     GemmCfg y = c;
                     y.MT = x.MT; y.NT = x.NT; y.half = x.half;
-                    const int t = (blocks_of(y) + 255) / 256 * x.us;
+                    if ((m_tiles + y.MT - 1) / y.MT * y.MT > m_total) continue;      // (blocks must stay inside the operand buffers)
+                    const int t = rounds_of(y) * x.us;
                     if (!best || t < best) { best = t; c = y; }
                 }
             }
