@@ -1488,13 +1488,14 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
     }
     // Up to 64 rows: no split, and no fix-up kernel, where the narrowest blocks fill most of the chip by themselves (gate/up
     // of the 8B shape: 224 blocks of 128 columns, 38.1 us at 32 rows and 46.0 at 64 as with two slices of twice the width,
-    // whose fix-up took 5.1 and 5.5 more), or where K is so short that a slice is all pipeline fill (K = 512: QKV 6.3 us
-    // against 4.1 + 5.0, gate/up 5.7 against 4.1 + 3.8; K = 1024 with 4 blocks is 7 against 10).
+    // whose fix-up took 5.1 and 5.5 more; with two row tiles up to that shape's K of 4096: at K = 5120 and 216 blocks 40 to
+    // 64 rows take 62.7 us unsplit, 60.1 split), or where K is so short that a slice is all pipeline fill (K = 512: QKV
+    // 6.3 us against 4.1 + 5.0, gate/up 5.7 against 4.1 + 3.8).
     if (splittable && m_tiles <= 2 && c.S > 1) {
         GemmCfg x = c;
         x.NT = 1;
         x.S = 1;
-        if ((blocks_of(x) >= 192 && blocks_of(x) <= 256) || k_steps <= 32) c = x;
+        if ((blocks_of(x) >= 192 && blocks_of(x) <= 256 && (m_tiles == 1 || k_steps <= 256)) || k_steps <= 32) c = x;
     }
     if (tune.has_gemm[which]) {                          // "MT,NT,S,PF"; S = 0 keeps the automatic split
         const int mt = tune.gemm[which][0], nt = tune.gemm[which][1], sp = tune.gemm[which][2], pf = tune.gemm[which][3];
