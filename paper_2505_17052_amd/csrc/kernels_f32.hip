@@ -24,7 +24,7 @@ __global__ void embed_f32_kernel(const float *E, const int32_t *row_tok, float *
 // ---------------------------------------------------------------------------
 // Y[m][c] = sum_k X[m][k] * W[c][k], with the norm in front and the stage behind it fused in.
 //
-// A wave owns P column PAIRS x R rows and splits K over its lanes (16 bytes per lane and matrix row), so nothing goes
+// Up to 16 rows a wave owns P column PAIRS x all R rows and splits K over its lanes (16 bytes per lane and matrix row), so nothing goes
 // through LDS and no barrier is needed; the 64 partial sums are then folded by exchanging halves (an accumulator array of
 // V values takes V - 1 exchanges instead of 6 V) and every group of 64 / V lanes ends up with one finished pair.  A pair
 // is what the following stage has to see together: the two halves of a rotary pair, gate and up of one feed-forward
@@ -50,6 +50,50 @@ struct GemmF32 {
     int hd, Hq, Hkv;
 };
 
+// columns of pair j
+template <int EPI>
+__device__ __forceinline__ void f32_cols(const GemmF32 &g, int j, int &c0, int &c1) {
+    if constexpr (EPI == F32_SWIGLU) { c0 = j; c1 = g.n_pairs + j; }
+    else if constexpr (EPI == F32_QKV) { const int half = g.hd >> 1, head = j / half; c0 = head * g.hd + j - head * half; c1 = c0 + half; }
+    else { c0 = 2 * j; c1 = min(2 * j + 1, g.N - 1); }
+}
+
+// what happens to the finished pair j of row m
+template <int EPI>
+__device__ __forceinline__ void f32_finish(const GemmF32 &g, int m, int j, float va, float vb) {
+    int c0, c1;
+    f32_cols<EPI>(g, j, c0, c1);
+    float *y = g.Y + (size_t)m * g.N;
+    if constexpr (EPI == F32_SWIGLU) {
+        y[j] = va / (1.0f + expf(-va)) * vb;
+    } else if constexpr (EPI == F32_QKV) {
+        // rotary embedding of q and k; k and v go to the paged cache at position P + node
+        const int half = g.hd >> 1, head = j / half, i = j - head * half;
+        if (head < g.Hq + g.Hkv) {
+            const float2 cs = g.row_cs[(size_t)m * half + i];
+            const float t = va * cs.x - vb * cs.y;
+            vb = vb * cs.x + va * cs.y;
+            va = t;
+        }
+        if (head < g.Hq) {
+            y[c0] = va;
+            y[c1] = vb;
+        } else {
+            const bool is_k = head < g.Hq + g.Hkv;
+            const int loc = g.row_kvloc[m], h = head - g.Hq - (is_k ? 0 : g.Hkv);
+            float *c = (is_k ? g.k_layer : g.v_layer) + (((size_t)(loc >> 4) * g.Hkv + h) * SEV_PAGE + (loc & 15)) * g.hd + i;
+            c[0] = va;
+            c[half] = vb;
+        }
+    } else if constexpr (EPI == F32_RESID) {
+        y[c0] += va;
+        if (c1 != c0) y[c1] += vb;
+    } else {
+        y[c0] = va;
+        if (c1 != c0) y[c1] = vb;
+    }
+}
+
 // Sum over the wave of V values per lane: lane ends up with value lane / (64 / V).
 template <int V>
 __device__ __forceinline__ float wave_sum_split(float (&a)[V], int lane) {
@@ -72,23 +116,18 @@ template <int R, int P, int EPI, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g) {
     constexpr int V = R * P, E = VEC ? 4 : 1;
     const int lane = threadIdx.x & 63;
-    const int pair0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * P, m0 = blockIdx.y * R;
+    const int pair0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * P;
     if (pair0 >= g.n_pairs) return;                           // (no barrier in this kernel)
-    auto cols = [&](int j, int &c0, int &c1) {
-        if constexpr (EPI == F32_SWIGLU) { c0 = j; c1 = g.n_pairs + j; }
-        else if constexpr (EPI == F32_QKV) { const int half = g.hd >> 1, head = j / half; c0 = head * g.hd + j - head * half; c1 = c0 + half; }
-        else { c0 = 2 * j; c1 = min(2 * j + 1, g.N - 1); }
-    };
     const float *w0[P], *w1[P], *x[R];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         int c0, c1;
-        cols(min(pair0 + p, g.n_pairs - 1), c0, c1);
+        f32_cols<EPI>(g, min(pair0 + p, g.n_pairs - 1), c0, c1);
         w0[p] = g.W + (size_t)c0 * g.K;
         w1[p] = g.W + (size_t)c1 * g.K;
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) x[r] = g.X + (size_t)min(m0 + r, g.M - 1) * g.K;
+    for (int r = 0; r < R; ++r) x[r] = g.X + (size_t)min(r, g.M - 1) * g.K;
     float a0[V], a1[V], ss[R];
 #pragma unroll
     for (int i = 0; i < V; ++i) a0[i] = a1[i] = 0.f;
@@ -126,7 +165,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g) {
     }
     float va = wave_sum_split<V>(a0, lane), vb = wave_sum_split<V>(a1, lane);
     constexpr int LPV = 64 / V;
-    const int idx = lane / LPV, p = idx / R, r = idx - p * R, m = m0 + r, j = pair0 + p;
+    const int idx = lane / LPV, p = idx / R, m = idx - p * R, j = pair0 + p;
     if (norm) {
         float sq[V];                                          // the same fold, so that every lane ends with its own row's sum
 #pragma unroll
@@ -136,48 +175,136 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g) {
         vb *= rs;
     }
     if (lane % LPV || m >= g.M || j >= g.n_pairs) return;
+    f32_finish<EPI>(g, m, j, va, vb);
+}
+
+// The same for more than 16 rows, where the kernel above would read each matrix row from the caches once per 16 rows of X,
+// which bound it: a block of 256 threads owns 16 pairs x 16 R rows, stages K in steps of 32 through LDS (the next step's
+// loads in flight behind the products of this one) and a thread keeps one pair of R rows.  Sums run over 8 products each
+// (four of them per value and step), are folded once a step and added to a total that carries its rounding errors along, so
+// that the logits are no further from a 64-bit forward than with the kernel above (2.0e-7 of their norm with K = 256 and 688
+// in both; 2.0e-7 against 2.9e-7 with K = 2048 and 5504).  A step of the two-layer 256-wide shape with the kernel above and
+// with this one: 64 rows 217 -> 133 us, 256 rows 581 -> 141, 1024 rows 1809 -> 196.
+template <int R, int EPI, bool VEC>
+__global__ __launch_bounds__(256) void gemm_f32_tile_kernel(GemmF32 g) {
+    constexpr int TM = 16 * R, KS = 32, LD = KS + 4, NX = R / 2;      // LD: rows stay 16-byte aligned and spread over the banks
+    static_assert(R % 2 == 0, "a step of X must be a whole number of 16 bytes per thread");
+    __shared__ float4 Ws[32 * LD / 4], Xs[TM * LD / 4];
+    __shared__ float s_ss[TM];
+    const int t = threadIdx.x, lr = t >> 3, lk = (t & 7) * 4;          // loads: matrix row, place in the K step
+    const int pl = t & 15, rl = t >> 4;                                // products: pair, row
+    const int pair0 = blockIdx.x * 16, m0 = blockIdx.y * TM;
     int c0, c1;
-    cols(j, c0, c1);
-    float *y = g.Y + (size_t)m * g.N;
-    if constexpr (EPI == F32_SWIGLU) {
-        y[j] = va / (1.0f + expf(-va)) * vb;
-    } else if constexpr (EPI == F32_QKV) {
-        // rotary embedding of q and k; k and v go to the paged cache at position P + node
-        const int half = g.hd >> 1, head = j / half, i = j - head * half;
-        if (head < g.Hq + g.Hkv) {
-            const float2 cs = g.row_cs[(size_t)m * half + i];
-            const float t = va * cs.x - vb * cs.y;
-            vb = vb * cs.x + va * cs.y;
-            va = t;
-        }
-        if (head < g.Hq) {
-            y[c0] = va;
-            y[c1] = vb;
+    f32_cols<EPI>(g, min(pair0 + (lr & 15), g.n_pairs - 1), c0, c1);
+    const float *w = g.W + (size_t)(lr < 16 ? c0 : c1) * g.K, *x[NX];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) x[i] = g.X + (size_t)min(m0 + lr + 32 * i, g.M - 1) * g.K;
+    const bool norm = g.gain != nullptr;
+    auto load = [&](const float *p, int k) {                           // past the end: zeros
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if constexpr (VEC) {
+            if (k < g.K) v = *(const float4 *)(p + k);
         } else {
-            const bool is_k = head < g.Hq + g.Hkv;
-            const int loc = g.row_kvloc[m], h = head - g.Hq - (is_k ? 0 : g.Hkv);
-            float *c = (is_k ? g.k_layer : g.v_layer) + (((size_t)(loc >> 4) * g.Hkv + h) * SEV_PAGE + (loc & 15)) * g.hd + i;
-            c[0] = va;
-            c[half] = vb;
+            if (k < g.K) v.x = p[k];
+            if (k + 1 < g.K) v.y = p[k + 1];
+            if (k + 2 < g.K) v.z = p[k + 2];
+            if (k + 3 < g.K) v.w = p[k + 3];
         }
-    } else if constexpr (EPI == F32_RESID) {
-        y[c0] += va;
-        if (c1 != c0) y[c1] += vb;
-    } else {
-        y[c0] = va;
-        if (c1 != c0) y[c1] = vb;
+        return v;
+    };
+    auto add = [](float &sum, float &err, float v) {                   // sum + v, its rounding error kept for the next one
+        const float y = v - err, s = sum + y;
+        err = (s - sum) - y;
+        sum = s;
+    };
+    float ss[NX], ss_err[NX], a0[R], a1[R], e0[R], e1[R];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) ss[i] = ss_err[i] = 0.f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) a0[r] = a1[r] = e0[r] = e1[r] = 0.f;
+    float4 wn = load(w, lk), xn[NX], gn = make_float4(1.f, 1.f, 1.f, 1.f);
+#pragma unroll
+    for (int i = 0; i < NX; ++i) xn[i] = load(x[i], lk);
+    if (norm) gn = load(g.gain, lk);
+    for (int k0 = 0; k0 < g.K; k0 += KS) {
+        Ws[(lr * LD + lk) / 4] = wn;
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            float4 v = xn[i];
+            if (norm) {
+                add(ss[i], ss_err[i], (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w));
+                v = make_float4(v.x * gn.x, v.y * gn.y, v.z * gn.z, v.w * gn.w);
+            }
+            Xs[((lr + 32 * i) * LD + lk) / 4] = v;
+        }
+        __syncthreads();
+        if (k0 + KS < g.K) {
+            wn = load(w, k0 + KS + lk);
+#pragma unroll
+            for (int i = 0; i < NX; ++i) xn[i] = load(x[i], k0 + KS + lk);
+            if (norm) gn = load(g.gain, k0 + KS + lk);
+        }
+        float4 p0[R], p1[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) p0[r] = p1[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int k = 0; k < KS; k += 4) {
+            const float4 wa = Ws[(pl * LD + k) / 4], wb = Ws[((16 + pl) * LD + k) / 4];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float4 v = Xs[((rl + 16 * r) * LD + k) / 4];
+                p0[r].x += v.x * wa.x; p0[r].y += v.y * wa.y; p0[r].z += v.z * wa.z; p0[r].w += v.w * wa.w;
+                p1[r].x += v.x * wb.x; p1[r].y += v.y * wb.y; p1[r].z += v.z * wb.z; p1[r].w += v.w * wb.w;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            add(a0[r], e0[r], (p0[r].x + p0[r].y) + (p0[r].z + p0[r].w));
+            add(a1[r], e1[r], (p1[r].x + p1[r].y) + (p1[r].z + p1[r].w));
+        }
+        __syncthreads();                                               // the next step overwrites the tiles
+    }
+    if (norm) {
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+#pragma unroll
+            for (int o = 1; o < 8; o <<= 1) ss[i] += __shfl_xor(ss[i], o);
+            if ((t & 7) == 0) s_ss[lr + 32 * i] = ss[i];
+        }
+        __syncthreads();
+    }
+    const int j = pair0 + pl;
+    if (j >= g.n_pairs) return;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int m = m0 + rl + 16 * r;
+        if (m >= g.M) continue;
+        const float rs = norm ? 1.0f / sqrtf(s_ss[rl + 16 * r] * g.inv_k + g.eps) : 1.0f;
+        f32_finish<EPI>(g, m, j, a0[r] * rs, a1[r] * rs);
     }
 }
 
 template <int EPI>
 static void gemm_f32(GemmF32 g, hipStream_t st) {
     const bool vec = g.K % 4 == 0;       // matrices start on 256 bytes (or a multiple of K values behind that), so every row is 16-byte aligned then
-    // rows of a wave: as many as there are, up to 16; two pairs per wave (half the reads of X) only where there are
-    // waves enough without them (4 per compute unit)
+    // From 17 rows on the blocks of the tile kernel: a step of 16 rows takes 131 us with either (two-layer 256-wide shape), of
+    // 32 rows 137 and 132, of 128 rows 335 and 136; with matrices eight times as wide 16 rows take 664 and 783, 32 rows 1026
+    // and 805.  64 rows per block (half the reads of W) where those still give every compute unit one.
+    if (g.M > 16) {
+        const unsigned pb = (unsigned)((g.n_pairs + 15) / 16);
+        const bool tall = (int64_t)pb * ((g.M + 63) / 64) >= 256;
+        const dim3 grid(pb, (unsigned)((g.M + (tall ? 63 : 31)) / (tall ? 64 : 32)));
+        if (tall && vec) hipLaunchKernelGGL((gemm_f32_tile_kernel<4, EPI, true>), grid, dim3(256), 0, st, g);
+        else if (tall) hipLaunchKernelGGL((gemm_f32_tile_kernel<4, EPI, false>), grid, dim3(256), 0, st, g);
+        else if (vec) hipLaunchKernelGGL((gemm_f32_tile_kernel<2, EPI, true>), grid, dim3(256), 0, st, g);
+        else hipLaunchKernelGGL((gemm_f32_tile_kernel<2, EPI, false>), grid, dim3(256), 0, st, g);
+        return;
+    }
+    // rows of a wave: all of them; two pairs per wave (half the reads of X) only where there are waves enough without them
+    // (4 per compute unit)
     const int R = g.M <= 4 ? 4 : (g.M <= 8 ? 8 : 16);
-    const int rb = (g.M + R - 1) / R;
-    const int P = R == 16 && (int64_t)g.n_pairs * rb >= 2048 ? 2 : 1;
-    const dim3 grid((unsigned)((g.n_pairs + 4 * P - 1) / (4 * P)), (unsigned)rb);
+    const int P = R == 16 && g.n_pairs >= 2048 ? 2 : 1;
+    const dim3 grid((unsigned)((g.n_pairs + 4 * P - 1) / (4 * P)));
 #define SEV_F32_LAUNCH(R_, P_)                                                                                                \
     do {                                                                                                                      \
         if (vec) hipLaunchKernelGGL((gemm_f32_kernel<R_, P_, EPI, true>), grid, dim3(256), 0, st, g);                         \

@@ -1,5 +1,6 @@
 """The float32 path over the shapes it accepts (odd model widths, head sizes that are no multiple of four, grouped heads, an
-odd vocabulary) and over block sizes around its row tiles (4, 8, 16 rows per wave), chains, trees and prefill, against the
+odd vocabulary) and over block sizes around its row tiles (4, 8, 16 rows per wave, from 17 rows on 32 per block and 64 where
+the matrix is wide), chains, trees and prefill, against the
 64-bit oracle.  A logit is a sum of d products after layers of such sums: with float32 rounding (6e-8) on values of order one
 and up to 700 terms in any order, 1e-4 leaves a factor of about ten."""
 import numpy as np
@@ -15,7 +16,7 @@ TOL = 1e-4
 
 #        layers d   Hq Hkv hd  ffn  vocab
 SHAPES = [(1, 33, 2, 1, 6, 50, 97), (2, 64, 4, 2, 34, 44, 130), (1, 100, 3, 3, 32, 129, 61), (2, 68, 2, 1, 128, 70, 256), (1, 48, 2, 2, 200, 36, 64),
-          (1, 256, 4, 4, 64, 688, 1024)]
+          (1, 256, 4, 4, 64, 688, 1024), (1, 33, 2, 1, 6, 50, 8191), (1, 64, 2, 1, 32, 40, 8200)]
 
 
 def _shape(i):
@@ -24,7 +25,8 @@ def _shape(i):
 
 
 @pytest.mark.parametrize("i,ns,tree", [(0, (1,), False), (0, (5, 12), True), (1, (3, 4, 9), False), (2, (64, 33), True), (3, (4,), True), (4, (16, 1), False),
-                                       (4, (7,), True), (5, (8,), False), (5, (60, 64), True)])
+                                       (4, (7,), True), (5, (8,), False), (5, (60, 64), True), (5, (16,), True), (5, (17,), False), (5, (32, 1), True),
+                                       (6, (17,), True), (6, (64, 1), False), (7, (64,), True), (7, (64, 64, 2), False)])
 def test_logits(i, ns, tree):
     import paper_2505_17052_amd as sev
     from paper_2505_17052_amd import harness
