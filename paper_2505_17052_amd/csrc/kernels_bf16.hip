@@ -907,16 +907,27 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void attn_bf16_kern
     g.Hkv = heads_ >> 16;
     g.v_offset = v_off_;
     extern __shared__ float lds[];                    // WAVES merge slots: 64 accumulator registers + max + sum per lane
-    // Block index -> (work item, KV head).  Consecutive block ids go round-robin to the 8 XCDs, each with its own L2;
-    // the blocks of one XCD (ids 8 apart) walk, in this order: the KV heads, the `sib` row groups of one (request, chunk)
-    // - items that read the same K/V, side by side in the work list - and then the next set of row groups.  The blocks
-    // that share a chunk so run on one XCD at about the same time and the chunk comes from memory once (trees of 64
-    // nodes, 8 row groups: 45 ns per page against 78 ns when the groups are spread over the XCDs).  sib = 1 when the
-    // requests differ in their number of row groups.  The grid is padded to whole groups of 8 sets; the padding leaves
-    // before the barrier.
+    // Block index -> (work item, KV head).  Consecutive block ids go round-robin to the 8 XCDs, each with its own L2.  A set
+    // is the `sib` row groups of one (request, chunk): items that read the same K/V, side by side in the work list.  The
+    // blocks of a (set, KV head) pair run on one XCD at about the same time, and its K/V comes from memory once (trees of 64
+    // nodes, 8 row groups: 45 ns per page against 78 ns when the groups are spread over the XCDs).  sib = 1 when the requests
+    // differ in their number of row groups.  The pairs go round the XCDs, so that few or unequal sets fill all of them (one
+    // tree of 64 nodes on 16 tokens 17.7 -> 11.0 us against whole sets per XCD, 9 ragged trees on up to 2900 39 -> 30);
+    // equal requests in a multiple of 8 sets fill them as well with whole sets, which an XCD then walks head by head, a page
+    // of all heads at a time (16 trees of 24 nodes on 1000 tokens: 36.2 us by pairs, 33.8 by sets).  The grid is padded to
+    // whole rounds of 8; the padding leaves before the barrier.
     const int n_items = n_items_sib & 0xffffff, sib = n_items_sib >> 24;
-    const int jb = (int)(blockIdx.x >> 3), kvh = jb % g.Hkv, tb = jb / g.Hkv;
-    const int item = ((tb / sib) * 8 + (int)(blockIdx.x & 7)) * sib + tb % sib;
+    const int jb = (int)(blockIdx.x >> 3), xcd = (int)(blockIdx.x & 7);
+    int item, kvh;
+    if (sib > 1 && n_items % (8 * sib) == 0) {
+        const int tb = jb / g.Hkv;
+        kvh = jb - tb * g.Hkv;
+        item = (tb / sib * 8 + xcd) * sib + tb % sib;
+    } else {
+        const int pair = jb / sib * 8 + xcd, set = pair / g.Hkv;
+        kvh = pair - set * g.Hkv;
+        item = set * sib + jb % sib;
+    }
     if (item >= n_items) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave index as a scalar: loop bounds stay uniform
     // everything the block needs to know comes from two 16-byte loads and one page-id load, all independent
@@ -1660,7 +1671,7 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
             Prof p(kv, st, PROF_ATTN);
             const bool once = att.n_groups == B;         // one row group per request: every K/V byte is read by one block
 #define SEV_ATTN(WAVES_, DIRECT_, ONCE_, THREADS_, LDS_)                                                                                   \
-    hipLaunchKernelGGL((attn_bf16_kernel<WAVES_, DIRECT_, ONCE_>), dim3((unsigned)((att.n_items / att.sib + 7) / 8 * 8 * att.sib * d.n_kv_heads)), dim3(THREADS_), LDS_, st, \
+    hipLaunchKernelGGL((attn_bf16_kernel<WAVES_, DIRECT_, ONCE_>), dim3((unsigned)((att.n_items / att.sib * d.n_kv_heads + 7) / 8 * 8 * att.sib)), dim3(THREADS_), LDS_, st, \
                        kv->plan.it_a, kv->plan.it_b, kv->plan.it_pages, qp, g.pool, (size_t)l * g.layer_stride, g.v_offset, rows,           \
                        d.n_q_heads | (d.n_kv_heads << 16), kv->plan, g, att.n_items | (att.sib << 24), kv->att_o, kv->att_ml, scale_log2e, op, m_tiles)
             if (att.quad > 1) {                          // blocks of 128 query rows, K/V through LDS

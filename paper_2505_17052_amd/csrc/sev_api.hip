@@ -580,11 +580,17 @@ static bool pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, AttList *out)
             return true;
         }
     }
+    // the row groups of a set run side by side on one XCD (see the kernel), unless its units then need more rounds than if they are spread
+    auto spread_siblings = [&](int slots) {
+        const int64_t sets = (int64_t)out->n_items / out->sib * d.n_kv_heads;
+        if (((sets + 7) / 8 * out->sib + slots - 1) / slots > ((sets * out->sib + 7) / 8 + slots - 1) / slots) out->sib = 1;
+    };
     if (!kv->tune.cp && total_groups <= kv->max_items &&
         (max_pages <= 32 || (max_pages <= 64 && total_groups * d.n_kv_heads * 2 >= n_cu))) {
         out->direct = true;
         out->n_items = (int)total_groups;
         out->chunk_pages = SEV_ATT_MAX_CP;
+        spread_siblings(std::max(1, n_cu / 8));
         return true;
     }
     int64_t cp = 0;
@@ -597,6 +603,7 @@ static bool pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, AttList *out)
         if (items <= kv->max_items) {
             out->n_items = (int)items;
             out->chunk_pages = (int)cp;
+            spread_siblings(std::max(1, n_cu / 4));
             return true;
         }
         if (cp >= SEV_ATT_MAX_CHUNK) return false;
