@@ -208,6 +208,8 @@ static void read_tune(Tune *t) {
             t->has_gemm[i] = sscanf(e, "%d,%d,%d,%d", &t->gemm[i][0], &t->gemm[i][1], &t->gemm[i][2], &t->gemm[i][3]) == 4;
     if (const char *e = getenv("SEV_TUNE_TPB")) t->tpb = atoi(e);
     if (const char *e = getenv("SEV_TUNE_CP")) t->cp = atoi(e);
+    t->quad = -1;
+    if (const char *e = getenv("SEV_TUNE_QUAD")) t->quad = atoi(e);
 }
 
 extern "C" int sev_kv_create(const sev_model *m, int max_requests, int max_rows, int64_t n_pages, int page_size,
@@ -554,8 +556,19 @@ static bool pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, AttList *out)
     // on an empty prefix 213 -> 85 us, on 2048 cached tokens 379 -> 198 us, 8 trees of 64 nodes (256 rows each) 76 -> 65 us.
     // (Blocks of eight row groups, one per unit, took 105, 211 and 65 us: half the staging, but one block's imbalance.)
     {
-        int64_t quads = 0;
-        for (int b = 0; b < pa.B; ++b) quads += (G * pa.nd[b] + 127) / 128;
+        int64_t quads = 0, quad_pairs = 0, longest = 0;      // blocks per KV head, their page pairs, pairs of the longest request
+        double direct_us = 0, direct_max = 0;
+        int n_max = 0;
+        for (int b = 0; b < pa.B; ++b) {
+            const int64_t q = (G * pa.nd[b] + 127) / 128, pairs = ((pa.prefix[b] + pa.nd[b] + SEV_PAGE - 1) / SEV_PAGE + 1) / 2;
+            const double us = 8.6 + 2.0 * (double)((pairs + 7) / 8);
+            quads += q;
+            quad_pairs += q * pairs;
+            longest = std::max(longest, pairs);
+            direct_us += us * ((G * pa.nd[b] + 31) / 32);
+            direct_max = std::max(direct_max, us);
+            n_max = std::max(n_max, pa.nd[b]);
+        }
         auto quad_items = [&](int64_t cp) {
             int64_t items = 0;
             for (int b = 0; b < pa.B; ++b) items += (G * pa.nd[b] + 127) / 128 * (((pa.prefix[b] + pa.nd[b] + SEV_PAGE - 1) / SEV_PAGE + cp - 1) / cp);
@@ -564,13 +577,28 @@ static bool pick_chunk_pages(const sev_kv *kv, const PlanArgs &pa, AttList *out)
         int64_t c = 8;
         while (c < SEV_ATT_MAX_CP && quad_items(c) * d.n_kv_heads > 2 * (int64_t)n_cu) c += 8;
         // a merge costs what six more page pairs do: sequences that are hardly longer than a chunk stay whole
-        const bool whole = max_pages <= std::min<int64_t>(c + 12, SEV_ATT_MAX_CP);
+        bool whole = max_pages <= std::min<int64_t>(c + 12, SEV_ATT_MAX_CP);
+        if (kv->tune.quad > 0) {
+            c = std::min(kv->tune.quad, SEV_ATT_MAX_CP);
+            whole = max_pages <= c;
+        }
+        // Is it worth it?  Chunks: from 30 pages with all four row groups in use (40 with three) there is enough to share
+        // (8 trees of 64 nodes: on 1700 tokens, chunks of 32 pages, 52.5 -> 50.5 us; on 6000, chunks of 96, 142 -> 110; shorter
+        // chunks cost more in the merge than they save: on 1000 tokens 34.5 us so, 40.9 with chunks of 24).  Whole sequences:
+        // a wave walks all page pairs of its row group, where the blocks of 8 waves below take an eighth each, but those run one
+        // per unit and need more rounds.  The two are estimated from their blocks (us, fitted to 560 batches of trees, chains and
+        // prompts on three shapes, 4 % off the better choice in 7 of them): 8 trees of 64 nodes on 100 tokens 21.2 -> 16.9 us,
+        // on 600 28.6 against 36.8 with four row groups; one tree of 64 on 200 12.7 against 19.0.
+        // Prompts (more than 64 rows) see half of their own keys, which blocks of 8 waves skip sooner.
+        const double nb = (double)quads * d.n_kv_heads, pair_us = nb <= 0.5 * n_cu ? 0.8 : (nb <= n_cu ? 1.13 : 1.7);
+        const double rounds = (double)((total_groups * d.n_kv_heads + n_cu - 1) / n_cu);
+        const double t_direct = std::max(rounds * direct_us / (double)total_groups, direct_max) * (n_max > 64 ? 0.76 : 1.0);
+        const double t_quad = 10.5 + std::max(0.8 * (double)longest, (double)quad_pairs / (double)quads * pair_us * std::max(1.0, nb / (2.0 * n_cu)));
+        bool worth = total_groups >= 3 * quads && (whole ? t_quad < t_direct : c * total_groups >= 120 * quads);
+        if (kv->tune.quad >= 0) worth = kv->tune.quad > 0;
         if (whole) c = SEV_ATT_MAX_CP;
         const int64_t items = quad_items(c);
-        // chunks of 8 pages: there is little to share, and the many chunks cost in the merge, unless a request has ten row
-        // groups and more (one tree of 32 nodes on 1000 tokens: 18 us so, 14 us one row group per block)
-        const bool worth = c >= 16 || total_groups >= 10 * (int64_t)pa.B;
-        if (!pa.pad_tokens && !kv->tune.cp && worth && total_groups >= 3 * quads && (whole ? items : 4 * items) <= kv->max_items) {
+        if (!pa.pad_tokens && !kv->tune.cp && worth && (whole ? items : 4 * items) <= kv->max_items) {
             out->quad = 4;
             out->sib = 1;
             out->n_groups = (int)quads;

@@ -90,11 +90,12 @@ struct ProfSpan {
 
 // Tile-shape overrides for tuning experiments, read from the environment ONCE, when the handle is created:
 // SEV_TUNE_QKV / _O / _GU / _DOWN / _LM = "MT,NT,S,PF" (S = 0 keeps the automatic split), SEV_TUNE_TPB = column tiles
-// per block of the gate/up GEMM, SEV_TUNE_CP = pages per attention chunk.  Unset (the normal case): all zero.
+// per block of the gate/up GEMM, SEV_TUNE_CP = pages per attention chunk, SEV_TUNE_QUAD = 0: no attention blocks of four
+// row groups, n > 0: always, with chunks of n pages.  Unset (the normal case): all zero, quad -1.
 struct Tune {
     int gemm[5][4];
     bool has_gemm[5];
-    int tpb, cp;
+    int tpb, cp, quad;
 };
 
 struct sev_kv {
