@@ -1,8 +1,9 @@
 """GEMM blocks whose waves share a column tile (64 x 192 for QKV, 128 x 448 for gate/up) and the 128 x 384 QKV block, forced on
 a small model through the tuning variables, against the oracle: 225 rows (the last row tile holds one row), a gate/up matrix of
 88 column tiles (the last block has 4 of 14) and 32 QKV tiles (2 of 6 in the last block of six, 8 of 12), whole and split K.
-Tolerances: the two-plane activations keep 16 bits, so logits of order one are off by 1e-4 and less; keys and values are
-rounded to bf16 (one step is 2^-7 of the value) and may lie one step apart."""
+Tolerances: keys and values are rounded to bf16 (one step is 2^-7 of the value) and may lie one step apart.  Everything else
+keeps 16 bits and more, so the logits (of order one) are off by what such flips leave: 1e-4 on average and 1e-3 at most,
+whichever shapes are taken, and the bounds are four times that."""
 import numpy as np
 import pytest
 import torch
@@ -30,7 +31,7 @@ def setup():
     return sev, harness, harness.build_model(SHAPE, SEED, gains=True), lens, prompts, tok, caches, want
 
 
-@pytest.mark.parametrize("qkv,gate_up", [("", ""), ("2,15,1,4", "4,35,1,4"), ("2,15,3,4", "4,35,2,4"), ("4,3,1,4", "4,4,1,4"), ("4,3,2,4", "4,2,1,4")])
+@pytest.mark.parametrize("qkv,gate_up", [("", ""), ("2,15,1,4", "4,35,1,4"), ("2,15,3,4", "4,35,2,4"), ("4,3,1,4", "4,4,1,4"), ("4,3,2,4", "4,2,1,4"), ("4,4,1,4", "4,4,1,4")])
 def test_forced_shapes(setup, monkeypatch, qkv, gate_up):
     sev, harness, model, lens, prompts, tok, caches, want = setup
     if qkv:
@@ -46,4 +47,4 @@ def test_forced_shapes(setup, monkeypatch, qkv, gate_up):
     torch.cuda.synchronize()
     diff = np.abs(out["logits"].cpu().numpy() - want)
     announce(f"  logits max {diff.max():.2e} mean {diff.mean():.2e}")
-    assert diff.max() < 3e-2 and diff.mean() < 3e-3
+    assert diff.max() < 4e-3 and diff.mean() < 4e-4
