@@ -213,8 +213,8 @@ __global__ __launch_bounds__(256) void gemm_f32_tile_kernel(GemmF32 g) {
         return v;
     };
     auto add = [](float &sum, float &err, float v) {                   // sum + v, its rounding error kept for the next one
-        const float y = v - err, s = sum + y;
-        err = (s - sum) - y;
+        const float y = v - err, s = sum + y, e = (s - sum) - y;
+        err = fabsf(e) < INFINITY ? e : 0.f;                           // an infinite sum has none (and would turn to NaN with one)
         sum = s;
     };
     float ss[NX], ss_err[NX], a0[R], a1[R], e0[R], e1[R];

@@ -54,3 +54,29 @@ def test_logits(i, ns, tree):
     want = np.concatenate(vo.forward_blocks(om, caches, [tok[b, :n] for b, n in enumerate(ns)], [par[b, :n] for b, n in enumerate(ns)])[0])
     assert np.abs(got - want).max() < TOL
     assert np.array_equal(out["row_argmax"].cpu().numpy(), np.argmax(got, axis=-1))
+
+
+@pytest.mark.parametrize("n", [5, 17, 64])
+def test_infinite_weights(n):
+    """An infinite weight makes its column's logits infinite, of the sign of the activation it meets, and leaves every other
+    column alone, whichever kernel the row count takes (a sum that turned infinite early must not end as NaN)."""
+    import paper_2505_17052_amd as sev
+    from paper_2505_17052_amd import harness
+    shape, seed = _shape(5), 95
+    model, om = harness.build_model(shape, seed), oracle_model(shape, seed)
+    head = synth.WeightSource(shape, seed).tensor("lm_head").copy()
+    head[7, 5], head[9, 200], head[1023, 255] = np.inf, -np.inf, np.inf
+    model.load_tensor("lm_head", 0, torch.from_numpy(head).cuda())
+    plain = om.tensor
+    om = vo.Model(shape.n_layers, shape.d_model, shape.n_q_heads, shape.n_kv_heads, shape.head_dim, shape.d_ffn, shape.vocab, shape.rope_base,
+                  shape.rms_eps, tensor=lambda name, layer=0: head if name == "lm_head" else plain(name, layer), dtype=np.float64)
+    rng = np.random.default_rng(n)
+    prompt, tok = rng.integers(0, shape.vocab, 9), rng.integers(0, shape.vocab, (1, n)).astype(np.int32)
+    announce(f"float32, infinite head weights, {n} rows")
+    batch = harness.Batch(model, shape, [9 + n], max_rows=70, seed=seed)
+    batch.prefill([prompt])
+    got = sev.verify_ex(model, batch.kv, [9], torch.tensor(tok, device="cuda"), n, want_logits=True)["logits"].cpu().numpy()
+    want = vo.forward_blocks(om, [vo.prefill(om, prompt, 9 + n)], [tok[0]], [vo.chain_parents(n)])[0][0]
+    infinite = np.isinf(want)
+    assert infinite[:, [7, 9, 1023]].all() and infinite.sum() == 3 * n
+    assert np.array_equal(got[infinite], want[infinite]) and np.abs(got[~infinite] - want[~infinite]).max() < TOL
