@@ -207,7 +207,7 @@ struct GemmArgs {
     const uint4 *W;          // re-tiled weights
     const uint4 *X;          // xpack activations
     int n_tiles, k_steps, m_tiles_total, M, N;
-    int col_groups, m_blocks, splits, mt, nt;   // grid decomposition (see the kernel's block index decode)
+    int col_groups, m_blocks, splits;   // grid decomposition (see the kernel's block index decode)
     float *part;             // split-K exchange: [S][column tile][row tile][4][64 lanes] float4
     const unsigned long long *ssq_in;   // [rows] sums of squares of the input rows, or null (input is not a normed stream)
     float inv_d, eps;
@@ -1558,8 +1558,6 @@ static void launch_gemm(GemmArgs ga, const GemmCfg &c, int m_tiles, hipStream_t 
     ga.col_groups = (ga.n_tiles + c.T - 1) / c.T;
     ga.m_blocks = (m_tiles + c.MT - 1) / c.MT;
     ga.splits = c.S;
-    ga.mt = c.MT;
-    ga.nt = c.NT;
     const int g8 = (ga.col_groups + 7) / 8 * 8;
     dim3 grid((unsigned)(g8 * ga.m_blocks * ga.splits));
     const size_t lds = (size_t)2 * gemm_ks(c.MT, c.NT) * c.MT * 2 * 64 * 16;
@@ -1655,7 +1653,7 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
             memcpy(src.row, tail->src, sizeof(src.row));
             hipLaunchKernelGGL(tail_gather_kernel, dim3(tail->F), dim3(256), 0, st, src, (const uint4 *)qp, (const uint4 *)kv->h, (uint4 *)kv->tail_q,
                                (uint4 *)kv->tail_h, rows, tail->F, m->q_dim / 8, d.d_model / 4);
-            launch_plan(kv, tail->pa, tail->tokens, nullptr, tail->F, tail->att, st);
+            launch_plan(kv, tail->pa, tail->tokens, nullptr, tail->att, st);
             rows = tail->F;
             B = tail->F;
             att = tail->att;

@@ -155,7 +155,6 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_
             const unsigned long long anc = d.parents ? s_anc[cur][i] : (i < 63 ? (2ull << i) - 1ull : ~0ull);
             d.p.row_req[row] = b;
             d.p.row_node[row] = i;
-            d.p.row_pos[row] = P + (d.parents ? __popcll(anc) - 1 : i);
             d.p.row_anc[row] = anc;
             d.p.row_tok[row] = tok;
             d.p.row_kvloc[row] = d.page_table[(size_t)slot * d.max_pages + (P + i) / SEV_PAGE] * SEV_PAGE + (P + i) % SEV_PAGE;
@@ -193,9 +192,8 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_
         d.p.it_pages[(size_t)it * SEV_ATT_MAX_CP + i] = d.page_table[(size_t)slot * d.max_pages + p0 + min(i, np - 1)];
 }
 
-void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_tokens, const int32_t *parents, int rows,
+void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_tokens, const int32_t *parents,
                  const AttList &att, hipStream_t st) {
-    (void)rows;
     const int n_items = att.n_items;
     PlanDev d;
     d.p = kv->plan;

@@ -68,7 +68,7 @@ struct DevPlan {
     // per request
     int32_t *req_slot, *req_P, *req_n, *req_row0;
     // per row (draft node)
-    int32_t *row_req, *row_node, *row_pos, *row_tok;
+    int32_t *row_req, *row_node, *row_tok;
     int32_t *row_kvloc;       // physical page * 16 + token in page of the cache position P + node the row is written to
     unsigned long long *row_anc;
     float2 *row_cs;           // [rows][hd/2] (cos, sin) of pos * theta_i
@@ -174,7 +174,7 @@ bool sev_capturing(hipStream_t st);
 // common
 void launch_fill_f32(float *p, float v, int64_t n, hipStream_t st);
 void launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st);
-void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_tokens, const int32_t *parents, int rows,
+void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_tokens, const int32_t *parents,
                  const AttList &att, hipStream_t st);
 void launch_theta(const sev_kv *kv, hipStream_t st);
 void launch_accept(const sev_kv *kv, int B, int k_max, int mode, const int32_t *draft_tokens, const int32_t *parents,
