@@ -1,4 +1,4 @@
-"""Turns rocprofv3 CSV output of a bench.py run into the short text summaries kept under profiles/.
+"""Turns rocprofv3 CSV output of a bench.py run, or of passes of a case of perf/cases.py, into the short text summaries kept under profiles/.
 
     python3 -m paper_2505_17052_amd.profile_summary kernel-stats --dir D --workload W --cmd "..." [--bench-json J] --out F
     python3 -m paper_2505_17052_amd.profile_summary counters     --dir D --workload W --cmd "..." --out F
@@ -57,7 +57,7 @@ def kernel_stats(a):
     for r in rows:
         agg[short_name(r["Kernel_Name"])].append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
     total = sum(sum(v) for v in agg.values())
-    out = [header("Kernel-time summary of a whole bench.py run", a.workload, a.cmd)]
+    out = [header("Kernel-time summary of a whole bench.py run" if a.bench_json else "Kernel-time summary of a whole run", a.workload, a.cmd)]
     if a.bench_json:
         bj = json.loads(open(a.bench_json).read().strip().splitlines()[-1])
         out.append(f"bench.py's JSON line from the same run: ms_per_step {bj['ms_per_step']:.3f}, {bj['value']:.0f} {bj['unit']}, rows per step "
