@@ -51,12 +51,12 @@ __device__ __forceinline__ void split_pack2(float a, float b, uint32_t &hi, uint
 }
 
 // Writes 8 consecutive-k activations of row m (k0 a multiple of 8) as hi and lo fragments.
-__device__ __forceinline__ void store_split8(uint16_t *xp, int m, int k0, int m_tiles, const float *v) {
+__device__ __forceinline__ void store_split8(uint16_t *xp, int m, int k0, int units, const float *v) {
     uint32_t h[4], l[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) split_pack2(v[2 * i], v[2 * i + 1], h[i], l[i]);
-    *(uint4 *)(xp + xpack_index(m, k0, 0, m_tiles)) = make_uint4(h[0], h[1], h[2], h[3]);
-    *(uint4 *)(xp + xpack_index(m, k0, 1, m_tiles)) = make_uint4(l[0], l[1], l[2], l[3]);
+    *(uint4 *)(xp + xpack_index(m, k0, 0, units)) = make_uint4(h[0], h[1], h[2], h[3]);
+    *(uint4 *)(xp + xpack_index(m, k0, 1, units)) = make_uint4(l[0], l[1], l[2], l[3]);
 }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -75,42 +75,38 @@ __device__ __forceinline__ float block_sum(float v, float *red) {
 }
 
 // ---------------------------------------------------------------------------
-// weight re-tiling: canonical [rows][K] bf16 -> [tile][K/16][lane 64][8], where lane
-// (n % 32) + 32*((k/8)%2) holds W[n][k..k+7]: exactly the A operand of a 32x32x16 MFMA.
+// weight re-tiling: canonical [rows][K] bf16 -> [tile of 32 rows][K/32][fragment 2][lane 64][8], where lane l of fragment f
+// holds W[16 f + l % 16][8 (l / 16) .. + 7 of the k-step]: exactly the A operand of a 16x16x32 MFMA.
 //
 // mode 0: source tile t lands at destination tile t + tile_add (plain, or a row range of a fused matrix).
 // mode 1 / 2 (gate / up of the SwiGLU pair): destination tile t holds feed-forward columns
-// [16t, 16t+16) of BOTH matrices, 4-row groups alternating so that an MFMA output lane owns the
-// gate and the up value of the same 4 columns: tile row n = 8j + 4h + r (j = 0..3, h = 0..1, r = 0..3)
-// is the gate (j even) or up (j odd) row 16t + 8(j/2) + 4h + r.
-// mode 3 (q, k, v projections, head_dim 128): the same interleave inside every head, with the two
-// halves of the head in the roles of gate and up: tile 4*head + t, row n holds the head's dim
-// 16t + 8(j/2) + 4h + r (j even) or that dim + 64 (j odd), so that a lane owns both members of a
-// rotary pair (i, i + 64).
+// [16t, 16t+16) of BOTH matrices, the gate in fragment 0 and up in fragment 1, so that an MFMA output lane owns the
+// gate and the up value of the same 4 columns.
+// mode 3 (q, k, v projections, head_dim 128): the same inside every head, with the two
+// halves of the head in the roles of gate and up: tile 4*head + t holds the head's dims 16t .. 16t+15 and those dims + 64,
+// so that a lane owns both members of a rotary pair (i, i + 64).
 // ---------------------------------------------------------------------------
 __global__ void pack_bf16_kernel(uint4 *dst, const uint16_t *src, int K, int64_t n_chunks, int mode, int tile_add) {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= n_chunks) return;
-    const int ksteps = K >> 4;
-    const int lane = (int)(c & 63);
-    const int64_t tk = c >> 6;
+    const int ksteps = K >> 5;
+    const int lane = (int)(c & 63), f = (int)(c >> 6) & 1;
+    const int64_t tk = c >> 7;
     const int kt = (int)(tk % ksteps);
     const int64_t t = tk / ksteps;                   // destination tile
-    const int n = lane & 31;
-    const int k = kt * 16 + 8 * (lane >> 5);
+    const int n = lane & 15;
+    const int k = kt * 32 + 8 * (lane >> 4);
     int64_t row;
     if (mode == 0) {
-        row = (t - tile_add) * 32 + n;
+        row = (t - tile_add) * 32 + 16 * f + n;
     } else if (mode == 3) {
-        const int j = n >> 3;
         const int64_t tt = t - tile_add;
-        row = (tt >> 2) * 128 + (j & 1) * 64 + (tt & 3) * 16 + 8 * (j >> 1) + (n & 7);
+        row = (tt >> 2) * 128 + f * 64 + (tt & 3) * 16 + n;
     } else {
-        const int j = n >> 3;
-        if ((j & 1) != mode - 1) return;             // this launch fills only its own 4-row groups
-        row = t * 16 + 8 * (j >> 1) + (n & 7);
+        if (f != mode - 1) return;                   // this launch fills only its own fragments
+        row = t * 16 + n;
     }
-    dst[(t * ksteps + kt) * 64 + lane] = *(const uint4 *)(src + row * K + k);
+    dst[c] = *(const uint4 *)(src + row * K + k);
 }
 
 // n_rows source rows.  modes 0, 3: destination tiles tile_add .. tile_add + n_rows/32 - 1;
@@ -118,8 +114,8 @@ __global__ void pack_bf16_kernel(uint4 *dst, const uint16_t *src, int K, int64_t
 void launch_pack_bf16(uint16_t *dst, const uint16_t *src, int n_rows, int K, int mode, int tile_add, hipStream_t st) {
     const bool whole = mode == 0 || mode == 3;
     const int64_t tiles = whole ? n_rows / 32 : n_rows / 16;
-    const int64_t n_chunks = tiles * (K / 16) * 64;
-    uint4 *d = (uint4 *)dst + (whole ? (int64_t)tile_add * (K / 16) * 64 : 0);
+    const int64_t n_chunks = tiles * (K / 32) * 128;
+    uint4 *d = (uint4 *)dst + (whole ? (int64_t)tile_add * (K / 32) * 128 : 0);
     hipLaunchKernelGGL(pack_bf16_kernel, dim3((unsigned)((n_chunks + 255) / 256)), dim3(256), 0, st, d, src, K, n_chunks,
                        mode, 0);
 }
@@ -140,7 +136,7 @@ __device__ __forceinline__ float rms_scale(unsigned long long q, float inv_d, fl
 
 __global__ __launch_bounds__(256) void embed_norm_kernel(const uint16_t *E, const int32_t *row_tok, const float *g,
                                                          float *h, uint16_t *xa, unsigned long long *ssq_out,
-                                                         unsigned long long *ssq_clear, int d, int m_tiles) {
+                                                         unsigned long long *ssq_clear, int d, int units) {
     __shared__ float red[4];
     const int m = blockIdx.x;
     const uint16_t *src = E + (size_t)row_tok[m] * d;
@@ -161,7 +157,7 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(const uint16_t *E, cons
         *(float4 *)(hr + c * 8 + 4) = make_float4(v[4], v[5], v[6], v[7]);
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] *= g[c * 8 + i];
-        store_split8(xa, m, c * 8, m_tiles, v);
+        store_split8(xa, m, c * 8, units, v);
     }
     ss = block_sum<256>(ss, red);
     if (threadIdx.x == 0) {
@@ -174,23 +170,27 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(const uint16_t *E, cons
 // skinny-M GEMM on the matrix cores:  Y[M][N] = X[M][K] * W[N][K]^T, with the stage that follows
 // the GEMM fused into its epilogue.
 //
-// A block of 4 waves covers up to 128 rows (MT tiles of 32) and 4*NT column tiles of 32 (NT = 1, 2, or 4
-// with all 256 accumulator registers in use); wave w owns NT column tiles.  Weights go global -> registers, one fully coalesced 1 KiB fragment per
-// load, PF stages ahead; each weight byte is read once per row block.  Activations (hi and lo
-// planes, already in fragment order) go global -> LDS once per block and are shared by the 4 waves.
-// MFMA 32x32x16: A = weight tile (32 n x 16 k), B = activation tile (16 k x 32 m), so a lane ends up
-// with 4 consecutive output columns of one row per register quad.
-// grid: 1-D over (column group, split-K slice, row block of MT tiles); see the block index decode.
+// A block of 4 waves covers MR row units of 16 (up to 160 rows) and 4*NT column tiles of 32; wave w owns NT column tiles.
+// Weights go global -> registers, one fully coalesced 1 KiB fragment per load, PF stages ahead; each weight byte is read
+// once per row block.  Activations (hi and lo planes, already in fragment order) go global -> LDS once per block and are
+// shared by the 4 waves.
+// MFMA 16x16x32: A = 16 columns of a weight tile (fragment 0 or 1 of it, 32 k), B = activation unit (32 k x 16 rows), so a
+// lane ends up with 4 consecutive output columns of one row per register quad.
+//
+// Matrix work of this chip is bound by its power: 32x32x16 on random hi/lo operands sustains 1.75-1.83 PFLOP/s (at 1.76 GHz),
+// 16x16x32 with the two planes of a product back to back on the same accumulators 2.11-2.15 (at 2.1 GHz; the second product
+// moves only the low bits of sums that the first has just read).  The same with the planes apart: 1.95-2.0.
+// grid: 1-D over (column group, split-K slice, row block of MR units); see the block index decode.
 //
 // Split-K.  With S = 1 the block runs the epilogue itself.  With S > 1 it stores its accumulators
-// in register order (coalesced 1 KiB stores, layout [slice][column tile][row tile]) and gemm_fixup_kernel,
-// one wave per 32x32 output tile, adds the S slices in slice order and runs the same epilogue code.
+// in register order (coalesced 1 KiB stores, layout [slice][column tile][row unit][fragment]) and gemm_fixup_kernel,
+// one wave per 32 columns x 16 rows, adds the S slices in slice order and runs the same epilogue code.
 //
 // Normalisation.  RMSNorm scales row m by r[m] = 1/rms(h[m]) and column k by the gain g[k].  The
 // producer of an activation matrix writes split(h * g) and the rows' sums of squares; the
 // consuming GEMM multiplies its accumulators by r[m] (the scale commutes with the contraction).
 //
-// Epilogues (per 32x32 tile):
+// Epilogues (per 32 columns x 16 rows):
 //   EPI_QKV    rotary embedding of q and k (weight rows of every head are interleaved so that a
 //              lane holds both members of 4 rotary pairs), q -> hi/lo planes for the attention
 //              kernel, k and v -> bf16 into the paged cache at position P + node
@@ -199,16 +199,17 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(const uint16_t *E, cons
 //   EPI_SWIGLU act = split(silu(gate) * up), gate and up rows interleaved in the weight tiles
 //   EPI_ARGMAX per-wave arg-max of every row (+ optional float32 logits); never split
 // ---------------------------------------------------------------------------
-__host__ __device__ constexpr int gemm_ks(int MT, int NT) { return MT * NT >= 12 ? 1 : 2; }      // k-steps per pipeline stage
+// A pipeline stage is KS steps of 32 k.
+__host__ __device__ constexpr int gemm_ks(int MR) { return MR % 2 ? 2 : 1; }      // (an odd number of units does not fill whole loads of 256 threads)
 
 enum { EPI_QKV = 0, EPI_SWIGLU = 1, EPI_ARGMAX = 2, EPI_RESID = 3 };
 
 struct GemmArgs {
     const uint4 *W;          // re-tiled weights
     const uint4 *X;          // xpack activations
-    int n_tiles, k_steps, m_tiles_total, M, N;
+    int n_tiles, k_steps, units_total, M, N;      // k_steps of 32; units_total: row units of the operand buffers
     int col_groups, m_blocks, splits;   // grid decomposition (see the kernel's block index decode)
-    float *part;             // split-K exchange: [S][column tile][row tile][4][64 lanes] float4
+    float *part;             // split-K exchange: [S][column tile][row unit][2][64 lanes] float4
     const unsigned long long *ssq_in;   // [rows] sums of squares of the input rows, or null (input is not a normed stream)
     float inv_d, eps;
     // EPI_RESID
@@ -232,15 +233,15 @@ struct GemmArgs {
     float *logits;           // optional: [M][N]
 };
 
-// Epilogue of one 32x32 output tile held in MFMA register order: lane (row = lane % 32, h = lane / 32)
-// owns columns 8j + 4h + r (j = 0..3, r = 0..3) in acc[4j + r].  T = column tile, m = the lane's row.
+// Epilogue of 32 columns x 16 rows held in MFMA register order: lane (row = lane % 16, q = lane / 16) owns columns
+// 4q + r (r = 0..3) in acc0 and 16 + 4q + r in acc1.  T = column tile, m = the lane's row, nsub = 4q.
 // tile_pre issues every load the epilogue needs that does not depend on the accumulators (so that a
 // caller can overlap them with its own loads); tile_epilogue consumes them and returns the lane's
 // share of the tile's sum of squares (EPI_RESID).
 struct TilePre {
     float rs;                // RMS scale of the row
-    float4 hv[4], gn[4];     // EPI_RESID: residual values and gains of the lane's 16 columns
-    float4 cs[4];            // EPI_QKV: (cos, sin) of the lane's 8 rotary pairs
+    float4 hv[2], gn[2];     // EPI_RESID: residual values and gains of the lane's 8 columns
+    float4 cs[2];            // EPI_QKV: (cos, sin) of the lane's 4 rotary pairs
     int kvloc;               // EPI_QKV: physical page * 16 + token in page of the row's cache position
 };
 
@@ -253,108 +254,92 @@ __device__ __forceinline__ TilePre tile_pre(const GemmArgs &g, int T, int m, int
     if (!RS_KNOWN && g.ssq_in) p.rs = rms_scale(g.ssq_in[m], g.inv_d, g.eps);
     if constexpr (EPI == EPI_RESID) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int nn = T * 32 + 8 * j + nsub;
+        for (int j = 0; j < 2; ++j) {
+            const int nn = T * 32 + 16 * j + nsub;
             p.hv[j] = *(const float4 *)(g.h + (size_t)m * g.N + nn);
             p.gn[j] = *(const float4 *)(g.gain + nn);
         }
     } else if constexpr (EPI == EPI_QKV) {
-        const int hy = T >> 2, th = T & 3;
+        const int hy = T >> 2, i0 = 16 * (T & 3) + nsub;
         if (hy >= g.Hq) p.kvloc = g.row_kvloc[m];
         if (hy < g.Hq + g.Hkv) {
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj) {
-                const int i0 = 16 * th + 8 * jj + nsub;
-                p.cs[2 * jj] = *(const float4 *)(g.row_cs + (size_t)m * 64 + i0);
-                p.cs[2 * jj + 1] = *(const float4 *)(g.row_cs + (size_t)m * 64 + i0 + 2);
-            }
+            p.cs[0] = *(const float4 *)(g.row_cs + (size_t)m * 64 + i0);
+            p.cs[1] = *(const float4 *)(g.row_cs + (size_t)m * 64 + i0 + 2);
         }
     }
     return p;
 }
 
 template <int EPI>
-__device__ __forceinline__ float tile_epilogue(const GemmArgs &g, const f32x16 &acc, int T, int m, int nsub, const TilePre &p) {
+__device__ __forceinline__ float tile_epilogue(const GemmArgs &g, const f32x4 &acc0, const f32x4 &acc1, int T, int m, int nsub, const TilePre &p) {
     float ss = 0.f;
     if (m >= g.M) return ss;
     const float rs = p.rs;
     if constexpr (EPI == EPI_RESID) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int nn = T * 32 + 8 * j + nsub;
+        for (int j = 0; j < 2; ++j) {
+            const int nn = T * 32 + 16 * j + nsub;
+            const f32x4 &a = j ? acc1 : acc0;
             float4 v = p.hv[j];
-            v.x += acc[4 * j]; v.y += acc[4 * j + 1]; v.z += acc[4 * j + 2]; v.w += acc[4 * j + 3];
+            v.x += a[0]; v.y += a[1]; v.z += a[2]; v.w += a[3];
             *(float4 *)(g.h + (size_t)m * g.N + nn) = v;
             ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
             const float4 gn = p.gn[j];
             uint32_t hi[2], lo[2];
             split_pack2(v.x * gn.x, v.y * gn.y, hi[0], lo[0]);
             split_pack2(v.z * gn.z, v.w * gn.w, hi[1], lo[1]);
-            *(uint2 *)(g.xout + xpack_index(m, nn, 0, g.m_tiles_total)) = make_uint2(hi[0], hi[1]);
-            *(uint2 *)(g.xout + xpack_index(m, nn, 1, g.m_tiles_total)) = make_uint2(lo[0], lo[1]);
+            *(uint2 *)(g.xout + xpack_index(m, nn, 0, g.units_total)) = make_uint2(hi[0], hi[1]);
+            *(uint2 *)(g.xout + xpack_index(m, nn, 1, g.units_total)) = make_uint2(lo[0], lo[1]);
         }
     } else if constexpr (EPI == EPI_SWIGLU) {
-        // the tile holds gate (register groups j = 0, 2) and up (j = 1, 3) of 16 feed-forward columns
+        // acc0 holds the gate and acc1 the up values of feed-forward columns 16 T + nsub .. + 3
+        float v[4];
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            float v[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float gt = acc[8 * jj + r] * rs, up = acc[8 * jj + 4 + r] * rs;
-                v[r] = gt / (1.0f + __expf(-gt)) * up;
-            }
-            uint32_t hi[2], lo[2];
-            split_pack2(v[0], v[1], hi[0], lo[0]);
-            split_pack2(v[2], v[3], hi[1], lo[1]);
-            const int f0 = T * 16 + 8 * jj + nsub;
-            *(uint2 *)(g.act + xpack_index(m, f0, 0, g.m_tiles_total)) = make_uint2(hi[0], hi[1]);
-            *(uint2 *)(g.act + xpack_index(m, f0, 1, g.m_tiles_total)) = make_uint2(lo[0], lo[1]);
+        for (int r = 0; r < 4; ++r) {
+            const float gt = acc0[r] * rs, up = acc1[r] * rs;
+            v[r] = gt / (1.0f + __expf(-gt)) * up;
         }
+        uint32_t hi[2], lo[2];
+        split_pack2(v[0], v[1], hi[0], lo[0]);
+        split_pack2(v[2], v[3], hi[1], lo[1]);
+        const int f0 = T * 16 + nsub;
+        *(uint2 *)(g.act + xpack_index(m, f0, 0, g.units_total)) = make_uint2(hi[0], hi[1]);
+        *(uint2 *)(g.act + xpack_index(m, f0, 1, g.units_total)) = make_uint2(lo[0], lo[1]);
     } else if constexpr (EPI == EPI_QKV) {
-        // tile T = 4 * head + t: register groups j = 0, 2 hold dims 16t + 8(j/2) + 4h + r of the head,
-        // groups j = 1, 3 the same dims + 64 (the rotary partners)
+        // tile T = 4 * head + t: acc0 holds dims 16 t + nsub .. + 3 of the head, acc1 the same dims + 64 (the rotary partners)
         const size_t qd = (size_t)g.Hq * 128;
-        const int hy = T >> 2, th = T & 3;
-        uint16_t *kc = nullptr, *vc = nullptr;
-        int tk = 0;
-        if (hy >= g.Hq) {
-            const int kvh = hy < g.Hq + g.Hkv ? hy - g.Hq : hy - g.Hq - g.Hkv;
-            const size_t pb = ((size_t)(p.kvloc >> 4) * g.Hkv + kvh) * (SEV_PAGE * 128);
-            kc = (uint16_t *)g.k_layer + pb;
-            vc = (uint16_t *)(g.k_layer + g.v_offset) + pb;
-            tk = p.kvloc & 15;
-        }
+        const int hy = T >> 2, i0 = 16 * (T & 3) + nsub;
+        float va[4], vb[4];
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-            const int i0 = 16 * th + 8 * jj + nsub;
-            float va[4], vb[4];
+        for (int r = 0; r < 4; ++r) {
+            va[r] = acc0[r] * rs;
+            vb[r] = acc1[r] * rs;
+        }
+        if (hy < g.Hq + g.Hkv) {
+            const float cs[4] = {p.cs[0].x, p.cs[0].z, p.cs[1].x, p.cs[1].z}, sn[4] = {p.cs[0].y, p.cs[0].w, p.cs[1].y, p.cs[1].w};
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                va[r] = acc[8 * jj + r] * rs;
-                vb[r] = acc[8 * jj + 4 + r] * rs;
+                const float x = va[r], y = vb[r];
+                va[r] = x * cs[r] - y * sn[r];
+                vb[r] = y * cs[r] + x * sn[r];
             }
+        }
+        if (hy < g.Hq) {
+            uint32_t hi[2], lo[2];
+            const size_t o = (size_t)m * qd + (size_t)hy * 128 + i0;
+            split_pack2(va[0], va[1], hi[0], lo[0]);
+            split_pack2(va[2], va[3], hi[1], lo[1]);
+            *(uint2 *)(g.q_planes + o) = make_uint2(hi[0], hi[1]);
+            *(uint2 *)(g.q_planes + (size_t)g.M * qd + o) = make_uint2(lo[0], lo[1]);
+            split_pack2(vb[0], vb[1], hi[0], lo[0]);
+            split_pack2(vb[2], vb[3], hi[1], lo[1]);
+            *(uint2 *)(g.q_planes + o + 64) = make_uint2(hi[0], hi[1]);
+            *(uint2 *)(g.q_planes + (size_t)g.M * qd + o + 64) = make_uint2(lo[0], lo[1]);
+        } else {
+            const int kvh = hy < g.Hq + g.Hkv ? hy - g.Hq : hy - g.Hq - g.Hkv, tk = p.kvloc & 15;
+            const size_t pb = ((size_t)(p.kvloc >> 4) * g.Hkv + kvh) * (SEV_PAGE * 128);
             if (hy < g.Hq + g.Hkv) {
-                const float4 c01 = p.cs[2 * jj], c23 = p.cs[2 * jj + 1];
-                const float cs[4] = {c01.x, c01.z, c23.x, c23.z}, sn[4] = {c01.y, c01.w, c23.y, c23.w};
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float x = va[r], y = vb[r];
-                    va[r] = x * cs[r] - y * sn[r];
-                    vb[r] = y * cs[r] + x * sn[r];
-                }
-            }
-            if (hy < g.Hq) {
-                uint32_t hi[2], lo[2];
-                const size_t o = (size_t)m * qd + (size_t)hy * 128 + i0;
-                split_pack2(va[0], va[1], hi[0], lo[0]);
-                split_pack2(va[2], va[3], hi[1], lo[1]);
-                *(uint2 *)(g.q_planes + o) = make_uint2(hi[0], hi[1]);
-                *(uint2 *)(g.q_planes + (size_t)g.M * qd + o) = make_uint2(lo[0], lo[1]);
-                split_pack2(vb[0], vb[1], hi[0], lo[0]);
-                split_pack2(vb[2], vb[3], hi[1], lo[1]);
-                *(uint2 *)(g.q_planes + o + 64) = make_uint2(hi[0], hi[1]);
-                *(uint2 *)(g.q_planes + (size_t)g.M * qd + o + 64) = make_uint2(lo[0], lo[1]);
-            } else if (hy < g.Hq + g.Hkv) {
+                uint16_t *kc = (uint16_t *)g.k_layer + pb;
                 *(uint2 *)(kc + k_in_page<true>(tk, i0, 128)) =
                     make_uint2(f32_to_bf16_bits(va[0]) | (f32_to_bf16_bits(va[1]) << 16),
                                f32_to_bf16_bits(va[2]) | (f32_to_bf16_bits(va[3]) << 16));
@@ -362,6 +347,7 @@ __device__ __forceinline__ float tile_epilogue(const GemmArgs &g, const f32x16 &
                     make_uint2(f32_to_bf16_bits(vb[0]) | (f32_to_bf16_bits(vb[1]) << 16),
                                f32_to_bf16_bits(vb[2]) | (f32_to_bf16_bits(vb[3]) << 16));
             } else {
+                uint16_t *vc = (uint16_t *)(g.k_layer + g.v_offset) + pb;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     vc[v_in_page<true>(tk, i0 + r, 128)] = (uint16_t)f32_to_bf16_bits(va[r]);
@@ -373,7 +359,7 @@ __device__ __forceinline__ float tile_epilogue(const GemmArgs &g, const f32x16 &
     return ss;
 }
 
-// Adds a block's per-row sums of squares (one value per lane < 32 and wave, in red[wave][row]) to
+// Adds a block's per-row sums of squares (one value per lane < 16 and wave, in red[wave][row]) to
 // ssq_out and clears ssq_clear; rows = number of rows covered, m0 = first row.
 template <int STRIDE>
 __device__ __forceinline__ void ssq_commit(const GemmArgs &g, float (*red)[STRIDE], int rows, int m0, bool clear) {
@@ -398,23 +384,42 @@ __device__ __forceinline__ void ssq_commit(const GemmArgs &g, float (*red)[STRID
 // dwords of the argument block to the wave in registers at launch, so the first loads can be issued
 // without waiting for a scalar load of the argument block.
 //
-// HALF: the wave's last column tile is shared with the wave beside it, each of the two doing half of the row tiles, so that
-// a block covers 4 (NT - 1) + 2 column tiles (6, 10 or 14) and every wave has the same MT (NT - 1/2) tiles of work.  The
-// odd wave of a pair carries its row tiles in the order "upper half first": its shared tile then uses the same registers
+// HALF: the wave's last column tile is shared with the wave beside it, each of the two doing half of the row units, so that
+// a block covers 4 (NT - 1) + 2 column tiles (6, 10 or 14) and every wave has the same MR (NT - 1/2) units of work.  The
+// odd wave of a pair carries its row units in the order "upper half first": its shared tile then uses the same registers
 // as the even wave's, and no fragment is indexed by a run-time value.
-template <int MT, int NT, int EPI, int PF, bool HALF = false>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const uint4 *X_, int n_tiles_, int k_steps_, int m_tiles_total_,
+//
+// Accumulators.  Left to itself the compiler gives every product of this instruction a destination of its own and moves
+// accumulators about in the loop (60-300 moves in 256 products).  Instances whose registers fit the 256 of a wave's
+// directly addressable file are compiled with the sums there (-amdgpu-mfma-vgpr-form), where it does not happen; the larger ones (ACC_A) name
+// the accumulator file and tie source and destination in mfma_pair's assembly statement.
+__host__ __device__ constexpr bool gemm_acc_a(int MR, int NT, int PF) {
+    return 8 * NT * MR + 4 * PF * gemm_ks(MR) * (2 * NT + MR / 2) + 32 > 190;      // sums, fragments in flight, the ring of units
+}
+
+// acc += w * (hi plane) + w * (lo plane).  (Statements keep their order; the products of a pair follow each other on the same
+// accumulators, which needs no wait states, and their operands come from loads, which the compiler awaits.)
+__device__ __forceinline__ void mfma_pair_a(f32x4 &acc, u32x4 w, u32x4 hi, u32x4 lo) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %3, %0" : "+a"(acc) : "v"(w), "v"(hi), "v"(lo));
+}
+
+template <int MR, int NT, int EPI, int PF, bool HALF = false>
+__global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const uint4 *X_, int n_tiles_, int k_steps_, int units_total_,
                                                         int col_groups_, int m_blocks_, int splits_, GemmArgs g) {
-    g.W = W_; g.X = X_; g.n_tiles = n_tiles_; g.k_steps = k_steps_; g.m_tiles_total = m_tiles_total_;
+    g.W = W_; g.X = X_; g.n_tiles = n_tiles_; g.k_steps = k_steps_; g.units_total = units_total_;
     g.col_groups = col_groups_; g.m_blocks = m_blocks_; g.splits = splits_ & 0xffff;
     const int tpb = splits_ >> 16;                      // column tiles per block: 4 * NT, or fewer (the last wave then has fewer tiles)
-    // a pipeline stage is KS k-steps of 16: two for the narrow tiles, one from 12 tiles per wave on (24 ... 32 MFMAs)
-    constexpr int KS = gemm_ks(MT, NT);
-    constexpr int XI = KS * MT / 2;                     // 16-byte activation loads per thread and stage
-    static_assert(KS * MT % 2 == 0, "a stage of activations must be a whole number of 4 KiB");
-    extern __shared__ u32x4 xs[];                       // [2 buffers][KS k-steps][MT][2 planes][64 lanes]
-    __shared__ float red[4][MT * 32 < 128 ? 128 : MT * 32];
-    constexpr int STAGE_U4 = KS * MT * 2 * 64;          // uint4 per stage
+    constexpr int KS = gemm_ks(MR);
+    constexpr int NF = 2 * NT;                          // weight fragments per wave and k-step: two per column tile
+    constexpr int XI = KS * MR / 2;                     // 16-byte activation loads per thread and stage
+    static_assert(KS * MR % 2 == 0, "a stage of activations must be a whole number of 4 KiB");
+    constexpr bool ACC_A = gemm_acc_a(MR, NT, PF);
+    constexpr int G = KS * MR;                          // groups of products per stage: one activation unit x all weight fragments
+    constexpr int AHEAD = G < 3 ? G : 3;                // an activation unit is read from LDS that many groups before its products
+    static_assert(PF * G % 4 == 0, "the ring of four activation units must close with the loop body");
+    extern __shared__ u32x4 xs[];                       // [3 buffers][KS k-steps][MR][2 planes][64 lanes]
+    __shared__ float red[4][MR * 16 < 128 ? 128 : MR * 16];
+    constexpr int STAGE_U4 = KS * MR * 2 * 64;          // uint4 per stage
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // Block index decode, XCD-aware: consecutive block ids go round-robin to the 8 XCDs, each with its
     // own L2.  Blocks that share weight tiles (the row blocks of one column group) get ids 8 apart,
@@ -430,79 +435,76 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     auto lct = [&](int a) { return !HALF ? wave * NT + a : (a < NT - 1 ? wave * (NT - 1) + a : 4 * (NT - 1) + (wave >> 1)); };
     auto have = [&](int a) { return lct(a) < block_tiles; };
     auto coltile = [&](int a) { return cg * tpb + lct(a); };
-    const int mt0 = mb * MT;
-    constexpr int MH = MT / 2;
-    static_assert(!HALF || MT % 2 == 0, "a shared tile is split into two halves of the row tiles");
+    const int u0 = mb * MR;                              // first row unit
+    constexpr int MH = MR / 2;
+    static_assert(!HALF || MR % 2 == 0, "a shared tile is split into two halves of the row units");
     const int par = HALF ? wave & 1 : 0;
-    auto rt = [&](int b) { return !HALF ? b : (b < MH ? b + par * MH : b - par * MH); };      // row tile behind register slot b
-    auto rows_of = [&](int a) { return HALF && a == NT - 1 ? MH : MT; };                       // slots of column tile a
+    auto ru = [&](int b) { return !HALF ? b : (b < MH ? b + par * MH : b - par * MH); };      // row unit behind register slot b
+    auto rows_of = [&](int a) { return HALF && a == NT - 1 ? MH : MR; };                       // slots of column tile a
     const int n_stages = g.k_steps / KS;
     const int s_begin = (int)((unsigned)n_stages * (unsigned)split / (unsigned)g.splits);          // small numbers: 32-bit division
     const int s_end = (int)((unsigned)n_stages * (unsigned)(split + 1) / (unsigned)g.splits);
     const int n = s_end - s_begin;
-    const int mrow = lane & 31, nsub = 4 * (lane >> 5);
+    const int mrow = lane & 15, nsub = 4 * (lane >> 4);
 
-    f32x16 acc[NT][MT];
+    f32x4 acc[NF][MR];
 #pragma unroll
-    for (int a = 0; a < NT; ++a)
+    for (int a = 0; a < NF; ++a)
 #pragma unroll
-        for (int b = 0; b < MT; ++b)
+        for (int b = 0; b < MR; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+            for (int r = 0; r < 4; ++r) acc[a][b][r] = 0.f;
 
     // weight fragment pointers of this lane (clamped to a valid tile so idle waves load harmlessly)
     const u32x4 *wp[NT];
 #pragma unroll
     for (int a = 0; a < NT; ++a) {
         const int t = min(coltile(a), g.n_tiles - 1);
-        wp[a] = (const u32x4 *)g.W + ((size_t)t * g.k_steps) * 64 + lane;
+        wp[a] = (const u32x4 *)g.W + ((size_t)t * g.k_steps) * 128 + lane;
     }
     // The gate/up GEMM reads its weights through a buffer descriptor that covers exactly the block's column tiles: a
     // tile the wave does not have (blocks of fewer than 4 * NT tiles, the matrix edge) lies past the descriptor's
     // end, where a load returns zeros and reads nothing, so the loop stays free of branches and the missing tile
     // costs no memory traffic.
-    constexpr bool WBUF = EPI == EPI_SWIGLU && MT <= 2;      // the 128-row blocks never run narrower than 4 * NT tiles
+    constexpr bool WBUF = EPI == EPI_SWIGLU && MR <= 4;      // the 128-row blocks never run narrower than 4 * NT tiles
     const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)((const u32x4 *)g.W + (size_t)cg * tpb * g.k_steps * 64), 0, block_tiles * g.k_steps * 1024, 0x00020000);
+        (void *)((const u32x4 *)g.W + (size_t)cg * tpb * g.k_steps * 128), 0, block_tiles * g.k_steps * 2048, 0x00020000);
     int woff[NT];
 #pragma unroll
-    for (int a = 0; a < NT; ++a) woff[a] = ((lct(a) * g.k_steps) * 64 + lane) * 16;
-    auto load_w = [&](int a, int step) -> u32x4 {      // 16 bytes per lane of k-step `step` of the wave's column tile a
+    for (int a = 0; a < NT; ++a) woff[a] = ((lct(a) * g.k_steps) * 128 + lane) * 16;
+    auto load_w = [&](int f, int step) -> u32x4 {      // 16 bytes per lane of k-step `step`: fragment f & 1 of the wave's column tile f / 2
         // The streaming hint keeps the weights from displacing the activations in the L2s (gate/up: 7 % faster with it).
-        // The QKV projection streams the fewest weights per activation byte and is 4 % faster with plain loads.  Blocks of 3
-        // and 4 row tiles keep the hint although their row blocks share the weights through an L2; plain loads there, timed in
+        // The QKV projection streams the fewest weights per activation byte and is 4 % faster with plain loads.  Blocks of 96
+        // and 128 rows keep the hint although their row blocks share the weights through an L2; plain loads there, timed in
         // turn: 192 rows of the 8B shape gate/up 88.6 -> 89.8 us and QKV behind it 33.5 -> 34.4, 416 rows down 105.2 -> 106.7,
         // 480 rows of the 70B shape O 131.3 -> 132.9.  The one that gains from plain loads is down of the 70B shape at 176 rows
         // (178.5 -> 176.4, where gate/up loses twice that).
-        if constexpr (WBUF) return __builtin_amdgcn_raw_buffer_load_b128(wrs, woff[a] + step * 1024, 0, 2);      // 2: streaming hint
-        else if constexpr (EPI == EPI_QKV) return wp[a][(size_t)step * 64];
-        else return __builtin_nontemporal_load(&wp[a][(size_t)step * 64]);
+        if constexpr (WBUF) return __builtin_amdgcn_raw_buffer_load_b128(wrs, woff[f >> 1] + step * 2048 + (f & 1) * 1024, 0, 2);      // 2: streaming hint
+        else if constexpr (EPI == EPI_QKV) return wp[f >> 1][(size_t)step * 128 + (f & 1) * 64];
+        else return __builtin_nontemporal_load(&wp[f >> 1][(size_t)step * 128 + (f & 1) * 64]);
     };
     // Software pipeline.  Loads return in issue order, so a wait on one load drains every older one:
     // to keep PF stages in flight, weights AND activations are fetched PF stages ahead into registers
     // and consumed in the order they were issued.  At the start of stage st (slot u = st % PF):
-    //   xf holds the activation fragments of stage st;  LDS buffer (st+1)&1 holds X(st+1);
-    //   wreg[u] holds W(st);  xreg[u] holds X(st+2).
-    // During the stage each fragment register is refilled from LDS with its stage st+1 contents right
-    // after its last MFMA, so the LDS reads of the next stage overlap the MFMAs of this one, and
-    // X(st+2) goes from registers into the LDS buffer that stage st no longer reads (free since the
-    // barrier that ended stage st-1).
+    //   LDS buffers st % 3 and (st+1) % 3 hold X(st) and X(st+1);  wreg[u] holds W(st);  xreg[u] holds X(st+2).
+    // The activation units pass through a ring of four register pairs: during a group's products the unit AHEAD groups later
+    // is read from LDS, so that no product waits for LDS and the reads are spread evenly.  X(st+2) goes from registers into
+    // the third LDS buffer, whose contents (stage st-1) were last read before the barrier that ended stage st-1; one barrier
+    // per stage.
     // The loop body is PF stages of straight-line code (no branches), which lets the compiler's
     // wait-count bookkeeping follow the loads across the back-edge.  The slice is padded to a multiple
-    // of PF stages: padded stages re-load the last stage (cached) and feed zero activations.
-    // Weights are read exactly once per row block: their loads carry the streaming (non-temporal) hint.
-    static_assert(PF % 2 == 0, "LDS buffer parity must follow the slot index");
-    u32x4 wreg[PF][NT][KS];
+    // of PF stages; padded stages re-load the last stage (cached) and are not multiplied.
+    u32x4 wreg[PF][KS][NF];
     u32x4 xreg[PF][XI];
-    u32x4 xf[KS][MT][2];
+    u32x4 xf[4][2];
     const u32x4 *xsrc[XI];
 #pragma unroll
     for (int i = 0; i < XI; ++i) {
         const int u = threadIdx.x + 256 * i;
-        const int ksl = u / (MT * 128), within = u - ksl * (MT * 128);
-        xsrc[i] = (const u32x4 *)g.X + ((size_t)ksl * g.m_tiles_total + mt0) * 128 + within;
+        const int ksl = u / (MR * 128), within = u - ksl * (MR * 128);
+        xsrc[i] = (const u32x4 *)g.X + ((size_t)ksl * g.units_total + u0) * 128 + within;
     }
-    const size_t x_stage = (size_t)KS * g.m_tiles_total * 128;      // 16-byte units per stage of all row tiles
+    const size_t x_stage = (size_t)KS * g.units_total * 128;        // 16-byte units per stage of all row units
     const int n_pad = (n + PF - 1) / PF * PF;
     // Every column group walks its K range from a different starting stage (and wraps around): the
     // blocks that run at the same time would otherwise all read the same few KiB of activations at the
@@ -511,13 +513,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     // slices keep the common start: they are mostly pipeline fill, where sharing the first misses wins.
     // So do four and more row blocks: their activations no longer fit an L2, and the column groups of an XCD then share
     // what one of them fetched (512 rows: a step of 17.0 -> 16.7 ms, 2048 rows -2 %).
-    const int rot = n >= 64 && g.m_blocks < 4 ? (int)((unsigned)cg * (unsigned)n / (unsigned)g.col_groups) : 0;
+    const int rot = n * KS >= 64 && g.m_blocks < 4 ? (int)((unsigned)cg * (unsigned)n / (unsigned)g.col_groups) : 0;
     auto phys = [&](int t) {                                        // logical stage -> stage index in K
         int i = min(t, n - 1) + rot;
         if (i >= n) i -= n;
         return s_begin + i;
     };
-    const u32x4 zero4 = (u32x4){0u, 0u, 0u, 0u};
 
     {
         u32x4 x0[XI], x1[XI];
@@ -532,22 +533,22 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
 #pragma unroll
             for (int i = 0; i < XI; ++i) xreg[u][i] = xsrc[i][(size_t)sx * x_stage];
 #pragma unroll
-            for (int a = 0; a < NT; ++a)
+            for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) wreg[u][a][ks] = load_w(a, KS * sw + ks);
+                for (int f = 0; f < NF; ++f) wreg[u][ks][f] = load_w(f, KS * sw + ks);
         }
 #pragma unroll
         for (int i = 0; i < XI; ++i) {
             xs[threadIdx.x + 256 * i] = x0[i];
-            xs[STAGE_U4 + threadIdx.x + 256 * i] = (1 < n) ? x1[i] : zero4;
+            xs[STAGE_U4 + threadIdx.x + 256 * i] = x1[i];
         }
     }
     // a block that runs the epilogue itself fetches its rows' sums of squares now, so that the row scales are
     // there when the loop ends
-    unsigned long long sq_rows[MT];
+    unsigned long long sq_rows[MR];
 #pragma unroll
-    for (int b = 0; b < MT; ++b) {
-        const int m = (mt0 + rt(b)) * 32 + mrow;
+    for (int b = 0; b < MR; ++b) {
+        const int m = (u0 + ru(b)) * 16 + mrow;
         sq_rows[b] = (g.splits == 1 && g.ssq_in && m < g.M) ? g.ssq_in[m] : 0ull;
     }
     // the rest of the argument block (epilogue pointers): fetched now, behind the first loads
@@ -555,18 +556,20 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     else if constexpr (EPI == EPI_ARGMAX) SEV_ARGS_NOW("s"(g.part), "s"(g.ssq_in), "s"(g.lm_val), "s"(g.logits));
     else SEV_ARGS_NOW("s"(g.part), "s"(g.ssq_in), "s"(g.act));
     __syncthreads();
+    // LDS places of X(st), X(st+1) and X(st+2), in 16-byte units
+    int xb0 = 0, xb1 = STAGE_U4, xb2 = 2 * STAGE_U4;
+    auto read_unit = [&](int at, int grp, u32x4 (&to)[2]) {      // group grp of the stage at `at`
+        const int ks = grp / MR, b = grp % MR;
+        const u32x4 *p = xs + at + lane + (HALF ? (b < MH ? par * MH * 128 : -par * MH * 128) : 0);
+        to[0] = p[((ks * MR + b) * 2) * 64];
+        to[1] = p[((ks * MR + b) * 2 + 1) * 64];
+    };
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int b = 0; b < MT; ++b)
-#pragma unroll
-            for (int pl = 0; pl < 2; ++pl) xf[ks][b][pl] = xs[((ks * MT + rt(b)) * 2 + pl) * 64 + lane];
-    __syncthreads();                                    // stage 0 overwrites buffer 0 early: every wave must have read its X(0) fragments
+    for (int i = 0; i < AHEAD; ++i) read_unit(xb0, i, xf[i & 3]);
 
     // One group of PF stages.  The last group of a slice issues no global loads: what it would
     // prefetch lies beyond the slice, and the epilogue would have to wait for those loads to return
     // before it may reuse their registers.
-    auto last_use = [&](int b) { return HALF && b >= MH ? NT - 2 : NT - 1; };                  // column tile after which fragment b is refilled
     auto group = [&](int base, auto load_tag) {
         constexpr bool LOAD = decltype(load_tag)::value;
 #pragma unroll
@@ -575,84 +578,84 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
             if constexpr (!LOAD) {
                 if (st >= n) break;                     // padding of the slice (uniform): nothing left to multiply
             }
-            const u32x4 *xnext = xs + ((u + 1) & 1) * STAGE_U4 + lane;      // X(st+1)
-            const u32x4 *xnext_lo = xnext + (HALF ? par * MH * 128 : 0), *xnext_hi = xnext - (HALF ? par * MH * 128 : 0);
-            // X(st+2): registers -> the LDS buffer whose fragments (stage st) were read during stage st-1
-            const bool live = st + 2 < n;
-            u32x4 *xd = xs + (u & 1) * STAGE_U4 + threadIdx.x;
             const int sx = phys(st + PF + 2), sw = phys(st + PF);
             // Everything else a stage has to do is spread between its MFMAs, so that the matrix pipe
-            // never waits for a run of address arithmetic, loads and LDS traffic at the stage's end:
-            // a weight fragment is refilled right after its last MFMA (column tiles are the outer loop),
-            // the LDS write of X(st+2) and the loads that refill its registers follow the first group,
-            // and every activation fragment is re-read from LDS (stage st+1) after its last use, which
-            // falls into the last column tile's group.
+            // never waits for a run of address arithmetic, loads and LDS traffic: the LDS write of X(st+2) and the loads that
+            // refill its registers sit in the first group, a weight fragment is refilled right after its last product.
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
+            for (int grp = 0; grp < G; ++grp) {
+                const int ks = grp / MR, b = grp % MR, slot = (u * G + grp) & 3, far = (u * G + grp + AHEAD) & 3;
+                if (grp + AHEAD < G) read_unit(xb0, grp + AHEAD, xf[far]);
+                else read_unit(xb1, grp + AHEAD - G, xf[far]);
 #pragma unroll
-                for (int a = 0; a < NT; ++a) {
-                    const bf16x8 w = as_bf16x8(wreg[u][a][ks]);
+                for (int f = 0; f < NF; ++f) {
+                    const bool mine = b < rows_of(f >> 1);
+                    if (mine) {
+                        const bf16x8 w = as_bf16x8(wreg[u][ks][f]);
+                        if constexpr (ACC_A) mfma_pair_a(acc[f][b], wreg[u][ks][f], xf[slot][0], xf[slot][1]);
+                        else acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, as_bf16x8(xf[slot][0]), acc[f][b], 0, 0, 0);
+                        if constexpr (!ACC_A) acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, as_bf16x8(xf[slot][1]), acc[f][b], 0, 0, 0);
+                    }
+                    if constexpr (LOAD) {
+                        if (b == rows_of(f >> 1) - 1) wreg[u][ks][f] = load_w(f, KS * sw + ks);
+                    }
+                }
+                if (grp == 0) {
 #pragma unroll
-                    for (int pl = 0; pl < 2; ++pl)
+                    for (int i = 0; i < XI; ++i) xs[xb2 + threadIdx.x + 256 * i] = xreg[u][i];
+                    if constexpr (LOAD) {
 #pragma unroll
-                        for (int b = 0; b < MT; ++b) {
-                            if (b >= rows_of(a)) continue;
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, as_bf16x8(xf[ks][b][pl]), acc[a][b], 0, 0, 0);
-                            if (a == last_use(b)) xf[ks][b][pl] = (b < MH ? xnext_lo : xnext_hi)[((ks * MT + b) * 2 + pl) * 64];
-                        }
-                    if constexpr (LOAD) wreg[u][a][ks] = load_w(a, KS * sw + ks);
-                    if (ks == 0 && a == 0) {
-#pragma unroll
-                        for (int i = 0; i < XI; ++i) xd[256 * i] = live ? xreg[u][i] : zero4;
-                        if constexpr (LOAD) {
-#pragma unroll
-                            for (int i = 0; i < XI; ++i) xreg[u][i] = xsrc[i][(size_t)sx * x_stage];
-                        }
+                        for (int i = 0; i < XI; ++i) xreg[u][i] = xsrc[i][(size_t)sx * x_stage];
                     }
                 }
             }
             // the same order for the instruction scheduler (0x008 MFMA, 0x100 DS read, 0x200 DS write, 0x020 VMEM read)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
+            for (int grp = 0; !ACC_A && grp < G; ++grp) {
+                const int b = grp % MR;
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
-                for (int a = 0; a < NT; ++a) {
-                    if (a < NT - (HALF ? 2 : 1)) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 2 * MT, 0);
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 2 * MT; ++i) {
-                            const int b = i % MT;
-                            if (b >= rows_of(a)) continue;
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                            if (a == last_use(b)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                        }
-                    }
-                    if constexpr (LOAD) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-                    if (ks == 0 && a == 0) {
-                        __builtin_amdgcn_sched_group_barrier(0x200, XI, 0);
-                        if constexpr (LOAD) __builtin_amdgcn_sched_group_barrier(0x020, XI, 0);
-                    }
+                for (int f = 0; f < NF; ++f) {
+                    if (b < rows_of(f >> 1)) __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+                    if (LOAD && b == rows_of(f >> 1) - 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                }
+                if (grp == 0) {
+                    __builtin_amdgcn_sched_group_barrier(0x200, XI, 0);
+                    if constexpr (LOAD) __builtin_amdgcn_sched_group_barrier(0x020, XI, 0);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
             __syncthreads();
+            const int t = xb0;
+            xb0 = xb1;
+            xb1 = xb2;
+            xb2 = t;
         }
     };
     for (int base = 0; base + PF < n_pad; base += PF) group(base, std::true_type{});
     group(n_pad - PF, std::false_type{});
+    if constexpr (ACC_A) {                              // the last products must have left the pipe before their sums are read
+        asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+        for (int a = 0; a < NF; ++a)
+#pragma unroll
+            for (int b = 0; b < MR; ++b) asm volatile("" : "+a"(acc[a][b]));
+    }
 
     // ------------------------------------------------------------------ split-K: hand the slice to the fix-up kernel
     if (g.splits > 1) {
-        // exchange layout [slice][column tile][row tile][4][64 lanes] float4: register order, 1 KiB per store instruction
+        // exchange layout [slice][column tile][row unit][2][64 lanes] float4: register order, 1 KiB per store instruction
 #pragma unroll
         for (int a = 0; a < NT; ++a)
             if (have(a)) {
 #pragma unroll
                 for (int b = 0; b < rows_of(a); ++b) {
-                    float4 *mine = (float4 *)g.part + (((size_t)split * g.n_tiles + coltile(a)) * g.m_tiles_total + mt0 + rt(b)) * 256 + lane;
+                    float4 *mine = (float4 *)g.part + (((size_t)split * g.n_tiles + coltile(a)) * g.units_total + u0 + ru(b)) * 128 + lane;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        mine[j * 64] = make_float4(acc[a][b][4 * j], acc[a][b][4 * j + 1], acc[a][b][4 * j + 2], acc[a][b][4 * j + 3]);
+                    for (int j = 0; j < 2; ++j) {
+                        const f32x4 &v = acc[2 * a + j][b];
+                        mine[j * 64] = make_float4(v[0], v[1], v[2], v[3]);
+                    }
                 }
             }
         return;
@@ -660,57 +663,56 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
 
     // ------------------------------------------------------------------ epilogues
     if constexpr (EPI != EPI_ARGMAX) {
-        float ss[MT];
+        float ss[MR];
 #pragma unroll
-        for (int b = 0; b < MT; ++b) {
+        for (int b = 0; b < MR; ++b) {
             ss[b] = 0.f;
-            const int m = (mt0 + rt(b)) * 32 + mrow;
+            const int m = (u0 + ru(b)) * 16 + mrow;
             const float rs_b = g.ssq_in ? rms_scale(sq_rows[b], g.inv_d, g.eps) : 1.0f;
 #pragma unroll
             for (int a = 0; a < NT; ++a)
                 if (b < rows_of(a) && have(a)) {
                     const TilePre pre = tile_pre<EPI, true>(g, coltile(a), m, nsub, rs_b);
-                    ss[b] += tile_epilogue<EPI>(g, acc[a][b], coltile(a), m, nsub, pre);
+                    ss[b] += tile_epilogue<EPI>(g, acc[2 * a][b], acc[2 * a + 1][b], coltile(a), m, nsub, pre);
                 }
         }
         if constexpr (EPI == EPI_RESID) {
 #pragma unroll
-            for (int b = 0; b < MT; ++b) {
+            for (int b = 0; b < MR; ++b) {
+                ss[b] += __shfl_xor(ss[b], 16);
                 ss[b] += __shfl_xor(ss[b], 32);
-                if (lane < 32) red[wave][rt(b) * 32 + mrow] = ss[b];
+                if (lane < 16) red[wave][ru(b) * 16 + mrow] = ss[b];
             }
-            ssq_commit(g, red, MT * 32, mt0 * 32, cg == 0);
+            ssq_commit(g, red, MR * 16, u0 * 16, cg == 0);
         }
     } else {
         // arg-max over this wave's columns for every row (lowest index wins ties); the row scale is
         // positive, so it only matters for the logits that are written out
 #pragma unroll
-        for (int b = 0; b < MT; ++b) {
-            const int m = (mt0 + rt(b)) * 32 + mrow;
+        for (int b = 0; b < MR; ++b) {
+            const int m = (u0 + ru(b)) * 16 + mrow;
             const float rsb = (g.logits && g.ssq_in && m < g.M) ? rms_scale(sq_rows[b], g.inv_d, g.eps) : 1.0f;
             float bv = -INFINITY;
             int bi = 0x7fffffff;
 #pragma unroll
-            for (int a = 0; a < NT; ++a) {
-                if (b >= rows_of(a) || !have(a)) continue;
+            for (int f = 0; f < NF; ++f) {
+                if (b >= rows_of(f >> 1) || !have(f >> 1)) continue;
+                const int nn = coltile(f >> 1) * 32 + 16 * (f & 1) + nsub;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int nn = coltile(a) * 32 + 8 * j + nsub;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float v = acc[a][b][4 * j + r];
-                        if (v > bv) { bv = v; bi = nn + r; }       // indices ascend, so ">" keeps the lowest
-                    }
-                    if (g.logits && m < g.M)
-                        *(float4 *)(g.logits + (size_t)m * g.N + nn) =
-                            make_float4(acc[a][b][4 * j] * rsb, acc[a][b][4 * j + 1] * rsb, acc[a][b][4 * j + 2] * rsb,
-                                        acc[a][b][4 * j + 3] * rsb);
+                for (int r = 0; r < 4; ++r) {
+                    const float v = acc[f][b][r];
+                    if (v > bv) { bv = v; bi = nn + r; }       // indices ascend, so ">" keeps the lowest
                 }
+                if (g.logits && m < g.M)
+                    *(float4 *)(g.logits + (size_t)m * g.N + nn) = make_float4(acc[f][b][0] * rsb, acc[f][b][1] * rsb, acc[f][b][2] * rsb, acc[f][b][3] * rsb);
             }
-            const float ov = __shfl_xor(bv, 32);
-            const int oi = __shfl_xor(bi, 32);
-            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-            if (lane < 32 && m < g.M) {
+#pragma unroll
+            for (int o = 16; o < 64; o *= 2) {
+                const float ov = __shfl_xor(bv, o);
+                const int oi = __shfl_xor(bi, o);
+                if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+            }
+            if (lane < 16 && m < g.M) {
                 const size_t slot = (size_t)(cg * 4 + wave) * g.lm_stride + m;
                 g.lm_val[slot] = bv;
                 g.lm_idx[slot] = bi;
@@ -719,40 +721,40 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     }
 }
 
-// Split-K fix-up: block (group of 4 column tiles, row tile mt) of 4 waves; wave w sums the S slices of the
-// 32x32 tile (column tile 4 * group + w, row tile mt) in slice order and runs its epilogue.
+// Split-K fix-up: block (group of 4 column tiles, row unit) of 4 waves; wave w sums the S slices of 32 columns x 16 rows
+// (column tile 4 * group + w, row unit ru) in slice order and runs the epilogue.
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_fixup_kernel(const float *part_, const void *pa_, const void *pb_, const unsigned long long *ssq_in_,
-                                                         int m_tiles_real_, int m_tiles_total_, int splits_, int n_tiles_, int M_, int N_, int heads_,
+                                                         int units_real_, int units_total_, int splits_, int n_tiles_, int M_, int N_, int heads_,
                                                          GemmArgs g) {
     __shared__ float red[4][128];
     // leading scalars (preloaded at wave launch): everything the first loads need; pa_ / pb_ are the residual stream and
     // the gains (EPI_RESID) or the rotary table and the rows' cache locations (EPI_QKV); heads_ = query heads | KV heads << 16
-    g.part = const_cast<float *>(part_); g.ssq_in = ssq_in_; g.m_tiles_total = m_tiles_total_;
+    g.part = const_cast<float *>(part_); g.ssq_in = ssq_in_; g.units_total = units_total_;
     g.splits = splits_; g.n_tiles = n_tiles_; g.M = M_; g.N = N_;
     g.Hq = heads_ & 0xffff; g.Hkv = heads_ >> 16;
     if constexpr (EPI == EPI_RESID) { g.h = (float *)const_cast<void *>(pa_); g.gain = (const float *)pb_; }
     if constexpr (EPI == EPI_QKV) { g.row_cs = (const float2 *)pa_; g.row_kvloc = (const int32_t *)pb_; }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int mt = blockIdx.x % m_tiles_real_, grp = blockIdx.x / m_tiles_real_;
+    const int unit = blockIdx.x % units_real_, grp = blockIdx.x / units_real_;
     const int T = grp * 4 + wave;
-    const int mrow = lane & 31, nsub = 4 * (lane >> 5);
-    const int m = mt * 32 + mrow;
-    const size_t slice_stride = (size_t)g.n_tiles * g.m_tiles_total * 256;
-    const float4 *src = (const float4 *)g.part + ((size_t)min(T, g.n_tiles - 1) * g.m_tiles_total + mt) * 256 + lane;
-    f32x16 acc;
+    const int mrow = lane & 15, nsub = 4 * (lane >> 4);
+    const int m = unit * 16 + mrow;
+    const size_t slice_stride = (size_t)g.n_tiles * g.units_total * 128;
+    const float4 *src = (const float4 *)g.part + ((size_t)min(T, g.n_tiles - 1) * g.units_total + unit) * 128 + lane;
+    f32x4 acc[2];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int r = 0; r < 4; ++r) acc[0][r] = acc[1][r] = 0.f;
     const bool live = T < g.n_tiles;
     float ss = 0.f;
     if (live) {
         const TilePre pre = tile_pre<EPI>(g, T, m, nsub);       // issued ahead of the slice loads
         for (int s0 = 0; s0 < g.splits; s0 += 8) {
-            float4 v[8][4];
+            float4 v[8][2];
 #pragma unroll
             for (int u = 0; u < 8; ++u)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < 2; ++j)
                     v[u][j] = src[(size_t)min(s0 + u, g.splits - 1) * slice_stride + j * 64];
             if (s0 == 0) {                                      // the rest of the argument block, behind the first loads
                 if constexpr (EPI == EPI_QKV) SEV_ARGS_NOW("s"(g.q_planes), "s"(g.k_layer), "s"(g.inv_d));
@@ -762,18 +764,19 @@ __global__ __launch_bounds__(256) void gemm_fixup_kernel(const float *part_, con
             for (int u = 0; u < 8; ++u)
                 if (s0 + u < g.splits) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        acc[4 * j] += v[u][j].x; acc[4 * j + 1] += v[u][j].y;
-                        acc[4 * j + 2] += v[u][j].z; acc[4 * j + 3] += v[u][j].w;
+                    for (int j = 0; j < 2; ++j) {
+                        acc[j][0] += v[u][j].x; acc[j][1] += v[u][j].y;
+                        acc[j][2] += v[u][j].z; acc[j][3] += v[u][j].w;
                     }
                 }
         }
-        ss = tile_epilogue<EPI>(g, acc, T, m, nsub, pre);
+        ss = tile_epilogue<EPI>(g, acc[0], acc[1], T, m, nsub, pre);
     }
     if constexpr (EPI == EPI_RESID) {
+        ss += __shfl_xor(ss, 16);
         ss += __shfl_xor(ss, 32);
-        if (lane < 32) red[wave][mrow] = ss;
-        ssq_commit(g, red, 32, mt * 32, grp == 0);
+        if (lane < 16) red[wave][mrow] = ss;
+        ssq_commit(g, red, 16, unit * 16, grp == 0);
     }
 }
 
@@ -899,7 +902,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void attn_bf16_kern
                                                                                     int M, int heads_,
                                                                                     DevPlan p, KvGeom g, int n_items_sib,
                                                                                     float *att_o, float2 *att_ml, float scale_log2e,
-                                                                                    uint16_t *o_pack, int m_tiles) {
+                                                                                    uint16_t *o_pack, int units) {
     // (leading scalars: preloaded at wave launch; layer_off_ = layer * layer stride of the pool, v_off_ = offset of the
     // V pages, heads_ = query heads | KV heads << 16)
     p.it_a = const_cast<int4 *>(it_a_); p.it_b = const_cast<int4 *>(it_b_); p.it_pages = const_cast<int32_t *>(it_pages_);
@@ -1111,8 +1114,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 2 : 1) void attn_bf16_kern
                 split_pack2(o[0] * inv, o[1] * inv, hi[0], lo[0]);
                 split_pack2(o[2] * inv, o[3] * inv, hi[1], lo[1]);
                 const int m = row0 + node, kk = (kvh * G + hg) * 128 + dim;
-                *(uint2 *)(o_pack + xpack_index(m, kk, 0, m_tiles)) = make_uint2(hi[0], hi[1]);
-                *(uint2 *)(o_pack + xpack_index(m, kk, 1, m_tiles)) = make_uint2(lo[0], lo[1]);
+                *(uint2 *)(o_pack + xpack_index(m, kk, 0, units)) = make_uint2(hi[0], hi[1]);
+                *(uint2 *)(o_pack + xpack_index(m, kk, 1, units)) = make_uint2(lo[0], lo[1]);
             }
         } else {
             *(float4 *)(att_o + (base + qrow) * 128 + dim) = make_float4(o[0], o[1], o[2], o[3]);
@@ -1134,7 +1137,7 @@ template <bool DIRECT>
 __global__ __launch_bounds__(256, 2) void attn_bf16_shared_kernel(const int4 *it_a, const int4 *it_b, const int32_t *it_pages, const uint16_t *q_planes,
                                                                   const char *pool, size_t layer_off, size_t v_off, int M, int heads,
                                                                   const unsigned long long *row_anc, int causal, int n_items, float scale_log2e,
-                                                                  float *att_o, float2 *att_ml, uint16_t *o_pack, int m_tiles) {
+                                                                  float *att_o, float2 *att_ml, uint16_t *o_pack, int units) {
     __shared__ u32x4 kv[2][1024];                       // per buffer: K page 0, K page 1, V page 0, V page 1 of one head
     const int Hq = heads & 0xffff, Hkv = heads >> 16, G = Hq / Hkv;
     const int kvh = (int)blockIdx.x % Hkv, idx = (int)blockIdx.x / Hkv;
@@ -1311,8 +1314,8 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_shared_kernel(const int4 *it
                 split_pack2(o[0] * inv, o[1] * inv, hi[0], lo[0]);
                 split_pack2(o[2] * inv, o[3] * inv, hi[1], lo[1]);
                 const int m = row0 + node, kk = (kvh * G + hg) * 128 + dim;
-                *(uint2 *)(o_pack + xpack_index(m, kk, 0, m_tiles)) = make_uint2(hi[0], hi[1]);
-                *(uint2 *)(o_pack + xpack_index(m, kk, 1, m_tiles)) = make_uint2(lo[0], lo[1]);
+                *(uint2 *)(o_pack + xpack_index(m, kk, 0, units)) = make_uint2(hi[0], hi[1]);
+                *(uint2 *)(o_pack + xpack_index(m, kk, 1, units)) = make_uint2(lo[0], lo[1]);
             }
         } else {
             *(float4 *)(att_o + base * 128 + dim) = make_float4(o[0], o[1], o[2], o[3]);
@@ -1324,7 +1327,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_shared_kernel(const int4 *it
 // grid (merge groups, Hkv, row groups per work item), 256 threads: thread owns (row q = t/8, 16 dims).
 template <int PER>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const int4 *mg_rec, const float *att_o, const float2 *att_ml, uint16_t *o_pack,
-                                                         int Hq, int Hkv, int m_tiles) {
+                                                         int Hq, int Hkv, int units) {
     // (all arguments are scalars: preloaded at wave launch; one 16-byte record describes the group of PER query rows)
     const int grpi = blockIdx.x, kvh = blockIdx.y;
     const int4 rec = mg_rec[grpi];
@@ -1373,15 +1376,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int4 *mg_rec, con
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] *= inv;
     const int m = row0 + node, k0 = (kvh * G + hg) * 128 + d0;
-    store_split8(o_pack, m, k0, m_tiles, acc);
-    store_split8(o_pack, m, k0 + 8, m_tiles, acc + 8);
+    store_split8(o_pack, m, k0, units, acc);
+    store_split8(o_pack, m, k0 + 8, units, acc + 8);
 }
 
 // ---------------------------------------------------------------------------
 // host orchestration of one forward pass
 // ---------------------------------------------------------------------------
 struct GemmCfg {
-    int MT, NT, S, PF;
+    int MT, NT, S;          // row tiles of 32 per block, column tiles per wave, K slices
     bool half;              // the last of the NT column tiles is shared by two waves: 4 (NT - 1) + 2 tiles per block
     int T;                  // column tiles per block (cols() unless a narrower block fills the chip better)
     int cols() const { return half ? 4 * (NT - 1) + 2 : 4 * NT; }
@@ -1390,10 +1393,11 @@ struct GemmCfg {
 enum { G_QKV = 0, G_O, G_GU, G_DOWN, G_LM };
 
 // Tile configuration of one GEMM.  Row tiles per block MT (weights are re-read through L2 by each row
-// block), column tiles per wave NT, split-K slices S, prefetch depth PF.  The handle's tuning overrides
+// block), column tiles per wave NT, split-K slices S.  The handle's tuning overrides
 // (struct Tune: read from the environment when the handle was created) replace the choice in experiments.
-static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size_t part_elems, const Tune &tune) {
+static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t part_elems, const Tune &tune) {
     GemmCfg c;
+    const int m_tiles = (rows + 31) / 32;
     c.MT = (which == G_LM && m_tiles >= 3) ? 4 : (m_tiles >= 2 ? 2 : 1);
     c.NT = (n_tiles % 2 == 0) ? 2 : 1;
     if (which == G_LM && c.MT == 4) c.NT = 4;            // never split: the widest tile halves the activation re-reads
@@ -1401,7 +1405,6 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
         c.MT = 4;                                        // enough rows to fill the chip with 128 x 512 blocks, no split needed
         c.NT = 4;
     }
-    c.PF = 4;
     c.S = 1;
     c.half = false;
     const bool splittable = which != G_LM;
@@ -1513,12 +1516,11 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
         const bool half = nt > 10;                           // 15 (QKV), 35 (gate/up): a shared half tile
         if (mt >= 1 && mt <= 5 && (half ? (pf == 4 && ((which == G_QKV && mt == 2 && nt == 15) || (which == G_GU && mt == 4 && nt == 35))) :
                                    (nt == 1 || nt == 2 || ((nt == 4 || (nt == 3 && which == G_QKV)) && mt == 4 && pf == 4))) &&
-            sp >= 0 && sp <= 32 && (pf == 4 || (pf == 6 && mt <= 2)) &&
+            sp >= 0 && sp <= 32 && pf == 4 &&
             (m_tiles + mt - 1) / mt * mt <= (m_tiles + 3) / 4 * 4) {     // the row blocks must stay inside the padded row tiles
             c.MT = mt;
             c.NT = half ? nt / 10 + 1 : nt;
             c.half = half;
-            c.PF = pf;
             pick_s();
             if (splittable && sp > 0) c.S = sp;
         }
@@ -1545,45 +1547,46 @@ static GemmCfg choose_cfg(int which, int m_tiles, int n_tiles, int k_steps, size
     return c;
 }
 
-// one wave per 32x32 output tile; ga.splits slices in the exchange buffer
+// one wave per 32 columns x 16 rows; ga.splits slices in the exchange buffer
 template <int EPI>
-static void launch_fixup(const GemmArgs &ga, int m_tiles, hipStream_t st) {
-    hipLaunchKernelGGL((gemm_fixup_kernel<EPI>), dim3((unsigned)((ga.n_tiles + 3) / 4 * m_tiles)), dim3(256), 0, st, (const float *)ga.part,
+static void launch_fixup(const GemmArgs &ga, hipStream_t st) {
+    const int units = (ga.M + 15) / 16;
+    hipLaunchKernelGGL((gemm_fixup_kernel<EPI>), dim3((unsigned)((ga.n_tiles + 3) / 4 * units)), dim3(256), 0, st, (const float *)ga.part,
                        EPI == EPI_QKV ? (const void *)ga.row_cs : (const void *)ga.h, EPI == EPI_QKV ? (const void *)ga.row_kvloc : (const void *)ga.gain,
-                       ga.ssq_in, m_tiles, ga.m_tiles_total, ga.splits, ga.n_tiles, ga.M, ga.N, ga.Hq | (ga.Hkv << 16), ga);
+                       ga.ssq_in, units, ga.units_total, ga.splits, ga.n_tiles, ga.M, ga.N, ga.Hq | (ga.Hkv << 16), ga);
 }
 
 template <int EPI>
-static void launch_gemm(GemmArgs ga, const GemmCfg &c, int m_tiles, hipStream_t st) {
+static void launch_gemm(GemmArgs ga, const GemmCfg &c, hipStream_t st) {
     ga.col_groups = (ga.n_tiles + c.T - 1) / c.T;
-    ga.m_blocks = (m_tiles + c.MT - 1) / c.MT;
+    ga.m_blocks = ((ga.M + 31) / 32 + c.MT - 1) / c.MT;
     ga.splits = c.S;
     const int g8 = (ga.col_groups + 7) / 8 * 8;
     dim3 grid((unsigned)(g8 * ga.m_blocks * ga.splits));
-    const size_t lds = (size_t)2 * gemm_ks(c.MT, c.NT) * c.MT * 2 * 64 * 16;
-#define SEV_LAUNCH(MT_, NT_, PF_, ...)                                                                                \
-    hipLaunchKernelGGL((gemm_bf16_kernel<MT_, NT_, EPI, PF_ __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), lds, st, ga.W, ga.X, ga.n_tiles, ga.k_steps,         \
-                       ga.m_tiles_total, ga.col_groups, ga.m_blocks, ga.splits | (c.T << 16), ga)
-#define SEV_BY_NT(MT_, PF_)                                                                                           \
+    const size_t lds = (size_t)3 * gemm_ks(2 * c.MT) * 2 * c.MT * 2 * 64 * 16;
+#define SEV_LAUNCH(MR_, NT_, PF_, ...)                                                                                \
+    hipLaunchKernelGGL((gemm_bf16_kernel<MR_, NT_, EPI, PF_ __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), lds, st, ga.W, ga.X, ga.n_tiles, ga.k_steps,         \
+                       ga.units_total, ga.col_groups, ga.m_blocks, ga.splits | (c.T << 16), ga)
+#define SEV_BY_NT(MR_, PF_)                                                                                           \
     do {                                                                                                              \
-        if (c.NT == 2) SEV_LAUNCH(MT_, 2, PF_); else SEV_LAUNCH(MT_, 1, PF_);                                         \
+        if (c.NT == 2) SEV_LAUNCH(MR_, 2, PF_); else SEV_LAUNCH(MR_, 1, PF_);                                         \
     } while (0)
     if (c.half) {
-        if constexpr (EPI == EPI_SWIGLU) SEV_LAUNCH(4, 4, 4, true);
-        if constexpr (EPI == EPI_QKV) SEV_LAUNCH(2, 2, 4, true);
-    } else if (c.MT == 4 && c.NT == 4) SEV_LAUNCH(4, 4, 4);
+        if constexpr (EPI == EPI_SWIGLU) SEV_LAUNCH(8, 4, 2, true);
+        if constexpr (EPI == EPI_QKV) SEV_LAUNCH(4, 2, 4, true);
+    } else if (c.MT == 4 && c.NT == 4) SEV_LAUNCH(8, 4, 2);
     else if (c.MT == 4 && c.NT == 3) {
-        if constexpr (EPI == EPI_QKV) SEV_LAUNCH(4, 3, 4);
+        if constexpr (EPI == EPI_QKV) SEV_LAUNCH(8, 3, 2);
     }
-    else if (c.MT == 5) SEV_BY_NT(5, 4);
-    else if (c.MT == 4) SEV_BY_NT(4, 4);
-    else if (c.MT == 3) SEV_BY_NT(3, 4);
-    else if (c.MT == 2) { if (c.PF == 6) SEV_BY_NT(2, 6); else SEV_BY_NT(2, 4); }
-    else { if (c.PF == 6) SEV_BY_NT(1, 6); else SEV_BY_NT(1, 4); }
+    else if (c.MT == 5) SEV_BY_NT(10, 4);
+    else if (c.MT == 4) SEV_BY_NT(8, 4);
+    else if (c.MT == 3) SEV_BY_NT(6, 4);
+    else if (c.MT == 2) SEV_BY_NT(4, 4);
+    else SEV_BY_NT(2, 4);
 #undef SEV_BY_NT
 #undef SEV_LAUNCH
     if constexpr (EPI != EPI_ARGMAX) {
-        if (c.S > 1) launch_fixup<EPI>(ga, m_tiles, st);
+        if (c.S > 1) launch_fixup<EPI>(ga, st);
     }
 }
 
@@ -1605,8 +1608,7 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
     AttList att = att_all;
     const sev_model_desc &d = m->d;
     KvGeom g = sev_kv_geom(kv);
-    int m_tiles_real = (rows + 31) / 32;
-    int m_tiles = (m_tiles_real + 3) / 4 * 4;
+    int units = sev_row_units(rows);                     // row units of the operand buffers
     auto Wp = [&](size_t off) { return (const uint4 *)(m->arena + off); };
     auto Gp = [&](size_t off) { return (const float *)(m->arena + off); };
     uint16_t *xa = (uint16_t *)kv->xa, *qp = (uint16_t *)kv->q_buf, *op = (uint16_t *)kv->o_buf, *act = (uint16_t *)kv->act;
@@ -1615,19 +1617,19 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
     {
         Prof p(kv, st, PROF_OTHER);
         hipLaunchKernelGGL(embed_norm_kernel, dim3(rows), dim3(256), 0, st, (const uint16_t *)(m->arena + m->off_embed),
-                           kv->plan.row_tok, Gp(m->layers[0].g_attn), kv->h, xa, kv->ssq[1], kv->ssq[0], d.d_model, m_tiles);
+                           kv->plan.row_tok, Gp(m->layers[0].g_attn), kv->h, xa, kv->ssq[1], kv->ssq[0], d.d_model, units);
     }
-    const GemmCfg pq = choose_cfg(G_QKV, m_tiles_real, m->n_qkv / 32, d.d_model / 16, kv->part_elems, kv->tune);
+    const GemmCfg pq = choose_cfg(G_QKV, rows, m->n_qkv / 32, d.d_model / 16, kv->part_elems, kv->tune);
     GemmCfg po, pg, pd;
     auto choose = [&]() {
-        po = choose_cfg(G_O, m_tiles_real, d.d_model / 32, m->q_dim / 16, kv->part_elems, kv->tune);
-        pg = choose_cfg(G_GU, m_tiles_real, d.d_ffn / 16, d.d_model / 16, kv->part_elems, kv->tune);
-        pd = choose_cfg(G_DOWN, m_tiles_real, d.d_model / 32, d.d_ffn / 16, kv->part_elems, kv->tune);
+        po = choose_cfg(G_O, rows, d.d_model / 32, m->q_dim / 16, kv->part_elems, kv->tune);
+        pg = choose_cfg(G_GU, rows, d.d_ffn / 16, d.d_model / 16, kv->part_elems, kv->tune);
+        pd = choose_cfg(G_DOWN, rows, d.d_model / 32, d.d_ffn / 16, kv->part_elems, kv->tune);
     };
     choose();
     GemmArgs base;
     memset(&base, 0, sizeof(base));
-    base.m_tiles_total = m_tiles;
+    base.units_total = units;
     base.M = rows;
     base.part = kv->part;
     base.inv_d = 1.0f / (float)d.d_model;
@@ -1638,11 +1640,11 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
         {   // QKV projection; rotary embedding, q planes and the cache append in its epilogue
             Prof p(kv, st, PROF_GEMM_QKV);
             GemmArgs ga = base;
-            ga.W = Wp(lo.wqkv); ga.X = (const uint4 *)xa; ga.n_tiles = m->n_qkv / 32; ga.k_steps = d.d_model / 16;
+            ga.W = Wp(lo.wqkv); ga.X = (const uint4 *)xa; ga.n_tiles = m->n_qkv / 32; ga.k_steps = d.d_model / 32;
             ga.N = m->n_qkv; ga.ssq_in = kv->ssq[1];
             ga.row_cs = kv->plan.row_cs; ga.row_kvloc = kv->plan.row_kvloc; ga.Hq = d.n_q_heads; ga.Hkv = d.n_kv_heads;
             ga.k_layer = g.pool + (size_t)l * g.layer_stride; ga.v_offset = g.v_offset; ga.q_planes = qp;
-            launch_gemm<EPI_QKV>(ga, pq, m_tiles_real, st);
+            launch_gemm<EPI_QKV>(ga, pq, st);
         }
         if (tail && l == d.n_layers - 1) {
             // The rest of the last layer and the head only feed the next token of the prompts that end here: their last
@@ -1657,12 +1659,11 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
             rows = tail->F;
             B = tail->F;
             att = tail->att;
-            m_tiles_real = (rows + 31) / 32;
-            m_tiles = (m_tiles_real + 3) / 4 * 4;
+            units = sev_row_units(rows);
             qp = kv->tail_q;
             base.h = kv->tail_h;
             base.M = rows;
-            base.m_tiles_total = m_tiles;
+            base.units_total = units;
             choose();
         }
         {
@@ -1671,14 +1672,14 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
 #define SEV_ATTN(WAVES_, DIRECT_, ONCE_, THREADS_, LDS_)                                                                                   \
     hipLaunchKernelGGL((attn_bf16_kernel<WAVES_, DIRECT_, ONCE_>), dim3((unsigned)((att.n_items / att.sib * d.n_kv_heads + 7) / 8 * 8 * att.sib)), dim3(THREADS_), LDS_, st, \
                        kv->plan.it_a, kv->plan.it_b, kv->plan.it_pages, qp, g.pool, (size_t)l * g.layer_stride, g.v_offset, rows,           \
-                       d.n_q_heads | (d.n_kv_heads << 16), kv->plan, g, att.n_items | (att.sib << 24), kv->att_o, kv->att_ml, scale_log2e, op, m_tiles)
+                       d.n_q_heads | (d.n_kv_heads << 16), kv->plan, g, att.n_items | (att.sib << 24), kv->att_o, kv->att_ml, scale_log2e, op, units)
             if (att.quad > 1) {                          // blocks of 128 query rows, K/V through LDS
                 const dim3 grid((unsigned)(att.n_items * d.n_kv_heads));
 #define SEV_ATTN_SHARED(DIRECT_)                                                                                                            \
     hipLaunchKernelGGL((attn_bf16_shared_kernel<DIRECT_>), grid, dim3(256), 0, st, (const int4 *)kv->plan.it_a, (const int4 *)kv->plan.it_b,      \
                        (const int32_t *)kv->plan.it_pages, (const uint16_t *)qp, (const char *)g.pool, (size_t)l * g.layer_stride, g.v_offset, rows,  \
                        d.n_q_heads | (d.n_kv_heads << 16), (const unsigned long long *)kv->plan.row_anc, kv->plan.causal, att.n_items, scale_log2e,  \
-                       kv->att_o, kv->att_ml, op, m_tiles)
+                       kv->att_o, kv->att_ml, op, units)
                 if (att.direct) SEV_ATTN_SHARED(true); else SEV_ATTN_SHARED(false);
 #undef SEV_ATTN_SHARED
             } else if (att.direct) {                     // one block of 8 waves per (request, row group, KV head): no chunks, no merge
@@ -1690,7 +1691,7 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
             }
 #define SEV_MERGE(PER_)                                                                                                                     \
     hipLaunchKernelGGL((attn_merge_kernel<PER_>), dim3(att.n_groups, d.n_kv_heads, PER_ / 32), dim3(256), 0, st, (const int4 *)kv->plan.mg_rec,  \
-                       (const float *)kv->att_o, (const float2 *)kv->att_ml, op, d.n_q_heads, d.n_kv_heads, m_tiles)
+                       (const float *)kv->att_o, (const float2 *)kv->att_ml, op, d.n_q_heads, d.n_kv_heads, units)
             if (!att.direct) {
                 if (att.quad > 1) SEV_MERGE(128); else SEV_MERGE(32);
             }
@@ -1700,34 +1701,34 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
         {   // output projection; residual add, FFN-norm operand and scale in its epilogue
             Prof p(kv, st, PROF_GEMM_O);
             GemmArgs ga = base;
-            ga.W = Wp(lo.wo); ga.X = (const uint4 *)op; ga.n_tiles = d.d_model / 32; ga.k_steps = m->q_dim / 16;
+            ga.W = Wp(lo.wo); ga.X = (const uint4 *)op; ga.n_tiles = d.d_model / 32; ga.k_steps = m->q_dim / 32;
             ga.N = d.d_model; ga.gain = Gp(lo.g_ffn); ga.xout = xa; ga.ssq_out = kv->ssq[0]; ga.ssq_clear = kv->ssq[1];
-            launch_gemm<EPI_RESID>(ga, po, m_tiles_real, st);
+            launch_gemm<EPI_RESID>(ga, po, st);
         }
         {   // gate/up projection with fused SwiGLU
             Prof p(kv, st, PROF_GEMM_GU);
             GemmArgs ga = base;
-            ga.W = Wp(lo.wgu); ga.X = (const uint4 *)xa; ga.n_tiles = d.d_ffn / 16; ga.k_steps = d.d_model / 16;
+            ga.W = Wp(lo.wgu); ga.X = (const uint4 *)xa; ga.n_tiles = d.d_ffn / 16; ga.k_steps = d.d_model / 32;
             ga.N = 2 * d.d_ffn; ga.act = act; ga.ssq_in = kv->ssq[0];
-            launch_gemm<EPI_SWIGLU>(ga, pg, m_tiles_real, st);
+            launch_gemm<EPI_SWIGLU>(ga, pg, st);
         }
         {   // down projection; residual add, next norm's operand and scale in its epilogue
             Prof p(kv, st, PROF_GEMM_DOWN);
             GemmArgs ga = base;
-            ga.W = Wp(lo.wd); ga.X = (const uint4 *)act; ga.n_tiles = d.d_model / 32; ga.k_steps = d.d_ffn / 16;
+            ga.W = Wp(lo.wd); ga.X = (const uint4 *)act; ga.n_tiles = d.d_model / 32; ga.k_steps = d.d_ffn / 32;
             ga.N = d.d_model; ga.gain = (l + 1 < d.n_layers) ? Gp(m->layers[l + 1].g_attn) : Gp(m->off_gfinal); ga.xout = xa;
             ga.ssq_out = kv->ssq[1]; ga.ssq_clear = kv->ssq[0];
-            launch_gemm<EPI_RESID>(ga, pd, m_tiles_real, st);
+            launch_gemm<EPI_RESID>(ga, pd, st);
         }
     }
     {   // LM head with fused arg-max
         Prof p(kv, st, PROF_GEMM_LM);
-        const GemmCfg pl = choose_cfg(G_LM, m_tiles_real, d.vocab / 32, d.d_model / 16, kv->part_elems, kv->tune);
+        const GemmCfg pl = choose_cfg(G_LM, rows, d.vocab / 32, d.d_model / 16, kv->part_elems, kv->tune);
         GemmArgs ga = base;
-        ga.W = Wp(m->off_lm); ga.X = (const uint4 *)xa; ga.n_tiles = d.vocab / 32; ga.k_steps = d.d_model / 16; ga.N = d.vocab;
+        ga.W = Wp(m->off_lm); ga.X = (const uint4 *)xa; ga.n_tiles = d.vocab / 32; ga.k_steps = d.d_model / 32; ga.N = d.vocab;
         ga.ssq_in = kv->ssq[1];
-        ga.lm_val = kv->lm_val; ga.lm_idx = kv->lm_idx; ga.lm_stride = m_tiles * 32; ga.logits = logits_out;
-        launch_gemm<EPI_ARGMAX>(ga, pl, m_tiles_real, st);
+        ga.lm_val = kv->lm_val; ga.lm_idx = kv->lm_idx; ga.lm_stride = units * 16; ga.logits = logits_out;
+        launch_gemm<EPI_ARGMAX>(ga, pl, st);
         const int n_part = ((ga.n_tiles + 4 * pl.NT - 1) / (4 * pl.NT)) * 4;
         hipLaunchKernelGGL(lm_reduce_kernel, dim3(rows), dim3(256), 0, st, kv->lm_val, kv->lm_idx, n_part, ga.lm_stride,
                            kv->row_argmax);

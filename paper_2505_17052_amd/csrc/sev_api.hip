@@ -165,9 +165,9 @@ extern "C" int sev_model_load_tensor(sev_model *m, int kind, int layer, const vo
     } else if (kind == SEV_W_EMBED) {
         SEV_HIP(hipMemcpyAsync(m->arena + off, src, (size_t)rows * K * 2, hipMemcpyDeviceToDevice, st));
     } else {
-        // bf16 matrices are re-tiled into 32x16 MFMA operand fragments; a row offset inside a fused
+        // bf16 matrices are re-tiled into MFMA operand fragments, tiles of 32 rows x 32 k; a row offset inside a fused
         // matrix is a tile offset (all offsets are multiples of 32 by construction of the shapes)
-        if (rows % 32 || row0 % 32 || K % 16) return sev_fail(SEV_EINVAL, "tensor %d: rows/K not tileable", kind);
+        if (rows % 32 || row0 % 32 || K % 32) return sev_fail(SEV_EINVAL, "tensor %d: rows/K not tileable", kind);
         launch_pack_bf16((uint16_t *)(m->arena + off), (const uint16_t *)src, rows, K, mode, (mode == 0 || mode == 3) ? row0 / 32 : 0, st);
     }
     hipError_t e = hipGetLastError();

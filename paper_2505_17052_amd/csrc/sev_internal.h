@@ -25,15 +25,17 @@ int sev_fail(int code, const char *fmt, ...);
 // packed activation layout for the matrix-core GEMMs ("xpack")
 //
 // A [M][K] activation matrix is carried as two bf16 planes (hi = bf16(x),
-// lo = bf16(x - hi)), already arranged as MFMA 32x32x16 operand fragments:
-//   [K/16 k-steps][m_tiles][plane 2][lane 64][8 bf16]
-// lane = (m % 32) + 32 * ((k / 8) % 2), element = k % 8.  One fragment is 1 KiB.
-// m_tiles is ceil(M/32) rounded up to a multiple of 4.
+// lo = bf16(x - hi)), already arranged as MFMA 16x16x32 operand fragments:
+//   [K/32 k-steps][row units of 16][plane 2][lane 64][8 bf16]
+// lane = (m % 16) + 16 * ((k / 8) % 4), element = k % 8.  One fragment is 1 KiB.
+// units = row units of the buffer: ceil(M/16) rounded up to a multiple of 8.
 // ---------------------------------------------------------------------------
-__host__ __device__ inline int64_t xpack_index(int m, int k, int plane, int m_tiles) {
-    return ((((int64_t)(k >> 4) * m_tiles + (m >> 5)) * 2 + plane) << 9) + (((m & 31) + (((k >> 3) & 1) << 5)) << 3) +
+__host__ __device__ inline int64_t xpack_index(int m, int k, int plane, int units) {
+    return ((((int64_t)(k >> 5) * units + (m >> 4)) * 2 + plane) << 9) + (((m & 15) + (((k >> 3) & 3) << 4)) << 3) +
            (k & 7);
 }
+
+inline int sev_row_units(int rows) { return (rows + 127) / 128 * 8; }
 
 struct LayerOffsets {
     size_t wqkv, wo, wgu, wd, g_attn, g_ffn;

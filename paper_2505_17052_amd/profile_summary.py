@@ -69,7 +69,7 @@ def kernel_stats(a):
     for name, v in sorted(agg.items(), key=lambda kv: -sum(kv[1]))[:a.top]:
         s = sorted(v)
         out.append(f"{name[:72]:72s} {len(v):7d} {sum(v) / 1e3:9.2f} {sum(v) / len(v):8.2f} {s[len(s) // 2]:8.2f} {s[0]:8.2f} {s[-1]:8.2f} {100 * sum(v) / total:6.2f}\n")
-    out.append("\ngemm_bf16_kernel<MT, NT, EPI, PF>: row tiles per block, column tiles per wave, epilogue, prefetch depth.  EPI: " +
+    out.append("\ngemm_bf16_kernel<MR, NT, EPI, PF>: row units of 16 per block, column tiles per wave, epilogue, prefetch depth.  EPI: " +
                "; ".join(f"{k} = {v}" for k, v in EPI_NAMES.items()) +
                ".\ngemm_fixup_kernel<EPI> sums the split-K slices and runs the same epilogue; attn_merge_kernel combines the KV chunks.\n")
     open(a.out, "w").write("".join(out))
