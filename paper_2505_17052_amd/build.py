@@ -11,9 +11,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-tar
          "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-Wno-unused-value", "-Wno-unused-result",
          # the first 16 dwords of a kernel's scalar arguments arrive in registers at wave launch (no scalar load of
          # the argument block on the critical path of the prologue); kernels list what they need first in front
-         "-mllvm", "-amdgpu-kernarg-preload-count=16",
-         # matrix products keep their sums in the directly addressable registers (kernels_bf16.hip, gemm_acc_a)
-         "-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+         "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 
 def build(verbose: bool = False) -> str:

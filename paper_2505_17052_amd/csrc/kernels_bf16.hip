@@ -390,16 +390,12 @@ __device__ __forceinline__ void ssq_commit(const GemmArgs &g, float (*red)[STRID
 // as the even wave's, and no fragment is indexed by a run-time value.
 //
 // Accumulators.  Left to itself the compiler gives every product of this instruction a destination of its own and moves
-// accumulators about in the loop (60-300 moves in 256 products).  Instances whose registers fit the 256 of a wave's
-// directly addressable file are compiled with the sums there (-amdgpu-mfma-vgpr-form), where it does not happen; the larger ones (ACC_A) name
-// the accumulator file and tie source and destination in mfma_pair's assembly statement.
-__host__ __device__ constexpr bool gemm_acc_a(int MR, int NT, int PF) {
-    return 8 * NT * MR + 4 * PF * gemm_ks(MR) * (2 * NT + MR / 2) + 32 > 190;      // sums, fragments in flight, the ring of units
-}
+// accumulators about in the loop (60-300 moves in 256 products), so mfma_pair names the accumulator file and ties source and
+// destination in an assembly statement.  Such statements keep their order, which makes the loop's instruction order the one written here.
 
-// acc += w * (hi plane) + w * (lo plane).  (Statements keep their order; the products of a pair follow each other on the same
-// accumulators, which needs no wait states, and their operands come from loads, which the compiler awaits.)
-__device__ __forceinline__ void mfma_pair_a(f32x4 &acc, u32x4 w, u32x4 hi, u32x4 lo) {
+// acc += w * (hi plane) + w * (lo plane).  The products of a pair follow each other on the same accumulators, which needs no wait
+// states, and their operands come from loads, which the compiler awaits.
+__device__ __forceinline__ void mfma_pair(f32x4 &acc, u32x4 w, u32x4 hi, u32x4 lo) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %3, %0" : "+a"(acc) : "v"(w), "v"(hi), "v"(lo));
 }
 
@@ -413,11 +409,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     constexpr int NF = 2 * NT;                          // weight fragments per wave and k-step: two per column tile
     constexpr int XI = KS * MR / 2;                     // 16-byte activation loads per thread and stage
     static_assert(KS * MR % 2 == 0, "a stage of activations must be a whole number of 4 KiB");
-    constexpr bool ACC_A = gemm_acc_a(MR, NT, PF);
     constexpr int G = KS * MR;                          // groups of products per stage: one activation unit x all weight fragments
-    constexpr int AHEAD = G < 3 ? G : 3;                // an activation unit is read from LDS that many groups before its products
-    static_assert(PF * G % 4 == 0, "the ring of four activation units must close with the loop body");
-    extern __shared__ u32x4 xs[];                       // [3 buffers][KS k-steps][MR][2 planes][64 lanes]
+    constexpr int AHEAD = G < PF ? G : PF - 1;          // an activation unit is read from LDS that many groups before its products
+    static_assert(PF >= 3, "X(st+2) is written while X(st) and X(st+1) are read");
+    extern __shared__ u32x4 xs[];                       // [PF buffers][KS k-steps][MR][2 planes][64 lanes]
     __shared__ float red[4][MR * 16 < 128 ? 128 : MR * 16];
     constexpr int STAGE_U4 = KS * MR * 2 * 64;          // uint4 per stage
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -455,56 +450,57 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[a][b][r] = 0.f;
 
-    // weight fragment pointers of this lane (clamped to a valid tile so idle waves load harmlessly)
-    const u32x4 *wp[NT];
+    // Both streams are read at a uniform address plus a 32-bit offset of the thread, so that a stage costs a few scalar
+    // instructions and no vector ones: with one wave per SIMD everything that is issued between two products beyond three
+    // instructions or so is idle time of the matrix pipe (64-bit addresses per load and stage: about 290 cycles of a stage).
+    // Weights: tiles the wave does not have are clamped to a valid one, so idle waves load harmlessly.
+    const char *const W = (const char *)g.W + (size_t)cg * tpb * g.k_steps * 2048;
+    unsigned woff[NT];
 #pragma unroll
-    for (int a = 0; a < NT; ++a) {
-        const int t = min(coltile(a), g.n_tiles - 1);
-        wp[a] = (const u32x4 *)g.W + ((size_t)t * g.k_steps) * 128 + lane;
-    }
+    for (int a = 0; a < NT; ++a) woff[a] = (unsigned)((min(coltile(a), g.n_tiles - 1) - cg * tpb) * g.k_steps) * 2048u + lane * 16u;
     // The gate/up GEMM reads its weights through a buffer descriptor that covers exactly the block's column tiles: a
     // tile the wave does not have (blocks of fewer than 4 * NT tiles, the matrix edge) lies past the descriptor's
     // end, where a load returns zeros and reads nothing, so the loop stays free of branches and the missing tile
     // costs no memory traffic.
     constexpr bool WBUF = EPI == EPI_SWIGLU && MR <= 4;      // the 128-row blocks never run narrower than 4 * NT tiles
-    const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)((const u32x4 *)g.W + (size_t)cg * tpb * g.k_steps * 128), 0, block_tiles * g.k_steps * 2048, 0x00020000);
-    int woff[NT];
+    const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void *)W, 0, block_tiles * g.k_steps * 2048, 0x00020000);
+    if constexpr (WBUF) {
 #pragma unroll
-    for (int a = 0; a < NT; ++a) woff[a] = ((lct(a) * g.k_steps) * 128 + lane) * 16;
-    auto load_w = [&](int f, int step) -> u32x4 {      // 16 bytes per lane of k-step `step`: fragment f & 1 of the wave's column tile f / 2
+        for (int a = 0; a < NT; ++a) woff[a] = (unsigned)(lct(a) * g.k_steps) * 2048u + lane * 16u;
+    }
+    auto load_w = [&](int f, unsigned at) -> u32x4 {      // 16 bytes per lane of the k-step at byte `at` of a tile: fragment f & 1 of the wave's column tile f / 2
         // The streaming hint keeps the weights from displacing the activations in the L2s (gate/up: 7 % faster with it).
         // The QKV projection streams the fewest weights per activation byte and is 4 % faster with plain loads.  Blocks of 96
         // and 128 rows keep the hint although their row blocks share the weights through an L2; plain loads there, timed in
         // turn: 192 rows of the 8B shape gate/up 88.6 -> 89.8 us and QKV behind it 33.5 -> 34.4, 416 rows down 105.2 -> 106.7,
         // 480 rows of the 70B shape O 131.3 -> 132.9.  The one that gains from plain loads is down of the 70B shape at 176 rows
         // (178.5 -> 176.4, where gate/up loses twice that).
-        if constexpr (WBUF) return __builtin_amdgcn_raw_buffer_load_b128(wrs, woff[f >> 1] + step * 2048 + (f & 1) * 1024, 0, 2);      // 2: streaming hint
-        else if constexpr (EPI == EPI_QKV) return wp[f >> 1][(size_t)step * 128 + (f & 1) * 64];
-        else return __builtin_nontemporal_load(&wp[f >> 1][(size_t)step * 128 + (f & 1) * 64]);
+        if constexpr (WBUF) return __builtin_amdgcn_raw_buffer_load_b128(wrs, woff[f >> 1] + (f & 1) * 1024, at, 2);      // 2: streaming hint
+        else if constexpr (EPI == EPI_QKV) return *(const u32x4 *)(W + at + woff[f >> 1] + (f & 1) * 1024);
+        else return __builtin_nontemporal_load((const u32x4 *)(W + at + woff[f >> 1] + (f & 1) * 1024));
     };
     // Software pipeline.  Loads return in issue order, so a wait on one load drains every older one:
     // to keep PF stages in flight, weights AND activations are fetched PF stages ahead into registers
     // and consumed in the order they were issued.  At the start of stage st (slot u = st % PF):
-    //   LDS buffers st % 3 and (st+1) % 3 hold X(st) and X(st+1);  wreg[u] holds W(st);  xreg[u] holds X(st+2).
-    // The activation units pass through a ring of four register pairs: during a group's products the unit AHEAD groups later
+    //   LDS buffers u and (u+1) % PF hold X(st) and X(st+1);  wreg[u] holds W(st);  xreg[u] holds X(st+2).
+    // The activation units pass through a ring of PF register pairs: during a group's products the unit AHEAD groups later
     // is read from LDS, so that no product waits for LDS and the reads are spread evenly.  X(st+2) goes from registers into
-    // the third LDS buffer, whose contents (stage st-1) were last read before the barrier that ended stage st-1; one barrier
-    // per stage.
+    // the LDS buffer after next, whose contents (stage st-1 or older) were last read before the barrier that ended stage st-1;
+    // one barrier per stage.  (Buffers and ring close with the loop body, so that no place is computed at run time.)
     // The loop body is PF stages of straight-line code (no branches), which lets the compiler's
-    // wait-count bookkeeping follow the loads across the back-edge.  The slice is padded to a multiple
-    // of PF stages; padded stages re-load the last stage (cached) and are not multiplied.
+    // wait-count bookkeeping follow the loads across the back-edge.  What a body prefetches past the slice's end wraps around to
+    // its start (cached) and is never multiplied.
     u32x4 wreg[PF][KS][NF];
     u32x4 xreg[PF][XI];
-    u32x4 xf[4][2];
-    const u32x4 *xsrc[XI];
+    u32x4 xf[PF][2];
+    unsigned xoff[XI];
 #pragma unroll
     for (int i = 0; i < XI; ++i) {
         const int u = threadIdx.x + 256 * i;
         const int ksl = u / (MR * 128), within = u - ksl * (MR * 128);
-        xsrc[i] = (const u32x4 *)g.X + ((size_t)ksl * g.units_total + u0) * 128 + within;
+        xoff[i] = (unsigned)((ksl * g.units_total + u0) * 128 + within) * 16u;
     }
-    const size_t x_stage = (size_t)KS * g.units_total * 128;        // 16-byte units per stage of all row units
+    const size_t x_stage = (size_t)KS * g.units_total * 2048;       // bytes per stage of all row units
     const int n_pad = (n + PF - 1) / PF * PF;
     // Every column group walks its K range from a different starting stage (and wraps around): the
     // blocks that run at the same time would otherwise all read the same few KiB of activations at the
@@ -514,28 +510,39 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     // So do four and more row blocks: their activations no longer fit an L2, and the column groups of an XCD then share
     // what one of them fetched (512 rows: a step of 17.0 -> 16.7 ms, 2048 rows -2 %).
     const int rot = n * KS >= 64 && g.m_blocks < 4 ? (int)((unsigned)cg * (unsigned)n / (unsigned)g.col_groups) : 0;
-    auto phys = [&](int t) {                                        // logical stage -> stage index in K
-        int i = min(t, n - 1) + rot;
-        if (i >= n) i -= n;
-        return s_begin + i;
+    // where the two streams stand: the next stage to be requested, counted within the slice, and its address
+    const char *const x_first = (const char *)g.X + (size_t)s_begin * x_stage, *x_at = x_first + (size_t)rot * x_stage;
+    const unsigned w_first = (unsigned)s_begin * (KS * 2048u);
+    unsigned w_at = w_first + (unsigned)rot * (KS * 2048u);
+    int x_i = rot, w_i = rot;
+    auto x_next = [&]() {
+        x_at += x_stage;
+        if (++x_i == n) { x_i = 0; x_at = x_first; }
     };
+    auto w_next = [&]() {
+        w_at += KS * 2048u;
+        if (++w_i == n) { w_i = 0; w_at = w_first; }
+    };
+    auto load_x = [&](int i) { return *(const u32x4 *)(x_at + xoff[i]); };
 
     {
         u32x4 x0[XI], x1[XI];
 #pragma unroll
-        for (int i = 0; i < XI; ++i) {
-            x0[i] = xsrc[i][(size_t)phys(0) * x_stage];
-            x1[i] = xsrc[i][(size_t)phys(1) * x_stage];
-        }
+        for (int i = 0; i < XI; ++i) x0[i] = load_x(i);
+        x_next();
+#pragma unroll
+        for (int i = 0; i < XI; ++i) x1[i] = load_x(i);
+        x_next();
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
-            const int sx = phys(u + 2), sw = phys(u);
 #pragma unroll
-            for (int i = 0; i < XI; ++i) xreg[u][i] = xsrc[i][(size_t)sx * x_stage];
+            for (int i = 0; i < XI; ++i) xreg[u][i] = load_x(i);
+            x_next();
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int f = 0; f < NF; ++f) wreg[u][ks][f] = load_w(f, KS * sw + ks);
+                for (int f = 0; f < NF; ++f) wreg[u][ks][f] = load_w(f, w_at + ks * 2048u);
+            w_next();
         }
 #pragma unroll
         for (int i = 0; i < XI; ++i) {
@@ -556,91 +563,65 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     else if constexpr (EPI == EPI_ARGMAX) SEV_ARGS_NOW("s"(g.part), "s"(g.ssq_in), "s"(g.lm_val), "s"(g.logits));
     else SEV_ARGS_NOW("s"(g.part), "s"(g.ssq_in), "s"(g.act));
     __syncthreads();
-    // LDS places of X(st), X(st+1) and X(st+2), in 16-byte units
-    int xb0 = 0, xb1 = STAGE_U4, xb2 = 2 * STAGE_U4;
-    auto read_unit = [&](int at, int grp, u32x4 (&to)[2]) {      // group grp of the stage at `at`
+    const u32x4 *const xr = xs + lane, *const xr_lo = xr + par * MH * 128, *const xr_hi = xr - par * MH * 128;
+    u32x4 *const xw = xs + threadIdx.x;
+    auto read_unit = [&](int buf, int grp, u32x4 (&to)[2]) {      // group grp of the stage in LDS buffer buf
         const int ks = grp / MR, b = grp % MR;
-        const u32x4 *p = xs + at + lane + (HALF ? (b < MH ? par * MH * 128 : -par * MH * 128) : 0);
-        to[0] = p[((ks * MR + b) * 2) * 64];
-        to[1] = p[((ks * MR + b) * 2 + 1) * 64];
+        const u32x4 *p = (!HALF ? xr : b < MH ? xr_lo : xr_hi) + buf * STAGE_U4 + (ks * MR + b) * 128;
+        to[0] = p[0];
+        to[1] = p[64];
     };
 #pragma unroll
-    for (int i = 0; i < AHEAD; ++i) read_unit(xb0, i, xf[i & 3]);
+    for (int i = 0; i < AHEAD; ++i) read_unit(0, i, xf[i]);
 
     // One group of PF stages.  The last group of a slice issues no global loads: what it would
     // prefetch lies beyond the slice, and the epilogue would have to wait for those loads to return
     // before it may reuse their registers.
+    // Everything a stage has to do besides its products is spread between them, a few instructions at a time: two LDS reads ahead
+    // of a group, one activation register at a time into LDS and requested anew from the second pair on, a weight fragment
+    // requested anew right after its last product.
     auto group = [&](int base, auto load_tag) {
         constexpr bool LOAD = decltype(load_tag)::value;
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
-            const int st = base + u;
             if constexpr (!LOAD) {
-                if (st >= n) break;                     // padding of the slice (uniform): nothing left to multiply
+                if (base + u >= n) break;               // padding of the slice (uniform): nothing left to multiply
             }
-            const int sx = phys(st + PF + 2), sw = phys(st + PF);
-            // Everything else a stage has to do is spread between its MFMAs, so that the matrix pipe
-            // never waits for a run of address arithmetic, loads and LDS traffic: the LDS write of X(st+2) and the loads that
-            // refill its registers sit in the first group, a weight fragment is refilled right after its last product.
+            int pair = 0;
 #pragma unroll
             for (int grp = 0; grp < G; ++grp) {
-                const int ks = grp / MR, b = grp % MR, slot = (u * G + grp) & 3, far = (u * G + grp + AHEAD) & 3;
-                if (grp + AHEAD < G) read_unit(xb0, grp + AHEAD, xf[far]);
-                else read_unit(xb1, grp + AHEAD - G, xf[far]);
+                const int ks = grp / MR, b = grp % MR, slot = (u * G + grp) % PF, far = (u * G + grp + AHEAD) % PF;
+                if (grp + AHEAD < G) read_unit(u, grp + AHEAD, xf[far]);
+                else read_unit((u + 1) % PF, grp + AHEAD - G, xf[far]);
 #pragma unroll
                 for (int f = 0; f < NF; ++f) {
-                    const bool mine = b < rows_of(f >> 1);
-                    if (mine) {
-                        const bf16x8 w = as_bf16x8(wreg[u][ks][f]);
-                        if constexpr (ACC_A) mfma_pair_a(acc[f][b], wreg[u][ks][f], xf[slot][0], xf[slot][1]);
-                        else acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, as_bf16x8(xf[slot][0]), acc[f][b], 0, 0, 0);
-                        if constexpr (!ACC_A) acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, as_bf16x8(xf[slot][1]), acc[f][b], 0, 0, 0);
+                    if (b >= rows_of(f >> 1)) continue;
+                    mfma_pair(acc[f][b], wreg[u][ks][f], xf[slot][0], xf[slot][1]);
+                    if (pair % 2 == 1 && pair / 2 < XI) {
+                        const int i = pair / 2;
+                        xw[(u + 2) % PF * STAGE_U4 + 256 * i] = xreg[u][i];
+                        if constexpr (LOAD) xreg[u][i] = load_x(i);
                     }
+                    ++pair;
                     if constexpr (LOAD) {
-                        if (b == rows_of(f >> 1) - 1) wreg[u][ks][f] = load_w(f, KS * sw + ks);
-                    }
-                }
-                if (grp == 0) {
-#pragma unroll
-                    for (int i = 0; i < XI; ++i) xs[xb2 + threadIdx.x + 256 * i] = xreg[u][i];
-                    if constexpr (LOAD) {
-#pragma unroll
-                        for (int i = 0; i < XI; ++i) xreg[u][i] = xsrc[i][(size_t)sx * x_stage];
+                        if (b == rows_of(f >> 1) - 1) wreg[u][ks][f] = load_w(f, w_at + ks * 2048u);
                     }
                 }
             }
-            // the same order for the instruction scheduler (0x008 MFMA, 0x100 DS read, 0x200 DS write, 0x020 VMEM read)
-#pragma unroll
-            for (int grp = 0; !ACC_A && grp < G; ++grp) {
-                const int b = grp % MR;
-                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-#pragma unroll
-                for (int f = 0; f < NF; ++f) {
-                    if (b < rows_of(f >> 1)) __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-                    if (LOAD && b == rows_of(f >> 1) - 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-                }
-                if (grp == 0) {
-                    __builtin_amdgcn_sched_group_barrier(0x200, XI, 0);
-                    if constexpr (LOAD) __builtin_amdgcn_sched_group_barrier(0x020, XI, 0);
-                }
+            if constexpr (LOAD) {
+                x_next();
+                w_next();
             }
-            __builtin_amdgcn_sched_barrier(0);
             __syncthreads();
-            const int t = xb0;
-            xb0 = xb1;
-            xb1 = xb2;
-            xb2 = t;
         }
     };
     for (int base = 0; base + PF < n_pad; base += PF) group(base, std::true_type{});
     group(n_pad - PF, std::false_type{});
-    if constexpr (ACC_A) {                              // the last products must have left the pipe before their sums are read
-        asm volatile("s_nop 15\n\ts_nop 15");
+    asm volatile("s_nop 15\n\ts_nop 15");              // the last products must have left the pipe before their sums are read
 #pragma unroll
-        for (int a = 0; a < NF; ++a)
+    for (int a = 0; a < NF; ++a)
 #pragma unroll
-            for (int b = 0; b < MR; ++b) asm volatile("" : "+a"(acc[a][b]));
-    }
+        for (int b = 0; b < MR; ++b) asm volatile("" : "+a"(acc[a][b]));
 
     // ------------------------------------------------------------------ split-K: hand the slice to the fix-up kernel
     if (g.splits > 1) {
@@ -1563,24 +1544,23 @@ static void launch_gemm(GemmArgs ga, const GemmCfg &c, hipStream_t st) {
     ga.splits = c.S;
     const int g8 = (ga.col_groups + 7) / 8 * 8;
     dim3 grid((unsigned)(g8 * ga.m_blocks * ga.splits));
-    const size_t lds = (size_t)3 * gemm_ks(2 * c.MT) * 2 * c.MT * 2 * 64 * 16;
 #define SEV_LAUNCH(MR_, NT_, PF_, ...)                                                                                \
-    hipLaunchKernelGGL((gemm_bf16_kernel<MR_, NT_, EPI, PF_ __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), lds, st, ga.W, ga.X, ga.n_tiles, ga.k_steps,         \
+    hipLaunchKernelGGL((gemm_bf16_kernel<MR_, NT_, EPI, PF_ __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), PF_ * gemm_ks(MR_) * MR_ * 2048, st, ga.W, ga.X, ga.n_tiles, ga.k_steps,         \
                        ga.units_total, ga.col_groups, ga.m_blocks, ga.splits | (c.T << 16), ga)
 #define SEV_BY_NT(MR_, PF_)                                                                                           \
     do {                                                                                                              \
-        if (c.NT == 2) SEV_LAUNCH(MR_, 2, PF_); else SEV_LAUNCH(MR_, 1, PF_);                                         \
+        if (c.NT == 2) SEV_LAUNCH(MR_, 2, PF_); else SEV_LAUNCH(MR_, 1, 4);                                           \
     } while (0)
     if (c.half) {
-        if constexpr (EPI == EPI_SWIGLU) SEV_LAUNCH(8, 4, 2, true);
+        if constexpr (EPI == EPI_SWIGLU) SEV_LAUNCH(8, 4, 3, true);
         if constexpr (EPI == EPI_QKV) SEV_LAUNCH(4, 2, 4, true);
-    } else if (c.MT == 4 && c.NT == 4) SEV_LAUNCH(8, 4, 2);
+    } else if (c.MT == 4 && c.NT == 4) SEV_LAUNCH(8, 4, 3);
     else if (c.MT == 4 && c.NT == 3) {
-        if constexpr (EPI == EPI_QKV) SEV_LAUNCH(8, 3, 2);
+        if constexpr (EPI == EPI_QKV) SEV_LAUNCH(8, 3, 3);
     }
-    else if (c.MT == 5) SEV_BY_NT(10, 4);
-    else if (c.MT == 4) SEV_BY_NT(8, 4);
-    else if (c.MT == 3) SEV_BY_NT(6, 4);
+    else if (c.MT == 5) SEV_BY_NT(10, 3);
+    else if (c.MT == 4) SEV_BY_NT(8, 3);
+    else if (c.MT == 3) SEV_BY_NT(6, 3);
     else if (c.MT == 2) SEV_BY_NT(4, 4);
     else SEV_BY_NT(2, 4);
 #undef SEV_BY_NT
