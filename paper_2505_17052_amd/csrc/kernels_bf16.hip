@@ -10,7 +10,10 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <math.h>
+
 #include <algorithm>
+#include <iterator>
 #include <type_traits>
 
 #include "sev_internal.h"
@@ -297,7 +300,7 @@ __device__ __forceinline__ float tile_epilogue(const GemmArgs &g, const f32x4 &a
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const float gt = acc0[r] * rs, up = acc1[r] * rs;
-            v[r] = gt / (1.0f + __expf(-gt)) * up;
+            v[r] = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;      // (v_rcp_f32: 1 ulp; a division is ten instructions more)
         }
         uint32_t hi[2], lo[2];
         split_pack2(v[0], v[1], hi[0], lo[0]);
@@ -502,14 +505,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     }
     const size_t x_stage = (size_t)KS * g.units_total * 2048;       // bytes per stage of all row units
     const int n_pad = (n + PF - 1) / PF * PF;
-    // Every column group walks its K range from a different starting stage (and wraps around): the
-    // blocks that run at the same time would otherwise all read the same few KiB of activations at the
-    // same moment, i.e. hammer a few L2 channels while the others idle.  The row blocks of a column
-    // group share the rotation, so they still read their common weight tiles together.  Short split-K
-    // slices keep the common start: they are mostly pipeline fill, where sharing the first misses wins.
-    // So do four and more row blocks: their activations no longer fit an L2, and the column groups of an XCD then share
-    // what one of them fetched (512 rows: a step of 17.0 -> 16.7 ms, 2048 rows -2 %).
-    const int rot = n * KS >= 64 && g.m_blocks < 4 ? (int)((unsigned)cg * (unsigned)n / (unsigned)g.col_groups) : 0;
+    // Where the activations are small enough to stay in an L2 (4 MiB) beside the weight stream, every column group walks its K range
+    // from a different starting stage and wraps around: blocks that run at the same time then do not all read the same few KiB
+    // of activations, i.e. hammer a few L2 channels while the others idle (8B shape, QKV: 64 rows 17.4 -> 15.4 us, 32 rows
+    // 13.9 -> 12.9).  Larger ones are fetched chunk by chunk once for all column groups of an XCD, which then have to
+    // walk together (rotated: down of the 8B shape at 64 rows 28 -> 39 us, of the 70B shape 83 -> 112, gate/up of that shape at 256 rows
+    // 335 -> 363).  In between, from 1.5 to 2.5 MiB, the two are within 3 % of each other.
+    const bool resident = g.m_blocks * MR * g.k_steps <= 768;              // 2 KiB per unit and step
+    const int rot = resident ? (int)((unsigned)cg * (unsigned)n / (unsigned)g.col_groups) : 0;
     // where the two streams stand: the next stage to be requested, counted within the slice, and its address
     const char *const x_first = (const char *)g.X + (size_t)s_begin * x_stage, *x_at = x_first + (size_t)rot * x_stage;
     const unsigned w_first = (unsigned)s_begin * (KS * 2048u);
@@ -1364,167 +1367,113 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const int4 *mg_rec, con
 // ---------------------------------------------------------------------------
 // host orchestration of one forward pass
 // ---------------------------------------------------------------------------
-struct GemmCfg {
-    int MT, NT, S;          // row tiles of 32 per block, column tiles per wave, K slices
-    bool half;              // the last of the NT column tiles is shared by two waves: 4 (NT - 1) + 2 tiles per block
-    int T;                  // column tiles per block (cols() unless a narrower block fills the chip better)
-    int cols() const { return half ? 4 * (NT - 1) + 2 : 4 * NT; }
-};
-
 enum { G_QKV = 0, G_O, G_GU, G_DOWN, G_LM };
 
-// Tile configuration of one GEMM.  Row tiles per block MT (weights are re-read through L2 by each row
-// block), column tiles per wave NT, split-K slices S.  The handle's tuning overrides
-// (struct Tune: read from the environment when the handle was created) replace the choice in experiments.
+// Tile configuration of one GEMM: row units per block MR, column tiles per wave NT, split-K slices S.
+//
+// The row units go into the fewest row blocks that an MR allows (every row block reads the weights again through the L2s), and of
+// what remains the block shape with the smallest estimated time is taken.  The estimate, in us, adds up
+//   the main loop: products of the fullest unit's rounds (0.028 per row unit, column tile and k-step) and bytes into the units
+//     (weights from memory at 12.4 MB/us and re-reads with the activations at 20.4, slower where blocks do not fill the chip),
+//     which overlap in part: root of the sum of squares; and a barrier and its skew per stage,
+//   what follows it: the epilogue (per unit and tile of the block), or a split's partial sums out (per block) and through the
+//     fix-up kernel.
+// Its constants are fitted to which shape is best, not to times: 9000 timings of 256 (GEMM, row count) pairs, 8 to 2048 rows of five
+// shapes, where its choice is 1.3 % off the best shape on average, more than 5 % in 9 % of them and 19 % at most.  (The rules by
+// cases before it, for row tiles of 32, were 15 % off in the same pairs: 80 rows of the 8B shape, gate/up 64.5 -> 48.2 us, down 38.1 -> 31.5;
+// 64 rows of the 70B shape, down 112 -> 83; 128 rows, gate/up 251 -> 200.)
+// The handle's tuning overrides (struct Tune: read from the environment when the handle was created) replace the choice in experiments.
 static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t part_elems, const Tune &tune) {
-    GemmCfg c;
-    const int m_tiles = (rows + 31) / 32;
-    c.MT = (which == G_LM && m_tiles >= 3) ? 4 : (m_tiles >= 2 ? 2 : 1);
-    c.NT = (n_tiles % 2 == 0) ? 2 : 1;
-    if (which == G_LM && c.MT == 4) c.NT = 4;            // never split: the widest tile halves the activation re-reads
-    if (which == G_GU && m_tiles == 4 && ((n_tiles + 15) / 16) >= 200) {
-        c.MT = 4;                                        // enough rows to fill the chip with 128 x 512 blocks, no split needed
-        c.NT = 4;
-    }
-    c.S = 1;
-    c.half = false;
-    const bool splittable = which != G_LM;
-    auto blocks_of = [&](const GemmCfg &x) { return (n_tiles + x.cols() - 1) / x.cols() * ((m_tiles + x.MT - 1) / x.MT); };
-    // rounds of unsplit blocks on the fullest XCD (32 units): column group c runs on XCD c % 8 with all its row blocks
-    auto rounds_of = [&](const GemmCfg &x) { return (((n_tiles + x.cols() - 1) / x.cols() + 7) / 8 * ((m_tiles + x.MT - 1) / x.MT) + 31) / 32; };
-    auto pick_s = [&]() {
-        c.S = 1;
-        if (!splittable) return;
-        const int blocks = blocks_of(c);
-        c.S = std::min(16, std::max(1, 256 / blocks));
-        c.S = std::min(c.S, std::max(1, (k_steps / 2) / 8));          // at least 8 stages per slice
-    };
-    pick_s();
-    // From 5 row tiles on (more than 128 rows) the matrix pipe starts to bind and the shape of the row blocks decides
-    // how many rounds of blocks the chip needs: rows in as few blocks as 5 row tiles per block allow (5 -> 5, 6 -> 3 + 3,
-    // 7 -> 4 + 4, 9 -> 5 + 5, ... 16 -> 4 x 4), because every row block re-reads the weights through the L2s and issues
-    // its own barriers.  Measured on the 8B and 70B shapes at 160 ... 512 rows (per GEMM, fix-up included): gate/up
-    // -17 ... -25 % at 160, 192, 288 and 320 rows, down -5 ... -32 %, QKV -17 ... -25 % where it applies.
-    const int m_total = (m_tiles + 3) / 4 * 4;           // row tiles of the operand buffers (blocks must stay inside)
-    int few = (m_tiles + 4) / 5, mt_few = (m_tiles + few - 1) / few;
-    if (few * mt_few > m_total) { few = (m_tiles + 3) / 4; mt_few = 4; }      // (4 always fits the padding)
-    if (which != G_LM && m_tiles >= 5 && n_tiles % 2 == 0) {
-        const GemmCfg narrow = c;
-        c.MT = mt_few;
-        c.NT = 2;
-        pick_s();
-        if (which == G_GU) {
-            // never split: compare with the 128 x 512 blocks by rounds of blocks x tiles per block (the wide block's
-            // tiles are 14 % cheaper: one weight fragment feeds four row tiles and the stage has one barrier)
-            // The 128 x 448 block (half tiles) does 7/8 of the 128 x 512 block's work per round and is taken where it
-            // needs no more rounds on any XCD: 896 column tiles (8B shape) are 224 or 256 blocks per 4 row blocks.  The chip runs
-            // at its power limit here, so a fuller last round buys less than its 12 %: 512 rows 194 -> 188 us, 2048 rows
-            // 766 -> 731 us, 256 rows of the 70B shape 422 -> 412 us.
-            GemmCfg wide = c;
-            wide.MT = 4; wide.NT = 4;
-            GemmCfg wide_half = wide;
-            wide_half.half = true;
-            const double cost_few = (double)((blocks_of(c) + 255) / 256) * c.MT * c.NT;
-            if ((blocks_of(wide) + 255) / 256 * 16 * 0.86 < cost_few) c = rounds_of(wide_half) <= rounds_of(wide) ? wide_half : wide;
-        } else {
-            // split GEMMs: the slices must stay long (64 k-steps).  O and down (light epilogues) may also take the
-            // 128 x 512 block with more slices; the two are compared by rounds x tiles x (k-steps + pipeline fill) plus
-            // the fix-up's launch and exchange traffic, in units of one tile x k-step (0.055 us)
-            auto cost = [&](const GemmCfg &x) {
-                const double e = x.NT == 4 ? 0.86 : 1.0;
-                double u = (double)((blocks_of(x) * x.S + 255) / 256) * x.MT * x.NT * e * ((double)k_steps / x.S + 24.0);
-                if (x.S > 1) u += (5.0 + (double)x.S * m_tiles * n_tiles * 8192.0 / 6.5e6) / 0.0547;
-                return u;
-            };
-            const GemmCfg few_cfg = c;
-            const bool few_ok = c.S == 1 || k_steps / c.S >= 64;
-            bool wide_ok = false;
-            GemmCfg wide = c;
-            if (which == G_O || which == G_DOWN) {
-                c.MT = 4; c.NT = 4;
-                pick_s();
-                wide = c;
-                wide_ok = (wide.S == 1 || k_steps / wide.S >= 64) && (size_t)wide.S * n_tiles * m_total * 1024 <= part_elems;
-            }
-            if (few_ok && wide_ok) c = cost(wide) < cost(few_cfg) ? wide : few_cfg;
-            else if (few_ok) c = few_cfg;
-            else if (wide_ok) c = wide;
-            else c = narrow;
-            // a GEMM that runs unsplit in one round of 64-row blocks keeps them, rather than gain a fix-up kernel, when
-            // they occupy more units than the split blocks would (as many, if K is short: the fix-up then costs more
-            // than the larger tiles save)
-            const int wide_blocks = blocks_of(c) * c.S, narrow_blocks = blocks_of(narrow);
-            if (narrow.S == 1 && c.S > 1 && narrow_blocks <= 256 &&
-                (narrow_blocks > wide_blocks || (narrow_blocks == wide_blocks && k_steps < 512))) c = narrow;
-            // QKV unsplit: the block shape by rounds x time of one full round (us at K = 4096, 8B shape).  Rounds are those of
-            // the fullest XCD: 20 column groups of 11 row blocks are 220 blocks, but 3 x 11 = 33 on an XCD, two rounds (70B
-            // shape, 1408 rows: 128 x 512 713 us, 128 x 256 448).  Over 17 row counts from 512 to 2048 in both shapes the choice is
-            // within 3 % of the best shape in all but one, and 4.5 % there (512 rows of the 8B shape 64 x 256 66 -> 64 x 192
-            // 59 us, 768 rows 102 -> 96 x 256 88, 2048 rows 128 x 256 235 -> 128 x 384 173).
-            if (which == G_QKV && c.S == 1) {
-                static const struct { int MT, NT; bool half; int us; } shapes[] = {{2, 2, true, 55}, {2, 2, false, 62}, {3, 2, false, 88},
-                    {4, 2, false, 112}, {5, 2, false, 130}, {4, 3, false, 164}, {4, 4, false, 205}};
-                int best = 0;
-                for (const auto &x : shapes) {
-                    GemmCfg y = c;
-                    y.MT = x.MT; y.NT = x.NT; y.half = x.half;
-                    if ((m_tiles + y.MT - 1) / y.MT * y.MT > m_total) continue;      // (blocks must stay inside the operand buffers)
-                    const int t = rounds_of(y) * x.us;
-                    if (!best || t < best) { best = t; c = y; }
-                }
-            }
+    static const int row_units[] = {1, 2, 3, 4, 5, 6, 7, 8, 10};
+    const int units = (rows + 15) / 16, units_total = sev_row_units(rows);
+    const size_t slice = (size_t)n_tiles * units_total * 512;            // floats of one slice in the exchange buffer
+    GemmCfg best = {0, 0, 1, false, 0};
+    double best_us = 0;
+    auto slices_fit = [&](int MR, int S) { return S == 1 || (k_steps / gemm_ks(MR) / S >= 4 && (size_t)S * slice <= part_elems); };
+    auto consider = [&](GemmCfg c, int s_min, int s_max) {
+        const int mb = (units + c.MR - 1) / c.MR, cg = (n_tiles + c.cols() - 1) / c.cols();
+        const double nt = c.half ? c.NT - 0.5 : c.NT, weights = n_tiles * (double)k_steps * 2048e-6, acts = (double)cg * mb * c.MR * k_steps * 2048e-6;      // MB
+        c.T = c.cols();
+        for (c.S = s_min; c.S <= s_max && slices_fit(c.MR, c.S); ++c.S) {
+            const int blocks = cg * mb * c.S, rounds = ((cg + 7) / 8 * mb * c.S + 31) / 32;      // column group c runs on XCD c % 8 (32 units)
+            const double steps = (double)rounds * k_steps / c.S;
+            const double idle = cbrt(256.0 * ((blocks + 255) / 256) / blocks);
+            const double products = 0.028 * steps * c.MR * nt, bytes = (weights / 12.4 + (acts + (mb - 1) * weights) / 20.4) * idle * idle;
+            double us = sqrt(products * products + bytes * bytes) + 0.007 * steps / gemm_ks(c.MR);
+            if (c.S == 1) us += (which == G_QKV ? 1.45 : 1.2) * rounds * c.MR * nt;
+            else us += 1.8 + 0.63 * c.S * units * n_tiles * 2048e-6 + 4.7 * rounds * c.MR * std::min(c.T, n_tiles) * 2.048e-3;
+            if (!best.MR || us < best_us) { best = c; best_us = us; }
         }
+    };
+    if (which == G_LM) {
+        // never split: 64 x 256 blocks for up to 64 rows; above, 128 x 512 blocks (their units are 14 % cheaper) or, where those pad the
+        // rows by more, the fewest row blocks of 256 columns (8B shape: 160 rows 405 -> 283 us, 304 rows 586 -> 530, 96 rows 222 -> 192)
+        int MR = units <= 4 ? (units + 1) / 2 * 2 : 0;
+        const int mb = (units + 9) / 10;
+        for (int m : {5, 6, 7, 10})
+            if (!MR && (units + m - 1) / m == mb) MR = m;
+        const bool wide = units > 4 && (!MR || 1.16 * mb * MR > (units + 7) / 8 * 8 || mb * MR > units_total);
+        best = wide ? GemmCfg{8, 4, 1, false, 0} : GemmCfg{MR, 2, 1, false, 0};
+        best.T = best.cols();
+        return best;
     }
-    // short slices are mostly pipeline fill: halve the block width instead of splitting that deep (one row tile, down
-    // projection of the 8B shape: 16 slices of 28 stages 22.7 + 5.8 us with the fix-up, 8 slices of the half width 21.6 + 5.2)
-    if (splittable && c.NT == 2 && c.S > 1 && (k_steps / 2) / c.S < (c.MT == 1 ? 32 : 24)) {
-        c.NT = 1;
-        pick_s();
+    int seen = 0;
+    for (int MR : row_units) {
+        const int mb = (units + MR - 1) / MR;
+        if (mb == seen || MR > units || mb * MR > units_total) continue;      // (blocks must stay inside the operand buffers)
+        seen = mb;                                           // the smallest MR of every number of row blocks
+        for (int NT : {1, 2, 3, 4})
+            for (bool half : {false, true}) {
+                // which instances there are (launch_gemm)
+                if (NT == 1 && half) continue;
+                if (NT == 2 && half && (which != G_QKV || MR != 4)) continue;
+                if (NT == 3 && (which != G_QKV || MR != 8 || half)) continue;
+                if (NT == 4 && (MR != 8 || (half && which != G_GU))) continue;
+                const GemmCfg c = {MR, NT, 1, half, 0};
+                const int cg = (n_tiles + c.cols() - 1) / c.cols();
+                consider(c, 1, std::min(16, std::max(1, 256 / (cg * mb))));
+            }
     }
-    // Up to 64 rows: no split, and no fix-up kernel, where the narrowest blocks fill most of the chip by themselves (gate/up
-    // of the 8B shape: 224 blocks of 128 columns, 38.1 us at 32 rows and 46.0 at 64 as with two slices of twice the width,
-    // whose fix-up took 5.1 and 5.5 more; with two row tiles up to that shape's K of 4096: at K = 5120 and 216 blocks 40 to
-    // 64 rows take 62.7 us unsplit, 60.1 split), or where K is so short that a slice is all pipeline fill (K = 512: QKV
-    // 6.3 us against 4.1 + 5.0, gate/up 5.7 against 4.1 + 3.8).
-    if (splittable && m_tiles <= 2 && c.S > 1) {
-        GemmCfg x = c;
-        x.NT = 1;
-        x.S = 1;
-        if ((blocks_of(x) >= 192 && blocks_of(x) <= 256 && (m_tiles == 1 || k_steps <= 256)) || k_steps <= 32) c = x;
-    }
-    if (tune.has_gemm[which]) {                          // "MT,NT,S,PF"; S = 0 keeps the automatic split
+    if (tune.has_gemm[which]) {                          // "MT,NT,S,PF": MT row tiles of 32 (-MT: row units), NT > 10: half tiles; S = 0 keeps the automatic split
         const int mt = tune.gemm[which][0], nt = tune.gemm[which][1], sp = tune.gemm[which][2], pf = tune.gemm[which][3];
         const bool half = nt > 10;                           // 15 (QKV), 35 (gate/up): a shared half tile
-        if (mt >= 1 && mt <= 5 && (half ? (pf == 4 && ((which == G_QKV && mt == 2 && nt == 15) || (which == G_GU && mt == 4 && nt == 35))) :
-                                   (nt == 1 || nt == 2 || ((nt == 4 || (nt == 3 && which == G_QKV)) && mt == 4 && pf == 4))) &&
-            sp >= 0 && sp <= 32 && pf == 4 &&
-            (m_tiles + mt - 1) / mt * mt <= (m_tiles + 3) / 4 * 4) {     // the row blocks must stay inside the padded row tiles
-            c.MT = mt;
-            c.NT = half ? nt / 10 + 1 : nt;
-            c.half = half;
-            pick_s();
-            if (splittable && sp > 0) c.S = sp;
+        const int MR = mt < 0 ? -mt : 2 * mt;
+        const bool known = std::find(std::begin(row_units), std::end(row_units), MR) != std::end(row_units);
+        if (known && (half ? ((which == G_QKV && MR == 4 && nt == 15) || (which == G_GU && MR == 8 && nt == 35)) :
+                             (nt == 1 || nt == 2 || ((nt == 4 || (nt == 3 && which == G_QKV)) && MR == 8))) &&
+            sp >= 0 && sp <= 32 && pf == 4 && (units + MR - 1) / MR * MR <= units_total && sp <= std::max(1, k_steps / gemm_ks(MR)) &&
+            (sp <= 1 || (size_t)sp * slice <= part_elems)) {
+            best.MR = 0;
+            const GemmCfg c = {MR, half ? nt / 10 + 1 : nt, 1, half, 0};
+            const int blocks = (n_tiles + c.cols() - 1) / c.cols() * ((units + MR - 1) / MR);
+            consider(c, 1, std::min(16, std::max(1, 256 / blocks)));
+            if (sp > 0) best.S = sp;
         }
     }
-    c.S = std::min(c.S, std::max(1, k_steps / 2));
     // The unsplit gate/up GEMM, when it leaves compute units idle: blocks one or two column tiles narrower (the last
     // wave of a block then has fewer tiles than the others) if that brings the block count closer to the number of
     // compute units.  With few rows the kernel is bound by the requests a compute unit can keep in flight, so every
     // unit counts: the 8B shape has 896 column tiles, 112 x 2 = 224 blocks of 8 or 128 x 2 = 256 blocks of 7.
-    c.T = c.cols();
-    if (c.S == 1 && which == G_GU && c.MT <= 2 && !c.half) {
-        const int m_blocks = (m_tiles + c.MT - 1) / c.MT;
+    if (best.S == 1 && which == G_GU && best.MR <= 4 && !best.half) {
+        const int m_blocks = (units + best.MR - 1) / best.MR;
         auto blocks_t = [&](int t) { return ((n_tiles + t - 1) / t) * m_blocks; };
-        for (int t = 4 * c.NT - 1; t >= 3 * c.NT + 1; --t)
-            if (blocks_t(4 * c.NT) < 256 && blocks_t(t) <= 256 && blocks_t(t) > blocks_t(c.T)) c.T = t;
+        for (int t = 4 * best.NT - 1; t >= 3 * best.NT + 1; --t)
+            if (blocks_t(4 * best.NT) < 256 && blocks_t(t) <= 256 && blocks_t(t) > blocks_t(best.T)) best.T = t;
     }
     if (tune.tpb) {                                      // tuning experiments: tiles per block of the gate/up GEMM
         const int t = tune.tpb;
-        if (which == G_GU && c.S == 1 && !c.half && t >= 3 * c.NT + 1 && t <= 4 * c.NT) c.T = t;
+        if (which == G_GU && best.S == 1 && best.MR <= 4 && !best.half && t >= 3 * best.NT + 1 && t <= 4 * best.NT) best.T = t;
     }
-    // the exchange buffer holds S slices of (padded columns) x (padded rows)
-    const size_t slice = (size_t)n_tiles * ((m_tiles + 3) / 4 * 4) * 1024;
-    while (c.S > 1 && (size_t)c.S * slice > part_elems) --c.S;
+    return best;
+}
+
+// The choice depends on the handle's model and the number of row units alone; it is kept with the handle for up to 2048 rows.
+static GemmCfg gemm_cfg(sev_kv *kv, int which, int rows, int n_tiles, int k_steps) {
+    const int units = (rows + 15) / 16;
+    GemmCfg *kept = units <= SEV_KEPT_UNITS ? &kv->gemm_kept[which * SEV_KEPT_UNITS + units - 1] : nullptr;
+    if (kept && kept->MR) return *kept;
+    const GemmCfg c = choose_cfg(which, rows, n_tiles, k_steps, kv->part_elems, kv->tune);
+    if (kept) *kept = c;
     return c;
 }
 
@@ -1540,29 +1489,41 @@ static void launch_fixup(const GemmArgs &ga, hipStream_t st) {
 template <int EPI>
 static void launch_gemm(GemmArgs ga, const GemmCfg &c, hipStream_t st) {
     ga.col_groups = (ga.n_tiles + c.T - 1) / c.T;
-    ga.m_blocks = ((ga.M + 31) / 32 + c.MT - 1) / c.MT;
+    ga.m_blocks = ((ga.M + 15) / 16 + c.MR - 1) / c.MR;
     ga.splits = c.S;
     const int g8 = (ga.col_groups + 7) / 8 * 8;
     dim3 grid((unsigned)(g8 * ga.m_blocks * ga.splits));
 #define SEV_LAUNCH(MR_, NT_, PF_, ...)                                                                                \
-    hipLaunchKernelGGL((gemm_bf16_kernel<MR_, NT_, EPI, PF_ __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), PF_ * gemm_ks(MR_) * MR_ * 2048, st, ga.W, ga.X, ga.n_tiles, ga.k_steps,         \
+    hipLaunchKernelGGL((gemm_bf16_kernel<MR_, NT_, EPI, PF_ __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), (PF_) * gemm_ks(MR_) * (MR_) * 2048, st, ga.W, ga.X, ga.n_tiles, ga.k_steps,         \
                        ga.units_total, ga.col_groups, ga.m_blocks, ga.splits | (c.T << 16), ga)
 #define SEV_BY_NT(MR_, PF_)                                                                                           \
     do {                                                                                                              \
-        if (c.NT == 2) SEV_LAUNCH(MR_, 2, PF_); else SEV_LAUNCH(MR_, 1, 4);                                           \
+        if (c.NT == 2) SEV_LAUNCH(MR_, 2, PF_); else SEV_LAUNCH(MR_, 1, (MR_ % 2 ? 3 : 4));                               \
     } while (0)
-    if (c.half) {
+    if constexpr (EPI == EPI_ARGMAX) {
+        if (c.NT == 4) SEV_LAUNCH(8, 4, 3);
+        else if (c.MR == 10) SEV_LAUNCH(10, 2, 3);
+        else if (c.MR == 7) SEV_LAUNCH(7, 2, 3);
+        else if (c.MR == 6) SEV_LAUNCH(6, 2, 3);
+        else if (c.MR == 5) SEV_LAUNCH(5, 2, 3);
+        else if (c.MR == 4) SEV_LAUNCH(4, 2, 4);
+        else SEV_LAUNCH(2, 2, 4);
+    } else if (c.half) {
         if constexpr (EPI == EPI_SWIGLU) SEV_LAUNCH(8, 4, 3, true);
         if constexpr (EPI == EPI_QKV) SEV_LAUNCH(4, 2, 4, true);
-    } else if (c.MT == 4 && c.NT == 4) SEV_LAUNCH(8, 4, 3);
-    else if (c.MT == 4 && c.NT == 3) {
+    } else if (c.NT == 4) SEV_LAUNCH(8, 4, 3);
+    else if (c.NT == 3) {
         if constexpr (EPI == EPI_QKV) SEV_LAUNCH(8, 3, 3);
     }
-    else if (c.MT == 5) SEV_BY_NT(10, 3);
-    else if (c.MT == 4) SEV_BY_NT(8, 3);
-    else if (c.MT == 3) SEV_BY_NT(6, 3);
-    else if (c.MT == 2) SEV_BY_NT(4, 4);
-    else SEV_BY_NT(2, 4);
+    else if (c.MR == 10) SEV_BY_NT(10, 3);
+    else if (c.MR == 8) SEV_BY_NT(8, 3);
+    else if (c.MR == 7) SEV_BY_NT(7, 3);
+    else if (c.MR == 6) SEV_BY_NT(6, 3);
+    else if (c.MR == 5) SEV_BY_NT(5, 3);
+    else if (c.MR == 4) SEV_BY_NT(4, 4);
+    else if (c.MR == 3) SEV_BY_NT(3, 3);
+    else if (c.MR == 2) SEV_BY_NT(2, 4);
+    else SEV_BY_NT(1, 3);
 #undef SEV_BY_NT
 #undef SEV_LAUNCH
     if constexpr (EPI != EPI_ARGMAX) {
@@ -1599,12 +1560,12 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
         hipLaunchKernelGGL(embed_norm_kernel, dim3(rows), dim3(256), 0, st, (const uint16_t *)(m->arena + m->off_embed),
                            kv->plan.row_tok, Gp(m->layers[0].g_attn), kv->h, xa, kv->ssq[1], kv->ssq[0], d.d_model, units);
     }
-    const GemmCfg pq = choose_cfg(G_QKV, rows, m->n_qkv / 32, d.d_model / 16, kv->part_elems, kv->tune);
+    const GemmCfg pq = gemm_cfg(kv, G_QKV, rows, m->n_qkv / 32, d.d_model / 32);
     GemmCfg po, pg, pd;
     auto choose = [&]() {
-        po = choose_cfg(G_O, rows, d.d_model / 32, m->q_dim / 16, kv->part_elems, kv->tune);
-        pg = choose_cfg(G_GU, rows, d.d_ffn / 16, d.d_model / 16, kv->part_elems, kv->tune);
-        pd = choose_cfg(G_DOWN, rows, d.d_model / 32, d.d_ffn / 16, kv->part_elems, kv->tune);
+        po = gemm_cfg(kv, G_O, rows, d.d_model / 32, m->q_dim / 32);
+        pg = gemm_cfg(kv, G_GU, rows, d.d_ffn / 16, d.d_model / 32);
+        pd = gemm_cfg(kv, G_DOWN, rows, d.d_model / 32, d.d_ffn / 32);
     };
     choose();
     GemmArgs base;
@@ -1703,7 +1664,7 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
     }
     {   // LM head with fused arg-max
         Prof p(kv, st, PROF_GEMM_LM);
-        const GemmCfg pl = choose_cfg(G_LM, rows, d.vocab / 32, d.d_model / 16, kv->part_elems, kv->tune);
+        const GemmCfg pl = gemm_cfg(kv, G_LM, rows, d.vocab / 32, d.d_model / 32);
         GemmArgs ga = base;
         ga.W = Wp(m->off_lm); ga.X = (const uint4 *)xa; ga.n_tiles = d.vocab / 32; ga.k_steps = d.d_model / 32; ga.N = d.vocab;
         ga.ssq_in = kv->ssq[1];

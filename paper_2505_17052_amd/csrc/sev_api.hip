@@ -201,9 +201,9 @@ KvGeom sev_kv_geom(const sev_kv *kv) {
 #define ATT_ITEMS_CAP 4096
 
 static void read_tune(Tune *t) {
-    static const char *names[5] = {"SEV_TUNE_QKV", "SEV_TUNE_O", "SEV_TUNE_GU", "SEV_TUNE_DOWN", "SEV_TUNE_LM"};
+    static const char *names[4] = {"SEV_TUNE_QKV", "SEV_TUNE_O", "SEV_TUNE_GU", "SEV_TUNE_DOWN"};
     memset(t, 0, sizeof(*t));
-    for (int i = 0; i < 5; ++i)
+    for (int i = 0; i < 4; ++i)
         if (const char *e = getenv(names[i]))
             t->has_gemm[i] = sscanf(e, "%d,%d,%d,%d", &t->gemm[i][0], &t->gemm[i][1], &t->gemm[i][2], &t->gemm[i][3]) == 4;
     if (const char *e = getenv("SEV_TUNE_TPB")) t->tpb = atoi(e);
@@ -241,6 +241,7 @@ extern "C" int sev_kv_create(const sev_model *m, int max_requests, int max_rows,
     kv->prof_on = 0;
     memset(kv->prof_ms, 0, sizeof(kv->prof_ms));
     memset(kv->prof_n, 0, sizeof(kv->prof_n));
+    kv->gemm_kept.assign(5 * SEV_KEPT_UNITS, GemmCfg());
     kv->host_pages.assign(max_requests, 0);
     kv->host_tree.assign(max_requests, 0);
 

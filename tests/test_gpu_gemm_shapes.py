@@ -48,3 +48,20 @@ def test_forced_shapes(setup, monkeypatch, qkv, gate_up):
     diff = np.abs(out["logits"].cpu().numpy() - want)
     announce(f"  logits max {diff.max():.2e} mean {diff.mean():.2e}")
     assert diff.max() < 4e-3 and diff.mean() < 4e-4
+
+
+@pytest.mark.parametrize("requests,shape", [(15, "-1,1,1,4"), (15, "-3,1,2,4"), (15, "-3,2,1,4"), (15, "-5,1,1,4"), (15, "-5,2,3,4"), (7, "-7,1,2,4"), (7, "-7,2,1,4"), (3, "-3,1,1,4"), (1, "-1,2,3,4")])
+def test_blocks_of_an_odd_number_of_row_units(setup, monkeypatch, requests, shape):
+    """Blocks of 16, 48, 80 and 112 rows (two k-steps of activations per stage), whole and split K, on all four projections: 225,
+    105, 45 and 15 rows, the last unit of each with a row missing or 15.  Same bounds as above."""
+    sev, harness, model, lens, prompts, tok, caches, want = setup
+    for name in ("SEV_TUNE_QKV", "SEV_TUNE_O", "SEV_TUNE_GU", "SEV_TUNE_DOWN"):
+        monkeypatch.setenv(name, shape)
+    announce(f"GEMM row units {shape}, {requests} requests of 15")
+    batch = harness.Batch(model, SHAPE, [p + 15 for p in lens], max_rows=225, seed=SEED)
+    batch.prefill(prompts)
+    out = sev.verify_ex(model, batch.kv, lens[:requests], torch.tensor(tok[:requests], device="cuda"), 15, want_logits=True)
+    torch.cuda.synchronize()
+    diff = np.abs(out["logits"].cpu().numpy() - want[:15 * requests])
+    announce(f"  logits max {diff.max():.2e} mean {diff.mean():.2e}")
+    assert diff.max() < 4e-3 and diff.mean() < 4e-4
