@@ -18,6 +18,7 @@
 
 #include "sev_internal.h"
 #include "kv_layout.h"
+#include "row_ops.h"
 
 KvGeom sev_kv_geom(const sev_kv *kv);
 
@@ -33,7 +34,6 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
     uint32_t u = __float_as_uint(f);
     return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;          // round to nearest even (finite inputs)
 }
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 
 // hi/lo split of one float: hi = bf16(x), lo = bf16(x - hi)
 __device__ __forceinline__ void split_bf16(float x, uint32_t &hi, uint32_t &lo) {
@@ -41,41 +41,8 @@ __device__ __forceinline__ void split_bf16(float x, uint32_t &hi, uint32_t &lo) 
     lo = f32_to_bf16_bits(x - bf16_bits_to_f32(hi));
 }
 
-// hi/lo split of two floats at once with the packed hardware conversion (round to nearest even):
-// hi = {bf16(a), bf16(b)}, lo = {bf16(a - hi_a), bf16(b - hi_b)}, element 0 in the low half.
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void split_pack2(float a, float b, uint32_t &hi, uint32_t &lo) {
-    const f32x2 v = {a, b};
-    const bf16x2 h = __builtin_convertvector(v, bf16x2);
-    const bf16x2 l = __builtin_convertvector(v - __builtin_convertvector(h, f32x2), bf16x2);
-    hi = __builtin_bit_cast(uint32_t, h);
-    lo = __builtin_bit_cast(uint32_t, l);
-}
-
-// Writes 8 consecutive-k activations of row m (k0 a multiple of 8) as hi and lo fragments.
-__device__ __forceinline__ void store_split8(uint16_t *xp, int m, int k0, int units, const float *v) {
-    uint32_t h[4], l[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) split_pack2(v[2 * i], v[2 * i + 1], h[i], l[i]);
-    *(uint4 *)(xp + xpack_index(m, k0, 0, units)) = make_uint4(h[0], h[1], h[2], h[3]);
-    *(uint4 *)(xp + xpack_index(m, k0, 1, units)) = make_uint4(l[0], l[1], l[2], l[3]);
-}
-
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-template <int THREADS>
-__device__ __forceinline__ float block_sum(float v, float *red) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float s = 0.f;
-#pragma unroll
-    for (int w = 0; w < THREADS / 64; ++w) s += red[w];
-    __syncthreads();
-    return s;
-}
 
 // ---------------------------------------------------------------------------
 // weight re-tiling: canonical [rows][K] bf16 -> [tile of 32 rows][K/32][fragment 2][lane 64][8], where lane l of fragment f
@@ -121,52 +88,6 @@ void launch_pack_bf16(uint16_t *dst, const uint16_t *src, int n_rows, int K, int
     uint4 *d = (uint4 *)dst + (whole ? (int64_t)tile_add * (K / 32) * 128 : 0);
     hipLaunchKernelGGL(pack_bf16_kernel, dim3((unsigned)((n_chunks + 255) / 256)), dim3(256), 0, st, d, src, K, n_chunks,
                        mode, 0);
-}
-
-// ---------------------------------------------------------------------------
-// embedding gather.  One block per row: h = E[token] (float32), xa = split(h * g) for the first
-// QKV GEMM (which applies the row's RMS scale in its epilogue), ssq = fixed-point sum of squares.
-// ---------------------------------------------------------------------------
-// Sums of squares of the residual rows are accumulated by many blocks; they are kept as 64-bit
-// fixed point (2^-20 units) so that the atomic additions commute and the result is reproducible.
-// One contribution (32 rows x <= 256 columns) is clamped to 1e10, so up to 1024 of them cannot wrap;
-// what is lost below 2^-20 is far under the norm's epsilon once divided by the row width.
-#define SSQ_SCALE 1048576.0f
-__device__ __forceinline__ unsigned long long ssq_fix(float v) { return (unsigned long long)(fminf(v, 1.0e10f) * SSQ_SCALE); }
-__device__ __forceinline__ float rms_scale(unsigned long long q, float inv_d, float eps) {
-    return 1.0f / sqrtf((float)((double)q * (1.0 / 1048576.0)) * inv_d + eps);
-}
-
-__global__ __launch_bounds__(256) void embed_norm_kernel(const uint16_t *E, const int32_t *row_tok, const float *g,
-                                                         float *h, uint16_t *xa, unsigned long long *ssq_out,
-                                                         unsigned long long *ssq_clear, int d, int units) {
-    __shared__ float red[4];
-    const int m = blockIdx.x;
-    const uint16_t *src = E + (size_t)row_tok[m] * d;
-    float *hr = h + (size_t)m * d;
-    float ss = 0.f;
-    for (int c = threadIdx.x; c < d / 8; c += 256) {
-        const uint4 raw = *(const uint4 *)(src + c * 8);
-        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-        float v[8];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[2 * i] = bf16_bits_to_f32(w[i] & 0xffffu);
-            v[2 * i + 1] = bf16_bits_to_f32(w[i] >> 16);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) ss += v[i] * v[i];
-        *(float4 *)(hr + c * 8) = make_float4(v[0], v[1], v[2], v[3]);
-        *(float4 *)(hr + c * 8 + 4) = make_float4(v[4], v[5], v[6], v[7]);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] *= g[c * 8 + i];
-        store_split8(xa, m, c * 8, units, v);
-    }
-    ss = block_sum<256>(ss, red);
-    if (threadIdx.x == 0) {
-        ssq_out[m] = ssq_fix(ss);
-        ssq_clear[m] = 0ull;
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1373,7 +1294,7 @@ enum { G_QKV = 0, G_O, G_GU, G_DOWN, G_LM };
 //
 // The row units go into the fewest row blocks that an MR allows (every row block reads the weights again through the L2s), and of
 // what remains the block shape with the smallest estimated time is taken.  The estimate, in us, adds up
-//   the main loop: products of the fullest unit's rounds (0.028 per row unit, column tile and k-step) and bytes into the units
+//   the main loop: products of the fullest unit's rounds (0.028 per row unit, column tile and k-step, 12 % less in the wide blocks) and bytes into the units
 //     (weights from memory at 12.4 MB/us and re-reads with the activations at 20.4, slower where blocks do not fill the chip),
 //     which overlap in part: root of the sum of squares; and a barrier and its skew per stage,
 //   what follows it: the epilogue (per unit and tile of the block), or a split's partial sums out (per block) and through the
@@ -1398,9 +1319,9 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
             const int blocks = cg * mb * c.S, rounds = ((cg + 7) / 8 * mb * c.S + 31) / 32;      // column group c runs on XCD c % 8 (32 units)
             const double steps = (double)rounds * k_steps / c.S;
             const double idle = cbrt(256.0 * ((blocks + 255) / 256) / blocks);
-            const double products = 0.028 * steps * c.MR * nt, bytes = (weights / 12.4 + (acts + (mb - 1) * weights) / 20.4) * idle * idle;
-            double us = sqrt(products * products + bytes * bytes) + 0.007 * steps / gemm_ks(c.MR);
-            if (c.S == 1) us += (which == G_QKV ? 1.45 : 1.2) * rounds * c.MR * nt;
+            const double products = (c.NT > 2 ? 0.0246 : 0.028) * steps * c.MR * nt, bytes = (weights / 12.4 + (acts + (mb - 1) * weights) / 20.4) * idle * idle;
+            double us = sqrt(products * products + bytes * bytes) + 0.0085 * steps / gemm_ks(c.MR);
+            if (c.S == 1) us += (which == G_QKV ? 1.45 : 1.0) * rounds * c.MR * nt;
             else us += 1.8 + 0.63 * c.S * units * n_tiles * 2048e-6 + 4.7 * rounds * c.MR * std::min(c.T, n_tiles) * 2.048e-3;
             if (!best.MR || us < best_us) { best = c; best_us = us; }
         }
@@ -1545,7 +1466,7 @@ __global__ __launch_bounds__(256) void tail_gather_kernel(TailSrc src, const uin
     for (int c = threadIdx.x; c < h4; c += 256) h2[(size_t)i * h4 + c] = h[(size_t)r * h4 + c];
 }
 
-void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList &att_all, float *logits_out, const TailRows *tail, hipStream_t st) {
+void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList &att_all, float *logits_out, const TailRows *tail, HeadOut *head, hipStream_t st) {
     AttList att = att_all;
     const sev_model_desc &d = m->d;
     KvGeom g = sev_kv_geom(kv);
@@ -1555,11 +1476,6 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
     uint16_t *xa = (uint16_t *)kv->xa, *qp = (uint16_t *)kv->q_buf, *op = (uint16_t *)kv->o_buf, *act = (uint16_t *)kv->act;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)d.head_dim);
 
-    {
-        Prof p(kv, st, PROF_OTHER);
-        hipLaunchKernelGGL(embed_norm_kernel, dim3(rows), dim3(256), 0, st, (const uint16_t *)(m->arena + m->off_embed),
-                           kv->plan.row_tok, Gp(m->layers[0].g_attn), kv->h, xa, kv->ssq[1], kv->ssq[0], d.d_model, units);
-    }
     const GemmCfg pq = gemm_cfg(kv, G_QKV, rows, m->n_qkv / 32, d.d_model / 32);
     GemmCfg po, pg, pd;
     auto choose = [&]() {
@@ -1671,7 +1587,8 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
         ga.lm_val = kv->lm_val; ga.lm_idx = kv->lm_idx; ga.lm_stride = units * 16; ga.logits = logits_out;
         launch_gemm<EPI_ARGMAX>(ga, pl, st);
         const int n_part = ((ga.n_tiles + 4 * pl.NT - 1) / (4 * pl.NT)) * 4;
-        hipLaunchKernelGGL(lm_reduce_kernel, dim3(rows), dim3(256), 0, st, kv->lm_val, kv->lm_idx, n_part, ga.lm_stride,
-                           kv->row_argmax);
+        if (head) *head = {HEAD_PARTS, nullptr, kv->lm_val, kv->lm_idx, n_part, ga.lm_stride};
+        else hipLaunchKernelGGL(lm_reduce_kernel, dim3(rows), dim3(256), 0, st, kv->lm_val, kv->lm_idx, n_part, ga.lm_stride,
+                                kv->row_argmax);
     }
 }

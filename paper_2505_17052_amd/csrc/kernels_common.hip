@@ -3,6 +3,7 @@
 
 #include "sev_internal.h"
 #include "kv_layout.h"
+#include "row_ops.h"
 
 // ---------------------------------------------------------------------------
 // fills
@@ -35,7 +36,8 @@ void launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st) {
 //
 // One kernel, bound by latency alone: every block scans the (at most 256) requests' sizes itself and then fills its
 // own share, so no block waits for another and no second launch is needed.  The first n_row_blocks blocks take 16 rows
-// of one request each, the others four work items (one per wave).  The ancestor sets of a tree come from pointer
+// of one request each, the next n_item_blocks four work items (one per wave), and the last, one per row, gather the rows' embeddings
+// (a kernel of its own behind the plan took 1.6-14 us and a launch).  The ancestor sets of a tree come from pointer
 // doubling in LDS (six rounds for 64 nodes); a depth is the number of ancestors.  (One thread per request walking
 // its tree, and a second kernel for the tables, took 55 + 6 us for 8 trees of 64 nodes and 5 + 5 us for 16 chains of 8.)
 // ---------------------------------------------------------------------------
@@ -49,6 +51,7 @@ struct PlanDev {
     const int32_t *tokens, *parents;
     const int32_t *page_table;
     int max_pages;
+    EmbedArgs emb;
 };
 static_assert(sizeof(PlanArgs) + sizeof(PlanDev) + 64 <= 4096, "kernel arguments of the plan");
 
@@ -75,7 +78,8 @@ __device__ __forceinline__ int plan_find(const int *first, int B, int m) {
     return lo;
 }
 
-__global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_row_blocks, int n_items) {
+template <bool BF16>
+__global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_row_blocks, int n_item_blocks, int n_items) {
     __shared__ int s_first[4][SEV_MAX_BATCH];                  // per request: first row, merge group, work item, row block
     __shared__ int s_tot[4][4];
     __shared__ unsigned long long s_anc[2][SEV_MAX_DRAFT];
@@ -150,13 +154,12 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_
         }
         if (t < PLAN_ROWS && i0 + t < n) {
             const int i = i0 + t, row = row0 + i;
-            int tok = d.tokens[(size_t)(a.first + b) * a.k_max + a.tok0[b] + i];
-            if (tok < 0 || tok >= d.vocab) { atomicOr(d.err, 4u); tok = 0; }
+            const int tok = d.tokens[(size_t)(a.first + b) * a.k_max + a.tok0[b] + i];
+            if (tok < 0 || tok >= d.vocab) atomicOr(d.err, 4u);
             const unsigned long long anc = d.parents ? s_anc[cur][i] : (i < 63 ? (2ull << i) - 1ull : ~0ull);
             d.p.row_req[row] = b;
             d.p.row_node[row] = i;
             d.p.row_anc[row] = anc;
-            d.p.row_tok[row] = tok;
             d.p.row_kvloc[row] = d.page_table[(size_t)slot * d.max_pages + (P + i) / SEV_PAGE] * SEV_PAGE + (P + i) % SEV_PAGE;
         }
         const int half = d.hd / 2, rows = min(PLAN_ROWS, n - i0);
@@ -167,6 +170,13 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs a, PlanDev d, int n_
             sincos((double)pos * d.p.theta[i], &s, &c);
             d.p.row_cs[(size_t)(row0 + node) * half + i] = make_float2((float)c, (float)s);
         }
+        return;
+    }
+    if (blk >= n_row_blocks + n_item_blocks) {                  // the embedding of one row
+        __shared__ float s_red[4];
+        const int m = blk - n_row_blocks - n_item_blocks, b = plan_find(s_first[0], B, m);
+        const int tok = d.tokens[(size_t)(a.first + b) * a.k_max + a.tok0[b] + (m - s_first[0][b])];
+        embed_row<BF16>(d.emb, m, tok < 0 || tok >= d.vocab ? 0 : tok, s_red);      // (the row's own block flags such a token)
         return;
     }
     // attention work items.  A request's pages are split evenly over its chunks; item order: chunk by chunk, the row
@@ -210,29 +220,97 @@ void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_toke
     d.parents = parents;
     d.page_table = kv->page_table;
     d.max_pages = kv->max_pages_per_req;
-    int row_blocks = 0;
-    for (int b = 0; b < pa.B; ++b) row_blocks += (pa.nd[b] + PLAN_ROWS - 1) / PLAN_ROWS;
-    hipLaunchKernelGGL(plan_kernel, dim3((unsigned)(row_blocks + (n_items + PLAN_ITEMS - 1) / PLAN_ITEMS)), dim3(256), 0, st, pa, d,
-                       row_blocks, n_items);
+    int row_blocks = 0, rows = 0;
+    for (int b = 0; b < pa.B; ++b) {
+        row_blocks += (pa.nd[b] + PLAN_ROWS - 1) / PLAN_ROWS;
+        rows += pa.nd[b];
+    }
+    const sev_model *m = kv->model;
+    const bool bf = m->d.dtype == SEV_BF16;
+    d.emb.E = m->arena + m->off_embed;
+    d.emb.h = kv->h;
+    d.emb.d = m->d.d_model;
+    d.emb.g = (const float *)(m->arena + m->layers[0].g_attn);
+    d.emb.xa = (uint16_t *)kv->xa;
+    d.emb.ssq_out = kv->ssq[1];
+    d.emb.ssq_clear = kv->ssq[0];
+    d.emb.units = sev_row_units(rows);
+    const int item_blocks = (n_items + PLAN_ITEMS - 1) / PLAN_ITEMS;
+    if (pa.tail) rows = 0;                              // (their rows are in the stream already)
+    const dim3 grid((unsigned)(row_blocks + item_blocks + rows));
+    if (bf) hipLaunchKernelGGL((plan_kernel<true>), grid, dim3(256), 0, st, pa, d, row_blocks, item_blocks, n_items);
+    else hipLaunchKernelGGL((plan_kernel<false>), grid, dim3(256), 0, st, pa, d, row_blocks, item_blocks, n_items);
 }
 
 // ---------------------------------------------------------------------------
 // greedy acceptance (paper section 4.1: accepted candidates plus one additional
-// token from the server's own forward pass).  One wave per request, one lane per candidate: a step of the walk is a
-// ballot over (parent, token), so the kernel is two loads deep whatever the tree (a thread per request, searching the
-// children in memory, took 50 us for 8 trees of 64 nodes and 11 us for chains of 8).
+// token from the server's own forward pass).  One block per request.  First the arg-max of its rows, from what the head left
+// (HEAD_PARTS: the matrix-core GEMM's partial results; HEAD_LOGITS: float32 logits; HEAD_ROWS: it is there already): the lanes
+// of a wave take the request's rows side by side (16 bytes to 256 of a line), the waves different parts.  Then one wave, one lane
+// per candidate: a step of the walk is a ballot over (parent, token), so it is two loads deep whatever the tree (a thread
+// per request, searching the children in memory, took 50 us for 8 trees of 64 nodes and 11 us for chains of 8).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void accept_kernel(DevPlan p, int k_max, int mode, const int32_t *tokens, const int32_t *parents,
-                                                    const int32_t *row_argmax, const int32_t *next_tok, int32_t *pend_n, int32_t *pend_a,
-                                                    int32_t *pend_bonus, int32_t *pend_path, int32_t *accept_len, int32_t *bonus_out,
-                                                    int32_t *path_out, int32_t *argmax_out) {
-    const int b = blockIdx.x, c = threadIdx.x;
+__device__ __forceinline__ void arg_max(float &v, int &i, float ov, int oi) {
+    if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }       // lowest index wins ties
+}
+
+#define ACCEPT_WAVES 16
+template <int HEAD>
+__global__ __launch_bounds__(HEAD == HEAD_ROWS ? 64 : ACCEPT_WAVES * 64) void accept_kernel(DevPlan p, HeadOut ho, int k_max, int mode, const int32_t *tokens,
+                                                                                            const int32_t *parents, const int32_t *next_tok, int32_t *pend_n,
+                                                                                            int32_t *pend_a, int32_t *pend_bonus, int32_t *pend_path,
+                                                                                            int32_t *accept_len, int32_t *bonus_out, int32_t *path_out,
+                                                                                            int32_t *argmax_out) {
+    const int b = blockIdx.x, c = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int slot = p.req_slot[b], n = p.req_n[b], row0 = p.req_row0[b];
+    int am = 0;
+    if constexpr (HEAD == HEAD_ROWS) {
+        am = c < n ? ho.rows[row0 + c] : 0;
+    } else {
+        __shared__ float s_v[ACCEPT_WAVES][64];
+        __shared__ int s_i[ACCEPT_WAVES][64];
+        if constexpr (HEAD == HEAD_PARTS) {
+            const int R = n > 1 ? 2 << (31 - __clz(n - 1)) : 1, sub = c / R, per = 64 / R;      // a power of two of lanes for the rows
+            const size_t at = row0 + min(c & (R - 1), n - 1);
+            float v = -INFINITY;
+            int i = 0x7fffffff;
+#pragma unroll 8
+            for (int q = wave * per + sub; q < ho.n_part; q += ACCEPT_WAVES * per)
+                arg_max(v, i, ho.val[(size_t)q * ho.stride + at], ho.idx[(size_t)q * ho.stride + at]);
+            for (int o = R; o < 64; o *= 2) {
+                const float ov = __shfl_xor(v, o);
+                const int oi = __shfl_xor(i, o);
+                arg_max(v, i, ov, oi);
+            }
+            s_v[wave][c] = v;
+            s_i[wave][c] = i;
+            __syncthreads();
+            if (wave) return;
+            for (int w = 1; w < ACCEPT_WAVES; ++w) arg_max(v, i, s_v[w][c], s_i[w][c]);
+            am = c < n ? i : 0;
+        } else {
+            for (int r = wave; r < n; r += ACCEPT_WAVES) {
+                const float *row = ho.val + (size_t)(row0 + r) * ho.n_part;
+                float v = -INFINITY;
+                int i = 0x7fffffff;
+#pragma unroll 8
+                for (int q = c; q < ho.n_part; q += 64) arg_max(v, i, row[q], q);
+                for (int o = 1; o < 64; o *= 2) {
+                    const float ov = __shfl_xor(v, o);
+                    const int oi = __shfl_xor(i, o);
+                    arg_max(v, i, ov, oi);
+                }
+                if (c == 0) s_i[0][r] = i;
+            }
+            __syncthreads();
+            if (wave) return;
+            am = c < n ? s_i[0][c] : 0;
+        }
+    }
     const bool live = c < n;
     const int tok = live ? tokens[(size_t)b * k_max + c] : -1;
     int par = live ? (parents ? parents[(size_t)b * k_max + c] : c - 1) : -2;
     if (live && (par < -1 || par >= c)) par = -1;
-    const int am = live ? row_argmax[row0 + c] : 0;
     int a = 0, want = next_tok[slot], mine = -1;
     if (mode == 1) {                       // append: keep the whole chain
         a = n;
@@ -261,11 +339,15 @@ __global__ __launch_bounds__(64) void accept_kernel(DevPlan p, int k_max, int mo
     }
 }
 
-void launch_accept(const sev_kv *kv, int B, int k_max, int mode, const int32_t *draft_tokens, const int32_t *parents,
+void launch_accept(const sev_kv *kv, const HeadOut &ho, int B, int k_max, int mode, const int32_t *draft_tokens, const int32_t *parents,
                    int32_t *accept_len, int32_t *bonus, int32_t *accept_path, int32_t *argmax_out, hipStream_t st) {
-    hipLaunchKernelGGL(accept_kernel, dim3(B), dim3(64), 0, st, kv->plan, k_max, mode, draft_tokens,
-                       parents, kv->row_argmax, kv->next_tok, kv->pend_n, kv->pend_a, kv->pend_bonus, kv->pend_path,
-                       accept_len, bonus, accept_path, argmax_out);
+#define SEV_ACCEPT(HEAD_, THREADS_)                                                                                                      \
+    hipLaunchKernelGGL((accept_kernel<HEAD_>), dim3(B), dim3(THREADS_), 0, st, kv->plan, ho, k_max, mode, draft_tokens, parents, kv->next_tok, \
+                       kv->pend_n, kv->pend_a, kv->pend_bonus, kv->pend_path, accept_len, bonus, accept_path, argmax_out)
+    if (ho.kind == HEAD_PARTS) SEV_ACCEPT(HEAD_PARTS, ACCEPT_WAVES * 64);
+    else if (ho.kind == HEAD_LOGITS) SEV_ACCEPT(HEAD_LOGITS, ACCEPT_WAVES * 64);
+    else SEV_ACCEPT(HEAD_ROWS, 64);
+#undef SEV_ACCEPT
 }
 
 // ---------------------------------------------------------------------------

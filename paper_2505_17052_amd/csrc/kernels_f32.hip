@@ -14,13 +14,6 @@ void launch_pack_f32(float *dst, const float *src, int64_t n, hipStream_t st) {
     if (n > 0) hipLaunchKernelGGL(copy_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, dst, src, n);
 }
 
-// h[m][:] = E[tok[m]][:]
-__global__ void embed_f32_kernel(const float *E, const int32_t *row_tok, float *h, int d) {
-    const float *src = E + (size_t)row_tok[blockIdx.x] * d;
-    float *dst = h + (size_t)blockIdx.x * d;
-    for (int i = threadIdx.x; i < d; i += blockDim.x) dst[i] = src[i];
-}
-
 // ---------------------------------------------------------------------------
 // Y[m][c] = sum_k X[m][k] * W[c][k], with the norm in front and the stage behind it fused in.
 //
@@ -423,13 +416,12 @@ static void attn_f32(const sev_model *m, sev_kv *kv, int rows, int layer, hipStr
 #undef SEV_ATTN_F32
 }
 
-void f32_forward(const sev_model *m, sev_kv *kv, int rows, int B, float *logits_out, hipStream_t st) {
+void f32_forward(const sev_model *m, sev_kv *kv, int rows, int B, float *logits_out, HeadOut *head, hipStream_t st) {
     (void)B;
     const sev_model_desc &d = m->d;
     const KvGeom geo = sev_kv_geom(kv);
     auto W = [&](size_t off) { return (const float *)(m->arena + off); };
     float *h = kv->h, *qkv = (float *)kv->q_buf, *ob = (float *)kv->o_buf, *act = (float *)kv->act;
-    hipLaunchKernelGGL(embed_f32_kernel, dim3(rows), dim3(256), 0, st, W(m->off_embed), kv->plan.row_tok, h, d.d_model);
     // X [rows][K] (normed in front where there are gains) times W, n_pairs column pairs, into rows of N
     auto gemm = [&](const float *X, const float *gain, const float *Wm, float *Y, int N, int n_pairs, int K) {
         GemmF32 g = {};
@@ -453,5 +445,11 @@ void f32_forward(const sev_model *m, sev_kv *kv, int rows, int B, float *logits_
     }
     float *lg = logits_out ? logits_out : kv->logits_f32;
     gemm_f32<F32_PLAIN>(gemm(h, W(m->off_gfinal), W(m->off_lm), lg, d.vocab, (d.vocab + 1) / 2, d.d_model), st);
+    // a request's block of the acceptance reads its rows by itself where they are short (a kernel less); longer ones want more blocks
+    if (head && d.vocab <= 4096) {
+        *head = {HEAD_LOGITS, nullptr, lg, nullptr, d.vocab, 0};
+        return;
+    }
     launch_argmax_rows_f32(lg, rows, d.vocab, kv->row_argmax, st);
+    if (head) *head = {HEAD_ROWS, kv->row_argmax, nullptr, nullptr, 0, 0};
 }

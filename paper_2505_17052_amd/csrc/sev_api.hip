@@ -267,7 +267,7 @@ extern "C" int sev_kv_create(const sev_model *m, int max_requests, int max_rows,
     const size_t o_pp = take((size_t)max_requests * SEV_MAX_DRAFT * 4);
     const size_t o_err = take(4);
     const size_t o_rq = take(4 * (size_t)(SEV_MAX_BATCH + 1) * 4);
-    const size_t o_row = take(4 * rows_pad * 4);
+    const size_t o_row = take(3 * rows_pad * 4);
     const size_t o_anc = take(rows_pad * 8);
     const size_t o_cs = take(rows_pad * (d.head_dim / 2) * 8);
     const size_t o_it = take((size_t)kv->max_items * (32 + SEV_ATT_MAX_CP * 4));
@@ -319,8 +319,7 @@ extern "C" int sev_kv_create(const sev_model *m, int max_requests, int max_rows,
     int32_t *rw = (int32_t *)(w + o_row);
     kv->plan.row_req = rw;
     kv->plan.row_node = rw + rows_pad;
-    kv->plan.row_tok = rw + 2 * rows_pad;
-    kv->plan.row_kvloc = rw + 3 * rows_pad;
+    kv->plan.row_kvloc = rw + 2 * rows_pad;
     kv->plan.row_anc = (unsigned long long *)(w + o_anc);
     kv->plan.row_cs = (float2 *)(w + o_cs);
     kv->plan.it_a = (int4 *)(w + o_it);
@@ -714,15 +713,16 @@ static int run_block(const sev_model *m, sev_kv *kv, const BlockCall &c, hipStre
         Prof p(kv, st, PROF_OTHER);
         launch_plan(kv, pa, c.tokens, c.parents, att, st);
     }
-    if (m->d.dtype == SEV_F32) f32_forward(m, kv, (int)rows, c.B, c.logits, st);
-    else bf16_forward(m, kv, (int)rows, c.B, att, c.logits, nullptr, st);
+    HeadOut head;
+    if (m->d.dtype == SEV_F32) f32_forward(m, kv, (int)rows, c.B, c.logits, &head, st);
+    else bf16_forward(m, kv, (int)rows, c.B, att, c.logits, nullptr, &head, st);
     {
         Prof p(kv, st, PROF_OTHER);
         if (c.draft_probs)
             launch_sample(kv, c.B, c.k_max, (int)rows, c.tokens, c.parents, c.logits, c.draft_probs, kv->row_stats, c.temperature,
                           c.u_accept, c.u_emit, c.accept_len, c.bonus_token, c.accept_path, st);
         else
-            launch_accept(kv, c.B, c.k_max, c.mode & 1, c.tokens, c.parents, c.accept_len, c.bonus_token, c.accept_path, c.row_argmax, st);
+            launch_accept(kv, head, c.B, c.k_max, c.mode & 1, c.tokens, c.parents, c.accept_len, c.bonus_token, c.accept_path, c.row_argmax, st);
     }
     SEV_HIP(hipGetLastError());
     if (!c.parents) sev_note_block(kv, pa.slot, pa.B, false, st);
@@ -893,8 +893,8 @@ extern "C" int sev_prefill(const sev_model *m, sev_kv *kv, const int32_t *slots,
             Prof p(kv, st, PROF_OTHER);
             launch_plan(kv, pa, tokens, nullptr, att, st);
         }
-        if (bf) bf16_forward(m, kv, rows, pa.B, att, nullptr, &tail, st);
-        else f32_forward(m, kv, rows, pa.B, nullptr, st);
+        if (bf) bf16_forward(m, kv, rows, pa.B, att, nullptr, &tail, nullptr, st);
+        else f32_forward(m, kv, rows, pa.B, nullptr, nullptr, st);
         {
             Prof p(kv, st, PROF_OTHER);
             launch_prefill_state(kv, pa, row, st);

@@ -70,7 +70,7 @@ struct DevPlan {
     // per request
     int32_t *req_slot, *req_P, *req_n, *req_row0;
     // per row (draft node)
-    int32_t *row_req, *row_node, *row_tok;
+    int32_t *row_req, *row_node;
     int32_t *row_kvloc;       // physical page * 16 + token in page of the cache position P + node the row is written to
     unsigned long long *row_anc;
     float2 *row_cs;           // [rows][hd/2] (cos, sin) of pos * theta_i
@@ -181,6 +181,16 @@ struct AttList {
     int quad;                // row groups of 32 query rows per work item: 1, or 4 (a block of four waves that share K/V in LDS)
 };
 
+// What the output head leaves for the acceptance: the arg-max of every row, or what it is taken from.
+enum HeadKind { HEAD_ROWS, HEAD_PARTS, HEAD_LOGITS };
+struct HeadOut {
+    HeadKind kind;
+    const int32_t *rows;      // HEAD_ROWS: [rows]
+    const float *val;         // HEAD_PARTS: [n_part][stride] largest values and their columns; HEAD_LOGITS: [rows][n_part] logits
+    const int32_t *idx;
+    int n_part, stride;
+};
+
 bool sev_capturing(hipStream_t st);
 
 // common
@@ -189,7 +199,7 @@ void launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st);
 void launch_plan(const sev_kv *kv, const PlanArgs &pa, const int32_t *draft_tokens, const int32_t *parents,
                  const AttList &att, hipStream_t st);
 void launch_theta(const sev_kv *kv, hipStream_t st);
-void launch_accept(const sev_kv *kv, int B, int k_max, int mode, const int32_t *draft_tokens, const int32_t *parents,
+void launch_accept(const sev_kv *kv, const HeadOut &ho, int B, int k_max, int mode, const int32_t *draft_tokens, const int32_t *parents,
                    int32_t *accept_len, int32_t *bonus, int32_t *accept_path, int32_t *argmax_out, hipStream_t st);
 void launch_sample(const sev_kv *kv, int B, int k_max, int rows, const int32_t *tokens, const int32_t *parents, const float *logits,
                    const float *draft_probs, float2 *stats, float temperature, const float *u_acc, const float *u_emit,
@@ -201,7 +211,8 @@ void launch_argmax_rows_f32(const float *logits, int rows, int vocab, int32_t *o
 
 // f32 path
 void launch_pack_f32(float *dst, const float *src, int64_t n, hipStream_t st);
-void f32_forward(const sev_model *m, sev_kv *kv, int rows, int B, float *logits_out, hipStream_t st);
+// both: head = nullptr takes the arg-max of every row into kv->row_argmax (prefill); else it says where to find it
+void f32_forward(const sev_model *m, sev_kv *kv, int rows, int B, float *logits_out, HeadOut *head, hipStream_t st);
 
 // bf16 path
 void launch_pack_bf16(uint16_t *dst, const uint16_t *src, int n_rows, int K, int mode, int tile_add, hipStream_t st);
@@ -214,4 +225,5 @@ struct TailRows {
     int32_t src[SEV_MAX_BATCH];      // their rows in the chunk
     const int32_t *tokens;
 };
-void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList &att, float *logits_out, const TailRows *tail, hipStream_t st);
+void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList &att, float *logits_out, const TailRows *tail, HeadOut *head,
+                  hipStream_t st);
