@@ -123,8 +123,9 @@ void launch_pack_bf16(uint16_t *dst, const uint16_t *src, int n_rows, int K, int
 //   EPI_SWIGLU act = split(silu(gate) * up), gate and up rows interleaved in the weight tiles
 //   EPI_ARGMAX per-wave arg-max of every row (+ optional float32 logits); never split
 // ---------------------------------------------------------------------------
-// A pipeline stage is KS steps of 32 k.
-__host__ __device__ constexpr int gemm_ks(int MR) { return MR % 2 ? 2 : 1; }      // (an odd number of units does not fill whole loads of 256 threads)
+// A pipeline stage is KS steps of 32 k.  An odd number of units does not fill whole loads of 256 threads: narrow blocks take two k-steps
+// per stage; in wide ones, whose registers that would not fit, half of the threads have no part in the stage's last load.
+__host__ __device__ constexpr int gemm_ks(int MR, int NT) { return MR % 2 && NT <= 2 ? 2 : 1; }
 
 enum { EPI_QKV = 0, EPI_SWIGLU = 1, EPI_ARGMAX = 2, EPI_RESID = 3 };
 
@@ -329,16 +330,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     g.W = W_; g.X = X_; g.n_tiles = n_tiles_; g.k_steps = k_steps_; g.units_total = units_total_;
     g.col_groups = col_groups_; g.m_blocks = m_blocks_; g.splits = splits_ & 0xffff;
     const int tpb = splits_ >> 16;                      // column tiles per block: 4 * NT, or fewer (the last wave then has fewer tiles)
-    constexpr int KS = gemm_ks(MR);
+    constexpr int KS = gemm_ks(MR, NT);
     constexpr int NF = 2 * NT;                          // weight fragments per wave and k-step: two per column tile
-    constexpr int XI = KS * MR / 2;                     // 16-byte activation loads per thread and stage
-    static_assert(KS * MR % 2 == 0, "a stage of activations must be a whole number of 4 KiB");
+    constexpr int XI = (KS * MR + 1) / 2;               // 16-byte activation loads per thread and stage
+    constexpr bool XHALF = KS * MR % 2 != 0;            // the last of them by the first 128 threads alone
     constexpr int G = KS * MR;                          // groups of products per stage: one activation unit x all weight fragments
     constexpr int AHEAD = G < PF ? G : PF - 1;          // an activation unit is read from LDS that many groups before its products
     static_assert(PF >= 3, "X(st+2) is written while X(st) and X(st+1) are read");
-    extern __shared__ u32x4 xs[];                       // [PF buffers][KS k-steps][MR][2 planes][64 lanes]
+    extern __shared__ u32x4 xs[];                       // [PF buffers][KS k-steps][MR][2 planes][64 lanes], a stage filled up to whole loads
     __shared__ float red[4][MR * 16 < 128 ? 128 : MR * 16];
-    constexpr int STAGE_U4 = KS * MR * 2 * 64;          // uint4 per stage
+    constexpr int STAGE_U4 = XI * 256;                  // uint4 per stage
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // Block index decode, XCD-aware: consecutive block ids go round-robin to the 8 XCDs, each with its
     // own L2.  Blocks that share weight tiles (the row blocks of one column group) get ids 8 apart,
@@ -422,8 +423,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     for (int i = 0; i < XI; ++i) {
         const int u = threadIdx.x + 256 * i;
         const int ksl = u / (MR * 128), within = u - ksl * (MR * 128);
-        xoff[i] = (unsigned)((ksl * g.units_total + u0) * 128 + within) * 16u;
+        xoff[i] = XHALF && ksl == KS ? 0x80000000u : (unsigned)((ksl * g.units_total + u0) * 128 + within) * 16u;
     }
+    // (XHALF: the activations through a buffer descriptor too; a thread without a part reads past its end, i.e. zeros and no memory)
+    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void *)g.X, 0, g.k_steps * g.units_total * 2048, 0x00020000);
     const size_t x_stage = (size_t)KS * g.units_total * 2048;       // bytes per stage of all row units
     const int n_pad = (n + PF - 1) / PF * PF;
     // Where the activations are small enough to stay in an L2 (4 MiB) beside the weight stream, every column group walks its K range
@@ -436,18 +439,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     const int rot = resident ? (int)((unsigned)cg * (unsigned)n / (unsigned)g.col_groups) : 0;
     // where the two streams stand: the next stage to be requested, counted within the slice, and its address
     const char *const x_first = (const char *)g.X + (size_t)s_begin * x_stage, *x_at = x_first + (size_t)rot * x_stage;
+    const unsigned xb_first = (unsigned)s_begin * (unsigned)x_stage;
+    unsigned xb_at = xb_first + (unsigned)rot * (unsigned)x_stage;
     const unsigned w_first = (unsigned)s_begin * (KS * 2048u);
     unsigned w_at = w_first + (unsigned)rot * (KS * 2048u);
     int x_i = rot, w_i = rot;
     auto x_next = [&]() {
-        x_at += x_stage;
-        if (++x_i == n) { x_i = 0; x_at = x_first; }
+        if constexpr (XHALF) xb_at += (unsigned)x_stage;
+        else x_at += x_stage;
+        if (++x_i == n) { x_i = 0; x_at = x_first; xb_at = xb_first; }
     };
     auto w_next = [&]() {
         w_at += KS * 2048u;
         if (++w_i == n) { w_i = 0; w_at = w_first; }
     };
-    auto load_x = [&](int i) { return *(const u32x4 *)(x_at + xoff[i]); };
+    auto load_x = [&](int i) -> u32x4 {
+        if constexpr (XHALF) return __builtin_amdgcn_raw_buffer_load_b128(xrs, xoff[i], xb_at, 0);
+        else return *(const u32x4 *)(x_at + xoff[i]);
+    };
 
     {
         u32x4 x0[XI], x1[XI];
@@ -1303,6 +1312,9 @@ enum { G_QKV = 0, G_O, G_GU, G_DOWN, G_LM };
 // shapes, where its choice is 1.3 % off the best shape on average, more than 5 % in 9 % of them and 19 % at most.  (The rules by
 // cases before it, for row tiles of 32, were 15 % off in the same pairs: 80 rows of the 8B shape, gate/up 64.5 -> 48.2 us, down 38.1 -> 31.5;
 // 64 rows of the 70B shape, down 112 -> 83; 128 rows, gate/up 251 -> 200.)
+// Blocks of 12 and 16 column tiles over 80 to 160 rows give it the row counts whose blocks of 8 tiles need a second, half-empty round
+// (4800 timings more, of 38 row counts of two shapes: 1.4 % off the best for gate/up, 3 % for the others): 323 rows of the 8B shape, gate/up in 112 x 384
+// blocks 133.7 -> 116.9 us (225 blocks, one round; 96 x 256 were 448), 304 rows 129 -> 122, 192 rows of the 70B shape 304 -> 263.
 // The handle's tuning overrides (struct Tune: read from the environment when the handle was created) replace the choice in experiments.
 static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t part_elems, const Tune &tune) {
     static const int row_units[] = {1, 2, 3, 4, 5, 6, 7, 8, 10};
@@ -1310,31 +1322,42 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
     const size_t slice = (size_t)n_tiles * units_total * 512;            // floats of one slice in the exchange buffer
     GemmCfg best = {0, 0, 1, false, 0};
     double best_us = 0;
-    auto slices_fit = [&](int MR, int S) { return S == 1 || (k_steps / gemm_ks(MR) / S >= 4 && (size_t)S * slice <= part_elems); };
+    auto slices_fit = [&](int MR, int NT, int S) { return S == 1 || (k_steps / gemm_ks(MR, NT) / S >= 4 && (size_t)S * slice <= part_elems); };
     auto consider = [&](GemmCfg c, int s_min, int s_max) {
         const int mb = (units + c.MR - 1) / c.MR, cg = (n_tiles + c.cols() - 1) / c.cols();
         const double nt = c.half ? c.NT - 0.5 : c.NT, weights = n_tiles * (double)k_steps * 2048e-6, acts = (double)cg * mb * c.MR * k_steps * 2048e-6;      // MB
         c.T = c.cols();
-        for (c.S = s_min; c.S <= s_max && slices_fit(c.MR, c.S); ++c.S) {
+        for (c.S = s_min; c.S <= s_max && slices_fit(c.MR, c.NT, c.S); ++c.S) {
             const int blocks = cg * mb * c.S, rounds = ((cg + 7) / 8 * mb * c.S + 31) / 32;      // column group c runs on XCD c % 8 (32 units)
             const double steps = (double)rounds * k_steps / c.S;
             const double idle = cbrt(256.0 * ((blocks + 255) / 256) / blocks);
             const double products = (c.NT > 2 ? 0.0246 : 0.028) * steps * c.MR * nt, bytes = (weights / 12.4 + (acts + (mb - 1) * weights) / 20.4) * idle * idle;
-            double us = sqrt(products * products + bytes * bytes) + 0.0085 * steps / gemm_ks(c.MR);
+            double us = sqrt(products * products + bytes * bytes) + 0.0085 * steps / gemm_ks(c.MR, c.NT);
             if (c.S == 1) us += (which == G_QKV ? 1.45 : 1.0) * rounds * c.MR * nt;
             else us += 1.8 + 0.63 * c.S * units * n_tiles * 2048e-6 + 4.7 * rounds * c.MR * std::min(c.T, n_tiles) * 2.048e-3;
             if (!best.MR || us < best_us) { best = c; best_us = us; }
         }
     };
+    const bool xbuf = (int64_t)k_steps * units_total < 1 << 20;            // an odd number of units in wide blocks: operand within 2 GiB (a buffer descriptor)
     if (which == G_LM) {
-        // never split: 64 x 256 blocks for up to 64 rows; above, 128 x 512 blocks (their units are 14 % cheaper) or, where those pad the
-        // rows by more, the fewest row blocks of 256 columns (8B shape: 160 rows 405 -> 283 us, 304 rows 586 -> 530, 96 rows 222 -> 192)
-        int MR = units <= 4 ? (units + 1) / 2 * 2 : 0;
-        const int mb = (units + 9) / 10;
-        for (int m : {5, 6, 7, 10})
-            if (!MR && (units + m - 1) / m == mb) MR = m;
-        const bool wide = units > 4 && (!MR || 1.16 * mb * MR > (units + 7) / 8 * 8 || mb * MR > units_total);
-        best = wide ? GemmCfg{8, 4, 1, false, 0} : GemmCfg{MR, 2, 1, false, 0};
+        // Never split.  Above 64 rows the wide blocks: the shape with the fewest products (rounds of the fullest XCD times a block's units and
+        // tiles), on a tie the one with fewer row blocks.  8B shape with its logits, us: 80 rows in 80 x 512 blocks 174, in 80 x 256 192; 192 rows in 96 x 512
+        // 293, in 96 x 256 358; 304 rows in 80 x 512 464, in 128 x 512 521; 400 rows in 80 x 512 572, in 128 x 512 708; 480 rows in 160 x 384
+        // 651, in 128 x 512 729.  64 x 256 blocks take up to four times as long per product, but fill the chip where a vocabulary is small.
+        double least = 0;
+        auto lm = [&](int MR, int NT, double factor) {
+            const int mb = (units + MR - 1) / MR, cg = (n_tiles + 4 * NT - 1) / (4 * NT), rounds = ((cg + 7) / 8 * mb + 31) / 32;
+            const double products = factor * rounds * MR * NT;
+            if (mb * MR > units_total || (MR % 2 && !xbuf) || (best.MR && products >= least)) return;
+            best = GemmCfg{MR, NT, 1, false, 0};
+            least = products;
+        };
+        if (units <= 4) lm((units + 1) / 2 * 2, 2, 1.0);
+        else {
+            for (int MR : {8, 7, 6, 5}) lm(MR, 4, 1.0);
+            lm(10, 3, 1.0);
+            lm(4, 2, 1.5);
+        }
         best.T = best.cols();
         return best;
     }
@@ -1348,8 +1371,9 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
                 // which instances there are (launch_gemm)
                 if (NT == 1 && half) continue;
                 if (NT == 2 && half && (which != G_QKV || MR != 4)) continue;
-                if (NT == 3 && (which != G_QKV || MR != 8 || half)) continue;
-                if (NT == 4 && (MR != 8 || (half && which != G_GU))) continue;
+                if (NT >= 3 && (MR < 5 || (NT == 4 && MR == 10))) continue;
+                if (NT >= 3 && MR % 2 && !xbuf) continue;
+                if (NT >= 3 && half && (NT == 3 || MR != 8 || which != G_GU)) continue;
                 const GemmCfg c = {MR, NT, 1, half, 0};
                 const int cg = (n_tiles + c.cols() - 1) / c.cols();
                 consider(c, 1, std::min(16, std::max(1, 256 / (cg * mb))));
@@ -1361,8 +1385,8 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
         const int MR = mt < 0 ? -mt : 2 * mt;
         const bool known = std::find(std::begin(row_units), std::end(row_units), MR) != std::end(row_units);
         if (known && (half ? ((which == G_QKV && MR == 4 && nt == 15) || (which == G_GU && MR == 8 && nt == 35)) :
-                             (nt == 1 || nt == 2 || ((nt == 4 || (nt == 3 && which == G_QKV)) && MR == 8))) &&
-            sp >= 0 && sp <= 32 && pf == 4 && (units + MR - 1) / MR * MR <= units_total && sp <= std::max(1, k_steps / gemm_ks(MR)) &&
+                             (nt == 1 || nt == 2 || ((nt == 3 || nt == 4) && MR >= 5 && !(nt == 4 && MR == 10) && (MR % 2 == 0 || xbuf)))) &&
+            sp >= 0 && sp <= 32 && pf == 4 && (units + MR - 1) / MR * MR <= units_total && sp <= std::max(1, k_steps / gemm_ks(MR, nt)) &&
             (sp <= 1 || (size_t)sp * slice <= part_elems)) {
             best.MR = 0;
             const GemmCfg c = {MR, half ? nt / 10 + 1 : nt, 1, half, 0};
@@ -1415,26 +1439,34 @@ static void launch_gemm(GemmArgs ga, const GemmCfg &c, hipStream_t st) {
     const int g8 = (ga.col_groups + 7) / 8 * 8;
     dim3 grid((unsigned)(g8 * ga.m_blocks * ga.splits));
 #define SEV_LAUNCH(MR_, NT_, PF_, ...)                                                                                \
-    hipLaunchKernelGGL((gemm_bf16_kernel<MR_, NT_, EPI, PF_ __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), (PF_) * gemm_ks(MR_) * (MR_) * 2048, st, ga.W, ga.X, ga.n_tiles, ga.k_steps,         \
+    hipLaunchKernelGGL((gemm_bf16_kernel<MR_, NT_, EPI, PF_ __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), (PF_) * ((gemm_ks(MR_, NT_) * (MR_) + 1) / 2) * 4096, st, ga.W, ga.X, ga.n_tiles, ga.k_steps,         \
                        ga.units_total, ga.col_groups, ga.m_blocks, ga.splits | (c.T << 16), ga)
 #define SEV_BY_NT(MR_, PF_)                                                                                           \
     do {                                                                                                              \
         if (c.NT == 2) SEV_LAUNCH(MR_, 2, PF_); else SEV_LAUNCH(MR_, 1, (MR_ % 2 ? 3 : 4));                               \
     } while (0)
     if constexpr (EPI == EPI_ARGMAX) {
-        if (c.NT == 4) SEV_LAUNCH(8, 4, 3);
-        else if (c.MR == 10) SEV_LAUNCH(10, 2, 3);
-        else if (c.MR == 7) SEV_LAUNCH(7, 2, 3);
-        else if (c.MR == 6) SEV_LAUNCH(6, 2, 3);
-        else if (c.MR == 5) SEV_LAUNCH(5, 2, 3);
+        if (c.MR == 10) SEV_LAUNCH(10, 3, 3);
+        else if (c.MR == 8) SEV_LAUNCH(8, 4, 3);
+        else if (c.MR == 7) SEV_LAUNCH(7, 4, 3);
+        else if (c.MR == 6) SEV_LAUNCH(6, 4, 3);
+        else if (c.MR == 5) SEV_LAUNCH(5, 4, 3);
         else if (c.MR == 4) SEV_LAUNCH(4, 2, 4);
         else SEV_LAUNCH(2, 2, 4);
     } else if (c.half) {
         if constexpr (EPI == EPI_SWIGLU) SEV_LAUNCH(8, 4, 3, true);
         if constexpr (EPI == EPI_QKV) SEV_LAUNCH(4, 2, 4, true);
-    } else if (c.NT == 4) SEV_LAUNCH(8, 4, 3);
-    else if (c.NT == 3) {
-        if constexpr (EPI == EPI_QKV) SEV_LAUNCH(8, 3, 3);
+    } else if (c.NT == 4) {
+        if (c.MR == 8) SEV_LAUNCH(8, 4, 3);
+        else if (c.MR == 7) SEV_LAUNCH(7, 4, 3);
+        else if (c.MR == 6) SEV_LAUNCH(6, 4, 3);
+        else SEV_LAUNCH(5, 4, 3);
+    } else if (c.NT == 3) {
+        if (c.MR == 10) SEV_LAUNCH(10, 3, 3);
+        else if (c.MR == 8) SEV_LAUNCH(8, 3, 3);
+        else if (c.MR == 7) SEV_LAUNCH(7, 3, 3);
+        else if (c.MR == 6) SEV_LAUNCH(6, 3, 3);
+        else SEV_LAUNCH(5, 3, 3);
     }
     else if (c.MR == 10) SEV_BY_NT(10, 3);
     else if (c.MR == 8) SEV_BY_NT(8, 3);

@@ -50,10 +50,11 @@ def test_forced_shapes(setup, monkeypatch, qkv, gate_up):
     assert diff.max() < 4e-3 and diff.mean() < 4e-4
 
 
-@pytest.mark.parametrize("requests,shape", [(15, "-1,1,1,4"), (15, "-3,1,2,4"), (15, "-3,2,1,4"), (15, "-5,1,1,4"), (15, "-5,2,3,4"), (7, "-7,1,2,4"), (7, "-7,2,1,4"), (3, "-3,1,1,4"), (1, "-1,2,3,4")])
+@pytest.mark.parametrize("requests,shape", [(15, "-1,1,1,4"), (15, "-3,1,2,4"), (15, "-3,2,1,4"), (15, "-5,1,1,4"), (15, "-5,2,3,4"), (7, "-7,1,2,4"), (7, "-7,2,1,4"), (3, "-3,1,1,4"), (1, "-1,2,3,4"),
+                                            (15, "-5,3,1,4"), (15, "-5,4,2,4"), (5, "-5,4,1,4"), (6, "-6,3,2,4"), (6, "-6,4,1,4"), (7, "-7,3,1,4"), (7, "-7,4,3,4"), (10, "-10,3,2,4")])
 def test_blocks_of_an_odd_number_of_row_units(setup, monkeypatch, requests, shape):
-    """Blocks of 16, 48, 80 and 112 rows (two k-steps of activations per stage), whole and split K, on all four projections: 225,
-    105, 45 and 15 rows, the last unit of each with a row missing or 15.  Same bounds as above."""
+    """Blocks of 16, 48, 80 and 112 rows, narrow (two k-steps of activations per stage) and wide (one, its last load by half of the threads),
+    and wide ones of 96 and 160, whole and split K, on all four projections: 225, 150, 105, 90, 75, 45 and 15 rows.  Same bounds as above."""
     sev, harness, model, lens, prompts, tok, caches, want = setup
     for name in ("SEV_TUNE_QKV", "SEV_TUNE_O", "SEV_TUNE_GU", "SEV_TUNE_DOWN"):
         monkeypatch.setenv(name, shape)
@@ -65,3 +66,30 @@ def test_blocks_of_an_odd_number_of_row_units(setup, monkeypatch, requests, shap
     diff = np.abs(out["logits"].cpu().numpy() - want[:15 * requests])
     announce(f"  logits max {diff.max():.2e} mean {diff.mean():.2e}")
     assert diff.max() < 4e-3 and diff.mean() < 4e-4
+
+
+LM_SHAPE = synth.workload.ModelShape("lm-shapes", 1, 256, 2, 1, 128, 512, 128256, 500000.0, "bf16")
+
+
+@pytest.mark.parametrize("requests", [5, 6, 7, 8, 9, 31])
+def test_head_blocks(requests):
+    """The output head over a vocabulary that fills the chip several times, in blocks of 80 to 160 rows (75, 90, 105, 120, 135 and 465 rows of 4008
+    column tiles, which neither 16 nor 12 divide evenly among the blocks): logits, and the arg-max of every row of them.  Same bounds as above."""
+    import paper_2505_17052_amd as sev
+    from paper_2505_17052_amd import harness
+    om = oracle_model(LM_SHAPE, SEED, dtype=np.float32, gains=True)
+    rng = np.random.default_rng(requests)
+    prompts = [rng.integers(0, LM_SHAPE.vocab, 3) for _ in range(requests)]
+    tok = rng.integers(0, LM_SHAPE.vocab, (requests, 15)).astype(np.int32)
+    caches = [vo.prefill(om, p, len(p) + 15) for p in prompts]
+    want = np.concatenate(vo.forward_blocks(om, caches, list(tok), [vo.chain_parents(15)] * requests)[0])
+    announce(f"LM head, {15 * requests} rows")
+    batch = harness.Batch(harness.build_model(LM_SHAPE, SEED, gains=True), LM_SHAPE, [18] * requests, max_rows=15 * requests, seed=SEED)
+    batch.prefill(prompts)
+    out = sev.verify_ex(batch.model, batch.kv, [3] * requests, torch.tensor(tok, device="cuda"), 15, want_argmax=True, want_logits=True)
+    torch.cuda.synchronize()
+    got = out["logits"].cpu().numpy()
+    diff = np.abs(got - want)
+    announce(f"  logits max {diff.max():.2e} mean {diff.mean():.2e}")
+    assert diff.max() < 4e-3 and diff.mean() < 4e-4
+    assert np.array_equal(out["row_argmax"].cpu().numpy(), got.argmax(axis=1))
