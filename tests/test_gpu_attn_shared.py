@@ -101,3 +101,26 @@ def test_long_prompt_equals_small_chunks(setup):
     b.prefill([prompt])
     for got, ref in zip(a.export_kv(0, 1, 0, 2600), b.export_kv(0, 1, 0, 2600)):
         assert np.all(np.abs(got - ref) <= 2.0 ** -7 * np.abs(ref) + 2e-3)
+
+
+@pytest.mark.parametrize("cp,lens,ns", [(8, [500, 60, 1], (5, 3, 8)), (8, [635, 636], (5, 4)), (4, [505, 500, 3], (7, 8, 1)), (4, [570], (24,)), (2, [700, 250, 33], (9, 17, 8))])
+def test_merge_of_many_chunks(setup, monkeypatch, cp, lens, ns):
+    """1, 4 and 5, 8 and 9, 36, and 45, 17 and 3 chunks of cp pages per request, groups of query rows that end inside and at the end of a
+    merge block's 8 rows (4 query heads x 1 to 24 nodes)."""
+    sev, harness, model, om = setup
+    monkeypatch.setenv("SEV_TUNE_CP", str(cp))
+    monkeypatch.setenv("SEV_TUNE_QUAD", "0")
+    rng = np.random.default_rng(sum(lens) + cp)
+    B, k = len(ns), max(ns)
+    announce(f"merge: chunks of {cp} pages, prefixes {lens}, nodes {ns}")
+    prompts = [rng.integers(0, SHAPE.vocab, p) for p in lens]
+    batch = harness.Batch(model, SHAPE, [p + k for p in lens], max_rows=128, seed=SEED)
+    batch.prefill(prompts)
+    caches = [vo.prefill(om, p, len(p) + k) for p in prompts]
+    tok = rng.integers(0, SHAPE.vocab, (B, k)).astype(np.int32)
+    out = sev.verify_ex(model, batch.kv, lens, torch.tensor(tok, device="cuda"), k, draft_lens=list(ns), want_logits=True)
+    torch.cuda.synchronize()
+    want = np.concatenate(vo.forward_blocks(om, caches, [tok[b, :n] for b, n in enumerate(ns)], [vo.chain_parents(n) for n in ns])[0])
+    diff = np.abs(out["logits"].cpu().numpy() - want)
+    announce(f"  logits max {diff.max():.2e} mean {diff.mean():.2e}")
+    assert diff.max() < 2.8e-3 and diff.mean() < 4e-4
