@@ -635,6 +635,118 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
     }
 }
 
+// The same GEMM for small matrices: a block takes one column tile x MR row units, its four waves a quarter of K each, and their sums meet in LDS, so that
+// a short contraction is spread over the chip without a fix-up kernel.  Operands go straight from memory to the products (both are stored in
+// fragment order), four k-steps at a time with the next four under way; no barrier before the sums.  It reads the activations again for
+// every column tile, which is what bounds its range (see choose_cfg).  (Eight waves per block are slower everywhere: 512-wide model, down 7.2 -> 7.6 us.)
+// Event-timed (about 5 us of each), 25 rows of a model 512 wide, us: QKV 7.1 -> 6.6, O with its fix-up 9.6 -> 6.4, gate/up 7.6 -> 6.5, down with its fix-up
+// 9.5 -> 7.2, head over 4224 ids 12.0 -> 6.8; of one 1024 wide: QKV 10.7 -> 6.6, O 9.9 -> 6.4, gate/up 11.6 -> 7.5, down 11.3 -> 9.9.
+template <int MR, int EPI>
+__global__ __launch_bounds__(256) void gemm_narrow_kernel(const uint4 *W_, const uint4 *X_, int n_tiles_, int k_steps_, int units_total_,
+                                                                int m_blocks_, GemmArgs g) {
+    g.W = W_; g.X = X_; g.n_tiles = n_tiles_; g.k_steps = k_steps_; g.units_total = units_total_;
+    constexpr int STEPS = 4;
+    __shared__ f32x4 sums[4][2 * MR][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int q = blockIdx.x >> 3, mb = q % m_blocks_, T = q / m_blocks_ * 8 + (blockIdx.x & 7);      // the row blocks of a tile on one XCD
+    if (T >= g.n_tiles) return;                          // whole block leaves before any barrier
+    const int u0 = mb * MR, mrow = lane & 15, nsub = 4 * (lane >> 4);
+    const int k0 = g.k_steps * wave / 4, k1 = g.k_steps * (wave + 1) / 4;      // (a wave without a step loads the first and adds nothing)
+    const u32x4 *const wp = (const u32x4 *)g.W + (size_t)T * g.k_steps * 128 + lane;
+    const u32x4 *const xp = (const u32x4 *)g.X + (size_t)u0 * 128 + lane;
+    const size_t x_step = (size_t)g.units_total * 128;
+    u32x4 w[2][STEPS][2], x[2][STEPS][MR][2];
+    auto load = [&](int buf, int k) {
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) {
+            const int at = max(min(k + i, k1 - 1), 0);   // past the wave's share: the last step again
+            w[buf][i][0] = wp[(size_t)at * 128];
+            w[buf][i][1] = wp[(size_t)at * 128 + 64];
+#pragma unroll
+            for (int b = 0; b < MR; ++b) {
+                x[buf][i][b][0] = xp[at * x_step + b * 128];
+                x[buf][i][b][1] = xp[at * x_step + b * 128 + 64];
+            }
+        }
+    };
+    load(0, k0);
+    // the epilogue's own loads: wave b finishes row unit b
+    const int m = (u0 + wave) * 16 + mrow;
+    TilePre pre;
+    if (wave < MR) pre = tile_pre<EPI>(g, T, m, nsub);
+    f32x4 acc[2][MR];
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int b = 0; b < MR; ++b) acc[f][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto products = [&](int buf, int k) {
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) {
+            if (k + i >= k1) break;                      // (uniform)
+#pragma unroll
+            for (int b = 0; b < MR; ++b)
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {
+                    acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(w[buf][i][f]), as_bf16x8(x[buf][i][b][0]), acc[f][b], 0, 0, 0);
+                    acc[f][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(w[buf][i][f]), as_bf16x8(x[buf][i][b][1]), acc[f][b], 0, 0, 0);
+                }
+        }
+    };
+    for (int k = k0; k < k1; k += 2 * STEPS) {
+        load(1, k + STEPS);
+        products(0, k);
+        load(0, k + 2 * STEPS);
+        products(1, k + STEPS);
+    }
+#pragma unroll
+    for (int b = 0; b < MR; ++b)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) sums[wave][2 * b + f][lane] = acc[f][b];
+    __syncthreads();
+    if (wave >= MR) return;
+    f32x4 a0 = sums[0][2 * wave][lane], a1 = sums[0][2 * wave + 1][lane];
+#pragma unroll
+    for (int v = 1; v < 4; ++v) {
+        a0 += sums[v][2 * wave][lane];
+        a1 += sums[v][2 * wave + 1][lane];
+    }
+    if constexpr (EPI == EPI_ARGMAX) {
+        const int nn = T * 32 + nsub;
+        float bv = -INFINITY;
+        int bi = 0x7fffffff;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const float v = r < 4 ? a0[r] : a1[r - 4];
+            if (v > bv) { bv = v; bi = nn + (r < 4 ? r : 12 + r); }      // indices ascend, so ">" keeps the lowest
+        }
+        if (g.logits && m < g.M) {
+            float *to = g.logits + (size_t)m * g.N + nn;
+            *(float4 *)to = make_float4(a0[0] * pre.rs, a0[1] * pre.rs, a0[2] * pre.rs, a0[3] * pre.rs);
+            *(float4 *)(to + 16) = make_float4(a1[0] * pre.rs, a1[1] * pre.rs, a1[2] * pre.rs, a1[3] * pre.rs);
+        }
+#pragma unroll
+        for (int o = 16; o < 64; o *= 2) {
+            const float ov = __shfl_xor(bv, o);
+            const int oi = __shfl_xor(bi, o);
+            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+        }
+        if (lane < 16 && m < g.M) {
+            g.lm_val[(size_t)T * g.lm_stride + m] = bv;
+            g.lm_idx[(size_t)T * g.lm_stride + m] = bi;
+        }
+    } else {
+        float ss = tile_epilogue<EPI>(g, a0, a1, T, m, nsub, pre);
+        if constexpr (EPI == EPI_RESID) {
+            ss += __shfl_xor(ss, 16);
+            ss += __shfl_xor(ss, 32);
+            if (lane < 16 && m < g.M) {
+                atomicAdd(g.ssq_out + m, ssq_fix(ss));
+                if (T == 0) g.ssq_clear[m] = 0ull;
+            }
+        }
+    }
+}
+
 // Split-K fix-up: block (group of 4 column tiles, row unit) of 4 waves; wave w sums the S slices of 32 columns x 16 rows
 // (column tile 4 * group + w, row unit ru) in slice order and runs the epilogue.
 template <int EPI>
@@ -1323,7 +1435,7 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
     GemmCfg best = {0, 0, 1, false, 0};
     double best_us = 0;
     auto slices_fit = [&](int MR, int NT, int S) { return S == 1 || (k_steps / gemm_ks(MR, NT) / S >= 4 && (size_t)S * slice <= part_elems); };
-    auto consider = [&](GemmCfg c, int s_min, int s_max) {
+    auto consider = [&](GemmCfg c, int s_min, int s_max, double epilogue) {
         const int mb = (units + c.MR - 1) / c.MR, cg = (n_tiles + c.cols() - 1) / c.cols();
         const double nt = c.half ? c.NT - 0.5 : c.NT, weights = n_tiles * (double)k_steps * 2048e-6, acts = (double)cg * mb * c.MR * k_steps * 2048e-6;      // MB
         c.T = c.cols();
@@ -1333,9 +1445,22 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
             const double idle = cbrt(256.0 * ((blocks + 255) / 256) / blocks);
             const double products = (c.NT > 2 ? 0.0246 : 0.028) * steps * c.MR * nt, bytes = (weights / 12.4 + (acts + (mb - 1) * weights) / 20.4) * idle * idle;
             double us = sqrt(products * products + bytes * bytes) + 0.0085 * steps / gemm_ks(c.MR, c.NT);
-            if (c.S == 1) us += (which == G_QKV ? 1.45 : 1.0) * rounds * c.MR * nt;
+            if (c.S == 1) us += epilogue * rounds * c.MR * nt;
             else us += 1.8 + 0.63 * c.S * units * n_tiles * 2048e-6 + 4.7 * rounds * c.MR * std::min(c.T, n_tiles) * 2.048e-3;
             if (!best.MR || us < best_us) { best = c; best_us = us; }
+        }
+    };
+    // Blocks of one column tile whose waves share K (gemm_narrow_kernel): their estimate is the bytes into the fullest unit, weights and activations alike, at 52 KB/us,
+    // less what the caches make of it and 1.4 us at least, and 0.4 us per round of blocks.  A split's fix-up kernel costs 1.5 us more than the other estimate says where everything is that small.
+    // Against 160 timings (4 to 256 rows of models 512 to 4096 wide) the choice between the two is 1.7 % off the better one on average (without these blocks 11 %).
+    auto consider_narrow = [&](double factor) {
+        for (int MR : {1, 2}) {
+            const int mb = (units + MR - 1) / MR, rounds = ((n_tiles + 7) / 8 * mb + 31) / 32;
+            const double us = factor * std::max(1.4, rounds * (double)k_steps * 2.048 * (1 + MR) / 52.0 - 0.8) + 0.4 * (rounds - 1);
+            if (MR <= units && us < best_us + (best.S > 1 ? 1.5 : 0.0)) {
+                best = GemmCfg{MR, 0, 1, false, 1};
+                best_us = us;
+            }
         }
     };
     const bool xbuf = (int64_t)k_steps * units_total < 1 << 20;            // an odd number of units in wide blocks: operand within 2 GiB (a buffer descriptor)
@@ -1358,7 +1483,10 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
             lm(10, 3, 1.0);
             lm(4, 2, 1.5);
         }
-        best.T = best.cols();
+        const GemmCfg wide = best;
+        best.MR = 0;
+        consider(wide, 1, 1, 0.6);
+        consider_narrow(1.15);
         return best;
     }
     int seen = 0;
@@ -1376,10 +1504,13 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
                 if (NT >= 3 && half && (NT == 3 || MR != 8 || which != G_GU)) continue;
                 const GemmCfg c = {MR, NT, 1, half, 0};
                 const int cg = (n_tiles + c.cols() - 1) / c.cols();
-                consider(c, 1, std::min(16, std::max(1, 256 / (cg * mb))));
+                consider(c, 1, std::min(16, std::max(1, 256 / (cg * mb))), which == G_QKV ? 1.45 : 1.0);
             }
     }
-    if (tune.has_gemm[which]) {                          // "MT,NT,S,PF": MT row tiles of 32 (-MT: row units), NT > 10: half tiles; S = 0 keeps the automatic split
+    consider_narrow(1.0);
+    if (tune.has_gemm[which] && tune.gemm[which][1] == 0) {      // "-MR,0,1,4": blocks of one column tile
+        if (tune.gemm[which][0] == -1 || tune.gemm[which][0] == -2) best = GemmCfg{-tune.gemm[which][0], 0, 1, false, 1};
+    } else if (tune.has_gemm[which]) {                          // "MT,NT,S,PF": MT row tiles of 32 (-MT: row units), NT > 10: half tiles; S = 0 keeps the automatic split
         const int mt = tune.gemm[which][0], nt = tune.gemm[which][1], sp = tune.gemm[which][2], pf = tune.gemm[which][3];
         const bool half = nt > 10;                           // 15 (QKV), 35 (gate/up): a shared half tile
         const int MR = mt < 0 ? -mt : 2 * mt;
@@ -1391,7 +1522,7 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
             best.MR = 0;
             const GemmCfg c = {MR, half ? nt / 10 + 1 : nt, 1, half, 0};
             const int blocks = (n_tiles + c.cols() - 1) / c.cols() * ((units + MR - 1) / MR);
-            consider(c, 1, std::min(16, std::max(1, 256 / blocks)));
+            consider(c, 1, std::min(16, std::max(1, 256 / blocks)), 1.0);
             if (sp > 0) best.S = sp;
         }
     }
@@ -1399,7 +1530,7 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
     // wave of a block then has fewer tiles than the others) if that brings the block count closer to the number of
     // compute units.  With few rows the kernel is bound by the requests a compute unit can keep in flight, so every
     // unit counts: the 8B shape has 896 column tiles, 112 x 2 = 224 blocks of 8 or 128 x 2 = 256 blocks of 7.
-    if (best.S == 1 && which == G_GU && best.MR <= 4 && !best.half) {
+    if (best.S == 1 && which == G_GU && best.NT && best.MR <= 4 && !best.half) {
         const int m_blocks = (units + best.MR - 1) / best.MR;
         auto blocks_t = [&](int t) { return ((n_tiles + t - 1) / t) * m_blocks; };
         for (int t = 4 * best.NT - 1; t >= 3 * best.NT + 1; --t)
@@ -1407,7 +1538,7 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
     }
     if (tune.tpb) {                                      // tuning experiments: tiles per block of the gate/up GEMM
         const int t = tune.tpb;
-        if (which == G_GU && best.S == 1 && best.MR <= 4 && !best.half && t >= 3 * best.NT + 1 && t <= 4 * best.NT) best.T = t;
+        if (which == G_GU && best.S == 1 && best.NT && best.MR <= 4 && !best.half && t >= 3 * best.NT + 1 && t <= 4 * best.NT) best.T = t;
     }
     return best;
 }
@@ -1433,6 +1564,13 @@ static void launch_fixup(const GemmArgs &ga, hipStream_t st) {
 
 template <int EPI>
 static void launch_gemm(GemmArgs ga, const GemmCfg &c, hipStream_t st) {
+    if (!c.NT) {
+        const int m_blocks = ((ga.M + 15) / 16 + c.MR - 1) / c.MR;
+        const dim3 narrow((unsigned)((ga.n_tiles + 7) / 8 * 8 * m_blocks));
+        if (c.MR == 2) hipLaunchKernelGGL((gemm_narrow_kernel<2, EPI>), narrow, dim3(256), 0, st, ga.W, ga.X, ga.n_tiles, ga.k_steps, ga.units_total, m_blocks, ga);
+        else hipLaunchKernelGGL((gemm_narrow_kernel<1, EPI>), narrow, dim3(256), 0, st, ga.W, ga.X, ga.n_tiles, ga.k_steps, ga.units_total, m_blocks, ga);
+        return;
+    }
     ga.col_groups = (ga.n_tiles + c.T - 1) / c.T;
     ga.m_blocks = ((ga.M + 15) / 16 + c.MR - 1) / c.MR;
     ga.splits = c.S;
@@ -1618,7 +1756,7 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
         ga.ssq_in = kv->ssq[1];
         ga.lm_val = kv->lm_val; ga.lm_idx = kv->lm_idx; ga.lm_stride = units * 16; ga.logits = logits_out;
         launch_gemm<EPI_ARGMAX>(ga, pl, st);
-        const int n_part = ((ga.n_tiles + 4 * pl.NT - 1) / (4 * pl.NT)) * 4;
+        const int n_part = pl.NT ? (ga.n_tiles + 4 * pl.NT - 1) / (4 * pl.NT) * 4 : ga.n_tiles;
         if (head) *head = {HEAD_PARTS, nullptr, kv->lm_val, kv->lm_idx, n_part, ga.lm_stride};
         else hipLaunchKernelGGL(lm_reduce_kernel, dim3(rows), dim3(256), 0, st, kv->lm_val, kv->lm_idx, n_part, ga.lm_stride,
                                 kv->row_argmax);

@@ -91,7 +91,7 @@ struct ProfSpan {
 };
 
 // Tile-shape overrides for tuning experiments, read from the environment ONCE, when the handle is created:
-// SEV_TUNE_QKV / _O / _GU / _DOWN = "MT,NT,S,PF" (MT row tiles of 32, or -MT row units of 16; S = 0 keeps the automatic split), SEV_TUNE_TPB = column tiles
+// SEV_TUNE_QKV / _O / _GU / _DOWN = "MT,NT,S,PF" (MT row tiles of 32, or -MT row units of 16; S = 0 keeps the automatic split; NT = 0: blocks of one column tile), SEV_TUNE_TPB = column tiles
 // per block of the gate/up GEMM, SEV_TUNE_CP = pages per attention chunk, SEV_TUNE_QUAD = 0: no attention blocks of four
 // row groups, n > 0: always, with chunks of n pages.  Unset (the normal case): all zero, quad -1.
 struct Tune {
@@ -102,7 +102,7 @@ struct Tune {
 
 // Tile configuration of a matrix-core GEMM (choose_cfg in kernels_bf16.hip).
 struct GemmCfg {
-    int MR, NT, S;          // row units of 16 per block, column tiles per wave, K slices
+    int MR, NT, S;          // row units of 16 per block, column tiles per wave (0: one tile per block, whose waves share K), K slices
     bool half;              // the last of the NT column tiles is shared by two waves: 4 (NT - 1) + 2 tiles per block
     int T;                  // column tiles per block (cols() unless a narrower block fills the chip better)
     int cols() const { return half ? 4 * (NT - 1) + 2 : 4 * NT; }

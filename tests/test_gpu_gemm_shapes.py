@@ -51,10 +51,12 @@ def test_forced_shapes(setup, monkeypatch, qkv, gate_up):
 
 
 @pytest.mark.parametrize("requests,shape", [(15, "-1,1,1,4"), (15, "-3,1,2,4"), (15, "-3,2,1,4"), (15, "-5,1,1,4"), (15, "-5,2,3,4"), (7, "-7,1,2,4"), (7, "-7,2,1,4"), (3, "-3,1,1,4"), (1, "-1,2,3,4"),
-                                            (15, "-5,3,1,4"), (15, "-5,4,2,4"), (5, "-5,4,1,4"), (6, "-6,3,2,4"), (6, "-6,4,1,4"), (7, "-7,3,1,4"), (7, "-7,4,3,4"), (10, "-10,3,2,4")])
+                                            (15, "-5,3,1,4"), (15, "-5,4,2,4"), (5, "-5,4,1,4"), (6, "-6,3,2,4"), (6, "-6,4,1,4"), (7, "-7,3,1,4"), (7, "-7,4,3,4"), (10, "-10,3,2,4"),
+                                            (15, "-1,0,1,4"), (15, "-2,0,1,4"), (3, "-2,0,1,4"), (1, "-1,0,1,4")])
 def test_blocks_of_an_odd_number_of_row_units(setup, monkeypatch, requests, shape):
     """Blocks of 16, 48, 80 and 112 rows, narrow (two k-steps of activations per stage) and wide (one, its last load by half of the threads),
-    and wide ones of 96 and 160, whole and split K, on all four projections: 225, 150, 105, 90, 75, 45 and 15 rows.  Same bounds as above."""
+    and wide ones of 96 and 160, whole and split K, on all four projections: 225, 150, 105, 90, 75, 45 and 15 rows.  Also blocks of one
+    column tile whose waves share K (16, 24 and 44 steps, the last not a multiple of their batch).  Same bounds as above."""
     sev, harness, model, lens, prompts, tok, caches, want = setup
     for name in ("SEV_TUNE_QKV", "SEV_TUNE_O", "SEV_TUNE_GU", "SEV_TUNE_DOWN"):
         monkeypatch.setenv(name, shape)
@@ -87,6 +89,32 @@ def test_head_blocks(requests):
     batch = harness.Batch(harness.build_model(LM_SHAPE, SEED, gains=True), LM_SHAPE, [18] * requests, max_rows=15 * requests, seed=SEED)
     batch.prefill(prompts)
     out = sev.verify_ex(batch.model, batch.kv, [3] * requests, torch.tensor(tok, device="cuda"), 15, want_argmax=True, want_logits=True)
+    torch.cuda.synchronize()
+    got = out["logits"].cpu().numpy()
+    diff = np.abs(got - want)
+    announce(f"  logits max {diff.max():.2e} mean {diff.mean():.2e}")
+    assert diff.max() < 4e-3 and diff.mean() < 4e-4
+    assert np.array_equal(out["row_argmax"].cpu().numpy(), got.argmax(axis=1))
+
+
+@pytest.mark.parametrize("d,ffn,rows", [(64, 64, 3), (128, 320, 17), (192, 1088, 40)])
+def test_narrow_blocks_of_few_steps(monkeypatch, d, ffn, rows):
+    """Blocks of one column tile whose waves have 0 or 1, 1 to 3, and 8 or 9 k-steps each (2 to 34 of them), on matrices of 2 to 68 column
+    tiles and 3, 17 and 40 rows; the head likewise.  Same bounds as above."""
+    import paper_2505_17052_amd as sev
+    from paper_2505_17052_amd import harness
+    shape = synth.workload.ModelShape("narrow", 2, d, 2, 1, 128, ffn, 1056, 500000.0, "bf16")
+    for name in ("SEV_TUNE_QKV", "SEV_TUNE_O", "SEV_TUNE_GU", "SEV_TUNE_DOWN"):
+        monkeypatch.setenv(name, "-2,0,1,4" if rows > 16 else "-1,0,1,4")
+    om = oracle_model(shape, SEED, dtype=np.float32, gains=True)
+    rng = np.random.default_rng(rows)
+    prompt, tok = rng.integers(0, shape.vocab, 5), rng.integers(0, shape.vocab, (1, rows)).astype(np.int32)
+    cache = vo.prefill(om, prompt, 5 + rows)
+    want = vo.forward_blocks(om, [cache], list(tok), [vo.chain_parents(rows)])[0][0]
+    announce(f"narrow blocks: model {d} wide, feed-forward {ffn}, {rows} rows")
+    batch = harness.Batch(harness.build_model(shape, SEED, gains=True), shape, [5 + rows], max_rows=64, seed=SEED)
+    batch.prefill([prompt])
+    out = sev.verify_ex(batch.model, batch.kv, [5], torch.tensor(tok, device="cuda"), rows, want_argmax=True, want_logits=True)
     torch.cuda.synchronize()
     got = out["logits"].cpu().numpy()
     diff = np.abs(got - want)
