@@ -121,7 +121,7 @@ void launch_pack_bf16(uint16_t *dst, const uint16_t *src, int n_rows, int K, int
 //   EPI_RESID  h += Y; xout = split(h * gain); adds the tile's sums of squares to ssq_out and
 //              clears the buffer the next producer will add to
 //   EPI_SWIGLU act = split(silu(gate) * up), gate and up rows interleaved in the weight tiles
-//   EPI_ARGMAX per-wave arg-max of every row (+ optional float32 logits); never split
+//   EPI_ARGMAX arg-max of every row over the block's columns (+ optional float32 logits); never split
 // ---------------------------------------------------------------------------
 // A pipeline stage is KS steps of 32 k.  An odd number of units does not fill whole loads of 256 threads: narrow blocks take two k-steps
 // per stage; in wide ones, whose registers that would not fit, half of the threads have no part in the stage's last load.
@@ -152,7 +152,7 @@ struct GemmArgs {
     size_t v_offset;
     uint16_t *q_planes;      // [2][M][Hq*128]
     // EPI_ARGMAX
-    float *lm_val;           // [col groups * 4][lm_stride]
+    float *lm_val;           // [col groups][lm_stride]
     int32_t *lm_idx;
     int lm_stride;
     float *logits;           // optional: [M][N]
@@ -600,8 +600,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
             ssq_commit(g, red, MR * 16, u0 * 16, cg == 0);
         }
     } else {
-        // arg-max over this wave's columns for every row (lowest index wins ties); the row scale is
-        // positive, so it only matters for the logits that are written out
+        // arg-max over the block's columns for every row (lowest index wins ties); the row scale is
+        // positive, so it only matters for the logits that are written out.  The waves meet in the activations' LDS, which
+        // nobody reads any more (the last stage ended with a barrier): what the acceptance reads per row is a quarter of the waves' results.
+        float *const wave_val = (float *)xs;
+        int *const wave_idx = (int *)(wave_val + 4 * MR * 16);
 #pragma unroll
         for (int b = 0; b < MR; ++b) {
             const int m = (u0 + ru(b)) * 16 + mrow;
@@ -626,11 +629,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(const uint4 *W_, const u
                 const int oi = __shfl_xor(bi, o);
                 if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
             }
-            if (lane < 16 && m < g.M) {
-                const size_t slot = (size_t)(cg * 4 + wave) * g.lm_stride + m;
-                g.lm_val[slot] = bv;
-                g.lm_idx[slot] = bi;
+            if (lane < 16) {
+                wave_val[wave * MR * 16 + ru(b) * 16 + mrow] = bv;
+                wave_idx[wave * MR * 16 + ru(b) * 16 + mrow] = bi;
             }
+        }
+        __syncthreads();
+        const int t = threadIdx.x, m = u0 * 16 + t;
+        if (t < MR * 16 && m < g.M) {
+            float bv = wave_val[t];
+            int bi = wave_idx[t];
+#pragma unroll
+            for (int v = 1; v < 4; ++v) {
+                const float ov = wave_val[v * MR * 16 + t];
+                const int oi = wave_idx[v * MR * 16 + t];
+                if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+            }
+            g.lm_val[(size_t)cg * g.lm_stride + m] = bv;
+            g.lm_idx[(size_t)cg * g.lm_stride + m] = bi;
         }
     }
 }
@@ -807,7 +823,7 @@ __global__ __launch_bounds__(256) void gemm_fixup_kernel(const float *part_, con
 }
 
 // ---------------------------------------------------------------------------
-// final arg-max over the per-wave partial results of the LM-head GEMM; one block per row
+// final arg-max over the per-block partial results of the LM-head GEMM; one block per row
 __global__ __launch_bounds__(256) void lm_reduce_kernel(const float *val, const int32_t *idx, int n_part, int stride,
                                                         int32_t *out) {
     __shared__ float sv[256];
@@ -1756,7 +1772,7 @@ void bf16_forward(const sev_model *m, sev_kv *kv, int rows, int B, const AttList
         ga.ssq_in = kv->ssq[1];
         ga.lm_val = kv->lm_val; ga.lm_idx = kv->lm_idx; ga.lm_stride = units * 16; ga.logits = logits_out;
         launch_gemm<EPI_ARGMAX>(ga, pl, st);
-        const int n_part = pl.NT ? (ga.n_tiles + 4 * pl.NT - 1) / (4 * pl.NT) * 4 : ga.n_tiles;
+        const int n_part = pl.NT ? (ga.n_tiles + 4 * pl.NT - 1) / (4 * pl.NT) : ga.n_tiles;
         if (head) *head = {HEAD_PARTS, nullptr, kv->lm_val, kv->lm_idx, n_part, ga.lm_stride};
         else hipLaunchKernelGGL(lm_reduce_kernel, dim3(rows), dim3(256), 0, st, kv->lm_val, kv->lm_idx, n_part, ga.lm_stride,
                                 kv->row_argmax);
