@@ -485,132 +485,270 @@ __global__ __launch_bounds__(1024) void softmax_stats_kernel(const float *logits
     }
 }
 
+// Division by a number that a whole pass divides by: its reciprocal once, then a quotient and one correction with the exact remainder, which rounds as
+// x / y does (as long as nothing underflows) in three instructions instead of about eleven.  The passes over the vocabulary below are bound by
+// their vector instructions and load latencies: 128256 ids, one rejection and the draw on one compute
+// unit: 86 us with divisions, 69 without, 57 with several places of a row requested together (current4).
+struct Divisor {
+    float y, inv;             // inv = 0: y is too small or not finite, divide
+    __device__ __forceinline__ void set(float y_) {
+        y = y_;
+        inv = y_ > 1e-30f && y_ < 1e30f ? 1.0f / y_ : 0.f;
+    }
+    __device__ __forceinline__ Divisor uniform() const {      // the same for all lanes: the branch below is then a scalar one
+        Divisor d;
+        d.y = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(y)));
+        d.inv = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(inv)));
+        return d;
+    }
+    __device__ __forceinline__ float of(float x) const {
+        if (inv == 0.f) return x / y;
+        const float q = x * inv;
+        return fmaf(fmaf(-q, y, x), inv, q);
+    }
+};
+
 struct WalkState {
     int cur, a, nrej, child, action;       // action: 0 accepted a child, 1 rejected one (in rej[nrej]), 2 no child left
     int rej[SEV_MAX_REJ + 1];
-    float R[SEV_MAX_REJ + 1];
+    Divisor R[SEV_MAX_REJ + 1];
+    Divisor den;                           // sum behind the softmax of `cur`
+    float top;                             // its largest logit
     int path[SEV_MAX_DRAFT];
 };
+
+// A request's block during the walk: its tokens and (sanitised) parents in LDS, and for every node the outcome of its acceptance test
+// against the plain softmax at its parent: the test the walk needs as long as no sibling was rejected at that
+// parent, taken for all nodes at once instead of one after the other along the path.
+struct WalkBlock {
+    int tk[SEV_MAX_DRAFT], par[SEV_MAX_DRAFT], acc0[SEV_MAX_DRAFT];
+};
+
+#define WALK_BATCH 4
+struct WalkIn {
+    const float *logits, *draft_probs;     // the request's rows
+    const float2 *stats;
+    const float *u_acc;
+    int vocab, n;
+    float inv_t;
+    bool vec;                              // rows can be read 16 bytes at a time
+    __device__ __forceinline__ WalkIn(const float *logits_, const float *draft_probs_, const float2 *stats_, const float *u_acc_, int b, int row0, int n_,
+                                      int k_max, int vocab_, float inv_t_)
+        : logits(logits_ + (size_t)row0 * vocab_), draft_probs(draft_probs_ + (size_t)row0 * vocab_), stats(stats_ + row0),
+          u_acc(u_acc_ + (size_t)b * k_max), vocab(vocab_), n(n_), inv_t(inv_t_),
+          vec(((vocab_ & 3) == 0) && ((((uintptr_t)logits_ | (uintptr_t)draft_probs_) & 15) == 0)) {}
+    __device__ __forceinline__ void block(WalkBlock &w, const int32_t *tokens, const int32_t *parents) const {      // tokens, parents: the request's
+        const int c = threadIdx.x;
+        if (c >= n) return;
+        const int q0 = parents ? parents[c] : c - 1;
+        const int q = (q0 < -1 || q0 >= c) ? -1 : q0;
+        int x = tokens[c];
+        if (x < 0 || x >= vocab) x = 0;                 // the embedding step has flagged it and used id 0 as well
+        w.tk[c] = x;
+        w.par[c] = q;
+        int ok = 0;
+        if (q >= 0) {
+            const float2 st = stats[q];
+            const float px = expf((logits[(size_t)q * vocab + x] - st.x) * inv_t) / st.y;
+            ok = u_acc[c] * draft_probs[(size_t)c * vocab + x] < px;
+        }
+        w.acc0[c] = ok;
+    }
+    __device__ __forceinline__ void enter(WalkState &s) const {      // (one thread) the node's softmax
+        const float2 st = stats[s.cur];
+        s.top = st.x;
+        s.den.set(st.y);
+    }
+    // value at token v of the current distribution: the node's softmax, then one residual step per rejected sibling
+    __device__ __forceinline__ float current(const WalkState &s, int v) const {
+        float r = s.den.of(expf((logits[(size_t)s.cur * vocab + v] - s.top) * inv_t));
+        for (int j = 0; j < s.nrej; ++j) r = s.R[j].of(fmaxf(r - draft_probs[(size_t)s.rej[j] * vocab + v], 0.f));
+        return r;
+    }
+    // the same for four consecutive ids at each of WALK_BATCH places i, i + stride, .. (in units of four ids; past the end: the last ones again).
+    // All places of a row are requested together: one after the other, a pass would wait a memory latency per place and row.
+    __device__ __forceinline__ void current4(const WalkState &s, int i, int stride, float4 (&r)[WALK_BATCH]) const {
+        const int last = (vocab >> 2) - 1;
+        const Divisor den = s.den.uniform();
+        const float top = s.top;
+        const float4 *row = (const float4 *)(logits + (size_t)s.cur * vocab);
+#pragma unroll
+        for (int u = 0; u < WALK_BATCH; ++u) r[u] = row[min(i + u * stride, last)];
+#pragma unroll
+        for (int u = 0; u < WALK_BATCH; ++u)
+            r[u] = make_float4(den.of(expf((r[u].x - top) * inv_t)), den.of(expf((r[u].y - top) * inv_t)), den.of(expf((r[u].z - top) * inv_t)),
+                               den.of(expf((r[u].w - top) * inv_t)));
+        for (int j = 0; j < s.nrej; ++j) {
+            const float4 *qrow = (const float4 *)(draft_probs + (size_t)s.rej[j] * vocab);
+            const Divisor R = s.R[j].uniform();
+            float4 q[WALK_BATCH];
+#pragma unroll
+            for (int u = 0; u < WALK_BATCH; ++u) q[u] = qrow[min(i + u * stride, last)];
+#pragma unroll
+            for (int u = 0; u < WALK_BATCH; ++u)
+                r[u] = make_float4(R.of(fmaxf(r[u].x - q[u].x, 0.f)), R.of(fmaxf(r[u].y - q[u].y, 0.f)), R.of(fmaxf(r[u].z - q[u].z, 0.f)),
+                                   R.of(fmaxf(r[u].w - q[u].w, 0.f)));
+        }
+    }
+    // the next child of the current node and its test (one thread)
+    __device__ __forceinline__ void try_child(WalkState &s, const WalkBlock &w) const {
+        s.action = 2;
+        for (int c = s.child; c < n; ++c) {
+            if (w.par[c] != s.cur) continue;
+            const int x = w.tk[c];
+            s.child = c + 1;
+            const bool ok = s.nrej == 0 ? w.acc0[c] != 0 : u_acc[c] * draft_probs[(size_t)c * vocab + x] < current(s, x);
+            if (ok) {
+                s.cur = c;
+                s.path[s.a++] = c;
+                s.nrej = 0;
+                s.action = 0;
+                enter(s);
+            } else {
+                s.rej[s.nrej] = c;
+                s.action = 1;
+            }
+            break;
+        }
+    }
+    // normaliser of the residual against the rejected child: a block-wide pass over the vocabulary, thread t at ids t, t + 1024, ...
+    // (coalesced); wave sums, then the 16 wave totals in order
+    __device__ __forceinline__ void reject(WalkState &s, float *s_part, uint32_t *err) const {
+        const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+        const float *qrow = draft_probs + (size_t)s.rej[s.nrej] * vocab;
+        float sum = 0.f;
+        if (vec) {
+            const int end = vocab >> 2;
+            for (int i = t; i < end; i += 1024 * WALK_BATCH) {
+                float4 r[WALK_BATCH], q[WALK_BATCH];
+#pragma unroll
+                for (int u = 0; u < WALK_BATCH; ++u) q[u] = ((const float4 *)qrow)[min(i + 1024 * u, end - 1)];
+                current4(s, i, 1024, r);
+#pragma unroll
+                for (int u = 0; u < WALK_BATCH; ++u)
+                    if (i + 1024 * u < end)
+                        sum += (fmaxf(r[u].x - q[u].x, 0.f) + fmaxf(r[u].y - q[u].y, 0.f)) + (fmaxf(r[u].z - q[u].z, 0.f) + fmaxf(r[u].w - q[u].w, 0.f));
+            }
+        } else {
+            for (int v = t; v < vocab; v += 1024) sum += fmaxf(current(s, v) - qrow[v], 0.f);
+        }
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+        if (lane == 0) s_part[wave] = sum;
+        __syncthreads();
+        if (t == 0) {
+            float tot = 0.f;
+            for (int i = 0; i < 16; ++i) tot += s_part[i];
+            if (s.nrej >= SEV_MAX_REJ) atomicOr(err, 8u);           // more rejected siblings than the walk remembers
+            else if (tot > 0.f) { s.R[s.nrej].set(tot); ++s.nrej; }    // an empty residual leaves the distribution as it is
+        }
+        __syncthreads();
+    }
+};
+
+// Trees: the tests at all nodes that the walk may reach, one block per node, so that the passes over the vocabulary that follow rejected
+// siblings run side by side and not one after the other along the path.  What happens at a node does not depend on how the walk came there.  A node is
+// left out if an ancestor's first child passes its test and the way to the node leads through another child.  At most SEV_NODE_REJ rejections are worked off,
+// so that a node with many children which the walk never sees cannot hold it up; the walk goes on from there.
+// 6 trees of up to 40 nodes, 128256 ids: the walk alone 455 us, 254 with the nodes' blocks in front of it and the passes below.
+__global__ __launch_bounds__(1024) void sample_nodes_kernel(DevPlan p, int k_max, const int32_t *tokens, const int32_t *parents, const float *logits,
+                                                            const float *draft_probs, const float2 *stats, int vocab, float inv_t, const float *u_acc,
+                                                            SampleNode *out) {
+    __shared__ WalkState s;
+    __shared__ WalkBlock w;
+    __shared__ float s_part[16];
+    __shared__ int s_go;
+    const int row = blockIdx.x, b = p.row_req[row], node = p.row_node[row], t = threadIdx.x;
+    const int n = p.req_n[b];
+    const WalkIn in(logits, draft_probs, stats, u_acc, b, p.req_row0[b], n, k_max, vocab, inv_t);
+    in.block(w, tokens + (size_t)b * k_max, parents + (size_t)b * k_max);
+    if (t == 0) { s.cur = node; s.a = 0; s.nrej = 0; s.child = node + 1; s.action = 1; s_go = 1; in.enter(s); }
+    __syncthreads();
+    if (t < n && t < node) {                             // thread q: is q an ancestor whose first child bars the way?
+        int at = node;
+        while (at > t && w.par[at] != t) at = w.par[at];
+        if (at > t) {
+            int first = t + 1;
+            while (w.par[first] != t) ++first;           // (at the latest `at`)
+            if (first != at && w.acc0[first]) s_go = 0;
+        }
+    }
+    __syncthreads();
+    if (s_go) {
+        for (int pass = 0;; ++pass) {
+            if (t == 0) {
+                if (pass < SEV_NODE_REJ) in.try_child(s, w);
+                else s.action = 3;
+            }
+            __syncthreads();
+            if (s.action != 1) break;
+            in.reject(s, s_part, nullptr);
+        }
+    }
+    if (t == 0) {
+        SampleNode &o = out[row];
+        o.state = !s_go ? NODE_OPEN : s.action == 0 ? NODE_ACCEPTED : NODE_REJECTED;
+        o.child = s.action == 0 && s_go ? s.cur : s.child;
+        o.nrej = s_go && s.action != 0 ? s.nrej : 0;
+        for (int j = 0; j < SEV_NODE_REJ; ++j)
+            if (j < o.nrej) { o.rej[j] = s.rej[j]; o.R[j] = s.R[j].y; }
+    }
+}
 
 __global__ __launch_bounds__(1024) void sample_walk_kernel(DevPlan p, int k_max, const int32_t *tokens, const int32_t *parents,
                                                            const float *logits, const float *draft_probs, const float2 *stats, int vocab,
                                                            float inv_t, const float *u_acc, const float *u_emit, const int32_t *next_tok,
                                                            uint32_t *err, int32_t *pend_n, int32_t *pend_a, int32_t *pend_bonus,
-                                                           int32_t *pend_path, int32_t *accept_len, int32_t *emitted, int32_t *path_out) {
+                                                           int32_t *pend_path, int32_t *accept_len, int32_t *emitted, int32_t *path_out,
+                                                           const SampleNode *nodes) {
     __shared__ WalkState s;
+    __shared__ WalkBlock w;
     __shared__ float s_part[16];
-    __shared__ int s_pick;
+    __shared__ int s_pick, s_state[SEV_MAX_DRAFT], s_child[SEV_MAX_DRAFT];
     extern __shared__ float s_grp[];                    // [ceil(vocab / 64)] sums of 64 consecutive ids (draw pass)
     const int b = blockIdx.x, t = threadIdx.x, wave = t >> 6, lane = t & 63;
     const int n_groups = (vocab + 63) >> 6;
     const int slot = p.req_slot[b], n = p.req_n[b], row0 = p.req_row0[b];
-    // the block's tokens and (sanitised) parents in LDS, and for every node the outcome of its acceptance test
-    // against the plain softmax at its parent: the test the walk needs as long as no sibling was rejected at that
-    // parent, taken for all nodes at once instead of one after the other along the path
-    __shared__ int s_tk[SEV_MAX_DRAFT], s_par[SEV_MAX_DRAFT], s_acc0[SEV_MAX_DRAFT];
-    if (t < n) {
-        const int c = t;
-        const int q0 = parents ? parents[(size_t)b * k_max + c] : c - 1;
-        const int q = (q0 < -1 || q0 >= c) ? -1 : q0;
-        int x = tokens[(size_t)b * k_max + c];
-        if (x < 0 || x >= vocab) x = 0;                 // the embedding step has flagged it and used id 0 as well
-        s_tk[c] = x;
-        s_par[c] = q;
-        int ok = 0;
-        if (q >= 0) {
-            const float2 st = stats[row0 + q];
-            const float px = expf((logits[(size_t)(row0 + q) * vocab + x] - st.x) * inv_t) / st.y;
-            ok = u_acc[(size_t)b * k_max + c] * draft_probs[(size_t)(row0 + c) * vocab + x] < px;
-        }
-        s_acc0[c] = ok;
-    }
+    const WalkIn in(logits, draft_probs, stats, u_acc, b, row0, n, k_max, vocab, inv_t);
+    in.block(w, tokens + (size_t)b * k_max, parents ? parents + (size_t)b * k_max : nullptr);
+    if (nodes && t < n) { s_state[t] = nodes[row0 + t].state; s_child[t] = nodes[row0 + t].child; }
+    const bool vec = in.vec;
+    auto current = [&](int v) { return in.current(s, v); };
     __syncthreads();
-    const int *tk = s_tk;
-    auto parent_of = [&](int c) { return s_par[c]; };
-    // value at token v of the current distribution: the node's softmax, then one residual step per rejected sibling
-    auto current = [&](int v) {
-        const float2 st = stats[row0 + s.cur];
-        float r = expf((logits[(size_t)(row0 + s.cur) * vocab + v] - st.x) * inv_t) / st.y;
-        for (int j = 0; j < s.nrej; ++j) r = fmaxf(r - draft_probs[(size_t)(row0 + s.rej[j]) * vocab + v], 0.f) / s.R[j];
-        return r;
-    };
-    // the same for four consecutive ids (16-byte loads: a block has one compute unit's worth of loads in flight, so the
-    // passes over the vocabulary are bound by how many bytes each load carries)
-    auto current4 = [&](int i) {
-        const float2 st = stats[row0 + s.cur];
-        const float4 l = ((const float4 *)(logits + (size_t)(row0 + s.cur) * vocab))[i];
-        float4 r = make_float4(expf((l.x - st.x) * inv_t) / st.y, expf((l.y - st.x) * inv_t) / st.y, expf((l.z - st.x) * inv_t) / st.y,
-                               expf((l.w - st.x) * inv_t) / st.y);
-        for (int j = 0; j < s.nrej; ++j) {
-            const float4 q = ((const float4 *)(draft_probs + (size_t)(row0 + s.rej[j]) * vocab))[i];
-            const float R = s.R[j];
-            r = make_float4(fmaxf(r.x - q.x, 0.f) / R, fmaxf(r.y - q.y, 0.f) / R, fmaxf(r.z - q.z, 0.f) / R, fmaxf(r.w - q.w, 0.f) / R);
-        }
-        return r;
-    };
-    const bool vec = ((vocab & 3) == 0) && ((((uintptr_t)logits | (uintptr_t)draft_probs) & 15) == 0);
     if (t == 0) {
         s.cur = -1;
         s.a = 0;
         s.nrej = 0;
         for (int c = 0; c < n; ++c)
-            if (parent_of(c) == -1 && tk[c] == next_tok[slot]) { s.cur = c; break; }
+            if (w.par[c] == -1 && w.tk[c] == next_tok[slot]) { s.cur = c; break; }
         if (s.cur >= 0) { s.path[0] = s.cur; s.a = 1; s.child = s.cur + 1; }
+        if (nodes && s.cur >= 0) {                       // as far as the nodes' own blocks have come
+            while (s_state[s.cur] == NODE_ACCEPTED) {    // (a child's index is larger than its parent's)
+                s.cur = s_child[s.cur];
+                s.path[s.a++] = s.cur;
+                s.child = s.cur + 1;
+            }
+            if (s_state[s.cur] == NODE_REJECTED) {      // (its first rejections)
+                const SampleNode &o = nodes[row0 + s.cur];
+                s.child = o.child;
+                s.nrej = o.nrej;
+                for (int j = 0; j < o.nrej; ++j) { s.rej[j] = o.rej[j]; s.R[j].set(o.R[j]); }
+            }
+        }
+        if (s.cur >= 0) in.enter(s);
     }
     __syncthreads();
     int tok = next_tok[slot];
     if (s.cur >= 0) {
         for (int guard = 0; guard <= 2 * SEV_MAX_DRAFT; ++guard) {          // every round consumes a child or ends the walk
-            if (t == 0) {
-                s.action = 2;
-                for (int c = s.child; c < n; ++c) {
-                    if (parent_of(c) != s.cur) continue;
-                    const int x = tk[c];
-                    s.child = c + 1;
-                    const bool ok = s.nrej == 0 ? s_acc0[c] != 0
-                                                : u_acc[(size_t)b * k_max + c] * draft_probs[(size_t)(row0 + c) * vocab + x] < current(x);
-                    if (ok) {
-                        s.cur = c;
-                        s.path[s.a++] = c;
-                        s.nrej = 0;
-                        s.action = 0;
-                    } else {
-                        s.rej[s.nrej] = c;
-                        s.action = 1;
-                    }
-                    break;
-                }
-            }
+            if (t == 0) in.try_child(s, w);
             __syncthreads();
             const int action = s.action;
             if (action == 0) {
                 __syncthreads();                                              // everyone has read the action before thread 0 writes the next one
                 continue;
             }
-            // a block-wide pass over the vocabulary, thread t at ids t, t + 1024, ... (coalesced)
             if (action == 1) {
-                // normaliser of the residual against the rejected child; wave sums, then the 16 wave totals in order
-                const float *qrow = draft_probs + (size_t)(row0 + s.rej[s.nrej]) * vocab;
-                float sum = 0.f;
-                if (vec) {
-#pragma unroll 2
-                    for (int i = t; i < (vocab >> 2); i += 1024) {
-                        const float4 r = current4(i), q = ((const float4 *)qrow)[i];
-                        sum += (fmaxf(r.x - q.x, 0.f) + fmaxf(r.y - q.y, 0.f)) + (fmaxf(r.z - q.z, 0.f) + fmaxf(r.w - q.w, 0.f));
-                    }
-                } else {
-                    for (int v = t; v < vocab; v += 1024) sum += fmaxf(current(v) - qrow[v], 0.f);
-                }
-                for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-                if (lane == 0) s_part[wave] = sum;
-                __syncthreads();
-                if (t == 0) {
-                    float tot = 0.f;
-                    for (int i = 0; i < 16; ++i) tot += s_part[i];
-                    if (s.nrej >= SEV_MAX_REJ) atomicOr(err, 8u);           // more rejected siblings than the walk remembers
-                    else if (tot > 0.f) { s.R[s.nrej] = tot; ++s.nrej; }    // an empty residual leaves the distribution as it is
-                }
-                __syncthreads();
+                in.reject(s, s_part, err);
                 continue;
             }
             // the draw: inverse CDF of the current distribution in token-id order.  Sums of groups of 64 consecutive ids
@@ -618,17 +756,17 @@ __global__ __launch_bounds__(1024) void sample_walk_kernel(DevPlan p, int k_max,
             // lane sums a run of groups, a scan over the lanes, then that lane's groups in order) and the id inside it.
             if (vec) {
                 // a wave takes 256 ids = four groups at a time, a lane four consecutive ids, 16 lanes a group
-#pragma unroll 2
-                for (int sg = wave; sg * 256 < vocab; sg += 16) {
-                    const int i = sg * 64 + lane;
-                    float x = 0.f;
-                    if (4 * i < vocab) {
-                        const float4 r = current4(i);
-                        x = (r.x + r.y) + (r.z + r.w);
+                for (int sg0 = wave; sg0 * 256 < vocab; sg0 += 16 * WALK_BATCH) {
+                    float4 r[WALK_BATCH];
+                    in.current4(s, sg0 * 64 + lane, 1024, r);
+#pragma unroll
+                    for (int u = 0; u < WALK_BATCH; ++u) {
+                        const int sg = sg0 + 16 * u;
+                        float x = 4 * (sg * 64 + lane) < vocab ? (r[u].x + r[u].y) + (r[u].z + r[u].w) : 0.f;
+                        for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o);
+                        const int g = sg * 4 + (lane >> 4);
+                        if ((lane & 15) == 0 && g < n_groups) s_grp[g] = x;
                     }
-                    for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o);
-                    const int g = sg * 4 + (lane >> 4);
-                    if ((lane & 15) == 0 && g < n_groups) s_grp[g] = x;
                 }
             } else {
                 for (int g = wave; g < n_groups; g += 16) {
@@ -701,9 +839,12 @@ void launch_sample(const sev_kv *kv, int B, int k_max, int rows, const int32_t *
     const int vocab = kv->model->d.vocab;
     const float inv_t = 1.0f / temperature;
     hipLaunchKernelGGL(softmax_stats_kernel, dim3(rows), dim3(1024), 0, st, logits, vocab, inv_t, stats);
+    if (parents)
+        hipLaunchKernelGGL(sample_nodes_kernel, dim3(rows), dim3(1024), 0, st, kv->plan, k_max, tokens, parents, logits, draft_probs, stats, vocab, inv_t, u_acc,
+                           kv->sample_nodes);
     hipLaunchKernelGGL(sample_walk_kernel, dim3(B), dim3(1024), (size_t)((vocab + 63) / 64) * 4, st, kv->plan, k_max, tokens, parents, logits, draft_probs, stats, vocab,
                        inv_t, u_acc, u_emit, kv->next_tok, kv->err_flags, kv->pend_n, kv->pend_a, kv->pend_bonus, kv->pend_path, accept_len,
-                       emitted, accept_path);
+                       emitted, accept_path, parents ? kv->sample_nodes : nullptr);
 }
 
 KvGeom sev_kv_geom(const sev_kv *kv);

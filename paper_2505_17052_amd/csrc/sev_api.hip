@@ -288,6 +288,7 @@ extern "C" int sev_kv_create(const sev_model *m, int max_requests, int max_rows,
     const size_t tail_rows = std::min(max_requests, SEV_MAX_BATCH);
     const size_t o_tq = take(bf ? tail_rows * 2 * m->q_dim * 2 : 4), o_thid = take(bf ? tail_rows * d.d_model * 4 : 4);
     const size_t o_rst = take(rows_pad * 8);
+    const size_t o_snd = take(rows_pad * sizeof(SampleNode));
     const size_t o_th = take((size_t)(d.head_dim / 2) * 8);
     kv->ws_bytes = off;
     hipError_t e = hipMalloc((void **)&kv->ws, kv->ws_bytes);
@@ -339,6 +340,7 @@ extern "C" int sev_kv_create(const sev_model *m, int max_requests, int max_rows,
     kv->row_argmax = (int32_t *)(w + o_am);
     kv->logits_f32 = (float *)(w + o_lg);
     kv->row_stats = (float2 *)(w + o_rst);
+    kv->sample_nodes = (SampleNode *)(w + o_snd);
     kv->tail_q = (uint16_t *)(w + o_tq);
     kv->tail_h = (float *)(w + o_thid);
     kv->ssq[0] = (unsigned long long *)(w + o_ssq);

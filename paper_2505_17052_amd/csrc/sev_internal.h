@@ -109,6 +109,15 @@ struct GemmCfg {
 };
 #define SEV_KEPT_UNITS 128   // row counts (in units of 16) whose configurations a handle keeps
 
+// What the stochastic rule found at one node of a tree (sample_nodes_kernel).
+enum { NODE_OPEN = 0, NODE_ACCEPTED, NODE_REJECTED };      // nothing yet; accepted `child`; rejected nrej of the children below `child`
+#define SEV_NODE_REJ 4       // rejections worked off there
+struct SampleNode {
+    int state, child, nrej;
+    int rej[SEV_NODE_REJ];   // the rejected children whose residual counts, and its normalisers
+    float R[SEV_NODE_REJ];
+};
+
 struct sev_kv {
     const sev_model *model;
     Tune tune;
@@ -148,6 +157,7 @@ struct sev_kv {
     int32_t *row_argmax;      // [rows]
     uint16_t *tail_q;         // bf16, end of a prefill: q planes [2][requests][Hq*hd] and residual rows [requests][d] of the last
     float *tail_h;            //   token of every prompt that ends in the chunk
+    SampleNode *sample_nodes; // [rows]
     float2 *row_stats;        // [rows] (largest logit, sum of exp((logit - max) / T)) of the stochastic rule
     float *logits_f32;        // f32 path only: [rows][vocab]
 

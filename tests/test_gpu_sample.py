@@ -4,6 +4,8 @@ numbers and the edge distributions are seeded inputs shared by both sides.  A de
 exactly where it is firm: an acceptance test whose two sides differ by more than 1e-3 relative, an
 inverse-CDF draw that lands more than 1e-4 (of the total weight) inside its cell; what float32 against
 float64 arithmetic can flip is exempt (and counted)."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -127,14 +129,17 @@ def _edge_trees(om, caches, parents, seed, noise):
     return toks, q
 
 
-def _run_tree(shape, seed, lens, dtype, noise, acc_eps, logit_tol):
+# root; three proposals for its successor; two of them continued, one twice
+TREE = [-1, 0, 0, 0, 1, 1, 2, 4, 4, 7]
+
+
+def _run_tree(shape, seed, lens, dtype, noise, acc_eps, logit_tol, parents=TREE):
     import paper_2505_17052_amd as sev
     from paper_2505_17052_amd import harness
     model = harness.build_model(shape, seed)
     om = oracle_model(shape, seed, dtype=dtype)
     B = len(lens)
-    # root; three proposals for its successor; two of them continued, one twice
-    parents = np.array([-1, 0, 0, 0, 1, 1, 2, 4, 4, 7], dtype=np.int64)
+    parents = np.array(parents, dtype=np.int64)
     n = len(parents)
     last = [int(synth.uniform_i32(seed, 6000 + b, 1, 0, shape.vocab)[0]) for b in range(B)]
     batch = harness.Batch(model, shape, [P + 80 for P in lens], max_rows=B * n, seed=seed)
@@ -181,3 +186,12 @@ def test_sample_tree_tiny_f32():
 def test_sample_tree_mini_bf16():
     announce("stochastic tree verification, mini bf16")
     _run_tree(synth.MINI_BF16, 606, [37, 300, 64, 129], np.float32, noise=1.0, acc_eps=3e-2, logit_tol=(3e-2, 3e-3))
+
+
+@pytest.mark.parametrize("vocab,seed", [(1024, 31), (1030, 32)])
+def test_sample_tree_many_siblings(vocab, seed):
+    """Nine proposals for the root's successor, the first and the last of them continued, and an edge far from the server: more rejections at
+    one node than the nodes' own blocks work off (4), rows that are and are not a whole number of 16-byte loads."""
+    announce(f"stochastic verification, trees with nine siblings, vocabulary {vocab}")
+    _run_tree(dataclasses.replace(synth.TINY, vocab=vocab), seed, [40, 64, 17, 5, 33, 90, 12, 50], np.float64, noise=3.0, acc_eps=1e-3, logit_tol=(1e-4, 1e-5),
+              parents=[-1] + [0] * 9 + [1, 1, 9, 9, 9, 10, 12])
