@@ -1467,12 +1467,13 @@ static GemmCfg choose_cfg(int which, int rows, int n_tiles, int k_steps, size_t 
         }
     };
     // Blocks of one column tile whose waves share K (gemm_narrow_kernel): their estimate is the bytes into the fullest unit, weights and activations alike, at 52 KB/us,
-    // less what the caches make of it and 1.4 us at least, and 0.4 us per round of blocks.  A split's fix-up kernel costs 1.5 us more than the other estimate says where everything is that small.
-    // Against 160 timings (4 to 256 rows of models 512 to 4096 wide) the choice between the two is 1.7 % off the better one on average (without these blocks 11 %).
+    // less what the caches make of it and 1.4 us at least, 0.6 us per further round of blocks, and 0.05 us per MB of weights, which come from memory (QKV of the 8B shape at
+    // 16 rows: 12.8 us, in split blocks 10.3).  A split's fix-up kernel costs 1.5 us more than the other estimate says where everything is that small.
+    // Against 160 timings (4 to 256 rows of models 512 to 4096 wide) the choice between the two is 1.4 % off the better one on average (without these blocks 11 %).
     auto consider_narrow = [&](double factor) {
         for (int MR : {1, 2}) {
             const int mb = (units + MR - 1) / MR, rounds = ((n_tiles + 7) / 8 * mb + 31) / 32;
-            const double us = factor * std::max(1.4, rounds * (double)k_steps * 2.048 * (1 + MR) / 52.0 - 0.8) + 0.4 * (rounds - 1);
+            const double us = factor * std::max(1.4, rounds * (double)k_steps * 2.048 * (1 + MR) / 52.0 - 0.8) + 0.6 * (rounds - 1) + 0.05 * n_tiles * k_steps * 2048e-6;
             if (MR <= units && us < best_us + (best.S > 1 ? 1.5 : 0.0)) {
                 best = GemmCfg{MR, 0, 1, false, 1};
                 best_us = us;
